@@ -147,6 +147,79 @@ __device__ __forceinline__ float bf16_absmax_finish(uint32_t m) {
     return __uint_as_float((hi > lo ? hi : lo) << 16);
 }
 
+// Tile lookup of the one-tile-per-workgroup GEMM kernels: the whole workgroup reads the device-resident offsets (E <= 1024,
+// a few per thread), checks them (inconsistent: error word, nothing is computed; decided alike by every workgroup) and
+// locates row tile `unit`, counted over the experts in order with ceil(rows / bm) tiles each; bm = 0: `unit` is the expert
+// itself.  A parallel prefix sum: one pass of loads and two barriers whatever E is.  Returns false (uniformly) if there is
+// nothing to do.  Every thread of the workgroup must call it.
+struct tile_pick_lds {
+    int wave_sum[16];
+    int wave_bad[16];
+    int found[4];  // expert, row tile, first row, end row
+};
+template <int THREADS>
+__device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
+                                          int unit, tile_pick_lds& l, int& e, int& ti, int& row_lo, int& row_hi) {
+    constexpr int PER = 1024 / THREADS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int o[PER + 1];
+#pragma unroll
+    for (int x = 0; x <= PER; ++x) {
+        const int i = tid * PER + x;
+        o[x] = offsets[i < E ? i : E];
+    }
+    bool bad = (tid == 0 && o[0] < 0) || o[PER] > Rcap;
+    int n = 0;
+#pragma unroll
+    for (int x = 0; x < PER; ++x) {
+        const int rows = o[x + 1] - o[x];
+        bad |= rows < 0;
+        n += bm ? (rows > 0 ? (rows + bm - 1) / bm : 0) : (tid * PER + x < E ? 1 : 0);
+    }
+    int incl = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int v = __shfl_up(incl, d);
+        if (lane >= d) incl += v;
+    }
+    const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
+    if (lane == 63) l.wave_sum[wave] = incl;
+    if (lane == 0) l.wave_bad[wave] = any_bad;
+    if (tid == 0) l.found[0] = -1;
+    __syncthreads();
+    int first = incl - n, wrong = 0;
+#pragma unroll
+    for (int w = 0; w < THREADS / 64; ++w) {
+        if (w < wave) first += l.wave_sum[w];
+        wrong |= l.wave_bad[w];
+    }
+    if (wrong) {
+        if (blockIdx.x == 0 && tid == 0) atomicExch(dev_err, 1);
+        return false;
+    }
+    if (unit >= first && unit < first + n) {
+        int at = unit - first;
+#pragma unroll
+        for (int x = 0; x < PER; ++x) {
+            const int rows = o[x + 1] - o[x];
+            const int k = bm ? (rows > 0 ? (rows + bm - 1) / bm : 0) : (tid * PER + x < E ? 1 : 0);
+            if (at >= 0 && at < k) {
+                l.found[0] = tid * PER + x;
+                l.found[1] = at;
+                l.found[2] = o[x];
+                l.found[3] = o[x + 1];
+            }
+            at -= k;
+        }
+    }
+    __syncthreads();
+    e = __builtin_amdgcn_readfirstlane(l.found[0]);
+    ti = __builtin_amdgcn_readfirstlane(l.found[1]);
+    row_lo = __builtin_amdgcn_readfirstlane(l.found[2]);
+    row_hi = __builtin_amdgcn_readfirstlane(l.found[3]);
+    return e >= 0;
+}
+
 // all-fp32 grouped GEMMs (gemm_f32.hip), reached from the public entry points with dt = MOE_F32
 moe_status moe_gg_f32_fwd(moe_ctx* ctx, hipStream_t s, const void* A, const void* B, const int32_t* offsets, int E, int N,
                           int K, int64_t Rcap, int swiglu, const float* row_prob, void* C, void* C_act);
