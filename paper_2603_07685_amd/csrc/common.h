@@ -149,20 +149,22 @@ __device__ __forceinline__ float bf16_absmax_finish(uint32_t m) {
 
 // Tile lookup of the one-tile-per-workgroup GEMM kernels: the whole workgroup reads the device-resident offsets (E <= 1024,
 // a few per thread), checks them (inconsistent: error word, nothing is computed; decided alike by every workgroup) and
-// locates row tile `unit`, counted over the experts in order with ceil(rows / bm) tiles each; bm = 0: `unit` is the expert
-// itself.  A parallel prefix sum: one pass of loads and two barriers whatever E is.  Returns false (uniformly) if there is
-// nothing to do.  Every thread of the workgroup must call it.
+// finds its tile in the list of all experts' tiles, expert by expert: mult * ceil(rows / bm) of them each, or mult if
+// bm = 0.  u = the tile's number inside its expert.  A parallel prefix sum: one pass of loads and two barriers whatever E
+// is.  Workgroups land on the 8 XCDs round-robin; each XCD gets a contiguous run of the tiles that exist (the grid is an
+// upper bound, rounded up to a multiple of 8), so that neighbours share their operands in its L2.  Returns false
+// (uniformly) if there is nothing to do.  Every thread of the workgroup must call it.
 struct tile_pick_lds {
     int wave_sum[16];
     int wave_bad[16];
-    int found[4];  // expert, row tile, first row, end row
+    int found[4];  // expert, tile, first row, end row
 };
 template <int THREADS>
 __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
-                                          int unit, tile_pick_lds& l, int& e, int& ti, int& row_lo, int& row_hi) {
+                                          int mult, tile_pick_lds& l, int& e, int& u, int& row_lo, int& row_hi) {
     constexpr int PER = 1024 / THREADS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int o[PER + 1];
+    int o[PER + 1], cnt[PER];
 #pragma unroll
     for (int x = 0; x <= PER; ++x) {
         const int i = tid * PER + x;
@@ -174,7 +176,8 @@ __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, i
     for (int x = 0; x < PER; ++x) {
         const int rows = o[x + 1] - o[x];
         bad |= rows < 0;
-        n += bm ? (rows > 0 ? (rows + bm - 1) / bm : 0) : (tid * PER + x < E ? 1 : 0);
+        cnt[x] = mult * (bm ? (rows > 0 ? (rows + bm - 1) / bm : 0) : (tid * PER + x < E ? 1 : 0));
+        n += cnt[x];
     }
     int incl = n;
 #pragma unroll
@@ -185,39 +188,40 @@ __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, i
     const bool any_bad = __builtin_amdgcn_ballot_w64(bad) != 0;
     if (lane == 63) l.wave_sum[wave] = incl;
     if (lane == 0) l.wave_bad[wave] = any_bad;
-    if (tid == 0) l.found[0] = -1;
     __syncthreads();
-    int first = incl - n, wrong = 0;
+    int first = incl - n, total = 0, wrong = 0;
 #pragma unroll
     for (int w = 0; w < THREADS / 64; ++w) {
         if (w < wave) first += l.wave_sum[w];
+        total += l.wave_sum[w];
         wrong |= l.wave_bad[w];
     }
     if (wrong) {
         if (blockIdx.x == 0 && tid == 0) atomicExch(dev_err, 1);
         return false;
     }
+    const int run = (total + 7) >> 3, at_run = (int)(blockIdx.x >> 3);
+    const int unit = (int)(blockIdx.x & 7) * run + at_run;
+    if (at_run >= run || unit >= total) return false;
     if (unit >= first && unit < first + n) {
         int at = unit - first;
 #pragma unroll
         for (int x = 0; x < PER; ++x) {
-            const int rows = o[x + 1] - o[x];
-            const int k = bm ? (rows > 0 ? (rows + bm - 1) / bm : 0) : (tid * PER + x < E ? 1 : 0);
-            if (at >= 0 && at < k) {
+            if (at >= 0 && at < cnt[x]) {
                 l.found[0] = tid * PER + x;
                 l.found[1] = at;
                 l.found[2] = o[x];
                 l.found[3] = o[x + 1];
             }
-            at -= k;
+            at -= cnt[x];
         }
     }
     __syncthreads();
     e = __builtin_amdgcn_readfirstlane(l.found[0]);
-    ti = __builtin_amdgcn_readfirstlane(l.found[1]);
+    u = __builtin_amdgcn_readfirstlane(l.found[1]);
     row_lo = __builtin_amdgcn_readfirstlane(l.found[2]);
     row_hi = __builtin_amdgcn_readfirstlane(l.found[3]);
-    return e >= 0;
+    return true;
 }
 
 // all-fp32 grouped GEMMs (gemm_f32.hip), reached from the public entry points with dt = MOE_F32

@@ -1,0 +1,119 @@
+// Shared by the grouped-GEMM kernels of gemm.hip (256 x 256 tiles) and gemm_tile.hip (smaller tiles): arguments, LDS access
+// and synchronisation primitives.
+#pragma once
+#include "common.h"
+
+#define GG_MAX_E 1024
+// k-major swizzle: two 128-byte rows share a 256-byte bank line; slot ^= bits 1..3 of the row makes
+// 16 consecutive rows hit 16 different (position in line, slot) pairs (SQ_LDS_BANK_CONFLICT = 0)
+#define KM_SWZ(row) (((row) >> 1) & 7)
+
+enum { GG_FWD = 0, GG_DGRAD = 1, GG_WGRAD = 2 };
+enum { GG_EPI_STORE = 0, GG_EPI_SWIGLU = 1, GG_EPI_SWIGLU_BWD = 2 };
+
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef const __attribute__((address_space(1))) void gbl_void_t;
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef short s16x8_t __attribute__((ext_vector_type(8)));
+typedef int i32x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+typedef int i32x8_t __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+typedef __attribute__((address_space(3))) i32x2_t lds_i32x2_t;
+
+// The LDS destination is passed as a wave-uniform register part plus a constant part (buffer + chunk).
+// The register part goes through an empty asm first: the sum is then formed at each use (one scalar add)
+// instead of sixteen loop-invariant sums each holding a scalar register across the stage loop.
+__device__ __forceinline__ uint32_t lds_addr(void* p) { return (uint32_t)(uintptr_t)(lds_void_t*)p; }
+__device__ __forceinline__ uint32_t m0_value(uint32_t lds_wave, uint32_t lds_const) {
+    asm volatile("" : "+s"(lds_wave));
+    return lds_wave + lds_const;
+}
+// Workgroup barrier without the memory fence __syncthreads() carries: the fence would drain every
+// DMA load in flight (vmcnt(0)) and serialise the pipeline.  The wave has already waited for its own
+// loads of the stage being published; LDS reads after the barrier are ordered by the hardware.
+// The empty asm statements and sched_barriers keep the compiler from moving anything across.
+__device__ __forceinline__ void stage_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0)
+// s_waitcnt vmcnt(0) only (gfx9 encoding, other counters at their maxima): this wave's DMA loads landed
+__device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// (hardware reciprocal, 1 ulp: an IEEE division is ten instructions per element in an epilogue one wave runs alone)
+__device__ __forceinline__ float sigmoid_f(float g) { return __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
+
+// ds_read_b64_tr_b16: within each group of 16 lanes, lane i supplies the address of 4 consecutive
+// 16-bit elements (row i/4, columns 4*(i%4)..+3 of a 4x16 block) and receives column i of that block
+// (rows 0..3).  Two of them give the 8 contraction values a lane feeds to the 32x32x16 MFMA.
+__device__ __forceinline__ bf16x8_t lds_read_tr16x8(const char* p_lo, const char* p_hi) {
+    s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p_lo);
+    s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p_hi);
+    s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    return __builtin_bit_cast(bf16x8_t, v);
+}
+// 4 consecutive bf16 <-> 4 floats, one 8-byte access
+__device__ __forceinline__ void st4_bf16(bf16_t* p, const float* v) {
+    u32x2_t w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    *(u32x2_t*)p = w;
+}
+__device__ __forceinline__ void ld4_bf16(const bf16_t* p, float* v) {
+    const u32x2_t w = *(const u32x2_t*)p;
+    v[0] = bf16_lo(w.x);
+    v[1] = bf16_hi(w.x);
+    v[2] = bf16_lo(w.y);
+    v[3] = bf16_hi(w.y);
+}
+
+struct gg_args {
+    const void* P;         // fwd: A, dgrad: dC, wgrad: dC   (bf16, or E4M3 codes)
+    const void* Q;         // fwd/dgrad: W [E,N,K], wgrad: A
+    const float* p_scale;  // fp8: [rows, C/128] for the row-indexed operand (C = contraction length)
+    const float* q_scale;  // fp8: [E, N/128, K/128] for the weights
+    const int32_t* offsets;
+    int E, N, K;
+    int64_t Rcap;
+    void* out;             // fwd: C (may be NULL with SWIGLU), dgrad: dA or dZ, wgrad: dW
+    bf16_t* out_act;       // fwd SWIGLU: activation output
+    const bf16_t* Zsaved;  // dgrad SWIGLU_BWD: saved pre-activation [rows, 2K]
+    const char* zeros;     // >= 16 zero bytes (feeds the wgrad contraction tail)
+    int* dev_err;
+    int accumulate;        // wgrad: out += result
+    const float* row_prob; // eq. (2): routing weight of each row (fwd SWIGLU: scales the activation;
+                           //   dgrad SWIGLU_BWD: scales dZ); NULL = 1
+    // blockwise fp8 only: the epilogue also emits the 1x128 codes and scales of its bf16 output (fwd SWIGLU: of the
+    // activation [rows, N/2]; dgrad SWIGLU_BWD: of dZ [rows, 2K]), the operand of the next GEMM (Sec. 5.4.2)
+    uint8_t* out_q;
+    float* out_q_scale;
+    // MXFP8: the same tensors as 1x32 codes + E8M0 bytes [rows, cols/32] (out_q, out_q_e8) and, optionally, as the
+    // 32x1 copy for the weight gradient (out_qc, scales [rows/128, cols, 4]: one dword = the four 32-row blocks)
+    uint8_t* out_q_e8;
+    uint8_t* out_qc;
+    uint8_t* out_qc_e8;
+    int* tile_counter;     // wgrad: zeroed device counter for the dynamic tile order under skewed loads (see the kernel)
+    // wgrad, bf16: deterministic split of the contraction for experts far above the mean load (see the kernel)
+    int split_cap;         // how many expert-sized slices of fp32 partial tiles `partials` can hold (0: never split)
+    float* partials;       // [split_cap][tiles per expert][256 x 256] fp32
+    int* split_info;       // [1 + 3 * GG_MAX_SPLIT_EXPERTS]: count, then (expert, pieces, first slice) for the reduce kernel
+    float* dprob_part;     // eq. (2), dgrad SWIGLU_BWD: [Rcap, 2 ceil(K/256)] partial <dA, act(Z)> per row, two per column tile
+    // Permutation fused into the operand fetch (Sec. 4.3.3; GATH variants): the gathered operand (P or Q) points to
+    // the unpermuted tensor [g_T, row length], and row r of the operand is its row g_src_of[r] / g_k, or zeros where
+    // g_src_of[r] < 0 (padding, rows behind offsets[E])
+    const int32_t* g_src_of;
+    uint32_t g_magic;      // ceil(2^31 / g_k): ((2 s + 1) * g_magic) >> 32 == s / g_k for every 0 <= s with s * g_k < 2^30
+    int g_k;
+    int g_T;
+};
+// offset of a gathered row that has no source: behind every record count a gathered operand can have (checked on the
+// host), and far enough from 2^32 that a column offset added to it cannot wrap
+#define GG_NO_ROW 0xF0000000u
+
+
+// Small-tile kernels for bf16 operands (gemm_tile.hip).  gt_tile: which of them serves a call (0: none, the 256 x 256
+// kernel of gemm.hip is the better one); gt_launch: run it.
+int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a);
+void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);

@@ -55,7 +55,7 @@
 // factor: at every 128-wide contraction block (= stage) it is multiplied by s_prev / s_new before the raw
 // products are added, and by the last factor in the epilogue.  No second set of accumulators.
 // The scales of a block reach LDS with the operands of its stage.
-#include "common.h"
+#include "gemm.h"
 
 #define GG_BM 256
 #define GG_BN 256
@@ -63,29 +63,10 @@
 #define GG_BAND 4  // row-tiles per band of the tile order
 #endif
 #define GG_THREADS 512
-#define GG_MAX_E 1024
 #define GG_MAX_SPLIT 8          // most slices of partial tiles a weight-gradient call uses (workspace: that many fp32 copies of one expert's dW)
 #define GG_MAX_SPLIT_EXPERTS 4  // an expert is split into at least two pieces
 #define GG_ROWB 128                     // bytes of a k-major tile row per stage: one cache line
 #define GG_STAGE_BYTES (GG_BM * GG_ROWB)  // one operand tile per stage: 32 KB
-// k-major swizzle: two 128-byte rows share a 256-byte bank line; slot ^= bits 1..3 of the row makes
-// 16 consecutive rows hit 16 different (position in line, slot) pairs (SQ_LDS_BANK_CONFLICT = 0)
-#define KM_SWZ(row) (((row) >> 1) & 7)
-
-enum { GG_FWD = 0, GG_DGRAD = 1, GG_WGRAD = 2 };
-enum { GG_EPI_STORE = 0, GG_EPI_SWIGLU = 1, GG_EPI_SWIGLU_BWD = 2 };
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef const __attribute__((address_space(1))) void gbl_void_t;
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-typedef short s16x8_t __attribute__((ext_vector_type(8)));
-typedef int i32x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
-typedef int i32x4_t __attribute__((ext_vector_type(4)));
-typedef int i32x8_t __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
-typedef __attribute__((address_space(3))) i32x2_t lds_i32x2_t;
-
 static_assert(2 * 2 * GG_STAGE_BYTES <= 144 * 1024, "pipeline stages exceed the LDS budget");
 
 // Global -> LDS DMA: each lane moves 16 (or 4) bytes; LDS destination = M0 + lane * size.
@@ -96,14 +77,6 @@ static_assert(2 * 2 * GG_STAGE_BYTES <= 144 * 1024, "pipeline stages exceed the 
 // stage it is about to read (wait_vm0 + barrier), so the compiler needs to see only an opaque memory
 // write.  (Waits the compiler adds for its own global loads stay correct: the memory counter completes
 // in order, so extra older or younger entries only make such a wait longer.)
-// The LDS destination is passed as a wave-uniform register part plus a constant part (buffer + chunk).
-// The register part goes through an empty asm first: the sum is then formed at each use (one scalar add)
-// instead of sixteen loop-invariant sums each holding a scalar register across the stage loop.
-__device__ __forceinline__ uint32_t lds_addr(void* p) { return (uint32_t)(uintptr_t)(lds_void_t*)p; }
-__device__ __forceinline__ uint32_t m0_value(uint32_t lds_wave, uint32_t lds_const) {
-    asm volatile("" : "+s"(lds_wave));
-    return lds_wave + lds_const;
-}
 // scalar base + 32-bit lane offset (readfirstlane: a no-op for a value the compiler already keeps in
 // scalar registers, and the guarantee the "s" constraint needs where it does not)
 __device__ __forceinline__ void dma16(const char* base, uint32_t off, uint32_t lds_wave, uint32_t lds_const) {
@@ -123,35 +96,9 @@ __device__ __forceinline__ void dma4(const void* src, uint32_t lds_wave, uint32_
                  :: "s"(m0_value(lds_wave, lds_const)), "v"(src) : "memory", "m0");
 }
 
-// Workgroup barrier without the memory fence __syncthreads() carries: the fence would drain every
-// DMA load in flight (vmcnt(0)) and serialise the pipeline.  The wave has already waited for its own
-// loads of the stage being published; LDS reads after the barrier are ordered by the hardware.
-// The empty asm statements and sched_barriers keep the compiler from moving anything across.
-__device__ __forceinline__ void stage_barrier() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }  // lgkmcnt(0)
-// s_waitcnt vmcnt(0) only (gfx9 encoding, other counters at their maxima): this wave's DMA loads landed
-__device__ __forceinline__ void wait_vm0() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // vmcnt(1): everything but the wave's youngest vector-memory operation (the L2 warm-up load, see PF below)
 __device__ __forceinline__ void wait_vm1() { __builtin_amdgcn_s_waitcnt(0x0F71); }
 
-// (hardware reciprocal, 1 ulp: an IEEE division is ten instructions per element in an epilogue one wave runs alone)
-__device__ __forceinline__ float sigmoid_f(float g) { return __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
-
-// ds_read_b64_tr_b16: within each group of 16 lanes, lane i supplies the address of 4 consecutive
-// 16-bit elements (row i/4, columns 4*(i%4)..+3 of a 4x16 block) and receives column i of that block
-// (rows 0..3).  Two of them give the 8 contraction values a lane feeds to the 32x32x16 MFMA.
-__device__ __forceinline__ bf16x8_t lds_read_tr16x8(const char* p_lo, const char* p_hi) {
-    s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p_lo);
-    s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)p_hi);
-    s16x8_t v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-    return __builtin_bit_cast(bf16x8_t, v);
-}
 // ds_read_b64_tr_b8: lane i of a 16-lane group supplies the address of 8 consecutive bytes (row i/2,
 // columns 8*(i%2)..+7 of an 8x16 block) and receives column i (rows 0..7).  Four reads, 8 rows apart,
 // give the 32 contraction values a lane feeds to the 32x32x64 fp8 MFMA.
@@ -164,62 +111,6 @@ __device__ __forceinline__ i32x8_t lds_read_tr8x32(const char* p, int second = 1
     i32x8_t v = {r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
     return v;
 }
-
-// 4 consecutive bf16 <-> 4 floats, one 8-byte access
-__device__ __forceinline__ void st4_bf16(bf16_t* p, const float* v) {
-    u32x2_t w = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-    *(u32x2_t*)p = w;
-}
-__device__ __forceinline__ void ld4_bf16(const bf16_t* p, float* v) {
-    const u32x2_t w = *(const u32x2_t*)p;
-    v[0] = bf16_lo(w.x);
-    v[1] = bf16_hi(w.x);
-    v[2] = bf16_lo(w.y);
-    v[3] = bf16_hi(w.y);
-}
-
-struct gg_args {
-    const void* P;         // fwd: A, dgrad: dC, wgrad: dC   (bf16, or E4M3 codes)
-    const void* Q;         // fwd/dgrad: W [E,N,K], wgrad: A
-    const float* p_scale;  // fp8: [rows, C/128] for the row-indexed operand (C = contraction length)
-    const float* q_scale;  // fp8: [E, N/128, K/128] for the weights
-    const int32_t* offsets;
-    int E, N, K;
-    int64_t Rcap;
-    void* out;             // fwd: C (may be NULL with SWIGLU), dgrad: dA or dZ, wgrad: dW
-    bf16_t* out_act;       // fwd SWIGLU: activation output
-    const bf16_t* Zsaved;  // dgrad SWIGLU_BWD: saved pre-activation [rows, 2K]
-    const char* zeros;     // >= 16 zero bytes (feeds the wgrad contraction tail)
-    int* dev_err;
-    int accumulate;        // wgrad: out += result
-    const float* row_prob; // eq. (2): routing weight of each row (fwd SWIGLU: scales the activation;
-                           //   dgrad SWIGLU_BWD: scales dZ); NULL = 1
-    // blockwise fp8 only: the epilogue also emits the 1x128 codes and scales of its bf16 output (fwd SWIGLU: of the
-    // activation [rows, N/2]; dgrad SWIGLU_BWD: of dZ [rows, 2K]), the operand of the next GEMM (Sec. 5.4.2)
-    uint8_t* out_q;
-    float* out_q_scale;
-    // MXFP8: the same tensors as 1x32 codes + E8M0 bytes [rows, cols/32] (out_q, out_q_e8) and, optionally, as the
-    // 32x1 copy for the weight gradient (out_qc, scales [rows/128, cols, 4]: one dword = the four 32-row blocks)
-    uint8_t* out_q_e8;
-    uint8_t* out_qc;
-    uint8_t* out_qc_e8;
-    int* tile_counter;     // wgrad: zeroed device counter for the dynamic tile order under skewed loads (see the kernel)
-    // wgrad, bf16: deterministic split of the contraction for experts far above the mean load (see the kernel)
-    int split_cap;         // how many expert-sized slices of fp32 partial tiles `partials` can hold (0: never split)
-    float* partials;       // [split_cap][tiles per expert][256 x 256] fp32
-    int* split_info;       // [1 + 3 * GG_MAX_SPLIT_EXPERTS]: count, then (expert, pieces, first slice) for the reduce kernel
-    float* dprob_part;     // eq. (2), dgrad SWIGLU_BWD: [Rcap, 2 ceil(K/256)] partial <dA, act(Z)> per row, two per column tile
-    // Permutation fused into the operand fetch (Sec. 4.3.3; GATH variants): the gathered operand (P or Q) points to
-    // the unpermuted tensor [g_T, row length], and row r of the operand is its row g_src_of[r] / g_k, or zeros where
-    // g_src_of[r] < 0 (padding, rows behind offsets[E])
-    const int32_t* g_src_of;
-    uint32_t g_magic;      // ceil(2^31 / g_k): ((2 s + 1) * g_magic) >> 32 == s / g_k for every 0 <= s with s * g_k < 2^30
-    int g_k;
-    int g_T;
-};
-// offset of a gathered row that has no source: behind every record count a gathered operand can have (checked on the
-// host), and far enough from 2^32 that a column offset added to it cannot wrap
-#define GG_NO_ROW 0xF0000000u
 
 // MODE: GG_FWD / GG_DGRAD / GG_WGRAD.  EPI: see enum.  OUT_F32: fp32 output (wgrad only).
 // F8: 0 = bf16 operands; 1 = E4M3 codes with fp32 block scales applied in software
@@ -2207,7 +2098,9 @@ extern "C" moe_status moe_grouped_gemm_fwd_gather(moe_ctx* ctx, void* stream, co
     if (st != MOE_OK) return st;
     a.out_act = (bf16_t*)C_act;
     a.row_prob = row_prob;
-    if (epi == MOE_EPI_SWIGLU) GG_LAUNCH_G(GG_FWD, GG_EPI_SWIGLU, false, 1);
+    const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
+    if (const int tile = gt_tile(ctx, GG_FWD, ge, a)) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 1, tile, a);
+    else if (epi == MOE_EPI_SWIGLU) GG_LAUNCH_G(GG_FWD, GG_EPI_SWIGLU, false, 1);
     else GG_LAUNCH_G(GG_FWD, GG_EPI_STORE, false, 1);
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<fwd, gather>");
     return MOE_OK;
@@ -2322,7 +2215,10 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
         a.out_qc = (uint8_t*)mxo->q_col;
         a.out_qc_e8 = mxo->e8_col;
     }
-    if (epi == MOE_EPI_SWIGLU) {
+    const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
+    if (const int tile = fp8 ? 0 : gt_tile(ctx, GG_FWD, ge, a)) {
+        gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
+    } else if (epi == MOE_EPI_SWIGLU) {
         if (mx) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 2);
         else if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 1);
         else GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 0);
@@ -2353,7 +2249,9 @@ extern "C" moe_status moe_grouped_gemm_dgrad_gather(moe_ctx* ctx, void* stream, 
     a.Zsaved = (const bf16_t*)Z_saved;
     a.row_prob = row_prob;
     a.dprob_part = dprob_part;
-    if (Z_saved) GG_LAUNCH_G(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
+    const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
+    if (const int tile = gt_tile(ctx, GG_DGRAD, ge, a)) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 1, tile, a);
+    else if (Z_saved) GG_LAUNCH_G(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
     else GG_LAUNCH_G(GG_DGRAD, GG_EPI_STORE, false, 1);
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<dgrad, gather>");
     return MOE_OK;
@@ -2444,7 +2342,10 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
         a.out_qc = (uint8_t*)mxo->q_col;
         a.out_qc_e8 = mxo->e8_col;
     }
-    if (Z_saved) {
+    const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
+    if (const int tile = fp8 ? 0 : gt_tile(ctx, GG_DGRAD, ge, a)) {
+        gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
+    } else if (Z_saved) {
         if (mx) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 2);
         else if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
         else GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 0);
@@ -2498,6 +2399,15 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     if (out_dt != MOE_BF16 && out_dt != MOE_F32) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_grouped_gemm_wgrad: out_dt must be bf16 or f32");
     gg_args a = gg_make(ctx, dC, A, offsets, E, N, K, Rcap, dB);
     a.accumulate = accumulate ? 1 : 0;
+    if (gath) {  // (bf16 operands; P = dC, Q = A)
+        st = gg_gather_args(ctx, "moe_grouped_gemm_wgrad_gather", a, T, src_of, k, gath == 2 ? K : N, Rcap);
+        if (st != MOE_OK) return st;
+    }
+    if (const int tile = (mx || bw) ? 0 : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
+        gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
+        MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
+        return MOE_OK;
+    }
     a.tile_counter = (int*)((char*)ctx->ws + MOE_WS_TILE_COUNTER);
     moe_launch_fill_i32(a.tile_counter, 1, 0, (hipStream_t)stream);
     a.p_scale = dc_scale;
@@ -2508,10 +2418,6 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     a.split_info = (int*)((char*)ctx->ws + MOE_WS_SPLIT_INFO);
     a.partials = (float*)((char*)ctx->ws + MOE_WS_RESERVED);
     a.split_cap = (!mx && !bw && GG_BF16_NW == 4) ? (int)(ws_free / slice_bytes < GG_MAX_SPLIT ? ws_free / slice_bytes : GG_MAX_SPLIT) : 0;
-    if (gath) {  // (bf16 operands; P = dC, Q = A)
-        st = gg_gather_args(ctx, "moe_grouped_gemm_wgrad_gather", a, T, src_of, k, gath == 2 ? K : N, Rcap);
-        if (st != MOE_OK) return st;
-    }
     if (gath == 2) {
         if (out_dt == MOE_F32) GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, true, 2);
         else GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, false, 2);

@@ -64,12 +64,12 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
     // ---- this workgroup's tile ----
     int e, ti, tj, row_lo, row_hi;
     {
-        const int b = blockIdx.x;
-        const int unit = b / tiles_j;                        // row tile over all experts / (expert, row tile of dW)
-        tj = b - unit * tiles_j;
+        int u;
         if (!tile_pick<F32_THREADS>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GF_WGRAD ? 0 : BT,
-                                    MODE == GF_WGRAD ? unit / tiles_iw : unit, pick, e, ti, row_lo, row_hi)) return;
-        if (MODE == GF_WGRAD) ti = unit % tiles_iw;
+                                    MODE == GF_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, e, u, row_lo, row_hi)) return;
+        const int tiles_i = MODE == GF_WGRAD ? tiles_iw : (row_hi - row_lo + BT - 1) / BT;
+        tj = u / tiles_i;
+        ti = u - tj * tiles_i;
     }
     const int64_t i0 = MODE == GF_WGRAD ? (int64_t)ti * BT : row_lo + (int64_t)ti * BT;
     const int64_t i_end = MODE == GF_WGRAD ? N : row_hi;
@@ -250,7 +250,7 @@ static moe_status gf_launch(moe_ctx* ctx, hipStream_t s, const char* who, const 
     const int bt = gf_tile(ctx, MODE, a, out_cols);
     const int64_t tiles_j = EPI == GF_SWIGLU ? ceil_div64(a.N / 2, bt / 2) : ceil_div64(out_cols, bt);
     // (every expert may end in a partly filled row tile)
-    const int64_t grid = tiles_j * (MODE == GF_WGRAD ? a.E * ceil_div64(a.N, bt) : ceil_div64(a.Rcap, bt) + a.E);
+    const int64_t grid = ceil_div64(tiles_j * (MODE == GF_WGRAD ? a.E * ceil_div64(a.N, bt) : ceil_div64(a.Rcap, bt) + a.E), 8) * 8;
     if (grid > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: problem too large for the fp32 path", who);
     const uintptr_t bits = (uintptr_t)a.P | (uintptr_t)a.Q | (uintptr_t)a.out | (uintptr_t)a.out_act | (uintptr_t)a.Zsaved;
     const bool vec = a.N % 4 == 0 && a.K % 4 == 0 && (EPI != GF_SWIGLU || a.N % 8 == 0) && bits % 16 == 0;

@@ -1,0 +1,428 @@
+// Grouped GEMM on small tiles (bf16 operands): the calls that the 256 x 256 kernel of gemm.hip serves badly, because its
+// tiles are too few for the 256 compute units, mostly padding (a few rows per expert), or because a contraction of a few
+// stages does not pay for that kernel's set-up and output phases.
+//
+// Same operation, operand layouts and LDS swizzles as there: OUT[i,j] = sum_c P[i,c] * Q[j,c], the contraction in stages
+// of 64 elements (128 bytes of a row: whole cache lines), row-major operands read with ds_read_b128, contraction-major
+// ones with the transposing ds_read_b64_tr_b16.  The contraction order inside a result is that kernel's too, so the two
+// give the same bits.
+//
+// A 256-thread workgroup computes one BM x 128 tile (BM = 64 or 128), four waves as 2 x 2, wave tile BM/2 x 64 in 16 x 16
+// blocks; operands come by global -> LDS DMA into a ring of NBUF stage buffers, NBUF - 1 stages ahead of their use, awaited
+// by count (vmcnt), with one barrier per stage.  The DMA goes through buffer descriptors: rows behind a tensor's or a
+// contraction's end arrive as zeros, without a branch.
+//
+// Bound: the fixed cost around a short contraction (finding the tile, the first operands' latency, the output: about 5 us)
+// and the rate at which a compute unit's L1 takes lines from the L2 (35-45 bytes per ns here, in the 256 x 256 kernel too;
+// the matrix pipes are 34 % busy, the LDS 17 %).  What helped is waves: NBUF = 2 keeps two (BM = 128) or three (64)
+// workgroups on a compute unit, which cover each other's waits; with a ring of four stages and one workgroup, the same
+// bytes ahead, a call takes 1.25-1.5 times as long (fc1 forward, T 2048, h 1024, f 512, 8 experts, top-2: 24 us against
+// 33, BM = 128).  A persistent form, whose operand stream runs on across tiles, was no faster (27 us) and its static share
+// of the tiles made it slower where there are many (BM = 64, 24 experts, 8000 rows: 309 us against 251).
+// Where the rows of an expert fit one tile and the call streams the weights, a third buffer is worth more than the third
+// workgroup (decoding, 32 rows on each of 16 experts, 403 MB of fc1 weights: 92 us against 98, 4.4 TB/s).
+#include "gemm.h"
+
+#define GT_BN 128
+#define GT_BAND 8   // row tiles per band of the tile order (tiles of a band that share a column run together)
+
+// 16 bytes per lane, descriptor in scalar registers, lane offset in bytes; LDS side: M0 + 16 * lane
+__device__ __forceinline__ void dma16_buf(i32x4_t rsrc, uint32_t off, uint32_t lds_wave, uint32_t lds_const) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 :: "s"(m0_value(lds_wave, lds_const)), "v"(off), "s"(rsrc) : "memory", "m0");
+}
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF>
+__global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
+    static_assert(GATH == 0 || GATH == 1 || (GATH == 2 && MODE == GG_WGRAD), "Q is gathered in the weight gradient only");
+    constexpr bool P_CMAJ = MODE == GG_WGRAD, Q_CMAJ = MODE != GG_FWD;
+    constexpr int P_BYTES = BM * 128, STAGE = P_BYTES + GT_BN * 128;
+    constexpr int PC = BM / 32, QC = 4;                 // 1 KB DMA chunks per wave, operand and stage
+    constexpr int NI = BM / 32;                         // 16-row blocks per wave
+    constexpr int STG_PITCH = 132;
+    static_assert(NBUF * STAGE >= 64 * STG_PITCH * 4, "the output phase stages 64 rows in the ring");
+    __shared__ __attribute__((aligned(1024))) char ring[NBUF * STAGE];
+    __shared__ tile_pick_lds pick;
+    // weight gradient with a gathered operand: byte offsets of the rows of two blocks of 16 stages (see rows_in)
+    constexpr bool G_CM = GATH != 0 && MODE == GG_WGRAD;
+    __shared__ uint32_t rows_at[G_CM ? 2048 : 1];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
+    const int N = a.N, K = a.K;
+    const int J = MODE == GG_FWD ? N : K;
+    const int half_cols = EPI == GG_EPI_SWIGLU ? N >> 1 : 0;
+    const int tiles_j = EPI == GG_EPI_SWIGLU ? (half_cols + 63) / 64 : (J + GT_BN - 1) / GT_BN;
+    const int tiles_iw = (N + BM - 1) / BM;             // wgrad
+
+    int e, u, row_lo, row_hi;
+    if (!tile_pick<256>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM,
+                        MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, e, u, row_lo, row_hi)) return;
+    int ti, tj;
+    {
+        const int tiles_i = MODE == GG_WGRAD ? tiles_iw : (row_hi - row_lo + BM - 1) / BM;
+        const int band_sz = GT_BAND * tiles_j, band = u / band_sz, in_band = u - band * band_sz;
+        const int band_rows = min(GT_BAND, tiles_i - band * GT_BAND);
+        ti = __builtin_amdgcn_readfirstlane(band * GT_BAND + in_band % band_rows);
+        tj = __builtin_amdgcn_readfirstlane(in_band / band_rows);
+    }
+    const int i0 = MODE == GG_WGRAD ? ti * BM : row_lo + ti * BM;
+    const int i_end = MODE == GG_WGRAD ? N : row_hi;
+    const int j0 = EPI == GG_EPI_SWIGLU ? tj * 64 : tj * GT_BN;
+    const int c_lo = MODE == GG_WGRAD ? row_lo : 0, c_hi = MODE == GG_WGRAD ? row_hi : (MODE == GG_FWD ? K : N);
+    const int KT = __builtin_amdgcn_readfirstlane((c_hi - c_lo + 63) / 64);
+
+    // ---- DMA sources: 32-bit lane offsets from a wave-uniform base ----
+    // row-major: a chunk = 8 rows x 128 B, lane -> row l / 8, slot l % 8 ^ KM_SWZ(row).  contraction-major: a chunk =
+    // 1024 / pitch rows (pitch = 2 x the tile's columns), lane -> 16-byte slot, ^ 2 * (row % 4 | separating bit << 2):
+    // the eight 4-row groups that the LDS serves in one pass of a transposing read (4 rows of two lane groups) then hit
+    // different 32-byte bank segments.  The separating bit is the row bit that tells the two lane groups apart.
+    constexpr int SEP = MODE == GG_WGRAD ? 4 : 3;
+    auto cm_f = [](int row) { return 2 * ((row & 3) | (((row >> SEP) & 1) << 2)); };
+    const int ldp = MODE == GG_FWD ? K : N;             // row length of P in memory (wgrad: dC [rows, N])
+    uint32_t po[PC], qo[QC];
+#pragma unroll
+    for (int i = 0; i < PC; ++i) {
+        const int c = wave * PC + i;
+        if (P_CMAJ) {
+            constexpr int SL = BM * 2 / 16;             // 16-byte slots per row
+            const int row = c * (64 / SL) + lane / SL, slot = (lane % SL) ^ cm_f(row);
+            po[i] = (uint32_t)((GATH == 1 ? 0 : row * ldp) + i0 + slot * 8) * 2u;
+        } else {
+            const int row = c * 8 + (lane >> 3), slot = (lane & 7) ^ KM_SWZ(row);
+            if (GATH == 1) {
+                const int s = i0 + row < i_end ? a.g_src_of[i0 + row] : -1;
+                const uint32_t tok = __umulhi(2u * (uint32_t)s + 1u, a.g_magic);  // s / g_k
+                po[i] = s >= 0 ? tok * (uint32_t)(ldp * 2) + slot * 16 : GG_NO_ROW;
+            } else {
+                po[i] = (uint32_t)(row * ldp) * 2u + slot * 16;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < QC; ++i) {
+        const int c = wave * QC + i;
+        if (Q_CMAJ) {
+            const int row = c * 4 + (lane >> 4), slot = (lane & 15) ^ cm_f(row);
+            qo[i] = (uint32_t)((GATH == 2 ? 0 : row * K) + j0 + slot * 8) * 2u;
+        } else {
+            const int p = c * 8 + (lane >> 3), slot = (lane & 7) ^ KM_SWZ(p);
+            const int n = EPI == GG_EPI_SWIGLU ? (p < 64 ? j0 + p : half_cols + j0 + p - 64) : j0 + p;
+            qo[i] = (uint32_t)n * (uint32_t)(K * 2) + slot * 16;
+        }
+    }
+    // base and byte count of each operand at stage s (past the last stage: nothing, the buffer fills with zeros)
+    const char* const p_base0 = GATH == 1 ? (const char*)a.P
+                                          : (const char*)a.P + (int64_t)(P_CMAJ ? c_lo : i0) * ldp * 2;
+    const char* const q_base0 = GATH == 2 ? (const char*)a.Q : MODE == GG_WGRAD ? (const char*)a.Q + (int64_t)c_lo * K * 2
+                                                 : (const char*)a.Q + (int64_t)e * N * K * 2;
+    const uint32_t p_all = GATH == 1 ? (uint32_t)a.g_T * (uint32_t)(ldp * 2) : (uint32_t)min(BM, i_end - i0) * (uint32_t)(ldp * 2);
+    const uint32_t q_all = GATH == 2 ? (uint32_t)a.g_T * (uint32_t)(K * 2) : (uint32_t)N * (uint32_t)(K * 2);
+    auto make = [](const char* base, uint32_t bytes) {
+        const uint64_t b = (uint64_t)base;
+        i32x4_t r = {(int)__builtin_amdgcn_readfirstlane((uint32_t)b), (int)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)),
+                     (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000};
+        return r;
+    };
+    // Gathered operand of the weight gradient: every stage brings 64 new rows, found through the row map.  The byte offsets
+    // of the rows of 16 stages at a time are looked up ahead by the whole workgroup and kept in LDS, two blocks in turn
+    // (rows without a source and rows behind the contraction range: an offset that reads as zeros).  Looking them up in
+    // the stage loop would wait for the map entry, and with it for every transfer in flight, in each stage.
+    auto rows_in = [&](int blk) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const int at = blk * 1024 + x * 256 + tid, c = c_lo + at;
+            const int s = c < c_hi ? a.g_src_of[c] : -1;
+            const uint32_t tok = __umulhi(2u * (uint32_t)s + 1u, a.g_magic);  // s / g_k
+            rows_at[at & 2047] = s >= 0 ? tok * (uint32_t)((GATH == 1 ? ldp : K) * 2) : GG_NO_ROW;
+        }
+    };
+    const uint32_t lds0 = lds_addr(ring);
+    // descriptors of stage s, and its transfers one by one (x < PC: P, then Q) into buffer `at`
+    i32x4_t rp, rq;
+    auto describe = [&](int s) {
+        const uint32_t left = (uint32_t)max(min(64, c_hi - c_lo - s * 64), 0);   // contraction rows of this stage
+        rp = G_CM && GATH == 1 ? make(p_base0, p_all)
+                               : make(p_base0 + (int64_t)s * (P_CMAJ ? 128 * (int64_t)ldp : 128),
+                                      P_CMAJ ? left * (uint32_t)(ldp * 2) : s < KT ? p_all - (uint32_t)s * 128 : 0u);
+        rq = G_CM && GATH == 2 ? make(q_base0, q_all)
+                               : make(q_base0 + (int64_t)s * (Q_CMAJ ? 128 * (int64_t)K : 128),
+                                      Q_CMAJ ? left * (uint32_t)(K * 2) : s < KT ? q_all - (uint32_t)s * 128 : 0u);
+    };
+    uint32_t g_off[G_CM ? 4 : 1];   // gathered rows of this lane's four chunks of the stage about to be requested
+    auto g_rows = [&](int s) {
+        if (G_CM) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) g_off[i] = rows_at[(s * 64 + (wave * 4 + i) * 4 + (lane >> 4)) & 2047];
+        }
+    };
+    auto issue_one = [&](uint32_t at, int x) {
+        if (x < PC) dma16_buf(rp, po[x] + (G_CM && GATH == 1 ? g_off[x] : 0u), at + wave * (PC * 1024), x * 1024);
+        else dma16_buf(rq, qo[x - PC] + (G_CM && GATH == 2 ? g_off[x - PC] : 0u), at + wave * (QC * 1024), P_BYTES + (x - PC) * 1024);
+    };
+    if (G_CM) {
+        rows_in(0);
+        __syncthreads();
+    }
+
+    // ---- fragment side (the lane groups' share of a 32-element step is the 256 x 256 kernel's: same sums) ----
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int kperm = MODE == GG_WGRAD ? 2 * (kq & 1) + (kq >> 1) : kq;
+    auto col_of = [&](int jb) { return EPI == GG_EPI_SWIGLU ? (jb >> 1) * 64 + wn * 32 + (jb & 1) * 16 : wn * 64 + jb * 16; };
+    const int km[2] = {(kperm ^ KM_SWZ(l16)) * 16, ((4 + kperm) ^ KM_SWZ(l16)) * 16};
+    const int cm_row = 8 * kperm + (l16 >> 2), cm_x = cm_f(cm_row), cm_lo = ((l16 & 3) >> 1) * 16 + (l16 & 1) * 8;
+    auto frag = [&](const char* t, bool cmaj, int pitch, int ks, int row) -> bf16x8_t {
+        if (!cmaj) return *(const bf16x8_t*)(t + (row + l16) * 128 + km[ks]);
+        const char* p = t + (32 * ks + cm_row) * pitch + ((row / 8) ^ cm_x) * 16 + cm_lo;
+        return lds_read_tr16x8(p, p + 4 * pitch);
+    };
+
+    f32x4_t acc[NI][4];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < NBUF; ++s) {
+        describe(s);
+        g_rows(s);
+#pragma unroll
+        for (int x = 0; x < PC + QC; ++x) issue_one(lds0 + s * STAGE, x);
+    }
+    // A stage is two contraction steps of 32 elements.  The fragments of a step are read while the MFMAs of the step
+    // before it run, and the transfers of the stage that takes over this buffer are slipped between the MFMAs of the
+    // second step.  In mid-stage: this wave's share of stage s + 1 has landed, its reads of this buffer are done, barrier.
+    bf16x8_t fp[2][NI], fq[2][4];
+    constexpr int NR = NI + 4, NM = NI * 4;               // fragment reads and MFMAs per step
+    auto read_one = [&](int set, const char* t, int ks, int r) {   // in the order of use: Q 0, P 0, Q 1..3, P 1..
+        const int j = r == 0 ? 0 : r - 1, i = r == 1 ? 0 : r - 4;
+        if (r == 0 || (r >= 2 && r < 5)) fq[set][j] = frag(t + P_BYTES, Q_CMAJ, GT_BN * 2, ks, col_of(j));
+        else fp[set][i] = frag(t, P_CMAJ, BM * 2, ks, wm * (BM / 2) + 16 * i);
+    };
+    auto step = [&](int set, auto&& slot) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fq[set][j], fp[set][i], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                slot(i * 4 + j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    };
+    wait_vm<(NBUF - 1) * (PC + QC)>();
+    stage_barrier();
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read_one(0, ring, 0, r);
+    int buf = 0;
+    for (int s = 0; s < KT; ++s) {
+        const char* const t0 = ring + buf * STAGE;
+        const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
+        const char* const t1 = ring + nbuf * STAGE;
+        step(0, [&](int m) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (r * (NM - 2) / NR == m) read_one(1, t0, 1, r);
+            if (m == NM - 2) describe(s + NBUF);
+            if (m == NM - 1) g_rows(s + NBUF);
+        });
+        wait_vm<(NBUF - 2) * (PC + QC)>();
+        wait_lgkm0();
+        stage_barrier();
+        step(1, [&](int m) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (r * (NM - 2) / NR == m) read_one(0, t1, 0, r);
+#pragma unroll
+            for (int x = 0; x < PC + QC; ++x)
+                if (x * NM / (PC + QC) == m) issue_one(lds0 + buf * STAGE, x);
+        });
+        // (the half written here was last read 8 stages ago, and is read from 8 stages on)
+        if (G_CM && ((s + NBUF) & 15) == 8 && s + NBUF < KT) rows_in(((s + NBUF) >> 4) + 1);
+        buf = nbuf;
+    }
+    wait_vm0();        // (the stages past the end: their zeros must not land in the staging area)
+    wait_lgkm0();
+    stage_barrier();
+
+    // ---- output: 64 rows at a time (32 of each wave half) through LDS in fp32, back as whole rows ----
+    // A lane's accumulators of a block are one row (l16) x 4 columns (4 kq ..); a staged row comes back to 16 lanes of 8
+    // consecutive columns each, so a store instruction is 4 rows x 256 contiguous bytes (bf16).
+    float* const stg = (float*)ring;
+    const int c8 = (lane & 15) * 8;
+#pragma unroll
+    for (int ps = 0; ps < BM / 64; ++ps) {
+        // staged row q (0..63) is tile row (q / 32) * (BM / 2) + 32 ps + q % 32
+        auto out_row = [&](int q) { return i0 + (q >> 5) * (BM / 2) + 32 * ps + (q & 31); };
+        u32x4_t zg[4], zu[4];
+        if (EPI == GG_EPI_SWIGLU_BWD) {   // the saved pre-activations: on their way while the accumulators are staged
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int r = out_row(wave * 16 + t * 4 + (lane >> 4));
+                if (r < i_end && j0 + c8 < K) {
+                    const bf16_t* z = a.Zsaved + (int64_t)r * 2 * K + j0 + c8;
+                    zg[t] = *(const u32x4_t*)z;
+                    zu[t] = *(const u32x4_t*)(z + K);
+                }
+            }
+        }
+        if (ps) __syncthreads();
+#pragma unroll
+        for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                *(f32x4_t*)(stg + (wm * 32 + 16 * i2 + l16) * STG_PITCH + col_of(j) + 4 * kq) = acc[2 * ps + i2][j];
+        __syncthreads();
+        auto pack8 = [](const float* v) {
+            return u32x4_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+        };
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int q = wave * 16 + t * 4 + (lane >> 4), r = out_row(q);
+            const bool live = r < i_end;
+            float v[8];
+            *(f32x4_t*)v = *(const f32x4_t*)(stg + q * STG_PITCH + c8);
+            *(f32x4_t*)(v + 4) = *(const f32x4_t*)(stg + q * STG_PITCH + c8 + 4);
+            if (EPI == GG_EPI_SWIGLU) {
+                const int f = j0 + (c8 & 63);
+                if (a.out && live && f < half_cols)
+                    *(u32x4_t*)((bf16_t*)a.out + (int64_t)r * N + (c8 < 64 ? f : half_cols + f)) = pack8(v);
+            } else if (EPI == GG_EPI_SWIGLU_BWD) {
+                float dot = 0.f;
+                if (live && j0 + c8 < K) {
+                    const float gt[8] = {bf16_lo(zg[t].x), bf16_hi(zg[t].x), bf16_lo(zg[t].y), bf16_hi(zg[t].y),
+                                         bf16_lo(zg[t].z), bf16_hi(zg[t].z), bf16_lo(zg[t].w), bf16_hi(zg[t].w)};
+                    const float up[8] = {bf16_lo(zu[t].x), bf16_hi(zu[t].x), bf16_lo(zu[t].y), bf16_hi(zu[t].y),
+                                         bf16_lo(zu[t].z), bf16_hi(zu[t].z), bf16_lo(zu[t].w), bf16_hi(zu[t].w)};
+                    const float pr = a.row_prob ? a.row_prob[r] : 1.0f;
+                    float dg[8], du[8];
+#pragma unroll
+                    for (int x = 0; x < 8; ++x) {
+                        const float sg = sigmoid_f(gt[x]);
+                        dg[x] = pr * v[x] * up[x] * sg * (1.0f + gt[x] * (1.0f - sg));
+                        du[x] = pr * v[x] * gt[x] * sg;
+                        dot += v[x] * (gt[x] * sg * up[x]);
+                    }
+                    bf16_t* o = (bf16_t*)a.out + (int64_t)r * 2 * K + j0 + c8;
+                    *(u32x4_t*)o = pack8(dg);
+                    *(u32x4_t*)(o + K) = pack8(du);
+                }
+                if (a.dprob_part) {   // one partial sum per row and 128-column tile; an odd tile count leaves one entry over
+#pragma unroll
+                    for (int x = 1; x < 16; x <<= 1) dot += __shfl_xor(dot, x);
+                    if (live && (lane & 15) == 0) {
+                        float* d = a.dprob_part + (int64_t)r * (2 * ((K + 255) / 256));
+                        d[tj] = dot;
+                        if (tj + 1 == tiles_j && (tiles_j & 1)) d[tj + 1] = 0.f;
+                    }
+                }
+            } else if (live && j0 + c8 < J) {
+                const int64_t at = (MODE == GG_WGRAD ? ((int64_t)e * N + r) * K : (int64_t)r * J) + j0 + c8;
+                if (OUT_F32) {
+                    f32x4_t* o = (f32x4_t*)((float*)a.out + at);
+                    f32x4_t lo = *(f32x4_t*)v, hi = *(f32x4_t*)(v + 4);
+                    if (a.accumulate) {
+                        lo += o[0];
+                        hi += o[1];
+                    }
+                    o[0] = lo;
+                    o[1] = hi;
+                } else {
+                    u32x4_t* o = (u32x4_t*)((bf16_t*)a.out + at);
+                    if (a.accumulate) {
+                        const u32x4_t w = *o;
+                        v[0] += bf16_lo(w.x); v[1] += bf16_hi(w.x); v[2] += bf16_lo(w.y); v[3] += bf16_hi(w.y);
+                        v[4] += bf16_lo(w.z); v[5] += bf16_hi(w.z); v[6] += bf16_lo(w.w); v[7] += bf16_hi(w.w);
+                    }
+                    *o = pack8(v);
+                }
+            }
+        }
+        if (EPI == GG_EPI_SWIGLU) {   // activation: 8 features per lane, 8 rows per instruction
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int q = wave * 16 + t * 8 + (lane >> 3), r = out_row(q), f8 = (lane & 7) * 8;
+                if (r < i_end && j0 + f8 < half_cols) {
+                    const float pr = a.row_prob ? a.row_prob[r] : 1.0f;
+                    float act[8];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const f32x4_t gt = *(const f32x4_t*)(stg + q * STG_PITCH + f8 + 4 * h);
+                        const f32x4_t up = *(const f32x4_t*)(stg + q * STG_PITCH + 64 + f8 + 4 * h);
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) act[4 * h + x] = pr * (gt[x] * sigmoid_f(gt[x]) * up[x]);
+                    }
+                    *(u32x4_t*)(a.out_act + (int64_t)r * half_cols + j0 + f8) = pack8(act);
+                }
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+// Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 0 = the 256 x 256
+// kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted to measured calls
+// (MI355X, bf16; rows of an expert unknown on the host, so every expert is given half a partly filled row tile, and at
+// least one tile):
+//   256 x 256: one workgroup per compute unit, whole rounds of tiles, a tile = 1.5 per stage + 15 (SwiGLU backward: 35);
+//              weight gradient: + 9 for the tile counter's fill and the second pass of a split contraction
+//   128 x 128: two workgroups per compute unit, rounds between the exact and the rounded-up count, a round = 2 x (0.62 per
+//              stage + 4)
+// Measured against each other (us, 256 x 256 : small tiles), fc1 forward unless said otherwise:
+//   T 256 h 128 f 256 E 8 k 2       16 : 6       T 2048 h 1024 f 512 E 8 k 2       41 : 23   (its weight gradients 38, 37 : 14, 16)
+//   T 4096 h 512 f 512 E 16 k 4     56 : 43      T 4096 h 2048 f 1024 E 8 k 2     122 : 113
+//   T 2048 h 2048 f 1024 E 8 k 2    65 : 74      T 1024 h 4096 f 1536 E 16 k 8    222 : 284  (fc2 dgrad of the former 72 : 36)
+//   T 8192 h 1024 f 1024 E 16 k 4  200 : 230     T 64 h 7168 f 2048 E 32 k 8      429 : 312  (fc2 274 : 168)
+// Few rows per expert (on average at most 48): the third buffer (T 64 h 4096 f 14336 E 8 k 2: 464 : 330 against 363 with two
+// buffers and 359 with 128 x 128).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill the chip's two workgroups per
+// unit (T 256 h 128 f 256: fc2 dgrad 6.9 against 9.5; T 4096 h 512 f 512: 27 against 34).
+int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
+    const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
+    const double E = a.E, R = (double)a.Rcap, one = E < R ? E : R;
+    auto row_tiles = [&](double bm) { return R / bm + E / 2 > one ? R / bm + E / 2 : one; };
+    const double cols = mode == GG_FWD ? a.N : a.K;
+    const double stages = mode == GG_WGRAD ? R / E / 64 + 0.5 : (mode == GG_FWD ? a.K : a.N) / 64.0;
+    const double n256 = __builtin_ceil(cols / 256) * (mode == GG_WGRAD ? E * __builtin_ceil(a.N / 256.0) : row_tiles(256));
+    const double n128 = __builtin_ceil(cols / 128) * (mode == GG_WGRAD ? E * __builtin_ceil(a.N / 128.0) : row_tiles(128));
+    const double r256 = __builtin_ceil(n256 / cu), r128 = n128 / (2 * cu);
+    const double t256 = r256 * (1.5 * stages + (epi == GG_EPI_SWIGLU_BWD ? 35 : 15)) + (mode == GG_WGRAD ? 9 : 0);
+    const double t128 = (r128 + __builtin_ceil(r128)) * (0.62 * stages + 4);
+    if (t128 > 1.1 * t256) return 0;
+    if (mode == GG_WGRAD) return 2;
+    if (R <= 48 * E) return 3;
+    return r128 < 1 ? 1 : 2;
+}
+
+template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF>
+static void gt_go(hipStream_t s, const gg_args& a) {
+    const int64_t cols = EPI == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(MODE == GG_FWD ? a.N : a.K, GT_BN);
+    const int64_t n = cols * (MODE == GG_WGRAD ? a.E * ceil_div64(a.N, BM) : ceil_div64(a.Rcap, BM) + a.E);
+    hipLaunchKernelGGL((gt_kernel<MODE, EPI, F32, GATH, BM, NBUF>), dim3((unsigned)(ceil_div64(n, 8) * 8)), dim3(256), 0, s, a);
+}
+template <int MODE, int EPI, int GATH>
+static void gt_rows(hipStream_t s, int tile, const gg_args& a) {
+    if (tile == 1) gt_go<MODE, EPI, false, GATH, 64, 2>(s, a);
+    else if (tile == 2) gt_go<MODE, EPI, false, GATH, 128, 2>(s, a);
+    else gt_go<MODE, EPI, false, GATH, 64, 3>(s, a);
+}
+template <bool F32>
+static void gt_wgrad(hipStream_t s, int gath, const gg_args& a) {
+    if (gath == 1) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 1, 128, 2>(s, a);
+    else if (gath == 2) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 2, 128, 2>(s, a);
+    else gt_go<GG_WGRAD, GG_EPI_STORE, F32, 0, 128, 2>(s, a);
+}
+void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
+    if (mode == GG_WGRAD) {
+        if (out_f32) gt_wgrad<true>(s, gath, a);
+        else gt_wgrad<false>(s, gath, a);
+    } else if (mode == GG_FWD) {
+        if (epi == GG_EPI_SWIGLU) gath ? gt_rows<GG_FWD, GG_EPI_SWIGLU, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_SWIGLU, 0>(s, tile, a);
+        else gath ? gt_rows<GG_FWD, GG_EPI_STORE, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_STORE, 0>(s, tile, a);
+    } else {
+        if (epi == GG_EPI_SWIGLU_BWD) gath ? gt_rows<GG_DGRAD, GG_EPI_SWIGLU_BWD, 1>(s, tile, a) : gt_rows<GG_DGRAD, GG_EPI_SWIGLU_BWD, 0>(s, tile, a);
+        else gath ? gt_rows<GG_DGRAD, GG_EPI_STORE, 1>(s, tile, a) : gt_rows<GG_DGRAD, GG_EPI_STORE, 0>(s, tile, a);
+    }
+}
