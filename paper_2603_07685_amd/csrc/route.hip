@@ -1,129 +1,152 @@
-// moe_route_topk: fused score function + top-k + weights + histogram (Sec. 2.1.2 item 2, Sec. 4.3.4).
+// The router: fused score function + top-k + weights + histogram (Sec. 2.1.2 item 2, Sec. 4.3.4), its group-limited and
+// biased branches, its backward, and the load-balancing loss.
 //
-// One 64-lane wavefront owns one token.  Lane l holds the logits of experts
-// l, l+64, l+128, ... in registers; the max / sum of the score function and each
-// of the k arg-max rounds are butterfly reductions over the wavefront, so a
-// token costs one coalesced read of its E logits and no LDS traffic.  Selection
-// is done on the raw logits (lower index wins ties), weights are computed for
-// the k winners only.  A workgroup accumulates its tokens' histogram in LDS and
-// adds it to the global counts once.
+// A group of LPT lanes owns one token: 16 lanes (four tokens per wavefront) up to 256 experts, a whole wavefront above.
+// Lane l of the group holds the logits of experts l, l + LPT, l + 2 LPT, ... in registers; what the group has to agree on
+// (maximum, sum, the winner of an arg-max round) is a reduction of four DPP steps over 16 lanes (two more, through the
+// LDS crossbar, over 64).  A wavefront handles one token per group and ends.
+// Bound: vector instructions at large T (one read of the logits: 3.6 us for T 16384, E 256 at the copy rate), one
+// token's chain of reductions at small T.  Values are compared as order-preserving integers, so that an arg-max round is
+// max3 over the lane's values, four DPP maxima, and a DPP minimum over the indices that hold the maximum.
+// Measured (us; one token per wavefront, eight in turn, butterfly shuffles : this), T 16384, E 256, k 8: top-k 59 : 17;
+// group-limited with bias, 8 groups: 150 : 36; backward 23 : 11.5; auxiliary loss 27 (two kernels) : 19.
+// T 64, E 128, k 8: 51 : 7.
 #include "common.h"
 
-#define ROUTE_MAX_VPL 16          // values per lane -> E <= 1024
-#define ROUTE_WAVES 4
-#define ROUTE_TOKENS_PER_WAVE 8
+#define ROUTE_MAX_E 1024
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+// ---- reductions over a token's lanes: every lane gets the result --------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) { return __uint_as_float(dpp<CTRL>(__float_as_uint(x))); }
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    return __longlong_as_double((long long)(((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b)));
+}
+// exchange with the neighbour, the neighbouring pair, the mirrored quad of 8, the mirrored half of 16, then 16 and 32 away
+template <int LPT, typename T, typename F>
+__device__ __forceinline__ T lanes_reduce(T v, F op) {
+    v = op(v, dpp<0xB1>(v));
+    v = op(v, dpp<0x4E>(v));
+    v = op(v, dpp<0x141>(v));
+    v = op(v, dpp<0x140>(v));
+    if (LPT == 64) {
+        v = op(v, __shfl_xor(v, 16));
+        v = op(v, __shfl_xor(v, 32));
+    }
     return v;
 }
-__device__ __forceinline__ float wave_sum(float v) {
+template <int LPT> __device__ __forceinline__ float lanes_max(float v) { return lanes_reduce<LPT>(v, [](float a, float b) { return fmaxf(a, b); }); }
+template <int LPT> __device__ __forceinline__ float lanes_sum(float v) { return lanes_reduce<LPT>(v, [](float a, float b) { return a + b; }); }
+template <int LPT> __device__ __forceinline__ double lanes_sum(double v) { return lanes_reduce<LPT>(v, [](double a, double b) { return a + b; }); }
+template <int LPT> __device__ __forceinline__ uint32_t lanes_max(uint32_t v) { return lanes_reduce<LPT>(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
+template <int LPT> __device__ __forceinline__ uint32_t lanes_min(uint32_t v) { return lanes_reduce<LPT>(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; }); }
+
+// fp32 values as unsigned integers in the same order (-0 counts as 0); every number, -inf included, is above 0, which
+// stands for "no candidate"
+__device__ __forceinline__ uint32_t order_key(float x) {
+    const uint32_t u = __float_as_uint(x + 0.0f);
+    return u ^ (uint32_t)(((int32_t)u >> 31) | (int32_t)0x80000000);
+}
+__device__ __forceinline__ float key_value(uint32_t k) { return __uint_as_float(k & 0x80000000u ? k ^ 0x80000000u : ~k); }
+
+// one round of arg-max over (value descending, index ascending): best value and its index; the winner leaves the list
+template <int LPT, int VPL>
+__device__ __forceinline__ void take_best(uint32_t (&key)[VPL], int l, uint32_t& best, uint32_t& idx) {
+    uint32_t m = key[0];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
+    for (int j = 1; j < VPL; ++j) m = key[j] > m ? key[j] : m;
+    best = lanes_max<LPT>(m);
+    uint32_t at = 0xffffffffu;
+#pragma unroll
+    for (int j = VPL - 1; j >= 0; --j) at = key[j] == best ? (uint32_t)(l + LPT * j) : at;
+    idx = lanes_min<LPT>(at);
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) key[j] = (uint32_t)(l + LPT * j) == idx ? 0u : key[j];
 }
 
-template <int VPL>
-__global__ __launch_bounds__(ROUTE_WAVES * 64) void route_topk_kernel(
-    const float* __restrict__ logits, int T, int E, int k, int fn, int norm_topk, float scale,
-    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts) {
-    extern __shared__ int32_t hist[];  // [E]
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    for (int e = threadIdx.x; e < E; e += blockDim.x) hist[e] = 0;
+// ---- the histogram: LDS per workgroup, then, with more than one workgroup, an accumulator in the context that is zero
+// between calls: the last workgroup to arrive takes the totals out and leaves zeros (a fill launch ahead of the kernel
+// costs more than the kernel at small T) -----------------------------------------------------------------------------
+// What is handed over are agent-scope atomics only, complete (at the memory side) once the wave's counter of outstanding
+// memory operations is zero; a device-wide fence instead would write back every dirty line of the L2 in each workgroup
+// (T 16384, E 256: top-k 77 us with it, 17 without).
+__device__ __forceinline__ bool last_workgroup(int* ticket) {   // every thread must call it
+    __shared__ int mine;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-
-    const int t0 = (blockIdx.x * ROUTE_WAVES + wave) * ROUTE_TOKENS_PER_WAVE;
-    for (int tt = 0; tt < ROUTE_TOKENS_PER_WAVE; ++tt) {
-        const int t = t0 + tt;
-        if (t >= T) break;  // uniform per wave
-        const float* l = logits + (int64_t)t * E;
-        float v[VPL];
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) {
-            int e = lane + 64 * j;
-            v[j] = e < E ? l[e] : -INFINITY;
-        }
-        float mx = 0.f, den = 1.f;
-        if (fn == MOE_SCORE_SOFTMAX) {
-            float m = v[0];
-#pragma unroll
-            for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
-            mx = wave_max(m);
-            float s = 0.f;
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) s += (lane + 64 * j < E) ? expf(v[j] - mx) : 0.f;
-            den = wave_sum(s);
-        }
-        // k rounds of arg-max over (logit desc, index asc)
-        uint32_t taken = 0;
-        float my_logit = 0.f;
-        int my_idx = 0;
-        for (int it = 0; it < k; ++it) {
-            float bv = -INFINITY;
-            int bi = 0x7fffffff;
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-                int e = lane + 64 * j;
-                bool ok = e < E && !((taken >> j) & 1u);
-                if (ok && (bi == 0x7fffffff || v[j] > bv)) { bv = v[j]; bi = e; }
-            }
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) {
-                float ov = __shfl_xor(bv, o);
-                int oi = __shfl_xor(bi, o);
-                bool take = (oi != 0x7fffffff) && (bi == 0x7fffffff || ov > bv || (ov == bv && oi < bi));
-                if (take) { bv = ov; bi = oi; }
-            }
-            if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
-            if (lane == it) { my_logit = bv; my_idx = bi; }
-        }
-        float p = 0.f;
-        if (lane < k) p = fn == MOE_SCORE_SOFTMAX ? expf(my_logit - mx) / den : 1.f / (1.f + expf(-my_logit));
-        if (norm_topk) {
-            float tot = wave_sum(lane < k ? p : 0.f);
-            p = p / tot;
-        }
-        if (lane < k) {
-            topk_idx[(int64_t)t * k + lane] = my_idx;
-            topk_prob[(int64_t)t * k + lane] = p * scale;
-            atomicAdd(&hist[my_idx], 1);
-        }
+    if (threadIdx.x == 0) {
+        const int t = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        mine = t + 1 == (int)gridDim.x;
+        if (mine) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (counts)
-        for (int e = threadIdx.x; e < E; e += blockDim.x)
-            if (hist[e]) atomicAdd(&counts[e], hist[e]);
+    return mine != 0;
+}
+__device__ __forceinline__ void finish_counts(const int32_t* hist, int E, int32_t* counts, int* ticket, int32_t* acc) {
+    __syncthreads();
+    if (!counts) return;
+    if (gridDim.x == 1) {
+        for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = hist[e];
+        return;
+    }
+    for (int e = threadIdx.x; e < E; e += blockDim.x)
+        if (hist[e]) atomicAdd(&acc[e], hist[e]);
+    if (last_workgroup(ticket))
+        for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = atomicExch(&acc[e], 0);
 }
 
-extern "C" moe_status moe_route_topk(moe_ctx* ctx, void* stream, const float* logits, int T, int E, int k,
-                                     moe_score fn, int norm_topk, float scale,
-                                     int32_t* topk_idx, float* topk_prob, int32_t* counts) {
-    if (!ctx) return MOE_ERR_ARG;
-    if (!logits || !topk_idx || !topk_prob) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk: NULL pointer");
-    if (T < 0 || E < 1 || E > 64 * ROUTE_MAX_VPL || k < 1 || k > 32 || k > E)
-        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk: need T>=0, 1<=k<=min(E,32), E<=%d (T=%d E=%d k=%d)",
-                 64 * ROUTE_MAX_VPL, T, E, k);
-    if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk: bad score fn");
-    hipStream_t s = (hipStream_t)stream;
-    if (counts) moe_launch_fill_i32(counts, E, 0, s);
-    if (T == 0) return MOE_OK;
-    const int per_block = ROUTE_WAVES * ROUTE_TOKENS_PER_WAVE;
-    dim3 grid((T + per_block - 1) / per_block), block(ROUTE_WAVES * 64);
-    size_t shm = (size_t)E * sizeof(int32_t);
-    const int vpl = (E + 63) / 64;
-#define ROUTE_LAUNCH(V)                                                                                     \
-    hipLaunchKernelGGL(route_topk_kernel<V>, grid, block, shm, s, logits, T, E, k, (int)fn, norm_topk, scale, \
-                       topk_idx, topk_prob, counts)
-    if (vpl <= 1) ROUTE_LAUNCH(1);
-    else if (vpl <= 2) ROUTE_LAUNCH(2);
-    else if (vpl <= 4) ROUTE_LAUNCH(4);
-    else if (vpl <= 8) ROUTE_LAUNCH(8);
-    else ROUTE_LAUNCH(16);
-#undef ROUTE_LAUNCH
-    MOE_LAUNCH_CHECK(ctx, "route_topk_kernel");
-    return MOE_OK;
+template <int LPT, int VPL>
+__global__ __launch_bounds__(1024) void route_topk_kernel(
+    const float* __restrict__ logits, int T, int E, int k, int fn, int norm_topk, float scale,
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts, int* ticket, int32_t* acc) {
+    extern __shared__ int32_t hist[];  // [E]
+    const int l = threadIdx.x & (LPT - 1);
+    const int t = blockIdx.x * (blockDim.x / LPT) + threadIdx.x / LPT;
+    for (int e = threadIdx.x; e < E; e += blockDim.x) hist[e] = 0;
+    const float* row = logits + (int64_t)(t < T ? t : T - 1) * E;
+    float v[VPL];
+    uint32_t key[VPL];
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) v[j] = l + LPT * j < E ? row[l + LPT * j] : -INFINITY;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) key[j] = l + LPT * j < E ? order_key(v[j]) : 0u;
+    float mx = 0.f, den = 1.f;
+    if (fn == MOE_SCORE_SOFTMAX) {
+        float m = v[0];
+#pragma unroll
+        for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
+        mx = lanes_max<LPT>(m);
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) s += l + LPT * j < E ? expf(v[j] - mx) : 0.f;
+        den = lanes_sum<LPT>(s);
+    }
+    float my_logit = 0.f;
+    uint32_t my_idx = 0;
+    for (int it = 0; it < k; ++it) {
+        uint32_t best, idx;
+        take_best<LPT, VPL>(key, l, best, idx);
+        if (l == it) {
+            my_logit = key_value(best);
+            my_idx = idx;
+        }
+    }
+    float p = 0.f;
+    if (l < k) p = fn == MOE_SCORE_SOFTMAX ? expf(my_logit - mx) / den : 1.f / (1.f + expf(-my_logit));
+    if (norm_topk) p = p / lanes_sum<LPT>(p);
+    __syncthreads();  // hist is zero
+    if (l < k && t < T) {
+        const int e = (int)min(my_idx, (uint32_t)E - 1);  // (NaN logits: some expert that exists)
+        topk_idx[(int64_t)t * k + l] = e;
+        topk_prob[(int64_t)t * k + l] = p * scale;
+        atomicAdd(&hist[e], 1);
+    }
+    finish_counts(hist, E, counts, ticket, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -132,184 +155,130 @@ extern "C" moe_status moe_route_topk(moe_ctx* ctx, void* stream, const float* lo
 //   s_e = score(logits)_e;  c_e = s_e + bias_e decides, s_e weighs;
 //   group score = sum of the k / topk_group largest c of the group; keep the topk_group best groups;
 //   select the k largest c among the kept groups' experts; ties to the lower index throughout.
-// Same wave-per-token layout as the plain kernel.  The decisions are taken on fp32 values that do not depend
-// on the precision of a fast exponential: the score is evaluated in double and rounded to fp32 once, the bias
-// add and the group sums (largest first) are single fp32 additions.  The group scores are formed by one lane
-// per group from the wave's c values in LDS (each wave has its own region, so program order is all the
-// synchronisation needed); groups and experts are then chosen by the same butterfly arg-max rounds.
+// The decisions are taken on fp32 values that do not depend on the precision of a fast exponential: the score is
+// evaluated in double and rounded to fp32 once, the bias add and the group sums (largest first) are single fp32
+// additions.  The c values of a token go through LDS for the group scores: `lpg` lanes share a group, each looking at
+// every lpg-th member.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    return v;
-}
-// one round of arg-max over (value desc, index asc) across the wave; idx 0x7fffffff = no candidate
-__device__ __forceinline__ void wave_argmax(float& bv, int& bi) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(bv, o);
-        const int oi = __shfl_xor(bi, o);
-        const bool take = (oi != 0x7fffffff) && (bi == 0x7fffffff || ov > bv || (ov == bv && oi < bi));
-        if (take) { bv = ov; bi = oi; }
-    }
-}
-
-template <int VPL>
-__global__ __launch_bounds__(ROUTE_WAVES * 64) void route_topk_grouped_kernel(
+template <int LPT, int VPL>
+__global__ __launch_bounds__(256) void route_topk_grouped_kernel(
     const float* __restrict__ logits, const float* __restrict__ bias, int T, int E, int k, int n_group, int topk_group,
-    int fn, int norm_topk, float scale,
-    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts) {
-    extern __shared__ int32_t hist[];  // [E] histogram, then ROUTE_WAVES x [E] floats
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    float* cw = (float*)(hist + E) + wave * E;
+    int lpg, uint32_t gs_magic, int fn, int norm_topk, float scale,
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts, int* ticket, int32_t* acc) {
+    extern __shared__ int32_t hist[];  // [E] histogram, then one [E + E / 16 + 1] row of c per token of the workgroup
+    const int l = threadIdx.x & (LPT - 1);
+    const int t = blockIdx.x * (blockDim.x / LPT) + threadIdx.x / LPT;
     for (int e = threadIdx.x; e < E; e += blockDim.x) hist[e] = 0;
-    __syncthreads();
     const int gs = E / n_group, m = k / topk_group;
-
-    const int t0 = (blockIdx.x * ROUTE_WAVES + wave) * ROUTE_TOKENS_PER_WAVE;
-    for (int tt = 0; tt < ROUTE_TOKENS_PER_WAVE; ++tt) {
-        const int t = t0 + tt;
-        if (t >= T) break;  // uniform per wave
-        const float* l = logits + (int64_t)t * E;
-        float v[VPL], sc[VPL], c[VPL];
+    const float* row = logits + (int64_t)(t < T ? t : T - 1) * E;
+    float v[VPL], sc[VPL];
+    uint32_t key[VPL];
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) v[j] = l + LPT * j < E ? row[l + LPT * j] : -INFINITY;
+    if (fn == MOE_SCORE_SOFTMAX) {
+        float mf = v[0];
+#pragma unroll
+        for (int j = 1; j < VPL; ++j) mf = fmaxf(mf, v[j]);
+        const double mx = (double)lanes_max<LPT>(mf);
+        double ex[VPL], part = 0.0;
 #pragma unroll
         for (int j = 0; j < VPL; ++j) {
-            const int e = lane + 64 * j;
-            v[j] = e < E ? l[e] : -INFINITY;
+            ex[j] = l + LPT * j < E ? exp((double)v[j] - mx) : 0.0;
+            part += ex[j];
         }
-        if (fn == MOE_SCORE_SOFTMAX) {
-            float mf = v[0];
+        const double den = lanes_sum<LPT>(part);
 #pragma unroll
-            for (int j = 1; j < VPL; ++j) mf = fmaxf(mf, v[j]);
-            const double mx = (double)wave_max(mf);
-            double part = 0.0;
+        for (int j = 0; j < VPL; ++j) sc[j] = (float)(ex[j] / den);
+    } else {
 #pragma unroll
-            for (int j = 0; j < VPL; ++j) part += (lane + 64 * j < E) ? exp((double)v[j] - mx) : 0.0;
-            const double den = wave_sum_f64(part);
+        for (int j = 0; j < VPL; ++j) sc[j] = (float)(1.0 / (1.0 + exp(-(double)v[j])));
+    }
+    float* const cw = (float*)(hist + E) + (threadIdx.x / LPT) * (E + E / 16 + 1);
+    auto at = [](int e) { return e + (e >> 4); };  // (a float of padding every 16 keeps the groups on different banks)
 #pragma unroll
-            for (int j = 0; j < VPL; ++j) sc[j] = (float)(exp((double)v[j] - mx) / den);
-        } else {
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) sc[j] = (float)(1.0 / (1.0 + exp(-(double)v[j])));
-        }
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) {
-            const int e = lane + 64 * j;
-            c[j] = (bias && e < E) ? sc[j] + bias[e] : sc[j];
-        }
+    for (int j = 0; j < VPL; ++j) {
+        const int e = l + LPT * j;
+        const float c = (bias && e < E) ? sc[j] + bias[e] : sc[j];
+        key[j] = e < E ? order_key(c) : 0u;
+        if (n_group > 1 && e < E) cw[at(e)] = c;
+    }
 
-        // ---- groups to keep ----
-        uint64_t keep = ~0ull;
-        if (n_group > 1) {
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-                const int e = lane + 64 * j;
-                if (e < E) cw[e] = c[j];
-            }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            // lane g: sum of the m largest c of group g, largest first; round r takes the best element that
-            // comes after round r-1's pick in (value desc, index asc) order
-            float gsum = -INFINITY;
-            int gi = 0x7fffffff;
-            if (lane < n_group) {
-                float pv = INFINITY;
-                int pi = -1;
-                gsum = 0.f;
-                for (int r = 0; r < m; ++r) {
-                    float bv = -INFINITY;
-                    int bi = 0x7fffffff;
-                    for (int x = 0; x < gs; ++x) {
-                        const float cv = cw[lane * gs + x];
-                        const bool after = cv < pv || (cv == pv && x > pi);
-                        if (after && (bi == 0x7fffffff || cv > bv)) { bv = cv; bi = x; }
+    // ---- groups to keep ----
+    if (n_group > 1) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // (a token's lanes are of one wavefront: program order suffices)
+        // sum of the m largest c of the lane's group, largest first; round r takes the best element that comes after
+        // round r - 1's pick in (value desc, index asc) order
+        const int g = l / lpg, sub = l & (lpg - 1);
+        uint32_t gkey = 0;
+        float gsum = 0.f, pv = INFINITY;
+        int pi = -1;
+        for (int r = 0; r < m; ++r) {
+            uint32_t bk = 0, bi = 0x7fffffff;
+            if (g < n_group) {
+                for (int x = sub; x < gs; x += lpg) {
+                    const float cv = cw[at(g * gs + x)];
+                    const uint32_t ck = order_key(cv);
+                    if ((cv < pv || (cv == pv && x > pi)) && ck > bk) {
+                        bk = ck;
+                        bi = x;
                     }
-                    gsum = r == 0 ? bv : gsum + bv;
-                    pv = bv;
-                    pi = bi;
                 }
-                gi = lane;
             }
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            bool kept = false;
-            for (int r = 0; r < topk_group; ++r) {
-                float bv = kept ? -INFINITY : gsum;
-                int bi = kept ? 0x7fffffff : gi;
-                wave_argmax(bv, bi);
-                if (bi == lane) kept = true;
+            for (int o = 1; o < lpg; o <<= 1) {
+                const uint32_t ok = __shfl_xor(bk, o), oi = __shfl_xor(bi, o);
+                if (ok > bk || (ok == bk && oi < bi)) {
+                    bk = ok;
+                    bi = oi;
+                }
             }
-            keep = __ballot(kept);
+            pv = key_value(bk);
+            pi = (int)bi;
+            gsum = r == 0 ? pv : gsum + pv;
         }
-
-        // ---- k rounds of arg-max over c among the kept groups ----
-        uint32_t taken = 0;
-        float my_s = 0.f;
-        int my_idx = 0;
-        for (int it = 0; it < k; ++it) {
-            float bv = -INFINITY;
-            int bi = 0x7fffffff;
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-                const int e = lane + 64 * j;
-                const bool ok = e < E && !((taken >> j) & 1u) && ((keep >> (e / gs)) & 1ull);
-                if (ok && (bi == 0x7fffffff || c[j] > bv)) { bv = c[j]; bi = e; }
+        if (g < n_group) gkey = order_key(gsum);
+        bool kept = false;
+        for (int r = 0; r < topk_group; ++r) {
+            const uint32_t best = lanes_max<LPT>(gkey);
+            const uint32_t win = lanes_min<LPT>(gkey == best ? (uint32_t)g : 0xffffffffu);
+            if ((uint32_t)g == win) {
+                kept = true;
+                gkey = 0;
             }
-            wave_argmax(bv, bi);
-            float sv = 0.f;
-#pragma unroll
-            for (int j = 0; j < VPL; ++j)
-                if (j == (bi >> 6)) sv = sc[j];
-            sv = __shfl(sv, bi & 63);  // the winner's unbiased score
-            if ((bi & 63) == lane) taken |= 1u << (bi >> 6);
-            if (lane == it) { my_s = sv; my_idx = bi; }
         }
-        float p = lane < k ? my_s : 0.f;
-        if (norm_topk) p = p / wave_sum(p);
-        if (lane < k) {
-            topk_idx[(int64_t)t * k + lane] = my_idx;
-            topk_prob[(int64_t)t * k + lane] = p * scale;
-            atomicAdd(&hist[my_idx], 1);
+        // bit lpg * g of the token's lanes = group g is kept
+        const uint64_t b = __ballot(kept) >> (LPT == 64 ? 0 : (threadIdx.x & 63 & ~(LPT - 1)));
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) {
+            const int eg = (int)(((uint32_t)(l + LPT * j) * gs_magic) >> 20);  // (l + LPT j) / gs
+            if (l + LPT * j < E && !((b >> (eg * lpg)) & 1ull)) key[j] = 0u;
         }
     }
-    __syncthreads();
-    if (counts)
-        for (int e = threadIdx.x; e < E; e += blockDim.x)
-            if (hist[e]) atomicAdd(&counts[e], hist[e]);
-}
 
-extern "C" moe_status moe_route_topk_grouped(moe_ctx* ctx, void* stream, const float* logits, const float* expert_bias,
-                                             int T, int E, int k, int n_group, int topk_group,
-                                             moe_score fn, int norm_topk, float scale,
-                                             int32_t* topk_idx, float* topk_prob, int32_t* counts) {
-    if (!ctx) return MOE_ERR_ARG;
-    if (!logits || !topk_idx || !topk_prob) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_grouped: NULL pointer");
-    if (T < 0 || E < 1 || E > 64 * ROUTE_MAX_VPL || k < 1 || k > 32 || k > E)
-        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_grouped: need T>=0, 1<=k<=min(E,32), E<=%d (T=%d E=%d k=%d)",
-                 64 * ROUTE_MAX_VPL, T, E, k);
-    if (n_group < 1 || n_group > 64 || E % n_group || topk_group < 1 || topk_group > n_group || k % topk_group ||
-        k / topk_group > E / n_group)
-        MOE_FAIL(ctx, MOE_ERR_ARG,
-                 "moe_route_topk_grouped: need 1<=topk_group<=n_group<=64, E %% n_group == 0, k %% topk_group == 0 and "
-                 "k/topk_group <= E/n_group (E=%d k=%d n_group=%d topk_group=%d)", E, k, n_group, topk_group);
-    if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_grouped: bad score fn");
-    hipStream_t s = (hipStream_t)stream;
-    if (counts) moe_launch_fill_i32(counts, E, 0, s);
-    if (T == 0) return MOE_OK;
-    const int per_block = ROUTE_WAVES * ROUTE_TOKENS_PER_WAVE;
-    dim3 grid((T + per_block - 1) / per_block), block(ROUTE_WAVES * 64);
-    size_t shm = (size_t)E * sizeof(int32_t) * (1 + ROUTE_WAVES);
-    const int vpl = (E + 63) / 64;
-#define ROUTE_LAUNCH(V)                                                                                            \
-    hipLaunchKernelGGL(route_topk_grouped_kernel<V>, grid, block, shm, s, logits, expert_bias, T, E, k, n_group,   \
-                       topk_group, (int)fn, norm_topk, scale, topk_idx, topk_prob, counts)
-    if (vpl <= 1) ROUTE_LAUNCH(1);
-    else if (vpl <= 2) ROUTE_LAUNCH(2);
-    else if (vpl <= 4) ROUTE_LAUNCH(4);
-    else if (vpl <= 8) ROUTE_LAUNCH(8);
-    else ROUTE_LAUNCH(16);
-#undef ROUTE_LAUNCH
-    MOE_LAUNCH_CHECK(ctx, "route_topk_grouped_kernel");
-    return MOE_OK;
+    // ---- the k best among the kept groups ----
+    float my_s = 0.f;
+    uint32_t my_idx = 0;
+    for (int it = 0; it < k; ++it) {
+        uint32_t best, idx;
+        take_best<LPT, VPL>(key, l, best, idx);
+        uint32_t sv = 0;  // the winner's unbiased score, from the lane that holds it
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) sv = (uint32_t)(l + LPT * j) == idx ? __float_as_uint(sc[j]) : sv;
+        sv = lanes_max<LPT>(sv);  // (scores are not negative: their bits order like the values, the other lanes hold 0)
+        if (l == it) {
+            my_s = __uint_as_float(sv);
+            my_idx = idx;
+        }
+    }
+    float p = l < k ? my_s : 0.f;
+    if (norm_topk) p = p / lanes_sum<LPT>(p);
+    __syncthreads();  // hist is zero
+    if (l < k && t < T) {
+        const int e = (int)min(my_idx, (uint32_t)E - 1);  // (NaN logits: some expert that exists)
+        topk_idx[(int64_t)t * k + l] = e;
+        topk_prob[(int64_t)t * k + l] = p * scale;
+        atomicAdd(&hist[e], 1);
+    }
+    finish_counts(hist, E, counts, ticket, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -317,109 +286,73 @@ extern "C" moe_status moe_route_topk_grouped(moe_ctx* ctx, void* stream, const f
 //   w_s = scale * q_s / D,  q_s = score of the s-th selected expert,  D = sum_s q_s (norm_topk) or 1
 //   dq_s = scale * (dw_s / D - [norm] <dw, q> / D^2)
 //   softmax: dl_j = p_j * ([j selected] dq_j - <dq, q>)      sigmoid: dl_j = [j selected] dq_j * q_j (1 - q_j)
-// One wavefront per token, same register layout as the forward kernel; lane s < k holds slot s.
+// Same layout as the forward kernel; lane s < k of a token's group holds slot s.
 // ---------------------------------------------------------------------------
-template <int VPL>
-__global__ __launch_bounds__(ROUTE_WAVES * 64) void route_topk_bwd_kernel(
+template <int LPT, int VPL>
+__global__ __launch_bounds__(256) void route_topk_bwd_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ topk_idx, const float* __restrict__ dprob,
     int T, int E, int k, int fn, int norm_topk, float scale, float* __restrict__ dlogits) {
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int t0 = (blockIdx.x * ROUTE_WAVES + wave) * ROUTE_TOKENS_PER_WAVE;
-    for (int tt = 0; tt < ROUTE_TOKENS_PER_WAVE; ++tt) {
-        const int t = t0 + tt;
-        if (t >= T) break;  // uniform per wave
-        const float* l = logits + (int64_t)t * E;
-        float v[VPL];
+    const int l = threadIdx.x & (LPT - 1);
+    const int t = blockIdx.x * (blockDim.x / LPT) + threadIdx.x / LPT;
+    const int tr = t < T ? t : T - 1;  // (whole wavefronts stay together: a token behind the last one computes, unused)
+    const float* row = logits + (int64_t)tr * E;
+    float v[VPL];
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) v[j] = l + LPT * j < E ? row[l + LPT * j] : -INFINITY;
+    // slot s lives in lane s: its expert, its score q_s and the incoming gradient
+    int my_idx = l < k ? topk_idx[(int64_t)tr * k + l] : -1;
+    if (my_idx < 0 || my_idx >= E) my_idx = -1;  // a slot that names no expert of this router contributes nothing
+    const float dw = my_idx >= 0 ? dprob[(int64_t)tr * k + l] : 0.f;
+    const float lg = my_idx >= 0 ? row[my_idx] : 0.f;
+    float mx = 0.f, den = 1.f;
+    if (fn == MOE_SCORE_SOFTMAX) {
+        float m = v[0];
+#pragma unroll
+        for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
+        mx = lanes_max<LPT>(m);
+        float s = 0.f;
 #pragma unroll
         for (int j = 0; j < VPL; ++j) {
-            const int e = lane + 64 * j;
-            v[j] = e < E ? l[e] : -INFINITY;
+            v[j] = l + LPT * j < E ? expf(v[j] - mx) : 0.f;
+            s += v[j];
         }
-        float mx = 0.f, den = 1.f;
-        if (fn == MOE_SCORE_SOFTMAX) {
-            float m = v[0];
+        den = lanes_sum<LPT>(s);
+    }
+    float q = 0.f;
+    if (my_idx >= 0) q = fn == MOE_SCORE_SOFTMAX ? expf(lg - mx) / den : 1.f / (1.f + expf(-lg));
+    float dq = scale * dw;
+    if (norm_topk) {
+        const float D = lanes_sum<LPT>(q);
+        const float dwq = lanes_sum<LPT>(dw * q);
+        dq = my_idx >= 0 ? scale * (dw / D - dwq / (D * D)) : 0.f;
+    }
+    const float dqq = lanes_sum<LPT>(dq * q);  // <dq, q>
+    // every lane collects the dq of the selected experts it owns
+    float gsel[VPL];
 #pragma unroll
-            for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
-            mx = wave_max(m);
-            float s = 0.f;
+    for (int j = 0; j < VPL; ++j) gsel[j] = 0.f;
+    for (int s = 0; s < k; ++s) {
+        const int e = __shfl(my_idx, s, LPT);
+        const float d = __shfl(dq, s, LPT);
 #pragma unroll
-            for (int j = 0; j < VPL; ++j) s += (lane + 64 * j < E) ? expf(v[j] - mx) : 0.f;
-            den = wave_sum(s);
-        }
-        // slot s lives in lane s: its expert, its score q_s and the incoming gradient
-        int my_idx = lane < k ? topk_idx[(int64_t)t * k + lane] : -1;
-        if (my_idx < 0 || my_idx >= E) my_idx = -1;  // a slot that names no expert of this router contributes nothing
-        const float dw = my_idx >= 0 ? dprob[(int64_t)t * k + lane] : 0.f;
-        float q = 0.f;
-        if (my_idx >= 0) {
-            const float lg = l[my_idx];
-            q = fn == MOE_SCORE_SOFTMAX ? expf(lg - mx) / den : 1.f / (1.f + expf(-lg));
-        }
-        float dq = scale * dw;
-        if (norm_topk) {
-            const float D = wave_sum(q);
-            const float dwq = wave_sum(dw * q);
-            dq = my_idx >= 0 ? scale * (dw / D - dwq / (D * D)) : 0.f;
-        }
-        const float dqq = wave_sum(dq * q);  // <dq, q>
-        // every lane collects the dq of the selected experts it owns
-        float gsel[VPL];
+        for (int j = 0; j < VPL; ++j) gsel[j] += e == l + LPT * j ? d : 0.f;
+    }
+    if (t >= T) return;
+    float* o = dlogits + (int64_t)t * E;
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) gsel[j] = 0.f;
-        for (int s = 0; s < k; ++s) {
-            const int e = __shfl(my_idx, s);
-            const float d = __shfl(dq, s);
-            if (e >= 0 && (e & 63) == lane) {
-#pragma unroll
-                for (int j = 0; j < VPL; ++j)
-                    if ((e >> 6) == j) gsel[j] += d;
+    for (int j = 0; j < VPL; ++j) {
+        const int e = l + LPT * j;
+        if (e < E) {
+            float r;
+            if (fn == MOE_SCORE_SOFTMAX) {
+                r = v[j] / den * (gsel[j] - dqq);
+            } else {
+                const float sg = 1.f / (1.f + expf(-v[j]));
+                r = gsel[j] * sg * (1.f - sg);
             }
-        }
-        float* o = dlogits + (int64_t)t * E;
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) {
-            const int e = lane + 64 * j;
-            if (e < E) {
-                float r;
-                if (fn == MOE_SCORE_SOFTMAX) {
-                    const float p = expf(v[j] - mx) / den;
-                    r = p * (gsel[j] - dqq);
-                } else {
-                    const float sg = 1.f / (1.f + expf(-v[j]));
-                    r = gsel[j] * sg * (1.f - sg);
-                }
-                o[e] = r;
-            }
+            o[e] = r;
         }
     }
-}
-
-extern "C" moe_status moe_route_topk_bwd(moe_ctx* ctx, void* stream, const float* logits, const int32_t* topk_idx,
-                                         const float* dprob, int T, int E, int k, moe_score fn, int norm_topk,
-                                         float scale, float* dlogits) {
-    if (!ctx) return MOE_ERR_ARG;
-    if (!logits || !topk_idx || !dprob || !dlogits) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_bwd: NULL pointer");
-    if (T < 0 || E < 1 || E > 64 * ROUTE_MAX_VPL || k < 1 || k > 32 || k > E)
-        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_bwd: need T>=0, 1<=k<=min(E,32), E<=%d (T=%d E=%d k=%d)",
-                 64 * ROUTE_MAX_VPL, T, E, k);
-    if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_bwd: bad score fn");
-    if (T == 0) return MOE_OK;
-    hipStream_t s = (hipStream_t)stream;
-    const int per_block = ROUTE_WAVES * ROUTE_TOKENS_PER_WAVE;
-    dim3 grid((T + per_block - 1) / per_block), block(ROUTE_WAVES * 64);
-    const int vpl = (E + 63) / 64;
-#define ROUTE_BWD_LAUNCH(V)                                                                                       \
-    hipLaunchKernelGGL(route_topk_bwd_kernel<V>, grid, block, 0, s, logits, topk_idx, dprob, T, E, k, (int)fn, norm_topk, \
-                       scale, dlogits)
-    if (vpl <= 1) ROUTE_BWD_LAUNCH(1);
-    else if (vpl <= 2) ROUTE_BWD_LAUNCH(2);
-    else if (vpl <= 4) ROUTE_BWD_LAUNCH(4);
-    else if (vpl <= 8) ROUTE_BWD_LAUNCH(8);
-    else ROUTE_BWD_LAUNCH(16);
-#undef ROUTE_BWD_LAUNCH
-    MOE_LAUNCH_CHECK(ctx, "route_topk_bwd_kernel");
-    return MOE_OK;
 }
 
 // ---------------------------------------------------------------------------
@@ -429,78 +362,183 @@ extern "C" moe_status moe_route_topk_bwd(moe_ctx* ctx, void* stream, const float
 //   loss   = coeff E sum_e f_e P_e,  f_e = counts[e] / (T k),  P_e = (1/T) sum_t p[t,e]
 //          = sum_t <w, p[t,:]>,      w_e = coeff E counts[e] / (T^2 k)
 //   dl[t,j] = g p_j (w_j - <w, p>) (softmax),  g (1 - sg_j) p_j (w_j - <w, p>) (sigmoid),  g = dloss
-// so both the loss and the gradient need only per-token quantities: one wavefront per token in the router's
-// register layout; the per-token terms are summed in double, per workgroup, into the context's workspace and a
-// one-wave kernel adds the partial sums in a fixed order (run-to-run identical, no floating-point atomics).
+// so both the loss and the gradient need only per-token quantities.  The per-token terms are summed in double: the
+// tokens of a workgroup in order, one partial sum per workgroup (32 tokens) into the context's workspace, and the last
+// workgroup to arrive adds the partial sums in a fixed order (run-to-run identical, no floating-point atomics).
 // ---------------------------------------------------------------------------
-template <int VPL>
-__global__ __launch_bounds__(ROUTE_WAVES * 64) void aux_loss_kernel(
+#define AUX_TOKENS 32  // tokens per workgroup (and 8 bytes of workspace for each)
+template <int LPT, int VPL>
+__global__ __launch_bounds__(AUX_TOKENS * LPT > 1024 ? 1024 : AUX_TOKENS * LPT) void aux_loss_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ counts, int T, int E, int fn, float wscale, float g,
-    int accumulate, float* __restrict__ dlogits, double* __restrict__ partial) {
-    extern __shared__ __attribute__((aligned(16))) float wsh[];  // [E] weights, then ROUTE_WAVES doubles
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    for (int e = threadIdx.x; e < E; e += blockDim.x) wsh[e] = wscale * (float)counts[e];
-    __syncthreads();
+    int accumulate, float* __restrict__ dlogits, double* partial, float* __restrict__ loss, int* ticket) {
+    __shared__ double terms[AUX_TOKENS];
+    const int l = threadIdx.x & (LPT - 1);
     float w[VPL];
 #pragma unroll
-    for (int j = 0; j < VPL; ++j) w[j] = lane + 64 * j < E ? wsh[lane + 64 * j] : 0.f;
-    double acc = 0.0;
-    const int t0 = (blockIdx.x * ROUTE_WAVES + wave) * ROUTE_TOKENS_PER_WAVE;
-    for (int tt = 0; tt < ROUTE_TOKENS_PER_WAVE; ++tt) {
-        const int t = t0 + tt;
-        if (t >= T) break;  // uniform per wave
-        const float* l = logits + (int64_t)t * E;
-        float v[VPL], p[VPL], sg[VPL];
+    for (int j = 0; j < VPL; ++j) w[j] = l + LPT * j < E ? wscale * (float)counts[l + LPT * j] : 0.f;
+    for (int i = threadIdx.x / LPT; i < AUX_TOKENS; i += blockDim.x / LPT) {
+        const int t = blockIdx.x * AUX_TOKENS + i;
+        const int tr = t < T ? t : T - 1;
+        const float* row = logits + (int64_t)tr * E;
+        float v[VPL], p[VPL], old[VPL];
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) v[j] = lane + 64 * j < E ? l[lane + 64 * j] : -INFINITY;
+        for (int j = 0; j < VPL; ++j) v[j] = l + LPT * j < E ? row[l + LPT * j] : -INFINITY;
+        if (dlogits && accumulate) {
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) old[j] = l + LPT * j < E ? dlogits[(int64_t)tr * E + l + LPT * j] : 0.f;
+        }
         float part = 0.f;
         if (fn == MOE_SCORE_SOFTMAX) {
             float m = v[0];
 #pragma unroll
             for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
-            m = wave_max(m);
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) { p[j] = lane + 64 * j < E ? expf(v[j] - m) : 0.f; part += p[j]; }
-        } else {
-#pragma unroll
-            for (int j = 0; j < VPL; ++j) { sg[j] = lane + 64 * j < E ? 1.f / (1.f + expf(-v[j])) : 0.f; p[j] = sg[j]; part += p[j]; }
-        }
-        const float inv = 1.f / wave_sum(part);
-        float d = 0.f;
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) { p[j] *= inv; d += w[j] * p[j]; }
-        d = wave_sum(d);  // <w, p[t,:]>
-        acc += (double)d;
-        if (dlogits) {
+            m = lanes_max<LPT>(m);
 #pragma unroll
             for (int j = 0; j < VPL; ++j) {
-                const int e = lane + 64 * j;
+                p[j] = l + LPT * j < E ? expf(v[j] - m) : 0.f;
+                part += p[j];
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) {
+                v[j] = l + LPT * j < E ? 1.f / (1.f + expf(-v[j])) : 0.f;
+                p[j] = v[j];
+                part += p[j];
+            }
+        }
+        const float inv = 1.f / lanes_sum<LPT>(part);
+        float d = 0.f;
+#pragma unroll
+        for (int j = 0; j < VPL; ++j) {
+            p[j] *= inv;
+            d += w[j] * p[j];
+        }
+        d = lanes_sum<LPT>(d);  // <w, p[t,:]>
+        if (l == 0) terms[i] = t < T ? (double)d : 0.0;
+        if (dlogits && t < T) {
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) {
+                const int e = l + LPT * j;
                 if (e < E) {
                     float gr = g * p[j] * (w[j] - d);
-                    if (fn != MOE_SCORE_SOFTMAX) gr *= 1.f - sg[j];
-                    float* o = dlogits + (int64_t)t * E + e;
-                    *o = accumulate ? *o + gr : gr;
+                    if (fn != MOE_SCORE_SOFTMAX) gr *= 1.f - v[j];
+                    dlogits[(int64_t)t * E + e] = accumulate ? old[j] + gr : gr;
                 }
             }
         }
     }
-    double* wpart = (double*)(wsh + ((E + 1) & ~1));
-    if (lane == 0) wpart[wave] = acc;  // every lane holds the same sum
     __syncthreads();
     if (threadIdx.x == 0) {
         double sum = 0.0;
-        for (int i = 0; i < ROUTE_WAVES; ++i) sum += wpart[i];
-        partial[blockIdx.x] = sum;
+        for (int i = 0; i < AUX_TOKENS; ++i) sum += terms[i];
+        if (gridDim.x == 1) *loss = (float)sum;
+        else __hip_atomic_store(&partial[blockIdx.x], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (gridDim.x == 1 || !last_workgroup(ticket)) return;
+    if (threadIdx.x < 64) {
+        double a = 0.0;
+        for (int i = threadIdx.x; i < (int)gridDim.x; i += 64)
+            a += __hip_atomic_load(&partial[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        a = lanes_sum<64>(a);
+        if (threadIdx.x == 0) *loss = (float)a;
     }
 }
 
-__global__ __launch_bounds__(64) void aux_loss_sum_kernel(const double* __restrict__ partial, int n, float* __restrict__ loss) {
-    double a = 0.0;
-    for (int i = threadIdx.x; i < n; i += 64) a += partial[i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
-    if (threadIdx.x == 0) *loss = (float)a;
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+// Lanes per token and values per lane.  16 lanes where a token's experts, slots and groups fit them: four tokens share
+// the instructions of a wavefront, and their reductions stay inside DPP rows.
+static inline bool route_narrow(int E, int k, int n_group) { return E <= 256 && k <= 16 && n_group <= 16; }
+#define ROUTE_CASES(KERNEL, ...)                                                                                  \
+    do {                                                                                                          \
+        const int vpl = (E + lpt - 1) / lpt;                                                                      \
+        if (lpt == 16) {                                                                                          \
+            if (vpl <= 1) hipLaunchKernelGGL((KERNEL<16, 1>), __VA_ARGS__);                                       \
+            else if (vpl <= 2) hipLaunchKernelGGL((KERNEL<16, 2>), __VA_ARGS__);                                  \
+            else if (vpl <= 4) hipLaunchKernelGGL((KERNEL<16, 4>), __VA_ARGS__);                                  \
+            else if (vpl <= 8) hipLaunchKernelGGL((KERNEL<16, 8>), __VA_ARGS__);                                  \
+            else hipLaunchKernelGGL((KERNEL<16, 16>), __VA_ARGS__);                                               \
+        } else {                                                                                                  \
+            if (vpl <= 1) hipLaunchKernelGGL((KERNEL<64, 1>), __VA_ARGS__);                                       \
+            else if (vpl <= 4) hipLaunchKernelGGL((KERNEL<64, 4>), __VA_ARGS__);                                  \
+            else if (vpl <= 8) hipLaunchKernelGGL((KERNEL<64, 8>), __VA_ARGS__);                                  \
+            else hipLaunchKernelGGL((KERNEL<64, 16>), __VA_ARGS__);                                               \
+        }                                                                                                         \
+    } while (0)
+
+extern "C" moe_status moe_route_topk(moe_ctx* ctx, void* stream, const float* logits, int T, int E, int k,
+                                     moe_score fn, int norm_topk, float scale,
+                                     int32_t* topk_idx, float* topk_prob, int32_t* counts) {
+    if (!ctx) return MOE_ERR_ARG;
+    if (!logits || !topk_idx || !topk_prob) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk: NULL pointer");
+    if (T < 0 || E < 1 || E > ROUTE_MAX_E || k < 1 || k > 32 || k > E)
+        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk: need T>=0, 1<=k<=min(E,32), E<=%d (T=%d E=%d k=%d)", ROUTE_MAX_E, T, E, k);
+    if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk: bad score fn");
+    hipStream_t s = (hipStream_t)stream;
+    if (T == 0) {
+        if (counts) moe_launch_fill_i32(counts, E, 0, s);
+        return MOE_OK;
+    }
+    const int lpt = route_narrow(E, k, 1) ? 16 : 64;
+    // many tokens: large workgroups, so that fewer of them add their histograms to the shared one
+    const int threads = T > 4096 ? 1024 : 256, tokens = threads / lpt;
+    const dim3 grid((T + tokens - 1) / tokens), block(threads);
+    ROUTE_CASES(route_topk_kernel, grid, block, (size_t)E * sizeof(int32_t), s, logits, T, E, k, (int)fn, norm_topk, scale,
+                topk_idx, topk_prob, counts, ctx->aux + MOE_AUX_ROUTE_TICKET, (int32_t*)(ctx->aux + MOE_AUX_ROUTE_COUNTS));
+    MOE_LAUNCH_CHECK(ctx, "route_topk_kernel");
+    return MOE_OK;
+}
+
+extern "C" moe_status moe_route_topk_grouped(moe_ctx* ctx, void* stream, const float* logits, const float* expert_bias,
+                                             int T, int E, int k, int n_group, int topk_group,
+                                             moe_score fn, int norm_topk, float scale,
+                                             int32_t* topk_idx, float* topk_prob, int32_t* counts) {
+    if (!ctx) return MOE_ERR_ARG;
+    if (!logits || !topk_idx || !topk_prob) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_grouped: NULL pointer");
+    if (T < 0 || E < 1 || E > ROUTE_MAX_E || k < 1 || k > 32 || k > E)
+        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_grouped: need T>=0, 1<=k<=min(E,32), E<=%d (T=%d E=%d k=%d)",
+                 ROUTE_MAX_E, T, E, k);
+    if (n_group < 1 || n_group > 64 || E % n_group || topk_group < 1 || topk_group > n_group || k % topk_group ||
+        k / topk_group > E / n_group)
+        MOE_FAIL(ctx, MOE_ERR_ARG,
+                 "moe_route_topk_grouped: need 1<=topk_group<=n_group<=64, E %% n_group == 0, k %% topk_group == 0 and "
+                 "k/topk_group <= E/n_group (E=%d k=%d n_group=%d topk_group=%d)", E, k, n_group, topk_group);
+    if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_grouped: bad score fn");
+    hipStream_t s = (hipStream_t)stream;
+    if (T == 0) {
+        if (counts) moe_launch_fill_i32(counts, E, 0, s);
+        return MOE_OK;
+    }
+    const int lpt = route_narrow(E, k, n_group) ? 16 : 64;
+    int lpg = lpt;  // lanes per group: the largest power of two with room for all groups
+    while (lpg > 1 && lpg * n_group > lpt) lpg >>= 1;
+    const int tokens = 256 / lpt, gs = E / n_group;
+    const uint32_t gs_magic = ((1u << 20) + gs - 1) / gs;  // (e * gs_magic) >> 20 == e / gs for e < 1024: the excess, e * gs at most, stays below 2^20
+    const dim3 grid((T + tokens - 1) / tokens), block(256);
+    const size_t shm = (size_t)E * sizeof(int32_t) + (size_t)tokens * (E + E / 16 + 1) * sizeof(float);
+    ROUTE_CASES(route_topk_grouped_kernel, grid, block, shm, s, logits, expert_bias, T, E, k, n_group, topk_group, lpg, gs_magic,
+                (int)fn, norm_topk, scale, topk_idx, topk_prob, counts, ctx->aux + MOE_AUX_ROUTE_TICKET,
+                (int32_t*)(ctx->aux + MOE_AUX_ROUTE_COUNTS));
+    MOE_LAUNCH_CHECK(ctx, "route_topk_grouped_kernel");
+    return MOE_OK;
+}
+
+extern "C" moe_status moe_route_topk_bwd(moe_ctx* ctx, void* stream, const float* logits, const int32_t* topk_idx,
+                                         const float* dprob, int T, int E, int k, moe_score fn, int norm_topk,
+                                         float scale, float* dlogits) {
+    if (!ctx) return MOE_ERR_ARG;
+    if (!logits || !topk_idx || !dprob || !dlogits) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_bwd: NULL pointer");
+    if (T < 0 || E < 1 || E > ROUTE_MAX_E || k < 1 || k > 32 || k > E)
+        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_bwd: need T>=0, 1<=k<=min(E,32), E<=%d (T=%d E=%d k=%d)", ROUTE_MAX_E, T, E, k);
+    if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_route_topk_bwd: bad score fn");
+    if (T == 0) return MOE_OK;
+    const int lpt = route_narrow(E, k, 1) ? 16 : 64, tokens = 256 / lpt;
+    const dim3 grid((T + tokens - 1) / tokens), block(256);
+    ROUTE_CASES(route_topk_bwd_kernel, grid, block, 0, (hipStream_t)stream, logits, topk_idx, dprob, T, E, k, (int)fn, norm_topk,
+                scale, dlogits);
+    MOE_LAUNCH_CHECK(ctx, "route_topk_bwd_kernel");
+    return MOE_OK;
 }
 
 extern "C" moe_status moe_aux_loss(moe_ctx* ctx, void* stream, const float* logits, const int32_t* counts,
@@ -508,29 +546,18 @@ extern "C" moe_status moe_aux_loss(moe_ctx* ctx, void* stream, const float* logi
                                    float* loss, float* dlogits) {
     if (!ctx) return MOE_ERR_ARG;
     if (!logits || !counts || !loss) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_aux_loss: NULL pointer");
-    if (T < 1 || E < 1 || E > 64 * ROUTE_MAX_VPL || k < 1)
-        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_aux_loss: need T>=1, 1<=E<=%d, k>=1 (T=%d E=%d k=%d)", 64 * ROUTE_MAX_VPL, T, E, k);
+    if (T < 1 || E < 1 || E > ROUTE_MAX_E || k < 1)
+        MOE_FAIL(ctx, MOE_ERR_ARG, "moe_aux_loss: need T>=1, 1<=E<=%d, k>=1 (T=%d E=%d k=%d)", ROUTE_MAX_E, T, E, k);
     if (fn != MOE_SCORE_SOFTMAX && fn != MOE_SCORE_SIGMOID) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_aux_loss: bad score fn");
-    const int per_block = ROUTE_WAVES * ROUTE_TOKENS_PER_WAVE;
-    const int nblocks = (T + per_block - 1) / per_block;
+    const int nblocks = (T + AUX_TOKENS - 1) / AUX_TOKENS;
     if (MOE_WS_RESERVED + (size_t)nblocks * sizeof(double) > ctx->ws_bytes)
         MOE_FAIL(ctx, MOE_ERR_WORKSPACE, "moe_aux_loss: workspace %zu B < %zu B", ctx->ws_bytes,
                  MOE_WS_RESERVED + (size_t)nblocks * sizeof(double));
-    hipStream_t s = (hipStream_t)stream;
-    double* partial = (double*)((char*)ctx->ws + MOE_WS_RESERVED);
+    const int lpt = E <= 256 ? 16 : 64;
     const float wscale = (float)((double)coeff * E / ((double)T * T * k));
-    const size_t shm = (size_t)((E + 1) & ~1) * sizeof(float) + ROUTE_WAVES * sizeof(double);
-    const int vpl = (E + 63) / 64;
-#define AUX_LAUNCH(V)                                                                                                \
-    hipLaunchKernelGGL(aux_loss_kernel<V>, dim3(nblocks), dim3(ROUTE_WAVES * 64), shm, s, logits, counts, T, E, (int)fn, \
-                       wscale, dloss, accumulate, dlogits, partial)
-    if (vpl <= 1) AUX_LAUNCH(1);
-    else if (vpl <= 2) AUX_LAUNCH(2);
-    else if (vpl <= 4) AUX_LAUNCH(4);
-    else if (vpl <= 8) AUX_LAUNCH(8);
-    else AUX_LAUNCH(16);
-#undef AUX_LAUNCH
-    hipLaunchKernelGGL(aux_loss_sum_kernel, dim3(1), dim3(64), 0, s, partial, nblocks, loss);
+    ROUTE_CASES(aux_loss_kernel, dim3(nblocks), dim3(lpt == 16 ? 16 * AUX_TOKENS : 1024), 0, (hipStream_t)stream, logits, counts, T, E,
+                (int)fn, wscale, dloss, accumulate, dlogits, (double*)((char*)ctx->ws + MOE_WS_RESERVED), loss,
+                ctx->aux + MOE_AUX_LOSS_TICKET);
     MOE_LAUNCH_CHECK(ctx, "aux_loss_kernel");
     return MOE_OK;
 }

@@ -1,0 +1,98 @@
+"""GPU parity of the router at the edges of its lane layout: experts around multiples of 16 and 64, slots beyond 16, groups
+beyond 16, token counts around a wavefront's and a workgroup's share, the histogram of one and of many workgroups, calls
+in a row (the shared histogram is left at zero by each), no histogram, values that order specially."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2603_07685_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def ctx(B):
+    c = B.Context(T=8192, k=8, E=64, h=64, f_max=64)
+    yield c
+    c.close()
+
+
+def _out(T, E, k):
+    e = lambda s, v, t: torch.full(s, v, dtype=t, device="cuda")
+    return e((T, k), -7, torch.int32), e((T, k), float("nan"), torch.float32), e((E,), -7, torch.int32)
+
+
+@pytest.mark.parametrize("T,E,k", [(1, 1, 1), (3, 16, 16), (4, 17, 17), (5, 15, 3), (16, 33, 16), (17, 64, 17), (63, 65, 4),
+                                   (257, 256, 16), (255, 257, 16), (4096, 129, 6), (4097, 128, 6), (4100, 512, 20)])
+@pytest.mark.parametrize("fn,norm", [(0, False), (1, True)])
+def test_top_k_and_backward(B, ctx, oracle, T, E, k, fn, norm):
+    from gpu_util import dev
+    g = np.random.default_rng(T + E + k)
+    logits = (np.round(g.normal(size=(T, E)) * 8) / 4).astype(np.float32)     # ties, and zeros of both signs
+    logits[g.random((T, E)) < 0.02] = -0.0
+    if E > 2 * k:
+        logits[::2, E // 2] = -np.inf
+    o_idx, o_prob, o_counts = oracle.route_topk(logits, k, fn, norm, 1.5)
+    d = dev(logits)
+    for _ in range(3):
+        idx, prob, counts = _out(T, E, k)
+        B.moe_route_topk(ctx, d, T, E, k, fn, norm, 1.5, idx, prob, counts)
+        torch.cuda.synchronize()
+        assert np.array_equal(idx.cpu().numpy(), o_idx) and np.array_equal(counts.cpu().numpy(), o_counts)
+        np.testing.assert_allclose(prob.cpu().numpy(), o_prob, rtol=2e-6, atol=1e-9)
+    B.moe_route_topk(ctx, d, T, E, k, fn, norm, 1.5, idx, prob, None)
+    assert np.array_equal(idx.cpu().numpy(), o_idx)
+    logits = np.where(np.isinf(logits), -3, logits).astype(np.float32)
+    o_idx, _, _ = oracle.route_topk(logits, k, fn, norm, 1.5)
+    dw = g.normal(size=(T, k)).astype(np.float32)
+    out = torch.full((T, E), float("nan"), dtype=torch.float32, device="cuda")
+    B.moe_route_topk_bwd(ctx, dev(logits), dev(o_idx), dev(dw), T, E, k, fn, norm, 1.5, out)
+    ref = oracle.route_topk_bwd(logits, o_idx, dw, fn, norm, 1.5)
+    got = out.cpu().numpy().astype(np.float64)
+    # (fp32 terms of size |dw|, which cancel where one weight is normalised by itself)
+    assert np.abs(got - ref).max() <= 2e-5 * np.abs(ref).max() + 2e-6 * np.abs(dw).max()
+
+
+@pytest.mark.parametrize("T,E,k,ng,tg", [(5, 48, 8, 16, 4), (33, 51, 4, 17, 2), (70, 128, 16, 8, 8), (9, 320, 8, 8, 4),
+                                         (130, 64, 32, 64, 32), (66, 96, 6, 3, 2), (20, 256, 17, 1, 1), (1030, 256, 8, 8, 4)])
+@pytest.mark.parametrize("fn", [0, 1])
+def test_group_limited_top_k(B, ctx, oracle, T, E, k, ng, tg, fn):
+    from gpu_util import dev
+    g = np.random.default_rng(T + E + k)
+    logits = (np.round(g.normal(size=(T, E)) * 4) / 4).astype(np.float32)
+    bias = (np.round(g.normal(size=E) * 4) / 16).astype(np.float32)
+    for b in (bias, None):
+        o_idx, o_prob, o_counts = oracle.route_topk_grouped(logits, k, ng, tg, b, fn, True, 2.5)
+        for _ in range(2):
+            idx, prob, counts = _out(T, E, k)
+            B.moe_route_topk_grouped(ctx, dev(logits), None if b is None else dev(b), T, E, k, ng, tg, fn, True, 2.5, idx, prob, counts)
+            torch.cuda.synchronize()
+            assert np.array_equal(idx.cpu().numpy(), o_idx) and np.array_equal(counts.cpu().numpy(), o_counts)
+            np.testing.assert_allclose(prob.cpu().numpy(), o_prob, rtol=2e-6, atol=1e-9)
+
+
+@pytest.mark.parametrize("T,E", [(31, 16), (32, 17), (33, 256), (65, 257), (2100, 1000)])
+@pytest.mark.parametrize("fn", [0, 1])
+def test_aux_loss(B, ctx, oracle, T, E, fn):
+    from gpu_util import dev
+    g = np.random.default_rng(T + E)
+    logits = g.normal(size=(T, E)).astype(np.float32)
+    counts = g.multinomial(2 * T, np.ones(E) / E).astype(np.int32)
+    ref_loss, ref_grad = oracle.aux_loss(logits, counts, 2, fn, 0.01)
+    base = (1e-4 * g.normal(size=(T, E))).astype(np.float32)
+    seen = []
+    for acc in (0, 1, 1):
+        dl, loss = dev(base), torch.full((1,), float("nan"), dtype=torch.float32, device="cuda")
+        B.moe_aux_loss(ctx, dev(logits), dev(counts), T, E, 2, fn, 0.01, 0.7, acc, loss, dl)
+        torch.cuda.synchronize()
+        want = 0.7 * ref_grad + (base if acc else 0)
+        assert np.abs(dl.cpu().numpy() - want).max() <= 2e-5 * np.abs(want).max()
+        assert abs(loss.item() - ref_loss) <= 2e-6 * abs(ref_loss)
+        seen.append(loss.item())
+    assert len(set(seen)) == 1
