@@ -23,6 +23,7 @@ struct moe_ctx {
 // ints of ctx->aux (each user leaves what it counted in at zero again)
 #define MOE_AUX_ROUTE_TICKET 0    // workgroups of a routing kernel that have added their histogram
 #define MOE_AUX_LOSS_TICKET 16    // ... of the auxiliary loss that have stored their partial sum
+#define MOE_AUX_TILE_COUNTER 32    // weight gradient: tiles drawn, then workgroups done drawing
 #define MOE_AUX_ROUTE_COUNTS 64   // [1024] the histogram being added up
 #define MOE_AUX_INTS (64 + 1024)
 

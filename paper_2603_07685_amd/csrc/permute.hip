@@ -3,13 +3,17 @@
 //
 // Row-ID map = stable counting sort of the T*k (token, slot) pairs by expert, with
 // no atomics on positions so the map is bit-reproducible:
-//   1. hist : one wavefront per chunk of PERMUTE_CHUNK consecutive pairs builds
-//             that chunk's per-expert histogram (LDS) and stores it to the workspace;
+//   1. hist : a workgroup per chunk of PERMUTE_CHUNK consecutive pairs builds that chunk's per-expert histogram (LDS) and
+//             stores it to the workspace;
 //   2. scan : per expert, exclusive scan of the chunk histograms (chunk bases),
 //             totals -> counts, padded exclusive scan over experts -> offsets;
-//   3. rank : the same wavefront walks its chunk again, 64 pairs at a time; a
-//             lane's rank among equal experts inside the 64 comes from ballots over
-//             the bits of the expert id, the running per-expert count sits in LDS.
+//   3. rank : a workgroup per chunk again, one wavefront per 64 pairs; a lane's rank among equal experts inside the 64
+//             comes from ballots over the bits of the expert id, the wavefronts' counts are scanned in LDS.  Further
+//             workgroups mark the rows that no pair owns (src_of = -1).
+// Up to PERMUTE_ONE_PAIRS pairs one workgroup does all of it in one launch.
+// Bound: launches and dependent latencies (the map of 131072 pairs is 1.5 MB).  Measured, all kernels of the map: T 256,
+// k 2, E 8: 13.5 us in four launches (and three gaps between them) : 4.2 in one; T 2048, k 2: 22 : 5.9; T 16384, k 8, E 32: 35 : 16.6
+// (fill, one wavefront per chunk, a serial scan over the chunks : this).
 // Row moves are token-major: a workgroup reads one source row once and writes
 // its k copies (permute), or reads the k expert rows once and writes one row
 // (combine), 16 bytes per lane per access, fp32 accumulation in registers.
@@ -28,105 +32,217 @@ __device__ __forceinline__ u32x4_t mk4(uint32_t a, uint32_t b, uint32_t c, uint3
 // ---------------------------------------------------------------------------
 // 1. per-chunk histograms
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void permute_hist_kernel(const int32_t* __restrict__ idx, int64_t pairs, int E,
-                                                          int32_t* __restrict__ chunk_hist) {
+static_assert(PERMUTE_CHUNK == 1024, "one pair per thread of a 1024-thread workgroup");
+__global__ __launch_bounds__(1024) void permute_hist_kernel(const int32_t* __restrict__ idx, int64_t pairs, int E,
+                                                            int32_t* __restrict__ chunk_hist) {
     extern __shared__ int32_t lds[];
-    const int lane = threadIdx.x;
-    for (int e = lane; e < E; e += 64) lds[e] = 0;
+    const int tid = threadIdx.x;
+    const int64_t j = (int64_t)blockIdx.x * PERMUTE_CHUNK + tid;
+    const int e = j < pairs ? idx[j] : -1;
+    if (tid < E) lds[tid] = 0;
     __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * PERMUTE_CHUNK;
-    for (int i = 0; i < PERMUTE_CHUNK; i += 64) {
-        int64_t j = base + i + lane;
-        if (j < pairs) {
-            int e = idx[j];
-            if (e >= 0 && e < E) atomicAdd(&lds[e], 1);
-        }
+    if (e >= 0 && e < E) atomicAdd(&lds[e], 1);
+    __syncthreads();
+    if (tid < E) chunk_hist[(int64_t)blockIdx.x * E + tid] = lds[tid];
+}
+
+// Exclusive scan over the 1024 threads of a workgroup (int64: sums of padded counts); *total = the sum of all.
+__device__ __forceinline__ int64_t block_scan_1024(int64_t v, int64_t (&wsum)[16], int64_t* total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t incl = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
     }
+    if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    for (int e = lane; e < E; e += 64) chunk_hist[(int64_t)blockIdx.x * E + e] = lds[e];
+    int64_t base = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) base += wsum[w];
+        all += wsum[w];
+    }
+    *total = all;
+    return base + incl - v;
 }
 
 // ---------------------------------------------------------------------------
 // 2. scans: chunk bases per expert, counts, padded offsets
 // ---------------------------------------------------------------------------
-#define SCAN_LDS_INTS 12288  // chunk histograms staged per pass (48 KB)
-__global__ __launch_bounds__(1024) void permute_scan_kernel(int32_t* __restrict__ chunk_hist, int nchunks, int E,
+__global__ __launch_bounds__(1024) void permute_scan_kernel(int32_t* __restrict__ chunk_hist, int nchunks, int E, int log_e,
                                                             int align, int32_t* __restrict__ counts,
                                                             int32_t* __restrict__ offsets) {
-    // One workgroup.  The [nchunks][E] histogram table is brought into LDS with coalesced loads, a block of
-    // chunks at a time; thread e then runs the exclusive scan of expert e down the block in LDS (the serial
-    // chain is over LDS latency, not over dependent global loads) and the block is written back coalesced.
-    __shared__ int32_t tab[SCAN_LDS_INTS];
-    __shared__ int32_t tot[1024];
+    // One workgroup.  Thread (segment, expert): the chunks are cut into up to 32 segments; a thread sums its segment, the
+    // segments' sums meet in LDS, then it walks its segment again and leaves the running base of every chunk.
+    __shared__ int32_t part[1024];
+    __shared__ int64_t wsum[16];
     const int tid = threadIdx.x;
-    const int per_pass = SCAN_LDS_INTS / E;  // chunks per pass (E <= 1024 is checked by the caller)
-    int32_t run = 0;
-    for (int c0 = 0; c0 < nchunks; c0 += per_pass) {
-        const int nc = min(per_pass, nchunks - c0);
-        int32_t* g = chunk_hist + (int64_t)c0 * E;
-        for (int i = tid; i < nc * E; i += 1024) tab[i] = g[i];
-        __syncthreads();
-        if (tid < E) {
-            for (int c = 0; c < nc; ++c) {
-                const int32_t v = tab[c * E + tid];
-                tab[c * E + tid] = run;
-                run += v;
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < nc * E; i += 1024) g[i] = tab[i];
-        __syncthreads();
-    }
-    if (tid < E) {
-        tot[tid] = run;
-        if (counts) counts[tid] = run;
-    }
+    const int e = tid & ((1 << log_e) - 1), seg = tid >> log_e;   // (E <= 1024 is checked by the caller)
+    const int nseg = min(1024 >> log_e, 32), len = (nchunks + nseg - 1) / nseg;
+    const int c0 = min(seg * len, nchunks), c1 = seg < nseg ? min(c0 + len, nchunks) : c0;
+    int32_t sum = 0;
+    if (e < E)
+        for (int c = c0; c < c1; ++c) sum += chunk_hist[(int64_t)c * E + e];
+    part[tid] = sum;
     __syncthreads();
-    if (tid == 0) {
-        int64_t r = 0;
-        for (int i = 0; i < E; ++i) {
-            offsets[i] = (int32_t)r;
-            r += ((int64_t)tot[i] + align - 1) / align * align;
-        }
-        offsets[E] = (int32_t)r;
+    int32_t run = 0, tot = 0;
+    for (int s = 0; s < nseg; ++s) {
+        const int32_t v = part[(s << log_e) + e];
+        run += s < seg ? v : 0;
+        tot += v;
     }
+    if (e < E) {
+        for (int c = c0; c < c1; ++c) {
+            int32_t* h = chunk_hist + (int64_t)c * E + e;
+            const int32_t v = *h;
+            *h = run;
+            run += v;
+        }
+    }
+    // (segment 0: thread = expert)
+    const bool mine = seg == 0 && e < E;
+    int64_t total;
+    const int64_t at = block_scan_1024(mine ? ((int64_t)tot + align - 1) / align * align : 0, wsum, &total);
+    if (mine) {
+        counts[e] = tot;
+        offsets[e] = (int32_t)at;
+    }
+    if (tid == 0) offsets[E] = (int32_t)total;
+}
+
+// The 64 pairs of a wavefront: each valid lane's peers (lanes with the same expert), and its rank among them.
+__device__ __forceinline__ uint64_t expert_peers(int e, bool valid, int nbits) {
+    uint64_t peers = __ballot(valid);
+    for (int b = 0; b < nbits; ++b) {
+        const uint64_t m = __ballot((e >> b) & 1);
+        peers &= ((e >> b) & 1) ? m : ~m;
+    }
+    return peers;
 }
 
 // ---------------------------------------------------------------------------
 // 3. stable ranks -> row_of, src_of
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void permute_rank_kernel(const int32_t* __restrict__ idx, int64_t pairs, int E,
-                                                          int nbits, const int32_t* __restrict__ chunk_base,
-                                                          const int32_t* __restrict__ offsets,
-                                                          int32_t* __restrict__ row_of, int32_t* __restrict__ src_of) {
-    extern __shared__ int32_t run[];  // next free position of each expert for this chunk
-    const int lane = threadIdx.x;
-    for (int e = lane; e < E; e += 64) run[e] = offsets[e] + chunk_base[(int64_t)blockIdx.x * E + e];
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * PERMUTE_CHUNK;
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int i = 0; i < PERMUTE_CHUNK; i += 64) {
-        int64_t j = base + i + lane;
-        if (base + i >= pairs) break;  // uniform
-        int e = j < pairs ? idx[j] : -1;
-        bool valid = e >= 0 && e < E;
-        uint64_t peers = __ballot(valid);
-        for (int b = 0; b < nbits; ++b) {
-            uint64_t m = __ballot((e >> b) & 1);
-            peers &= ((e >> b) & 1) ? m : ~m;
+#define FILL_ROWS 4096  // rows behind offsets[E] per filling workgroup
+__global__ __launch_bounds__(1024) void permute_rank_kernel(const int32_t* __restrict__ idx, int64_t pairs, int E,
+                                                            int nbits, int nchunks, int64_t Rcap,
+                                                            const int32_t* __restrict__ chunk_base,
+                                                            const int32_t* __restrict__ offsets, const int32_t* __restrict__ counts,
+                                                            int32_t* __restrict__ row_of, int32_t* __restrict__ src_of) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = blockIdx.x;
+    if (b >= nchunks) {  // rows that no pair owns: an expert's padding rows, then what lies behind the last expert
+        int64_t r0, r1;
+        if (b < nchunks + E) {
+            const int e = b - nchunks;
+            r0 = (int64_t)offsets[e] + counts[e];
+            r1 = offsets[e + 1];
+        } else {
+            r0 = offsets[E] + (int64_t)(b - nchunks - E) * FILL_ROWS;
+            r1 = min(r0 + FILL_ROWS, Rcap);
         }
-        const int rank = __popcll(peers & below);
+        for (int64_t r = r0 + tid; r < r1; r += 1024) src_of[r] = -1;
+        return;
+    }
+    extern __shared__ int32_t wcnt[];  // [16][E]: pairs per wavefront and expert, then the rows they start at
+    for (int i = tid; i < 16 * E; i += 1024) wcnt[i] = 0;
+    const int64_t j = (int64_t)b * PERMUTE_CHUNK + tid;
+    const int e = j < pairs ? idx[j] : -1;
+    const bool valid = e >= 0 && e < E;
+    const uint64_t peers = expert_peers(e, valid, nbits);
+    const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+    __syncthreads();
+    if (valid && rank == 0) wcnt[wave * E + e] = __popcll(peers);
+    __syncthreads();
+    if (tid < E) {
+        int32_t run = offsets[tid] + chunk_base[(int64_t)b * E + tid];
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int32_t v = wcnt[w * E + tid];
+            wcnt[w * E + tid] = run;
+            run += v;
+        }
+    }
+    __syncthreads();
+    if (valid) {
+        const int row = wcnt[wave * E + e] + rank;
+        row_of[j] = row;
+        src_of[row] = (int32_t)j;
+    } else if (j < pairs) {
+        row_of[j] = -1;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The whole map in one workgroup: wavefront w owns pairs [w * share, (w + 1) * share).
+// ---------------------------------------------------------------------------
+#define PERMUTE_ONE_PAIRS 8192
+#define PERMUTE_ONE_FREE 65536  // most rows without a pair that one workgroup marks
+__global__ __launch_bounds__(1024) void permute_one_kernel(const int32_t* __restrict__ idx, int pairs, int E, int nbits, int align,
+                                                           int64_t Rcap, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+                                                           int32_t* __restrict__ offsets, int32_t* __restrict__ counts) {
+    extern __shared__ int32_t wcnt[];  // [16][E], then [E + 1] ends of the experts' pairs, [E + 1] offsets
+    __shared__ int64_t wsum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < 16 * E; i += 1024) wcnt[i] = 0;
+    __syncthreads();
+    constexpr int STEPS = PERMUTE_ONE_PAIRS / 1024;
+    const int steps = (pairs + 1023) / 1024, j0 = wave * 64 * steps + lane;
+    int ex[STEPS];
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) ex[s] = s < steps && j0 + 64 * s < pairs ? idx[j0 + 64 * s] : -1;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s)
+        if (ex[s] >= 0 && ex[s] < E) atomicAdd(&wcnt[wave * E + ex[s]], 1);
+    __syncthreads();
+    int32_t tot = 0;
+    if (tid < E) {
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            const int32_t v = wcnt[w * E + tid];
+            wcnt[w * E + tid] = tot;
+            tot += v;
+        }
+    }
+    int64_t total;
+    const int64_t at = block_scan_1024(tid < E ? ((int64_t)tot + align - 1) / align * align : 0, wsum, &total);
+    int32_t* const ends = wcnt + 16 * E;
+    int32_t* const offs = ends + E + 1;
+    if (tid < E) {
+        offsets[tid] = (int32_t)at;
+        counts[tid] = tot;
+        offs[tid] = (int32_t)at;
+        ends[tid] = (int32_t)at + tot;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) wcnt[w * E + tid] += (int32_t)at;
+    }
+    if (tid == 0) {
+        offsets[E] = (int32_t)total;
+        offs[E] = (int32_t)total;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        if (s >= steps) break;
+        const int e = ex[s], j = j0 + 64 * s;
+        const bool valid = e >= 0 && e < E;
+        const uint64_t peers = expert_peers(e, valid, nbits);
+        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
         if (valid) {
-            int row = run[e] + rank;
+            const int row = wcnt[wave * E + e] + rank;
             row_of[j] = row;
-            src_of[row] = (int32_t)j;
+            src_of[row] = j;
         } else if (j < pairs) {
             row_of[j] = -1;
         }
-        __syncthreads();  // single wavefront: orders the LDS reads above before the update
-        if (valid && rank == 0) run[e] += __popcll(peers);  // lowest lane of each group
-        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // (a wavefront's own row: its program order suffices)
+        if (valid && rank == 0) wcnt[wave * E + e] += __popcll(peers);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     }
+    for (int e = wave; e < E; e += 16)
+        for (int r = ends[e] + lane; r < offs[e + 1]; r += 64) src_of[r] = -1;
+    for (int64_t r = total + tid; r < Rcap; r += 1024) src_of[r] = -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -273,16 +389,27 @@ __device__ __forceinline__ float dot_vec<true>(u32x4_t a, u32x4_t b) {
            __uint_as_float(a.z) * __uint_as_float(b.z) + __uint_as_float(a.w) * __uint_as_float(b.w);
 }
 
+#define ZERO_ROWS 64
 template <bool F32>
 __global__ __launch_bounds__(MOVE_THREADS) void combine_bwd_kernel(
     const u32x4_t* __restrict__ dY, const u32x4_t* __restrict__ O, const int32_t* __restrict__ row_of,
     const float* __restrict__ prob, int T, int k, int vec_per_row, u32x4_t* __restrict__ dO,
-    float* __restrict__ dprob) {
+    float* __restrict__ dprob, const int32_t* __restrict__ src_of, int64_t Rcap) {
     __shared__ int32_t rows[COMBINE_MAX_K];
     __shared__ float wts[COMBINE_MAX_K];
     __shared__ float part[COMBINE_MAX_K][MOVE_THREADS / 64];
     const int t = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (t >= T) {  // behind the tokens: workgroups that zero the rows no pair owns, ZERO_ROWS rows each
+        const int64_t r0 = (int64_t)(t - T) * ZERO_ROWS + wave * (ZERO_ROWS / (MOVE_THREADS / 64));
+        const int64_t r = r0 + lane;
+        uint64_t pad = __ballot(lane < ZERO_ROWS / (MOVE_THREADS / 64) && r < Rcap && src_of[min(r, Rcap - 1)] < 0);
+        for (; pad; pad &= pad - 1) {
+            u32x4_t* const row = dO + (r0 + __builtin_ctzll(pad)) * vec_per_row;
+            for (int c = lane; c < vec_per_row; c += 64) row[c] = mk4(0, 0, 0, 0);
+        }
+        return;
+    }
     for (int s = threadIdx.x; s < k; s += MOVE_THREADS) {
         rows[s] = row_of[(int64_t)t * k + s];
         wts[s] = prob ? prob[(int64_t)t * k + s] : 1.0f;
@@ -337,16 +464,6 @@ __global__ __launch_bounds__(MOVE_THREADS) void combine_bwd_kernel(
     }
 }
 
-// zero every row whose src_of is negative (padding)
-__global__ __launch_bounds__(MOVE_THREADS) void zero_pad_rows_kernel(const int32_t* __restrict__ src_of, int64_t Rcap,
-                                                                     int vec_per_row, u32x4_t* __restrict__ dO) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t r = (int64_t)blockIdx.x * (MOVE_THREADS / 64) + wave;
-    if (r >= Rcap || src_of[r] >= 0) return;
-    u32x4_t z = mk4(0, 0, 0, 0);
-    for (int c = lane; c < vec_per_row; c += 64) dO[r * vec_per_row + c] = z;
-}
-
 // ---------------------------------------------------------------------------
 // host entry points
 // ---------------------------------------------------------------------------
@@ -386,14 +503,22 @@ static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int
                            int align, void* Xp, int64_t Rcap, int32_t* row_of, int32_t* src_of, int32_t* offsets,
                            int32_t* counts, int32_t* chunk_hist) {
     const int64_t pairs = (int64_t)T * k;
-    const int nchunks = (int)moe_permute_chunks(pairs);
-    const size_t shm = (size_t)E * sizeof(int32_t);
-    moe_launch_fill_i32(src_of, Rcap, -1, s);
-    if (nchunks > 0) hipLaunchKernelGGL(permute_hist_kernel, dim3(nchunks), dim3(64), shm, s, idx, pairs, E, chunk_hist);
-    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, s, chunk_hist, nchunks, E, align, counts, offsets);
-    if (nchunks > 0)
-        hipLaunchKernelGGL(permute_rank_kernel, dim3(nchunks), dim3(64), shm, s, idx, pairs, E, bits_for(E), chunk_hist,
-                           offsets, row_of, src_of);
+    const int nchunks = (int)moe_permute_chunks(pairs), nbits = bits_for(E);
+    // One workgroup while its serial share is cheaper than three launches, kernel times alone: E 32, k 4, T 256: 4.5 us
+    // against 7.5; T 1024: 6.5 against 9.2; T 2048 (the most it takes): 9.2 against 9.3, and two launches fewer.  Up to 512
+    // experts (64 KB of LDS counters).
+    if (pairs <= PERMUTE_ONE_PAIRS && E <= 512 && Rcap - pairs <= PERMUTE_ONE_FREE) {
+        hipLaunchKernelGGL(permute_one_kernel, dim3(1), dim3(1024), (size_t)(18 * E + 2) * sizeof(int32_t), s, idx, (int)pairs, E,
+                           nbits, align, Rcap, row_of, src_of, offsets, counts);
+    } else {
+        if (nchunks > 0)
+            hipLaunchKernelGGL(permute_hist_kernel, dim3(nchunks), dim3(1024), (size_t)E * sizeof(int32_t), s, idx, pairs, E, chunk_hist);
+        hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, s, chunk_hist, nchunks, E, nbits, align, counts, offsets);
+        // (rows without a pair: at most Rcap of them behind the last expert, if every slot is skipped)
+        hipLaunchKernelGGL(permute_rank_kernel, dim3(nchunks + E + (unsigned)ceil_div64(Rcap, FILL_ROWS)), dim3(1024),
+                           (size_t)16 * E * sizeof(int32_t), s, idx, pairs, E, nbits, nchunks, Rcap, chunk_hist, offsets, counts,
+                           row_of, src_of);
+    }
     if (X) {
         const int vec = (int)((size_t)h * moe_dtype_size(dt) / 16);
         hipLaunchKernelGGL(permute_rows_kernel, dim3(T + E), dim3(MOVE_THREADS), 0, s, (const u32x4_t*)X, row_of, offsets,
@@ -506,16 +631,16 @@ extern "C" moe_status moe_unpermute_combine_bwd(moe_ctx* ctx, void* stream, cons
     if (row_bytes % 16) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_unpermute_combine_bwd: row size %zu B is not a multiple of 16", row_bytes);
     hipStream_t s = (hipStream_t)stream;
     const int vec = (int)(row_bytes / 16);
-    if (Rcap > 0 && dO)
-        hipLaunchKernelGGL(zero_pad_rows_kernel, dim3((unsigned)ceil_div64(Rcap, MOVE_THREADS / 64)), dim3(MOVE_THREADS), 0,
-                           s, src_of, Rcap, vec, (u32x4_t*)dO);
-    if (T > 0) {
+    // (one launch: the padding rows' workgroups follow the tokens')
+    const int64_t grid = T + (dO ? ceil_div64(Rcap, ZERO_ROWS) : 0);
+    if (grid > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_unpermute_combine_bwd: T and Rcap too large");
+    if (grid > 0) {
         if (dt == MOE_BF16)
-            hipLaunchKernelGGL(combine_bwd_kernel<false>, dim3(T), dim3(MOVE_THREADS), 0, s, (const u32x4_t*)dY,
-                               (const u32x4_t*)O, row_of, prob, T, k, vec, (u32x4_t*)dO, dprob);
+            hipLaunchKernelGGL(combine_bwd_kernel<false>, dim3((unsigned)grid), dim3(MOVE_THREADS), 0, s, (const u32x4_t*)dY,
+                               (const u32x4_t*)O, row_of, prob, T, k, vec, (u32x4_t*)dO, dprob, src_of, Rcap);
         else
-            hipLaunchKernelGGL(combine_bwd_kernel<true>, dim3(T), dim3(MOVE_THREADS), 0, s, (const u32x4_t*)dY,
-                               (const u32x4_t*)O, row_of, prob, T, k, vec, (u32x4_t*)dO, dprob);
+            hipLaunchKernelGGL(combine_bwd_kernel<true>, dim3((unsigned)grid), dim3(MOVE_THREADS), 0, s, (const u32x4_t*)dY,
+                               (const u32x4_t*)O, row_of, prob, T, k, vec, (u32x4_t*)dO, dprob, src_of, Rcap);
     }
     MOE_LAUNCH_CHECK(ctx, "combine_bwd kernels");
     return MOE_OK;
