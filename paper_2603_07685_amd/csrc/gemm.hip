@@ -269,20 +269,26 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             // about the mean expert's row count (whole stages), each piece is a work item of its own that leaves its
             // 256 x 256 result as an fp32 partial tile in the workspace, and a second kernel adds the pieces of a tile
             // in increasing order: the same sums in the same order whatever the timing.  Decided here, from the
-            // offsets alone and identically in every workgroup: experts in descending size, pieces = rows / mean
-            // rounded up for experts above twice the mean, while the workspace has slices left.
+            // offsets alone and identically in every workgroup: experts in descending size, those above twice the mean,
+            // into pieces of at most `lim` rows, while the workspace has slices left.  A piece costs a partial tile's
+            // way to memory and back, so lim is as large as the draw can balance: a third of a workgroup's share of the
+            // call (rows times tiles, over the workgroups), or the mean where that is more.  T 1999, k 4, h 2880, f 1472,
+            // 24 experts (12 row tiles' worth of experts per workgroup): fc1 gradient 334 us + 153 us of second pass with
+            // pieces of the mean, 334 + 5 now; T 16384, k 8, h 4096, f 1536, 16 experts, rank^-1.2: 2472 + 205 : 2434 + 28.
             const int tpe = tiles_i_w * tiles_j;
             const int64_t rows_all = offs[E] - offs[0];
             const int emax = tile_start[0];
             const bool skew = !bad && a.split_cap >= 2 && (int64_t)(offs[emax + 1] - offs[emax]) * E > 2 * rows_all;
-            const int mean = (int)((rows_all / E + 127) / 128 * 128);
+            const int64_t third = rows_all * tpe / (3 * (int64_t)gridDim.x), avg = rows_all / E;
+            const int64_t most = rows_all > 0 ? rows_all : 1;
+            const int lim = (int)((max(min(max(third, avg), most), (int64_t)1) + 127) / 128 * 128);
             int used = 0, nsplit = 0, items = 0;
             for (int i = 0; i < E; ++i) {
                 const int ee = tile_start[i];
                 const int rows = offs[ee + 1] - offs[ee];
                 int pieces = 1;
-                if (skew && mean > 0 && rows > 2 * mean && nsplit < GG_MAX_SPLIT_EXPERTS) {
-                    pieces = min((rows + mean - 1) / mean, a.split_cap - used);
+                if (skew && rows > 2 * avg && rows > lim && nsplit < GG_MAX_SPLIT_EXPERTS) {
+                    pieces = min((rows + lim - 1) / lim, a.split_cap - used);
                     if (pieces < 2) pieces = 1;
                 }
                 item_start[i] = items;
@@ -1958,6 +1964,13 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
         }
         t = t_next;
     }
+    // the counter the tiles were drawn from goes back to zero with the last workgroup that is done with it
+    if (MODE == GG_WGRAD && dyn && tid == 0) {
+        if (atomicAdd(a.tile_counter + 1, 1) + 1 == G) {
+            atomicExch(a.tile_counter, 0);
+            atomicExch(a.tile_counter + 1, 0);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1997,48 +2010,57 @@ static gg_args gg_make(moe_ctx* ctx, const void* P, const void* Q, const int32_t
     return a;
 }
 
-#define MOE_WS_TILE_COUNTER 48  // byte offset of the wgrad tile counter in the reserved head of the workspace
-#define MOE_WS_SPLIT_INFO 64    // ... of the list of split experts (1 + 3 * GG_MAX_SPLIT_EXPERTS ints)
+#define MOE_WS_SPLIT_INFO 64    // byte offset in the reserved head of the workspace: the list of split experts (1 + 3 * GG_MAX_SPLIT_EXPERTS ints)
 
 // Second step of a weight gradient with a split contraction: dW tile = sum of its pieces' partial tiles, piece 0
-// first, then the ordinary output step (type, accumulate, matrix edges).  grid = (tiles per expert,
-// GG_MAX_SPLIT_EXPERTS); the list of split experts was written by the first kernel.
+// first, then the ordinary output step (type, accumulate, matrix edges).  The list of split experts was written by the
+// first kernel; a fixed number of workgroups goes over (split expert, tile, eighth of the tile's rows), so that an empty
+// list costs one look at it.  Bound: HBM (pieces * 256 KB read and a tile written; T 1999, k 4, h 2880, f 1472, 24 experts: 44 us
+// for what took 123 with one workgroup per tile and expert and its rows in turn).
+#define GG_REDUCE_BLOCKS 2048
 template <bool OUT_F32>
 __global__ __launch_bounds__(256) void gg_split_reduce_kernel(const float* __restrict__ partials, const int* __restrict__ info,
                                                               int N, int K, int accumulate, void* __restrict__ out) {
-    const int j = blockIdx.y;
-    if (j >= info[0]) return;
-    const int e = info[1 + 3 * j], pieces = info[2 + 3 * j], slice0 = info[3 + 3 * j];
+    const int nsplit = info[0];
     const int tiles_j = (K + GG_BN - 1) / GG_BN, tiles_i = (N + GG_BM - 1) / GG_BM, tpe = tiles_i * tiles_j;
-    const int u = blockIdx.x;
-    // the tile order of the first kernel: bands of GG_BAND row tiles, column-major inside a band
-    const int band_sz = GG_BAND * tiles_j, band = u / band_sz, in_band = u - band * band_sz;
-    const int band_rows = min(GG_BAND, tiles_i - band * GG_BAND);
-    const int ti = band * GG_BAND + in_band % band_rows, tj = in_band / band_rows;
-    const int c = (threadIdx.x & 63) * 4, r0 = threadIdx.x >> 6;
-    const int col = tj * GG_BN + c;
-    if (col >= K) return;
-    for (int r = r0; r < GG_BM; r += 4) {
-        const int row = ti * GG_BM + r;
-        if (row >= N) break;
-        f32x4_t v = {0.f, 0.f, 0.f, 0.f};
-        for (int p = 0; p < pieces; ++p)
-            v += *(const f32x4_t*)(partials + ((int64_t)(slice0 + p) * tpe + u) * (GG_BM * GG_BN) + r * GG_BN + c);
-        const int64_t at = ((int64_t)e * N + row) * K + col;
-        if (OUT_F32) {
-            f32x4_t* o = (f32x4_t*)((float*)out + at);
-            if (accumulate) v += *o;
-            *o = v;
-        } else {
-            bf16_t* o = (bf16_t*)out + at;
-            float t4[4] = {v[0], v[1], v[2], v[3]};
-            if (accumulate) {
-                float old[4];
-                ld4_bf16(o, old);
+    const int c = (threadIdx.x & 63) * 4, w = threadIdx.x >> 6;
+    for (int64_t unit = blockIdx.x; unit < (int64_t)nsplit * tpe * 8; unit += gridDim.x) {
+        const int part = (int)(unit & 7), ju = (int)(unit >> 3), j = ju / tpe, u = ju - j * tpe;
+        const int e = info[1 + 3 * j], pieces = info[2 + 3 * j], slice0 = info[3 + 3 * j];
+        // the tile order of the first kernel: bands of GG_BAND row tiles, column-major inside a band
+        const int band_sz = GG_BAND * tiles_j, band = u / band_sz, in_band = u - band * band_sz;
+        const int band_rows = min(GG_BAND, tiles_i - band * GG_BAND);
+        const int ti = band * GG_BAND + in_band % band_rows, tj = in_band / band_rows;
+        const int col = tj * GG_BN + c, r0 = part * 32 + w * 8;   // eight rows of 64 x 16 bytes per wavefront
+        if (col >= K || ti * GG_BM + r0 >= N) continue;
+        const float* src = partials + ((int64_t)slice0 * tpe + u) * (GG_BM * GG_BN) + r0 * GG_BN + c;
+        f32x4_t v[8];
 #pragma unroll
-                for (int x = 0; x < 4; ++x) t4[x] += old[x];
+        for (int r = 0; r < 8; ++r) v[r] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int p = 0; p < pieces; ++p, src += (int64_t)tpe * (GG_BM * GG_BN)) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) v[r] += *(const f32x4_t*)(src + r * GG_BN);
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int row = ti * GG_BM + r0 + r;
+            if (row >= N) break;
+            const int64_t at = ((int64_t)e * N + row) * K + col;
+            if (OUT_F32) {
+                f32x4_t* o = (f32x4_t*)((float*)out + at);
+                if (accumulate) v[r] += *o;
+                *o = v[r];
+            } else {
+                bf16_t* o = (bf16_t*)out + at;
+                float t4[4] = {v[r][0], v[r][1], v[r][2], v[r][3]};
+                if (accumulate) {
+                    float old[4];
+                    ld4_bf16(o, old);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) t4[x] += old[x];
+                }
+                st4_bf16(o, t4);
             }
-            st4_bf16(o, t4);
         }
     }
 }
@@ -2408,8 +2430,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;
     }
-    a.tile_counter = (int*)((char*)ctx->ws + MOE_WS_TILE_COUNTER);
-    moe_launch_fill_i32(a.tile_counter, 1, 0, (hipStream_t)stream);
+    a.tile_counter = ctx->aux + MOE_AUX_TILE_COUNTER;
     a.p_scale = dc_scale;
     a.q_scale = a_scale;
     // split contraction (bf16 operands): as many slices of partial tiles as the workspace holds behind its reserved head
@@ -2435,7 +2456,8 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
         else GG_LAUNCH(GG_WGRAD, GG_EPI_STORE, false, 0);
     }
     if (a.split_cap >= 2) {
-        const dim3 grid((unsigned)(ceil_div64(N, GG_BM) * ceil_div64(K, GG_BN)), GG_MAX_SPLIT_EXPERTS);
+        const int64_t units = ceil_div64(N, GG_BM) * ceil_div64(K, GG_BN) * GG_MAX_SPLIT_EXPERTS * 8;
+        const dim3 grid((unsigned)(units < GG_REDUCE_BLOCKS ? units : GG_REDUCE_BLOCKS));
         if (out_dt == MOE_F32)
             hipLaunchKernelGGL(gg_split_reduce_kernel<true>, grid, dim3(256), 0, (hipStream_t)stream, a.partials, a.split_info, N, K,
                                a.accumulate, dB);

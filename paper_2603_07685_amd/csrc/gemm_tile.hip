@@ -365,10 +365,10 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
 // ---------------------------------------------------------------------------
 // Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 0 = the 256 x 256
 // kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted to measured calls
-// (MI355X, bf16; rows of an expert unknown on the host, so every expert is given half a partly filled row tile, and at
+// (MI355X, bf16; rows of an expert unknown on the host, so each of several is given half a partly filled row tile, and at
 // least one tile):
-//   256 x 256: one workgroup per compute unit, whole rounds of tiles, a tile = 1.5 per stage + 15 (SwiGLU backward: 35);
-//              weight gradient: + 9 for the tile counter's fill and the second pass of a split contraction
+//   256 x 256: one workgroup per compute unit, whole rounds of tiles (a tenth of one over is not rounded up: it comes from
+//              the guess), a tile = 1.5 per stage + 15 (SwiGLU backward: 35); weight gradient: + 6 for the second launch
 //   128 x 128: two workgroups per compute unit, rounds between the exact and the rounded-up count, a round = 2 x (0.62 per
 //              stage + 4)
 // Measured against each other (us, 256 x 256 : small tiles), fc1 forward unless said otherwise:
@@ -382,15 +382,18 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
     const double E = a.E, R = (double)a.Rcap, one = E < R ? E : R;
-    auto row_tiles = [&](double bm) { return R / bm + E / 2 > one ? R / bm + E / 2 : one; };
+    auto row_tiles = [&](double bm) {
+        const double n = E == 1 ? __builtin_ceil(R / bm) : R / bm + E / 2;
+        return n > one ? n : one;
+    };
     const double cols = mode == GG_FWD ? a.N : a.K;
     const double stages = mode == GG_WGRAD ? R / E / 64 + 0.5 : (mode == GG_FWD ? a.K : a.N) / 64.0;
     const double n256 = __builtin_ceil(cols / 256) * (mode == GG_WGRAD ? E * __builtin_ceil(a.N / 256.0) : row_tiles(256));
     const double n128 = __builtin_ceil(cols / 128) * (mode == GG_WGRAD ? E * __builtin_ceil(a.N / 128.0) : row_tiles(128));
-    const double r256 = __builtin_ceil(n256 / cu), r128 = n128 / (2 * cu);
-    const double t256 = r256 * (1.5 * stages + (epi == GG_EPI_SWIGLU_BWD ? 35 : 15)) + (mode == GG_WGRAD ? 9 : 0);
+    const double r256 = n256 / cu < 1 ? 1 : __builtin_ceil(n256 / cu - 0.1), r128 = n128 / (2 * cu);
+    const double t256 = r256 * (1.5 * stages + (epi == GG_EPI_SWIGLU_BWD ? 35 : 15)) + (mode == GG_WGRAD ? 6 : 0);
     const double t128 = (r128 + __builtin_ceil(r128)) * (0.62 * stages + 4);
-    if (t128 > 1.1 * t256) return 0;
+    if (t128 > (mode == GG_WGRAD ? 1.1 : 1.0) * t256) return 0;   // (weight gradients of a few stages are better than the estimate)
     if (mode == GG_WGRAD) return 2;
     if (R <= 48 * E) return 3;
     return r128 < 1 ? 1 : 2;
