@@ -112,8 +112,8 @@ moe_status moe_route_topk(moe_ctx* ctx, void* stream, const float* logits, int T
  * Gate GEMM in front of the router (Sec. 2.1.2 item 1): logits[t,e] = sum_i X[t,i] * Wr[e,i].
  * X [T,h] and Wr [E,h] bf16 (Wr is W_r of the paper stored expert-major, like an expert's Linear
  * weight), fp32 accumulation, logits [T,E] fp32 (Sec. 5.1 keeps the router in FP32).  E must be a
- * multiple of 8, h of 64.  Stream-ordered, no allocation or copy; uses 8 bytes of the context's
- * reserved workspace (calls on one context must not overlap).
+ * multiple of 8, h of 64.  Stream-ordered, no allocation or copy; keeps partial results in the
+ * context's workspace, as far as there is room (calls on one context must not overlap).
  */
 moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, const void* Wr, int T, int E, int h,
                          float* logits);

@@ -171,6 +171,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
     __shared__ int item_start[(MODE == GG_WGRAD && NW == 4) ? GG_MAX_E + 1 : 1];
     __shared__ int split_of[(MODE == GG_WGRAD && NW == 4) ? GG_MAX_E : 1];
     constexpr bool SPLITK = MODE == GG_WGRAD && NW == 4;
+    constexpr bool GATE = MODE == GG_FWD && OUT_F32;   // the router's projection: one group, split_cap pieces of the contraction
 
     constexpr bool P_CMAJ = (MODE == GG_WGRAD);
     constexpr bool Q_CMAJ = (MODE != GG_FWD);
@@ -230,7 +231,11 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
     const int tiles_i_w = (N + GG_BM - 1) / GG_BM;  // wgrad only
 
     // ---- tile schedule, computed by every workgroup from the device-resident offsets ----
-    for (int e = tid; e <= E; e += THREADS) offs[e] = a.offsets[e];
+    if (GATE) {   // one group of all rows
+        if (tid < 2) offs[tid] = tid ? (int)a.Rcap : 0;
+    } else {
+        for (int e = tid; e <= E; e += THREADS) offs[e] = a.offsets[e];
+    }
     __syncthreads();
     // wgrad: every expert has the same number of output tiles but a tile costs its expert's row count, so the
     // experts are walked in descending order of rows (rank sort, ties by index; tile_start[i] = i-th largest
@@ -261,6 +266,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             if (MXQ && a.out_qc) bad |= (rows & 127) != 0 || (offs[e] & 127) != 0;  // 32-row blocks inside one expert
             if (MODE == GG_WGRAD) run += tiles_i_w * tiles_j;
             else run += rows > 0 ? ((rows + GG_BM - 1) / GG_BM) * tiles_j : 0;
+            if (GATE) run *= a.split_cap;
         }
         tile_start[E] = run;
         if (SPLITK) {
@@ -483,6 +489,11 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             while (e + 1 < E && t >= __builtin_amdgcn_readfirstlane(tile_start[e + 1])) ++e;
             e_hint = e;
             u = t - __builtin_amdgcn_readfirstlane(tile_start[e]);
+            if (GATE) {   // piece by piece: the tiles that run together then share a piece's weights
+                const int nt = (int)((a.Rcap + GG_BM - 1) / GG_BM) * tiles_j;
+                part_slot = __builtin_amdgcn_readfirstlane(u / nt);
+                u -= part_slot * nt;
+            }
         }
         const int row_lo = __builtin_amdgcn_readfirstlane(offs[e]), row_hi = __builtin_amdgcn_readfirstlane(offs[e + 1]);
         int ti, tj;
@@ -510,6 +521,11 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             const int len = __builtin_amdgcn_readfirstlane(((row_hi - row_lo + pieces - 1) / pieces + BKE - 1) / BKE * BKE);
             c_lo = min(row_lo + piece * len, row_hi);
             c_hi = min(c_lo + len, row_hi);
+        }
+        if (GATE) {
+            const int len = ((K + a.split_cap - 1) / a.split_cap + BKE - 1) / BKE * BKE;
+            c_lo = min(part_slot * len, K);
+            c_hi = min(c_lo + len, K);
         }
         c_lo = __builtin_amdgcn_readfirstlane(c_lo);
         c_hi = __builtin_amdgcn_readfirstlane(c_hi);
@@ -555,9 +571,9 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
         } else {
             const int ldp = (MODE == GG_FWD) ? K : N;
             p_step = GG_ROWB;
-            p_base = (const char*)a.P + (int64_t)i0 * ldp * ES;
+            p_base = (const char*)a.P + (int64_t)i0 * ldp * ES + (GATE ? c_lo * ES : 0);
             {   // rows of the activation tensor from the tile's first row up to its capacity
-                const int64_t tot = (a.Rcap - i0) * (int64_t)ldp * ES;
+                const int64_t tot = (a.Rcap - i0) * (int64_t)ldp * ES - (GATE ? c_lo * ES : 0);
                 p_rec0 = __builtin_amdgcn_readfirstlane(tot > 0xffffffffLL ? 0xffffffffu : (uint32_t)tot);
             }
             p_cstride = (uint32_t)(16 * ldp * ES);
@@ -594,9 +610,9 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             }
         } else {
             q_step = GG_ROWB;
-            q_base = (const char*)a.Q + (int64_t)e * N * K * ES;
+            q_base = (const char*)a.Q + (int64_t)e * N * K * ES + (GATE ? c_lo * ES : 0);
             {   // the weights of this expert
-                const int64_t tot = (int64_t)N * K * ES;
+                const int64_t tot = (int64_t)N * K * ES - (GATE ? c_lo * ES : 0);
                 q_rec0 = __builtin_amdgcn_readfirstlane(tot > 0xffffffffLL ? 0xffffffffu : (uint32_t)tot);
             }
             q_cstride = (uint32_t)(16 * K * ES);
@@ -1580,7 +1596,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                     for (int g = 0; g < 2; ++g) {
                         const int rb = row0 + 16 * i + 8 * g;   // wave-uniform
                         if (rb + rr >= ep_i_end) continue;
-                        char* const at = (char*)a.out + ((MODE == GG_WGRAD) ? ((int64_t)ep_e * N + rb) : (int64_t)rb) * ld * OB +
+                        char* const at = (char*)a.out + (GATE ? (int64_t)ep_part * a.Rcap * ld * OB : 0) + ((MODE == GG_WGRAD) ? ((int64_t)ep_e * N + rb) : (int64_t)rb) * ld * OB +
                                          (hf == 0 ? vo_lo : vo_hi);
                         f32x4_t lo = o.v[g][0], hi = o.v[g][1];
                         if (OUT_F32) {
@@ -2472,14 +2488,21 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
 // ---------------------------------------------------------------------------
 // Gate GEMM (Sec. 2.1.2 item 1): logits[T,E] = X[T,h] * Wr[E,h]^T, bf16 operands, fp32 accumulation and fp32
 // output (the router works on fp32 logits, Sec. 5.1).  One group of T rows through the forward kernel with the
-// fp32 store; the two-entry offsets array lives in the context's reserved workspace and is written by a
-// one-thread kernel, so the call allocates and copies nothing.  With E <= 256 there is one column tile: T / 256
-// workgroups have work, which is a quarter of the chip at T = 16384 -- small next to the layer, not tuned.
+// fp32 store.  With E <= 256 there is one column tile, so T / 256 workgroups have a tile (a quarter of the chip at
+// T = 16384): the contraction is cut into as many pieces as fill the compute units, each a work item that leaves
+// an fp32 partial result in the context's workspace, and a second kernel adds the pieces in order.  A piece keeps at
+// least 8 stages (1.45 us each), less than which does not pay for the second launch and the partial results' way.
+// T 16384, E 256, h 7168 (64 tiles, 112 stages): one piece 176 us + 5 for a launch that wrote the group's offsets; four
+// pieces 73 + 13 for the sum.  T 2048, E 64, h 4096: 75 + 5 : 21 + 4.  Bound now: HBM (X once, 235 MB, and the partial results
+// out and in, 134 MB) and the 28 stages of a piece (41 us at the rate operands reach a compute unit).
 // ---------------------------------------------------------------------------
-#define MOE_WS_GATE_OFFSETS 32  // byte offset of {0, T} in the reserved head of the workspace
-__global__ void gate_offsets_kernel(int32_t* o, int T) {
-    o[0] = 0;
-    o[1] = T;
+#define GATE_MIN_STAGES 8
+__global__ __launch_bounds__(256) void gate_add_kernel(const f32x4_t* __restrict__ part, int pieces, int64_t n4, f32x4_t* __restrict__ out) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+        f32x4_t v = part[i];
+        for (int p = 1; p < pieces; ++p) v += part[p * n4 + i];
+        out[i] = v;
+    }
 }
 
 extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, const void* Wr, int T, int E, int h,
@@ -2487,13 +2510,24 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
     if (!ctx) return MOE_ERR_ARG;
     if (!logits) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_gate_gemm: logits is NULL");
     if (T < 1) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_gate_gemm: T must be positive");
-    int32_t* offsets = (int32_t*)((char*)ctx->ws + MOE_WS_GATE_OFFSETS);
-    moe_status st = gg_check_common(ctx, "moe_gate_gemm", X, Wr, offsets, 1, E, h, T, MOE_BF16);
+    moe_status st = gg_check_common(ctx, "moe_gate_gemm", X, Wr, (const int32_t*)ctx->ws, 1, E, h, T, MOE_BF16);
     if (st != MOE_OK) return st;
     if (h % 64) MOE_FAIL(ctx, MOE_ERR_UNSUPPORTED, "moe_gate_gemm: h=%d must be a multiple of 64", h);
-    hipLaunchKernelGGL(gate_offsets_kernel, dim3(1), dim3(1), 0, (hipStream_t)stream, offsets, T);
-    gg_args a = gg_make(ctx, X, Wr, offsets, 1, E, h, T, logits);
+    gg_args a = gg_make(ctx, X, Wr, nullptr, 1, E, h, T, logits);
+    const int64_t tiles = ceil_div64(T, GG_BM) * ceil_div64(E, GG_BN), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
+    const size_t one = (size_t)T * E * sizeof(float), room = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;
+    int64_t pieces = cu / tiles;
+    if (pieces > h / 64 / GATE_MIN_STAGES) pieces = h / 64 / GATE_MIN_STAGES;
+    if (pieces > (int64_t)(room / one)) pieces = (int64_t)(room / one);
+    if (pieces < 2) pieces = 1;
+    a.split_cap = (int)pieces;
+    if (pieces > 1) a.out = (char*)ctx->ws + MOE_WS_RESERVED;
     GG_LAUNCH(GG_FWD, GG_EPI_STORE, true, 0);
+    if (pieces > 1) {
+        const int64_t n4 = (int64_t)T * E / 4, blocks = ceil_div64(n4, 256);
+        hipLaunchKernelGGL(gate_add_kernel, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, (hipStream_t)stream,
+                           (const f32x4_t*)a.out, (int)pieces, n4, (f32x4_t*)logits);
+    }
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<gate>");
     return MOE_OK;
 }
