@@ -2178,6 +2178,15 @@ static moe_status gg_mx_out_check(moe_ctx* ctx, const char* who, const gg_mx_out
     return MOE_OK;
 }
 
+// The small-tile kernels' quantised copies of a stored tensor X [live rows, cols]: the stand-alone quantisers, which produce
+// the codes and scales of the quantising epilogues.
+static moe_status gg_quantise(moe_ctx* ctx, void* stream, const void* X, int64_t rows, int cols, const int32_t* live, bool mx,
+                              const gg_args& a) {
+    if (!mx) return moe_fp8_quantize(ctx, stream, X, MOE_Q_1x128, 1, rows, cols, live, a.out_q, a.out_q_scale);
+    if (!a.out_qc) return moe_mx_quantize(ctx, stream, X, MOE_MX_1x32, 1, rows, cols, live, a.out_q, a.out_q_e8);
+    return moe_mx_quantize_rowcol(ctx, stream, X, rows, cols, live, a.out_q, a.out_q_e8, a.out_qc, a.out_qc_e8);
+}
+
 static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const void* B, const int32_t* offsets, int E, int N,
                              int K, int64_t Rcap, moe_dtype dt, moe_epilogue epi, const float* a_scale, const float* b_scale,
                              const float* row_prob, void* C, void* C_act, void* act_q, float* act_q_scale,
@@ -2254,8 +2263,11 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
         a.out_qc_e8 = mxo->e8_col;
     }
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
-    if (const int tile = fp8 ? 0 : gt_tile(ctx, GG_FWD, ge, a)) {
-        gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
+    if (const int tile = fp8 ? gq_tile(ctx, GG_FWD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_FWD, ge, a)) {
+        if (!fp8) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
+        else gq_launch((hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
+        MOE_LAUNCH_CHECK(ctx, "gt_kernel<fwd>");
+        return a.out_q ? gg_quantise(ctx, stream, C_act, Rcap, N / 2, offsets + E, mx, a) : MOE_OK;
     } else if (epi == MOE_EPI_SWIGLU) {
         if (mx) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 2);
         else if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 1);
@@ -2381,8 +2393,11 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
         a.out_qc_e8 = mxo->e8_col;
     }
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
-    if (const int tile = fp8 ? 0 : gt_tile(ctx, GG_DGRAD, ge, a)) {
-        gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
+    if (const int tile = fp8 ? gq_tile(ctx, GG_DGRAD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_DGRAD, ge, a)) {
+        if (!fp8) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
+        else gq_launch((hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
+        MOE_LAUNCH_CHECK(ctx, "gt_kernel<dgrad>");
+        return a.out_q ? gg_quantise(ctx, stream, dA, Rcap, 2 * K, offsets + E, mx, a) : MOE_OK;
     } else if (Z_saved) {
         if (mx) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 2);
         else if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
@@ -2441,14 +2456,15 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
         st = gg_gather_args(ctx, "moe_grouped_gemm_wgrad_gather", a, T, src_of, k, gath == 2 ? K : N, Rcap);
         if (st != MOE_OK) return st;
     }
-    if (const int tile = (mx || bw) ? 0 : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
-        gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
+    a.p_scale = dc_scale;
+    a.q_scale = a_scale;
+    if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
+        if (mx || bw) gq_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
+        else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;
     }
     a.tile_counter = ctx->aux + MOE_AUX_TILE_COUNTER;
-    a.p_scale = dc_scale;
-    a.q_scale = a_scale;
     // split contraction (bf16 operands): as many slices of partial tiles as the workspace holds behind its reserved head
     const size_t slice_bytes = (size_t)ceil_div64(N, GG_BM) * ceil_div64(K, GG_BN) * GG_BM * GG_BN * sizeof(float);
     const size_t ws_free = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;

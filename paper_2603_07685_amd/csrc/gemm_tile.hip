@@ -21,17 +21,7 @@
 // of the tiles made it slower where there are many (BM = 64, 24 experts, 8000 rows: 309 us against 251).
 // Where the rows of an expert fit one tile and the call streams the weights, a third buffer is worth more than the third
 // workgroup (decoding, 32 rows on each of 16 experts, 403 MB of fc1 weights: 92 us against 98, 4.4 TB/s).
-#include "gemm.h"
-
-#define GT_BN 128
-#define GT_BAND 8   // row tiles per band of the tile order (tiles of a band that share a column run together)
-
-// 16 bytes per lane, descriptor in scalar registers, lane offset in bytes; LDS side: M0 + 16 * lane
-__device__ __forceinline__ void dma16_buf(i32x4_t rsrc, uint32_t off, uint32_t lds_wave, uint32_t lds_const) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(m0_value(lds_wave, lds_const)), "v"(off), "s"(rsrc) : "memory", "m0");
-}
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+#include "gemm_tile.h"
 
 template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF>
 __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
@@ -40,7 +30,6 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
     constexpr int P_BYTES = BM * 128, STAGE = P_BYTES + GT_BN * 128;
     constexpr int PC = BM / 32, QC = 4;                 // 1 KB DMA chunks per wave, operand and stage
     constexpr int NI = BM / 32;                         // 16-row blocks per wave
-    constexpr int STG_PITCH = 132;
     static_assert(NBUF * STAGE >= 64 * STG_PITCH * 4, "the output phase stages 64 rows in the ring");
     __shared__ __attribute__((aligned(1024))) char ring[NBUF * STAGE];
     __shared__ tile_pick_lds pick;
@@ -62,10 +51,7 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
     int ti, tj;
     {
         const int tiles_i = MODE == GG_WGRAD ? tiles_iw : (row_hi - row_lo + BM - 1) / BM;
-        const int band_sz = GT_BAND * tiles_j, band = u / band_sz, in_band = u - band * band_sz;
-        const int band_rows = min(GT_BAND, tiles_i - band * GT_BAND);
-        ti = __builtin_amdgcn_readfirstlane(band * GT_BAND + in_band % band_rows);
-        tj = __builtin_amdgcn_readfirstlane(in_band / band_rows);
+        gt_place(u, tiles_i, tiles_j, ti, tj);
     }
     const int i0 = MODE == GG_WGRAD ? ti * BM : row_lo + ti * BM;
     const int i_end = MODE == GG_WGRAD ? N : row_hi;
@@ -246,118 +232,14 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
     wait_lgkm0();
     stage_barrier();
 
-    // ---- output: 64 rows at a time (32 of each wave half) through LDS in fp32, back as whole rows ----
-    // A lane's accumulators of a block are one row (l16) x 4 columns (4 kq ..); a staged row comes back to 16 lanes of 8
-    // consecutive columns each, so a store instruction is 4 rows x 256 contiguous bytes (bf16).
-    float* const stg = (float*)ring;
-    const int c8 = (lane & 15) * 8;
-#pragma unroll
-    for (int ps = 0; ps < BM / 64; ++ps) {
-        // staged row q (0..63) is tile row (q / 32) * (BM / 2) + 32 ps + q % 32
-        auto out_row = [&](int q) { return i0 + (q >> 5) * (BM / 2) + 32 * ps + (q & 31); };
-        u32x4_t zg[4], zu[4];
-        if (EPI == GG_EPI_SWIGLU_BWD) {   // the saved pre-activations: on their way while the accumulators are staged
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int r = out_row(wave * 16 + t * 4 + (lane >> 4));
-                if (r < i_end && j0 + c8 < K) {
-                    const bf16_t* z = a.Zsaved + (int64_t)r * 2 * K + j0 + c8;
-                    zg[t] = *(const u32x4_t*)z;
-                    zu[t] = *(const u32x4_t*)(z + K);
-                }
-            }
-        }
-        if (ps) __syncthreads();
+    gt_output<MODE, EPI, OUT_F32, BM>(a, (float*)ring, e, i0, i_end, j0, tj, tiles_j, [&](int ps, float* stg) {
+        // a lane's accumulators of a block: one row (l16), columns 4 kq .. 4 kq + 3
 #pragma unroll
         for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 *(f32x4_t*)(stg + (wm * 32 + 16 * i2 + l16) * STG_PITCH + col_of(j) + 4 * kq) = acc[2 * ps + i2][j];
-        __syncthreads();
-        auto pack8 = [](const float* v) {
-            return u32x4_t{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
-        };
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int q = wave * 16 + t * 4 + (lane >> 4), r = out_row(q);
-            const bool live = r < i_end;
-            float v[8];
-            *(f32x4_t*)v = *(const f32x4_t*)(stg + q * STG_PITCH + c8);
-            *(f32x4_t*)(v + 4) = *(const f32x4_t*)(stg + q * STG_PITCH + c8 + 4);
-            if (EPI == GG_EPI_SWIGLU) {
-                const int f = j0 + (c8 & 63);
-                if (a.out && live && f < half_cols)
-                    *(u32x4_t*)((bf16_t*)a.out + (int64_t)r * N + (c8 < 64 ? f : half_cols + f)) = pack8(v);
-            } else if (EPI == GG_EPI_SWIGLU_BWD) {
-                float dot = 0.f;
-                if (live && j0 + c8 < K) {
-                    const float gt[8] = {bf16_lo(zg[t].x), bf16_hi(zg[t].x), bf16_lo(zg[t].y), bf16_hi(zg[t].y),
-                                         bf16_lo(zg[t].z), bf16_hi(zg[t].z), bf16_lo(zg[t].w), bf16_hi(zg[t].w)};
-                    const float up[8] = {bf16_lo(zu[t].x), bf16_hi(zu[t].x), bf16_lo(zu[t].y), bf16_hi(zu[t].y),
-                                         bf16_lo(zu[t].z), bf16_hi(zu[t].z), bf16_lo(zu[t].w), bf16_hi(zu[t].w)};
-                    const float pr = a.row_prob ? a.row_prob[r] : 1.0f;
-                    float dg[8], du[8];
-#pragma unroll
-                    for (int x = 0; x < 8; ++x) {
-                        const float sg = sigmoid_f(gt[x]);
-                        dg[x] = pr * v[x] * up[x] * sg * (1.0f + gt[x] * (1.0f - sg));
-                        du[x] = pr * v[x] * gt[x] * sg;
-                        dot += v[x] * (gt[x] * sg * up[x]);
-                    }
-                    bf16_t* o = (bf16_t*)a.out + (int64_t)r * 2 * K + j0 + c8;
-                    *(u32x4_t*)o = pack8(dg);
-                    *(u32x4_t*)(o + K) = pack8(du);
-                }
-                if (a.dprob_part) {   // one partial sum per row and 128-column tile; an odd tile count leaves one entry over
-#pragma unroll
-                    for (int x = 1; x < 16; x <<= 1) dot += __shfl_xor(dot, x);
-                    if (live && (lane & 15) == 0) {
-                        float* d = a.dprob_part + (int64_t)r * (2 * ((K + 255) / 256));
-                        d[tj] = dot;
-                        if (tj + 1 == tiles_j && (tiles_j & 1)) d[tj + 1] = 0.f;
-                    }
-                }
-            } else if (live && j0 + c8 < J) {
-                const int64_t at = (MODE == GG_WGRAD ? ((int64_t)e * N + r) * K : (int64_t)r * J) + j0 + c8;
-                if (OUT_F32) {
-                    f32x4_t* o = (f32x4_t*)((float*)a.out + at);
-                    f32x4_t lo = *(f32x4_t*)v, hi = *(f32x4_t*)(v + 4);
-                    if (a.accumulate) {
-                        lo += o[0];
-                        hi += o[1];
-                    }
-                    o[0] = lo;
-                    o[1] = hi;
-                } else {
-                    u32x4_t* o = (u32x4_t*)((bf16_t*)a.out + at);
-                    if (a.accumulate) {
-                        const u32x4_t w = *o;
-                        v[0] += bf16_lo(w.x); v[1] += bf16_hi(w.x); v[2] += bf16_lo(w.y); v[3] += bf16_hi(w.y);
-                        v[4] += bf16_lo(w.z); v[5] += bf16_hi(w.z); v[6] += bf16_lo(w.w); v[7] += bf16_hi(w.w);
-                    }
-                    *o = pack8(v);
-                }
-            }
-        }
-        if (EPI == GG_EPI_SWIGLU) {   // activation: 8 features per lane, 8 rows per instruction
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int q = wave * 16 + t * 8 + (lane >> 3), r = out_row(q), f8 = (lane & 7) * 8;
-                if (r < i_end && j0 + f8 < half_cols) {
-                    const float pr = a.row_prob ? a.row_prob[r] : 1.0f;
-                    float act[8];
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const f32x4_t gt = *(const f32x4_t*)(stg + q * STG_PITCH + f8 + 4 * h);
-                        const f32x4_t up = *(const f32x4_t*)(stg + q * STG_PITCH + 64 + f8 + 4 * h);
-#pragma unroll
-                        for (int x = 0; x < 4; ++x) act[4 * h + x] = pr * (gt[x] * sigmoid_f(gt[x]) * up[x]);
-                    }
-                    *(u32x4_t*)(a.out_act + (int64_t)r * half_cols + j0 + f8) = pack8(act);
-                }
-            }
-        }
-    }
+    });
 }
 
 // ---------------------------------------------------------------------------
