@@ -4,6 +4,8 @@ Every function has the name and argument order of its C entry point in
 include/moe_hip.h.  Tensors are torch CUDA tensors used as device memory; the
 current torch stream is passed as the HIP stream.  Nothing here computes: if
 the library is missing the import of `lib()` raises, there is no fallback.
+The entry points of a step are called through csrc/pycall.cpp, which converts
+the arguments in native code; the others through ctypes.
 """
 from __future__ import annotations
 
@@ -15,6 +17,7 @@ import torch
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("MOE_HIP_LIB") or os.path.join(_PKG, "libmoe_hip.so")
 _lib = None
+_native = None   # the module built from csrc/pycall.cpp; set by lib(), so before any Context exists
 
 BF16, FP8_E4M3, F32, MXFP8_E4M3 = 0, 1, 2, 3
 SOFTMAX, SIGMOID = 0, 1
@@ -90,8 +93,19 @@ def lib() -> C.CDLL:
         for name in EXPORTS:
             if name not in ("moe_workspace_bytes", "moe_last_error"):
                 getattr(L, name).restype = _i
+        _load_native(L)
         _lib = L
     return _lib
+
+
+def _load_native(L):
+    global _native
+    try:
+        from . import _pycall
+    except ImportError as e:
+        raise MoeError(f"_pycall.so is not built or does not load ({e}): run `python -m paper_2603_07685_amd.build` first") from e
+    _pycall.init({name: C.cast(getattr(L, name), _vp).value for name in EXPORTS}, _ptr)
+    _native = _pycall
 
 
 def _ptr(t):
@@ -116,6 +130,7 @@ class Context:
         if st != 0:
             raise MoeError(f"moe_ctx_create failed with status {st}")
         self.h = h_
+        self._addr = h_.value
 
     def check(self, st, what):
         if st != 0:
@@ -129,7 +144,7 @@ class Context:
     def close(self):
         if self.h:
             lib().moe_ctx_destroy(self.h)
-            self.h = None
+            self.h = self._addr = None
 
     def __del__(self):
         try:
@@ -143,25 +158,30 @@ def moe_workspace_bytes(T, k, E, h, f_max):
 
 
 def moe_route_topk(ctx, logits, T, E, k, fn, norm_topk, scale, topk_idx, topk_prob, counts):
-    ctx.check(lib().moe_route_topk(ctx.h, _stream(), _ptr(logits), T, E, k, fn, int(norm_topk), scale,
-                                   _ptr(topk_idx), _ptr(topk_prob), _ptr(counts)), "moe_route_topk")
+    st = _native.moe_route_topk(ctx._addr, logits, T, E, k, fn, int(norm_topk), scale, topk_idx, topk_prob, counts)
+    if st:
+        ctx.check(st, "moe_route_topk")
 
 
 def moe_route_topk_grouped(ctx, logits, expert_bias, T, E, k, n_group, topk_group, fn, norm_topk, scale,
                            topk_idx, topk_prob, counts):
-    ctx.check(lib().moe_route_topk_grouped(ctx.h, _stream(), _ptr(logits), _ptr(expert_bias), T, E, k, n_group,
-                                           topk_group, fn, int(norm_topk), float(scale), _ptr(topk_idx),
-                                           _ptr(topk_prob), _ptr(counts)), "moe_route_topk_grouped")
+    st = _native.moe_route_topk_grouped(ctx._addr, logits, expert_bias, T, E, k, n_group, topk_group, fn, int(norm_topk),
+                                        float(scale), topk_idx, topk_prob, counts)
+    if st:
+        ctx.check(st, "moe_route_topk_grouped")
 
 
 def moe_aux_loss(ctx, logits, counts, T, E, k, fn, coeff, dloss, accumulate, loss, dlogits):
-    ctx.check(lib().moe_aux_loss(ctx.h, _stream(), _ptr(logits), _ptr(counts), T, E, k, fn, float(coeff), float(dloss),
-                                 int(bool(accumulate)), _ptr(loss), _ptr(dlogits)), "moe_aux_loss")
+    st = _native.moe_aux_loss(ctx._addr, logits, counts, T, E, k, fn, float(coeff), float(dloss), bool(accumulate), loss,
+                              dlogits)
+    if st:
+        ctx.check(st, "moe_aux_loss")
 
 
 def moe_permute(ctx, X, dt, idx, T, k, h, E, align, Xp, Rcap, row_of, src_of, offsets, counts):
-    ctx.check(lib().moe_permute(ctx.h, _stream(), _ptr(X), dt, _ptr(idx), T, k, h, E, align, _ptr(Xp), Rcap,
-                                _ptr(row_of), _ptr(src_of), _ptr(offsets), _ptr(counts)), "moe_permute")
+    st = _native.moe_permute(ctx._addr, X, dt, idx, T, k, h, E, align, Xp, Rcap, row_of, src_of, offsets, counts)
+    if st:
+        ctx.check(st, "moe_permute")
 
 
 def moe_permute_static(X, dt, idx, T, k, h, E, align, Xp, Rcap, row_of, src_of, offsets, counts):
@@ -172,146 +192,163 @@ def moe_permute_static(X, dt, idx, T, k, h, E, align, Xp, Rcap, row_of, src_of, 
 
 
 def moe_grouped_gemm_fwd(ctx, A, B, offsets, E, N, K, Rcap, dt, epi, a_scale, b_scale, Cout, C_act):
-    ctx.check(lib().moe_grouped_gemm_fwd(ctx.h, _stream(), _ptr(A), _ptr(B), _ptr(offsets), E, N, K, Rcap, dt, epi,
-                                         _ptr(a_scale), _ptr(b_scale), _ptr(Cout), _ptr(C_act)),
-              "moe_grouped_gemm_fwd")
+    st = _native.moe_grouped_gemm_fwd(ctx._addr, A, B, offsets, E, N, K, Rcap, dt, epi, a_scale, b_scale, Cout, C_act)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_fwd")
 
 
 def moe_grouped_gemm_dgrad(ctx, dC, B, offsets, E, N, K, Rcap, dt, Z_saved, dc_scale, b_scale, dA):
-    ctx.check(lib().moe_grouped_gemm_dgrad(ctx.h, _stream(), _ptr(dC), _ptr(B), _ptr(offsets), E, N, K, Rcap, dt,
-                                           _ptr(Z_saved), _ptr(dc_scale), _ptr(b_scale), _ptr(dA)),
-              "moe_grouped_gemm_dgrad")
+    st = _native.moe_grouped_gemm_dgrad(ctx._addr, dC, B, offsets, E, N, K, Rcap, dt, Z_saved, dc_scale, b_scale, dA)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_dgrad")
 
 
 def moe_grouped_gemm_fwd_weighted(ctx, A, B, offsets, E, N, K, Rcap, dt, epi, a_scale, b_scale, row_prob, Cout, C_act):
-    ctx.check(lib().moe_grouped_gemm_fwd_weighted(ctx.h, _stream(), _ptr(A), _ptr(B), _ptr(offsets), E, N, K, Rcap, dt,
-                                                  epi, _ptr(a_scale), _ptr(b_scale), _ptr(row_prob), _ptr(Cout),
-                                                  _ptr(C_act)),
-              "moe_grouped_gemm_fwd_weighted")
+    st = _native.moe_grouped_gemm_fwd_weighted(ctx._addr, A, B, offsets, E, N, K, Rcap, dt, epi, a_scale, b_scale,
+                                               row_prob, Cout, C_act)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_fwd_weighted")
 
 
 def moe_grouped_gemm_dgrad_weighted(ctx, dC, B, offsets, E, N, K, Rcap, dt, Z_saved, dc_scale, b_scale, row_prob, dA,
                                     dprob_part):
-    ctx.check(lib().moe_grouped_gemm_dgrad_weighted(ctx.h, _stream(), _ptr(dC), _ptr(B), _ptr(offsets), E, N, K, Rcap,
-                                                    dt, _ptr(Z_saved), _ptr(dc_scale), _ptr(b_scale), _ptr(row_prob),
-                                                    _ptr(dA), _ptr(dprob_part)),
-              "moe_grouped_gemm_dgrad_weighted")
+    st = _native.moe_grouped_gemm_dgrad_weighted(ctx._addr, dC, B, offsets, E, N, K, Rcap, dt, Z_saved, dc_scale, b_scale,
+                                                 row_prob, dA, dprob_part)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_dgrad_weighted")
 
 
 def moe_grouped_gemm_fwd_quant(ctx, A, B, offsets, E, N, K, Rcap, dt, epi, a_scale, b_scale, row_prob, Cout, C_act,
                                act_q, act_q_scale):
-    ctx.check(lib().moe_grouped_gemm_fwd_quant(ctx.h, _stream(), _ptr(A), _ptr(B), _ptr(offsets), E, N, K, Rcap, dt, epi,
-                                               _ptr(a_scale), _ptr(b_scale), _ptr(row_prob), _ptr(Cout), _ptr(C_act),
-                                               _ptr(act_q), _ptr(act_q_scale)), "moe_grouped_gemm_fwd_quant")
+    st = _native.moe_grouped_gemm_fwd_quant(ctx._addr, A, B, offsets, E, N, K, Rcap, dt, epi, a_scale, b_scale, row_prob,
+                                            Cout, C_act, act_q, act_q_scale)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_fwd_quant")
 
 
 def moe_grouped_gemm_dgrad_quant(ctx, dC, B, offsets, E, N, K, Rcap, dt, Z_saved, dc_scale, b_scale, row_prob, dA,
                                  dprob_part, dz_q, dz_q_scale):
-    ctx.check(lib().moe_grouped_gemm_dgrad_quant(ctx.h, _stream(), _ptr(dC), _ptr(B), _ptr(offsets), E, N, K, Rcap, dt,
-                                                 _ptr(Z_saved), _ptr(dc_scale), _ptr(b_scale), _ptr(row_prob), _ptr(dA),
-                                                 _ptr(dprob_part), _ptr(dz_q), _ptr(dz_q_scale)),
-              "moe_grouped_gemm_dgrad_quant")
+    st = _native.moe_grouped_gemm_dgrad_quant(ctx._addr, dC, B, offsets, E, N, K, Rcap, dt, Z_saved, dc_scale, b_scale,
+                                              row_prob, dA, dprob_part, dz_q, dz_q_scale)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_dgrad_quant")
 
 
 def moe_grouped_gemm_fwd_quant_mx(ctx, A, B, offsets, E, N, K, Rcap, a_scale, b_scale, row_prob, Cout, C_act,
                                   act_q_row, act_e8_row, act_q_col, act_e8_col):
-    ctx.check(lib().moe_grouped_gemm_fwd_quant_mx(ctx.h, _stream(), _ptr(A), _ptr(B), _ptr(offsets), E, N, K, Rcap,
-                                                  _ptr(a_scale), _ptr(b_scale), _ptr(row_prob), _ptr(Cout), _ptr(C_act),
-                                                  _ptr(act_q_row), _ptr(act_e8_row), _ptr(act_q_col), _ptr(act_e8_col)),
-              "moe_grouped_gemm_fwd_quant_mx")
+    st = _native.moe_grouped_gemm_fwd_quant_mx(ctx._addr, A, B, offsets, E, N, K, Rcap, a_scale, b_scale, row_prob, Cout,
+                                               C_act, act_q_row, act_e8_row, act_q_col, act_e8_col)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_fwd_quant_mx")
 
 
 def moe_grouped_gemm_dgrad_quant_mx(ctx, dC, B, offsets, E, N, K, Rcap, Z_saved, dc_scale, b_scale, row_prob, dZ,
                                     dprob_part, dz_q_row, dz_e8_row, dz_q_col, dz_e8_col):
-    ctx.check(lib().moe_grouped_gemm_dgrad_quant_mx(ctx.h, _stream(), _ptr(dC), _ptr(B), _ptr(offsets), E, N, K, Rcap,
-                                                    _ptr(Z_saved), _ptr(dc_scale), _ptr(b_scale), _ptr(row_prob), _ptr(dZ),
-                                                    _ptr(dprob_part), _ptr(dz_q_row), _ptr(dz_e8_row), _ptr(dz_q_col),
-                                                    _ptr(dz_e8_col)), "moe_grouped_gemm_dgrad_quant_mx")
+    st = _native.moe_grouped_gemm_dgrad_quant_mx(ctx._addr, dC, B, offsets, E, N, K, Rcap, Z_saved, dc_scale, b_scale,
+                                                 row_prob, dZ, dprob_part, dz_q_row, dz_e8_row, dz_q_col, dz_e8_col)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_dgrad_quant_mx")
 
 
 def moe_gate_gemm(ctx, X, Wr, T, E, h, logits):
-    ctx.check(lib().moe_gate_gemm(ctx.h, _stream(), _ptr(X), _ptr(Wr), T, E, h, _ptr(logits)), "moe_gate_gemm")
+    st = _native.moe_gate_gemm(ctx._addr, X, Wr, T, E, h, logits)
+    if st:
+        ctx.check(st, "moe_gate_gemm")
 
 
 def moe_route_topk_bwd(ctx, logits, topk_idx, dprob, T, E, k, fn, norm_topk, scale, dlogits):
-    ctx.check(lib().moe_route_topk_bwd(ctx.h, _stream(), _ptr(logits), _ptr(topk_idx), _ptr(dprob), T, E, k, fn,
-                                       int(norm_topk), float(scale), _ptr(dlogits)), "moe_route_topk_bwd")
+    st = _native.moe_route_topk_bwd(ctx._addr, logits, topk_idx, dprob, T, E, k, fn, int(norm_topk), float(scale), dlogits)
+    if st:
+        ctx.check(st, "moe_route_topk_bwd")
 
 
 def moe_gather_row_prob(ctx, prob, src_of, Rcap, row_prob):
-    ctx.check(lib().moe_gather_row_prob(ctx.h, _stream(), _ptr(prob), _ptr(src_of), Rcap, _ptr(row_prob)),
-              "moe_gather_row_prob")
+    st = _native.moe_gather_row_prob(ctx._addr, prob, src_of, Rcap, row_prob)
+    if st:
+        ctx.check(st, "moe_gather_row_prob")
 
 
 def moe_scatter_row_dprob(ctx, dprob_part, parts, row_of, T, k, dprob):
-    ctx.check(lib().moe_scatter_row_dprob(ctx.h, _stream(), _ptr(dprob_part), parts, _ptr(row_of), T, k, _ptr(dprob)),
-              "moe_scatter_row_dprob")
+    st = _native.moe_scatter_row_dprob(ctx._addr, dprob_part, parts, row_of, T, k, dprob)
+    if st:
+        ctx.check(st, "moe_scatter_row_dprob")
 
 
 def moe_grouped_gemm_wgrad(ctx, A, dC, offsets, E, N, K, Rcap, dt, a_scale, dc_scale, accumulate, out_dt, dB):
-    ctx.check(lib().moe_grouped_gemm_wgrad(ctx.h, _stream(), _ptr(A), _ptr(dC), _ptr(offsets), E, N, K, Rcap, dt,
-                                           _ptr(a_scale), _ptr(dc_scale), int(accumulate), out_dt, _ptr(dB)),
-              "moe_grouped_gemm_wgrad")
+    st = _native.moe_grouped_gemm_wgrad(ctx._addr, A, dC, offsets, E, N, K, Rcap, dt, a_scale, dc_scale, int(accumulate),
+                                        out_dt, dB)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_wgrad")
 
 
 def moe_grouped_gemm_fwd_gather(ctx, X, T, src_of, k, B, offsets, E, N, K, Rcap, epi, row_prob, Cout, C_act):
-    ctx.check(lib().moe_grouped_gemm_fwd_gather(ctx.h, _stream(), _ptr(X), T, _ptr(src_of), k, _ptr(B), _ptr(offsets),
-                                                E, N, K, Rcap, epi, _ptr(row_prob), _ptr(Cout), _ptr(C_act)),
-              "moe_grouped_gemm_fwd_gather")
+    st = _native.moe_grouped_gemm_fwd_gather(ctx._addr, X, T, src_of, k, B, offsets, E, N, K, Rcap, epi, row_prob, Cout,
+                                             C_act)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_fwd_gather")
 
 
 def moe_grouped_gemm_dgrad_gather(ctx, G, T, src_of, k, B, offsets, E, N, K, Rcap, Z_saved, row_prob, dA, dprob_part):
-    ctx.check(lib().moe_grouped_gemm_dgrad_gather(ctx.h, _stream(), _ptr(G), T, _ptr(src_of), k, _ptr(B), _ptr(offsets),
-                                                  E, N, K, Rcap, _ptr(Z_saved), _ptr(row_prob), _ptr(dA),
-                                                  _ptr(dprob_part)), "moe_grouped_gemm_dgrad_gather")
+    st = _native.moe_grouped_gemm_dgrad_gather(ctx._addr, G, T, src_of, k, B, offsets, E, N, K, Rcap, Z_saved, row_prob,
+                                               dA, dprob_part)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_dgrad_gather")
 
 
 def moe_grouped_gemm_wgrad_gather(ctx, A, dC, which, T, src_of, k, offsets, E, N, K, Rcap, accumulate, out_dt, dB):
-    ctx.check(lib().moe_grouped_gemm_wgrad_gather(ctx.h, _stream(), _ptr(A), _ptr(dC), which, T, _ptr(src_of), k,
-                                                  _ptr(offsets), E, N, K, Rcap, int(accumulate), out_dt, _ptr(dB)),
-              "moe_grouped_gemm_wgrad_gather")
+    st = _native.moe_grouped_gemm_wgrad_gather(ctx._addr, A, dC, which, T, src_of, k, offsets, E, N, K, Rcap,
+                                               int(accumulate), out_dt, dB)
+    if st:
+        ctx.check(st, "moe_grouped_gemm_wgrad_gather")
 
 
 def moe_unpermute_combine(ctx, O, dt, row_of, prob, residual, T, k, h, Y):
-    ctx.check(lib().moe_unpermute_combine(ctx.h, _stream(), _ptr(O), dt, _ptr(row_of), _ptr(prob), _ptr(residual),
-                                          T, k, h, _ptr(Y)), "moe_unpermute_combine")
+    st = _native.moe_unpermute_combine(ctx._addr, O, dt, row_of, prob, residual, T, k, h, Y)
+    if st:
+        ctx.check(st, "moe_unpermute_combine")
 
 
 def moe_unpermute_combine_bwd(ctx, dY, O, dt, row_of, src_of, prob, T, k, h, Rcap, dO, dprob):
-    ctx.check(lib().moe_unpermute_combine_bwd(ctx.h, _stream(), _ptr(dY), _ptr(O), dt, _ptr(row_of), _ptr(src_of),
-                                              _ptr(prob), T, k, h, Rcap, _ptr(dO), _ptr(dprob)),
-              "moe_unpermute_combine_bwd")
+    st = _native.moe_unpermute_combine_bwd(ctx._addr, dY, O, dt, row_of, src_of, prob, T, k, h, Rcap, dO, dprob)
+    if st:
+        ctx.check(st, "moe_unpermute_combine_bwd")
 
 
 def moe_mx_quantize(ctx, X, block, groups, rows, cols, rows_dev, q, e8m0):
-    ctx.check(lib().moe_mx_quantize(ctx.h, _stream(), _ptr(X), block, groups, rows, cols, _ptr(rows_dev), _ptr(q),
-                                    _ptr(e8m0)), "moe_mx_quantize")
+    st = _native.moe_mx_quantize(ctx._addr, X, block, groups, rows, cols, rows_dev, q, e8m0)
+    if st:
+        ctx.check(st, "moe_mx_quantize")
 
 
 def moe_mx_quantize_rowcol(ctx, X, rows, cols, rows_dev, q_row, e8m0_row, q_col, e8m0_col):
-    ctx.check(lib().moe_mx_quantize_rowcol(ctx.h, _stream(), _ptr(X), rows, cols, _ptr(rows_dev), _ptr(q_row),
-                                           _ptr(e8m0_row), _ptr(q_col), _ptr(e8m0_col)), "moe_mx_quantize_rowcol")
+    st = _native.moe_mx_quantize_rowcol(ctx._addr, X, rows, cols, rows_dev, q_row, e8m0_row, q_col, e8m0_col)
+    if st:
+        ctx.check(st, "moe_mx_quantize_rowcol")
 
 
 def moe_mx_quantize_rowcol_gather(ctx, X, src_of, k, pair_scale, groups, rows, cols, rows_dev, q_row, e8m0_row, q_col,
                                   e8m0_col):
-    ctx.check(lib().moe_mx_quantize_rowcol_gather(ctx.h, _stream(), _ptr(X), _ptr(src_of), k, _ptr(pair_scale), groups, rows, cols,
-                                                  _ptr(rows_dev), _ptr(q_row), _ptr(e8m0_row), _ptr(q_col),
-                                                  _ptr(e8m0_col)), "moe_mx_quantize_rowcol_gather")
+    st = _native.moe_mx_quantize_rowcol_gather(ctx._addr, X, src_of, k, pair_scale, groups, rows, cols, rows_dev, q_row,
+                                               e8m0_row, q_col, e8m0_col)
+    if st:
+        ctx.check(st, "moe_mx_quantize_rowcol_gather")
 
 
 def moe_fp8_quantize(ctx, X, block, groups, rows, cols, rows_dev, q, scale):
-    ctx.check(lib().moe_fp8_quantize(ctx.h, _stream(), _ptr(X), block, groups, rows, cols, _ptr(rows_dev), _ptr(q),
-                                     _ptr(scale)), "moe_fp8_quantize")
+    st = _native.moe_fp8_quantize(ctx._addr, X, block, groups, rows, cols, rows_dev, q, scale)
+    if st:
+        ctx.check(st, "moe_fp8_quantize")
 
 
 def moe_fp8_quantize_rowcol(ctx, X, rows, cols, rows_dev, q_row, scale_row, q_col, scale_col):
-    ctx.check(lib().moe_fp8_quantize_rowcol(ctx.h, _stream(), _ptr(X), rows, cols, _ptr(rows_dev), _ptr(q_row),
-                                            _ptr(scale_row), _ptr(q_col), _ptr(scale_col)), "moe_fp8_quantize_rowcol")
+    st = _native.moe_fp8_quantize_rowcol(ctx._addr, X, rows, cols, rows_dev, q_row, scale_row, q_col, scale_col)
+    if st:
+        ctx.check(st, "moe_fp8_quantize_rowcol")
 
 
 def moe_fp8_quantize_rowcol_gather(ctx, X, src_of, k, pair_scale, groups, rows, cols, rows_dev, q_row, scale_row, q_col,
                                    scale_col):
-    ctx.check(lib().moe_fp8_quantize_rowcol_gather(ctx.h, _stream(), _ptr(X), _ptr(src_of), k, _ptr(pair_scale), groups, rows,
-                                                   cols, _ptr(rows_dev), _ptr(q_row), _ptr(scale_row), _ptr(q_col),
-                                                   _ptr(scale_col)), "moe_fp8_quantize_rowcol_gather")
+    st = _native.moe_fp8_quantize_rowcol_gather(ctx._addr, X, src_of, k, pair_scale, groups, rows, cols, rows_dev, q_row,
+                                                scale_row, q_col, scale_col)
+    if st:
+        ctx.check(st, "moe_fp8_quantize_rowcol_gather")

@@ -1,4 +1,4 @@
-"""Builds libmoe_hip.so (the C-ABI library) in-tree with hipcc for gfx950."""
+"""Builds libmoe_hip.so (the C-ABI library) in-tree with hipcc for gfx950, and _pycall.so, the native half of binding.py."""
 from __future__ import annotations
 
 import os
@@ -52,7 +52,28 @@ def build_library(verbose: bool = False, jobs: int = 8, extra_flags=(), out: str
     subprocess.check_call(cmd)
     if out is None:
         build_ceiling_probe(hipcc)
+        build_pycall()
     return lib
+
+
+PYCALL_LIB = os.path.join(PKG, "_pycall.so")
+
+
+def build_pycall() -> str:
+    """csrc/pycall.cpp against the installed torch: host code only (the define names the platform to HIP's host headers)."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+                           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+                           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include/torch/csrc/api/include"),
+                           "-isystem", os.path.join(rocm, "include"), os.path.join(CSRC, "pycall.cpp"),
+                           "-L", os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10",
+                           "-o", PYCALL_LIB])
+    return PYCALL_LIB
 
 
 CEILING_LIB = os.path.join(PKG, "libmfma_ceiling.so")
