@@ -355,10 +355,10 @@ moe_status moe_grouped_gemm_wgrad_gather(moe_ctx* ctx, void* stream, const void*
                                          int accumulate, moe_dtype out_dt, void* dB);
 
 /*
- * Quantisation of a GEMM's output fused into its epilogue (Sec. 5.4.2; the activation + quantisation
+ * Quantisation of a GEMM's output with the call itself (Sec. 5.4.2; the activation + quantisation
  * epilogue of Sec. 4.3.2), blockwise recipe (dt = MOE_FP8_E4M3) only.  The calls are the _weighted ones
- * with two more outputs, which receive the 1x128 codes and scales of the bf16 tensor the epilogue
- * stores, bit for bit what moe_fp8_quantize(MOE_Q_1x128) would make of it:
+ * with two more outputs, which receive the 1x128 codes and scales of the bf16 tensor the call
+ * stores (in the GEMM's epilogue, or, small calls, by one more launch), bit for bit what moe_fp8_quantize(MOE_Q_1x128) would make of it:
  *   fwd  (epi = MOE_EPI_SWIGLU): act_q [Rcap, N/2] codes, act_q_scale [Rcap, N/256] of C_act;
  *   dgrad (Z_saved != NULL)    : dz_q  [Rcap, 2K] codes,  dz_q_scale [Rcap, 2K/128] of dZ.
  * Both NULL = the _weighted call.  Rows >= offsets[E] are not written.
@@ -377,9 +377,9 @@ moe_status moe_grouped_gemm_dgrad_quant(moe_ctx* ctx, void* stream, const void* 
                                         void* dz_q, float* dz_q_scale);
 
 /*
- * The same fusion for the MXFP8 recipe (Sec. 5.3.3, 5.4.2; dt = MOE_MXFP8_E4M3 implied, operands and scales as
- * for the plain MXFP8 calls): the SwiGLU epilogue of fc1 / the SwiGLU-backward epilogue of the fc2 data gradient
- * also emit the quantised copies of the bf16 tensor they store (C_act [Rcap, N/2] / dZ [Rcap, 2K]; "cols" below is
+ * The same for the MXFP8 recipe (Sec. 5.3.3, 5.4.2; dt = MOE_MXFP8_E4M3 implied, operands and scales as
+ * for the plain MXFP8 calls): fc1 + SwiGLU / the fc2 data gradient + SwiGLU backward
+ * also emit, by one more launch, the quantised copies of the bf16 tensor they store (C_act [Rcap, N/2] / dZ [Rcap, 2K]; "cols" below is
  * that tensor's width), bit for bit what moe_mx_quantize_rowcol would make of it:
  *   q_row [Rcap, cols] codes, e8_row [Rcap, cols/32] E8M0 bytes: the 1x32 copy (operand of the next forward /
  *         data-gradient GEMM); required.

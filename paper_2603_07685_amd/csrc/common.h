@@ -167,12 +167,21 @@ struct tile_pick_lds {
     int wave_bad[16];
     int found[4];  // expert, tile, first row, end row
 };
+// In two parts for a workgroup that computes several tiles: the sums over the experts once (kept in registers), then one
+// look-up per tile.
 template <int THREADS>
-__device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
-                                          int mult, tile_pick_lds& l, int& e, int& u, int& row_lo, int& row_hi) {
-    constexpr int PER = 1024 / THREADS;
+struct tile_sums {
+    static constexpr int PER = 1024 / THREADS;   // experts per thread
+    int o[PER + 1], cnt[PER];                    // their offsets and tile counts
+    int n, first, total;                         // this thread's tiles, the first of them, all
+};
+template <int THREADS>
+__device__ __forceinline__ bool tile_scan(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
+                                          int mult, tile_pick_lds& l, tile_sums<THREADS>& st) {
+    constexpr int PER = tile_sums<THREADS>::PER;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    int o[PER + 1], cnt[PER];
+    auto& o = st.o;
+    auto& cnt = st.cnt;
 #pragma unroll
     for (int x = 0; x <= PER; ++x) {
         const int i = tid * PER + x;
@@ -208,20 +217,30 @@ __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, i
         if (blockIdx.x == 0 && tid == 0) atomicExch(dev_err, 1);
         return false;
     }
-    const int run = (total + 7) >> 3, at_run = (int)(blockIdx.x >> 3);
-    const int unit = (int)(blockIdx.x & 7) * run + at_run;
-    if (at_run >= run || unit >= total) return false;
-    if (unit >= first && unit < first + n) {
-        int at = unit - first;
+    st.n = n;
+    st.first = first;
+    st.total = total;
+    return true;
+}
+// `block`: the place in the launch (of a workgroup's further tiles: its own plus a multiple of 8)
+template <int THREADS>
+__device__ __forceinline__ bool tile_find(const tile_sums<THREADS>& st, int block, tile_pick_lds& l, int& e, int& u,
+                                          int& row_lo, int& row_hi) {
+    constexpr int PER = tile_sums<THREADS>::PER;
+    const int run = (st.total + 7) >> 3, at_run = block >> 3;
+    const int unit = (block & 7) * run + at_run;
+    if (at_run >= run || unit >= st.total) return false;
+    if (unit >= st.first && unit < st.first + st.n) {
+        int at = unit - st.first;
 #pragma unroll
         for (int x = 0; x < PER; ++x) {
-            if (at >= 0 && at < cnt[x]) {
-                l.found[0] = tid * PER + x;
+            if (at >= 0 && at < st.cnt[x]) {
+                l.found[0] = threadIdx.x * PER + x;
                 l.found[1] = at;
-                l.found[2] = o[x];
-                l.found[3] = o[x + 1];
+                l.found[2] = st.o[x];
+                l.found[3] = st.o[x + 1];
             }
-            at -= cnt[x];
+            at -= st.cnt[x];
         }
     }
     __syncthreads();
@@ -230,6 +249,12 @@ __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, i
     row_lo = __builtin_amdgcn_readfirstlane(l.found[2]);
     row_hi = __builtin_amdgcn_readfirstlane(l.found[3]);
     return true;
+}
+template <int THREADS>
+__device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
+                                          int mult, tile_pick_lds& l, int& e, int& u, int& row_lo, int& row_hi) {
+    tile_sums<THREADS> st;
+    return tile_scan(offsets, E, Rcap, dev_err, bm, mult, l, st) && tile_find(st, (int)blockIdx.x, l, e, u, row_lo, row_hi);
 }
 
 // all-fp32 grouped GEMMs (gemm_f32.hip), reached from the public entry points with dt = MOE_F32

@@ -1,7 +1,7 @@
 // Grouped GEMM for the expert MLP (Sec. 2.1.4, 4.3.2), device-initiated (Sec. 4.3.7): one
 // persistent launch per call, every expert's extent is read from `offsets` on the device;
-// forward, data-gradient and weight-gradient (Sec. 4.2.3 "W/D split") in bf16 and MXFP8 (Sec. 5.3.3),
-// forward and data-gradient also in blockwise fp8 (Sec. 5.3.2), are instantiations of one kernel.
+// forward, data-gradient and weight-gradient (Sec. 4.2.3 "W/D split") in bf16 and blockwise fp8 (Sec. 5.3.2) and the
+// weight-gradient in MXFP8 (Sec. 5.3.3) are instantiations of one kernel (MXFP8 forward and data gradient: gemm_tile8.hip).
 //
 // The kernel computes OUT[i,j] = sum_c P[i,c] * Q[j,c] on a 256x256 output tile per workgroup.  Two bodies share
 // the schedule, the tile set-up, the LDS layouts and the epilogue (template parameter NW):
@@ -114,8 +114,8 @@ __device__ __forceinline__ i32x8_t lds_read_tr8x32(const char* p, int second = 1
 
 // MODE: GG_FWD / GG_DGRAD / GG_WGRAD.  EPI: see enum.  OUT_F32: fp32 output (wgrad only).
 // F8: 0 = bf16 operands; 1 = E4M3 codes with fp32 block scales applied in software
-// (blockwise recipe, fwd and dgrad only); 2 = E4M3 codes with one E8M0 scale per 32 contraction elements, applied by the matrix
-// instruction itself (MXFP8, Sec. 5.3.3).
+// (blockwise recipe); 2 = E4M3 codes with one E8M0 scale per 32 contraction elements, applied by the matrix instruction
+// itself (MXFP8, Sec. 5.3.3; wgrad only).
 // NW: waves per workgroup.  8 = two groups of four waves (wave tile 128 x 64) that alternate between fragment reads
 // and MFMAs, operands by global -> LDS DMA; 4 = one wave per SIMD with 512 registers (wave tile 128 x 128 as 8 x 8
 // blocks of the 16x16x32 MFMA), operands staged through registers one stage ahead, fragment reads pipelined inside
@@ -148,6 +148,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
     // (blockwise weight gradient: both operands carry one scale per tile row / column and stage, and the rescaling
     // needs the previous stage's too: 256 + 256 current, then 256 + 256 previous)
     constexpr bool BW_WGRAD = F8 == 1 && MODE == GG_WGRAD;
+    static_assert(F8 != 2 || MODE == GG_WGRAD, "MXFP8 forward and data gradient: gemm_tile8.hip");
     constexpr int SC_BYTES = FP8 ? (BW_WGRAD ? 4096 : 2048) : 0;
     // One LDS array: [P0 | scales0 | Q0 | P1 | scales1 | Q1 | pad].  Buffer 1 (from P1 on) doubles as the
     // staging area of the epilogue: 64 tile rows x 260 floats.
@@ -160,10 +161,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
     char* const ldsQ0 = lds_buf + GG_STAGE_BYTES + SC_BYTES;
     char* const ldsP1 = lds_buf + BUF_BYTES;
     char* const ldsQ1 = ldsP1 + GG_STAGE_BYTES + SC_BYTES;
-    // MXFP8 quantising epilogues: column maxima of the four waves that share a 32-row block meet here
-    constexpr bool MXQ = F8 == 2 && NW == 8 && EPI != GG_EPI_STORE;
-    __shared__ __attribute__((aligned(16))) uint32_t qx[MXQ ? 8 * 64 * 4 : 4];
-    __shared__ __attribute__((aligned(16))) float qe[MXQ ? 2 * 512 : 4];  // per tile half: the block scale 2^e of every column
     __shared__ int offs[GG_MAX_E + 1];
     __shared__ int tile_start[GG_MAX_E + 1];
     __shared__ int dyn_next;
@@ -263,7 +260,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             // MXFP8 wgrad: a 32-row scale block (and the 128-row stage) must not straddle two experts
             // (the same for the 128-row scale blocks of the blockwise recipe)
             if (FP8 && MODE == GG_WGRAD) bad |= (rows & 127) != 0 || (offs[e] & 127) != 0;
-            if (MXQ && a.out_qc) bad |= (rows & 127) != 0 || (offs[e] & 127) != 0;  // 32-row blocks inside one expert
             if (MODE == GG_WGRAD) run += tiles_i_w * tiles_j;
             else run += rows > 0 ? ((rows + GG_BM - 1) / GG_BM) * tiles_j : 0;
             if (GATE) run *= a.split_cap;
@@ -648,36 +644,20 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             // one dword = the four E8M0 bytes (32-element blocks) of one tile row for this stage of 128 contraction
             // elements.  Waves 0..3 fetch the 256 P rows (position layout as below), waves 4..7 the 256 Q rows:
             // position p' = 64 (wave - 4) + lane holds Q tile row 128 (p' & 1) + (p' >> 1), so a lane finds the rows
-            // of its two column blocks in one 8-byte read.
-            // 1x32 copies (contraction along the memory row): [row, C/128] dwords, one step per stage;
-            // 32x1 copies (contraction along the rows): [c/128, columns] dwords, `columns` per stage.
+            // of its two column blocks in one 8-byte read.  32x1 copies: [c/128, columns] dwords, `columns` per stage.
             if (wave < 4) {
                 const int pp = wave * 64 + lane;
                 int64_t r = (int64_t)i0 + (pp >> 7) * 128 + (pp & 3) * 32 + ((pp & 127) >> 2);
-                if (MODE == GG_WGRAD) {  // P tile row = output row n
-                    r = r < N ? r : N - 1;
-                    sc_src = a.p_scale + (int64_t)(c_lo >> 7) * N + r;
-                    sc_step = N;
-                } else {
-                    r = r < a.Rcap ? r : a.Rcap - 1;
-                    sc_src = a.p_scale + r * CB;
-                    sc_step = 1;
-                }
+                r = r < N ? r : N - 1;   // P tile row = output row n
+                sc_src = a.p_scale + (int64_t)(c_lo >> 7) * N + r;
+                sc_step = N;
             } else {
                 const int pp = (wave - 4) * 64 + lane;
                 const int rho = 128 * (pp & 1) + (pp >> 1);
-                int col = (rho < 128 ? j0 : j1 - 128) + rho;  // output column = weight row (fwd) / weight column (dgrad)
-                col = col < J ? col : J - 1;
-                if (MODE == GG_FWD) {         // e8m0 [E*N, K/32]
-                    sc_src = a.q_scale + ((int64_t)e * N + col) * CB;
-                    sc_step = 1;
-                } else if (MODE == GG_DGRAD) {  // e8m0 [E*N/128, K, 4]
-                    sc_src = a.q_scale + (int64_t)e * (N >> 7) * K + col;
-                    sc_step = K;
-                } else {                      // e8m0 [Rcap/128, K, 4]
-                    sc_src = a.q_scale + (int64_t)(c_lo >> 7) * K + col;
-                    sc_step = K;
-                }
+                int col = (rho < 128 ? j0 : j1 - 128) + rho;  // output column k
+                col = col < K ? col : K - 1;
+                sc_src = a.q_scale + (int64_t)(c_lo >> 7) * K + col;
+                sc_step = K;
             }
         } else if (BW_WGRAD) {
             // 128x1 scales of both operands: [c / 128, columns] floats, one row of them per stage.  Waves 0..3 fetch the
@@ -925,8 +905,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
 
             auto fetch = [&](const char* sp, const char* sq, int half) {
                 if (FP8) {
-                    const int sl0 = MX ? 4 * half + fr_khalf : 4 * half + 2 * fr_khalf;  // 16-byte slot of the lane's first 16 K
-                    const int sl1 = MX ? sl0 + 2 : sl0 + 1;
+                    const int sl0 = 4 * half + 2 * fr_khalf, sl1 = sl0 + 1;  // 16-byte slots of the lane's 32 K (k-major: blockwise)
                     const int s0 = (sl0 ^ fr_swz) * 16, s1 = (sl1 ^ fr_swz) * 16;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -1675,7 +1654,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                     }
                 wait_lgkm0();
                 stage_barrier();
-                float cmx[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};  // MXFP8 column copy: column maxima of this wave's rows
                 auto out_row = [&](int x8, bool early, bool have, f32x4_t vin) {
                     const int rr = wave * RPW + x8;                           // staged row 0..63
                     const int r = ep_i0 + (rr >> 5) * 128 + i * 32 + (rr & 31);
@@ -1735,22 +1713,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                                     float* sc = a.out_q_scale + (int64_t)r * (2 * K / 128);
                                     sc[c >> 7] = sgs;
                                     sc[(K + c) >> 7] = sus;
-                                }
-                            }
-                            if (MXQ && a.out_q) {
-                                // MXFP8 copies of dZ: the values as stored (bf16) replace the row's consumed staging
-                                // words -- gate part at byte 8 * lane, up part 512 bytes further, i.e. the row in column
-                                // order -- and are quantised 16 columns per lane once the whole pass is there (below)
-                                const uint32_t g01 = pack_bf16(dg[0], dg[1]), g23 = pack_bf16(dg[2], dg[3]);
-                                const uint32_t u01 = pack_bf16(du[0], du[1]), u23 = pack_bf16(du[2], du[3]);
-                                uint32_t* srow = (uint32_t*)(stg + rr * STG_PITCH);
-                                *(u32x2_t*)(srow + 2 * lane) = u32x2_t{g01, g23};
-                                *(u32x2_t*)(srow + 128 + 2 * lane) = u32x2_t{u01, u23};
-                                if (a.out_qc) {
-                                    cmx[0] = fmaxf(cmx[0], fabsf(bf16_lo(g01))); cmx[1] = fmaxf(cmx[1], fabsf(bf16_hi(g01)));
-                                    cmx[2] = fmaxf(cmx[2], fabsf(bf16_lo(g23))); cmx[3] = fmaxf(cmx[3], fabsf(bf16_hi(g23)));
-                                    cmx[4] = fmaxf(cmx[4], fabsf(bf16_lo(u01))); cmx[5] = fmaxf(cmx[5], fabsf(bf16_hi(u01)));
-                                    cmx[6] = fmaxf(cmx[6], fabsf(bf16_lo(u23))); cmx[7] = fmaxf(cmx[7], fabsf(bf16_hi(u23)));
                                 }
                             }
                         }
@@ -1847,126 +1809,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                                     cvt4_e4m3(bf16_lo(a01), bf16_hi(a01), bf16_lo(a23), bf16_hi(a23), sa);
                                 if ((lane & 31) == 0) a.out_q_scale[(int64_t)r * (half_cols / 128) + ep_j0 / 128] = sa;
                             }
-                            if (MXQ && a.out_q) {
-                                // MXFP8 copies of A: the values as stored (bf16) go over the row's consumed gate words, in
-                                // feature order, and are quantised 16 features per lane once the pass is complete (below)
-                                const uint32_t a01 = pack_bf16(act[0], act[1]), a23 = pack_bf16(act[2], act[3]);
-                                *(u32x2_t*)((uint32_t*)(stg + rr * STG_PITCH) + 2 * (lane & 31)) = u32x2_t{a01, a23};
-                                if (a.out_qc) {
-                                    cmx[0] = fmaxf(cmx[0], fabsf(bf16_lo(a01))); cmx[1] = fmaxf(cmx[1], fabsf(bf16_hi(a01)));
-                                    cmx[2] = fmaxf(cmx[2], fabsf(bf16_lo(a23))); cmx[3] = fmaxf(cmx[3], fabsf(bf16_hi(a23)));
-                                }
-                            }
-                        }
-                    }
-                }
-                // MXFP8 quantising epilogue (Sec. 5.4.2), second half.  The pass's rows of this wave (eight) now lie in
-                // the staging area as bf16 in column order.  A lane takes 16 consecutive columns of one row (16 codes =
-                // one 16-byte store): the 1x32 copy needs the maximum of two neighbouring lanes; for the 32x1 copy the
-                // 32 rows of a block are this pass's rows of one tile half, eight per wave, so the four waves of the
-                // half first exchange their column maxima through LDS and each keeps the exponents of its columns as a
-                // byte table of its own.
-                if (MXQ && a.out_q) {
-                    const bool colq = a.out_qc != nullptr;                     // uniform over the grid
-                    const int hb = wave & 4;                                   // first wave of this wave's tile half
-                    const int r_blk = ep_i0 + (wave >> 2) * 128 + i * 32;      // first row of the 32-row block
-                    constexpr int HALVES = EPI == GG_EPI_SWIGLU ? 1 : 2;       // column parts per row (A: one; dZ: gate, up)
-                    const int width = HALVES == 1 ? half_cols : 2 * K;         // row length of the quantised tensor
-                    if (colq) {
-                        if (EPI == GG_EPI_SWIGLU) {
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) cmx[x] = fmaxf(cmx[x], __shfl_xor(cmx[x], 32));  // the two rows of a lane pair
-                            if (lane < 32) *(f32x4_t*)(qx + (wave * 64 + lane) * 4) = f32x4_t{cmx[0], cmx[1], cmx[2], cmx[3]};
-                        } else {
-                            // (maxima of bf16 values are bf16 values: packed without loss)
-                            *(u32x4_t*)(qx + (wave * 64 + lane) * 4) = u32x4_t{pack_bf16(cmx[0], cmx[1]), pack_bf16(cmx[2], cmx[3]),
-                                                                                pack_bf16(cmx[4], cmx[5]), pack_bf16(cmx[6], cmx[7])};
-                        }
-                        wait_lgkm0();
-                        stage_barrier();
-                        int ex[8];
-                        if (EPI == GG_EPI_SWIGLU) {
-                            f32x4_t m = *(const f32x4_t*)(qx + (hb * 64 + (lane & 31)) * 4);
-#pragma unroll
-                            for (int w2 = 1; w2 < 4; ++w2) {
-                                const f32x4_t o = *(const f32x4_t*)(qx + ((hb + w2) * 64 + (lane & 31)) * 4);
-#pragma unroll
-                                for (int x = 0; x < 4; ++x) m[x] = fmaxf(m[x], o[x]);
-                            }
-#pragma unroll
-                            for (int x = 0; x < 4; ++x) ex[x] = mx_exponent(m[x]);
-                        } else {
-                            u32x4_t pm = *(const u32x4_t*)(qx + (hb * 64 + lane) * 4);
-                            float m[8] = {bf16_lo(pm.x), bf16_hi(pm.x), bf16_lo(pm.y), bf16_hi(pm.y),
-                                          bf16_lo(pm.z), bf16_hi(pm.z), bf16_lo(pm.w), bf16_hi(pm.w)};
-#pragma unroll
-                            for (int w2 = 1; w2 < 4; ++w2) {
-                                const u32x4_t o = *(const u32x4_t*)(qx + ((hb + w2) * 64 + lane) * 4);
-                                const float of[8] = {bf16_lo(o.x), bf16_hi(o.x), bf16_lo(o.y), bf16_hi(o.y),
-                                                     bf16_lo(o.z), bf16_hi(o.z), bf16_lo(o.w), bf16_hi(o.w)};
-#pragma unroll
-                                for (int x = 0; x < 8; ++x) m[x] = fmaxf(m[x], of[x]);
-                            }
-#pragma unroll
-                            for (int x = 0; x < 8; ++x) ex[x] = mx_exponent(m[x]);
-                        }
-                        // the half's table of column scales 2^e (part p of the row at 256 p; its four waves write the same
-                        // values and each reads behind its own writes), and, from the first wave of each half, the E8M0
-                        // bytes: byte i of the dword of (128-row group, column)
-                        float* qh = qe + (wave >> 2) * 512;
-#pragma unroll
-                        for (int p2 = 0; p2 < HALVES; ++p2) {
-                            const int* e4 = ex + 4 * p2;
-                            const f32x4_t w = {mx_scale_f32(e4[0]), mx_scale_f32(e4[1]), mx_scale_f32(e4[2]), mx_scale_f32(e4[3])};
-                            if (HALVES == 2 || lane < 32) *(f32x4_t*)(qh + 256 * p2 + 4 * (HALVES == 2 ? lane : (lane & 31))) = w;
-                        }
-                        if ((wave & 3) == 0 && r_blk < ep_i_end) {
-                            if (EPI == GG_EPI_SWIGLU) {
-                                if (lane < 32) {
-                                    uint8_t* sc = a.out_qc_e8 + ((int64_t)(r_blk >> 7) * width + ep_j0 + lane * 4) * 4 + i;
-#pragma unroll
-                                    for (int x = 0; x < 4; ++x) sc[4 * x] = (uint8_t)(ex[x] + 127);
-                                }
-                            } else if (c < K) {
-                                uint8_t* sc = a.out_qc_e8 + ((int64_t)(r_blk >> 7) * width + c) * 4 + i;
-#pragma unroll
-                                for (int x = 0; x < 4; ++x) {
-                                    sc[4 * x] = (uint8_t)(ex[x] + 127);
-                                    sc[4 * (K + x)] = (uint8_t)(ex[4 + x] + 127);
-                                }
-                            }
-                        }
-                    }
-                    const int row = lane >> 3, rr = wave * RPW + row;             // RPW = 8 rows per wave and pass
-                    const int r = r_blk + (rr & 31);
-#pragma unroll
-                    for (int t2 = 0; t2 < 2 * HALVES; ++t2) {
-                        const int p2 = t2 >> 1;                                    // part of the row (dZ: gate / up)
-                        const int sc16 = ((lane & 7) + 8 * (t2 & 1)) * 16;         // first of the lane's 16 columns in the tile
-                        if (HALVES == 1 && t2 == 1) break;                         // (A: 128 columns per tile row, one task)
-                        const int colt = HALVES == 1 ? ep_j0 + sc16 : (sc16 < 128 ? ep_j0 + sc16 : ep_j1 + sc16 - 128);
-                        if (r >= ep_i_end || colt >= (HALVES == 1 ? half_cols : K)) continue;
-                        const u32x4_t* sp = (const u32x4_t*)((const uint32_t*)(stg + rr * STG_PITCH) + 128 * p2 + sc16 / 2);
-                        const u32x4_t v0 = sp[0], v1 = sp[1];
-                        uint32_t mb = 0;
-                        mb = bf16_absmax_bits(mb, v0.x); mb = bf16_absmax_bits(mb, v0.y); mb = bf16_absmax_bits(mb, v0.z);
-                        mb = bf16_absmax_bits(mb, v0.w); mb = bf16_absmax_bits(mb, v1.x); mb = bf16_absmax_bits(mb, v1.y);
-                        mb = bf16_absmax_bits(mb, v1.z); mb = bf16_absmax_bits(mb, v1.w);
-                        float m = bf16_absmax_finish(mb);
-                        m = fmaxf(m, __shfl_xor(m, 1));                            // a 1x32 block = two neighbouring lanes
-                        const int er = mx_exponent(m);
-                        const float sr = mx_scale_f32(er);
-                        const int64_t at = (int64_t)r * width + (int64_t)p2 * K + colt;
-                        *(u32x4_t*)(a.out_q + at) = u32x4_t{mx_cvt4_bf16(v0.x, v0.y, sr), mx_cvt4_bf16(v0.z, v0.w, sr),
-                                                            mx_cvt4_bf16(v1.x, v1.y, sr), mx_cvt4_bf16(v1.z, v1.w, sr)};
-                        if ((lane & 1) == 0) a.out_q_e8[at >> 5] = (uint8_t)(er + 127);
-                        if (colq) {
-                            const f32x4_t* sp4 = (const f32x4_t*)(qe + (wave >> 2) * 512 + 256 * p2 + sc16);
-                            const f32x4_t s0 = sp4[0], s1 = sp4[1], s2 = sp4[2], s3 = sp4[3];
-                            *(u32x4_t*)(a.out_qc + at) = u32x4_t{mx_cvt4_bf16_each(v0.x, v0.y, s0[0], s0[1], s0[2], s0[3]),
-                                                                 mx_cvt4_bf16_each(v0.z, v0.w, s1[0], s1[1], s1[2], s1[3]),
-                                                                 mx_cvt4_bf16_each(v1.x, v1.y, s2[0], s2[1], s2[2], s2[3]),
-                                                                 mx_cvt4_bf16_each(v1.z, v1.w, s3[0], s3[1], s3[2], s3[3])};
                         }
                     }
                 }
@@ -2265,16 +2107,14 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_FWD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_FWD, ge, a)) {
         if (!fp8) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
-        else gq_launch((hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
+        else gq_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<fwd>");
         return a.out_q ? gg_quantise(ctx, stream, C_act, Rcap, N / 2, offsets + E, mx, a) : MOE_OK;
     } else if (epi == MOE_EPI_SWIGLU) {
-        if (mx) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 2);
-        else if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 1);
+        if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 1);
         else GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 0);
     } else {
-        if (mx) GG_LAUNCH(GG_FWD, GG_EPI_STORE, false, 2);
-        else if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_STORE, false, 1);
+        if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_STORE, false, 1);
         else GG_LAUNCH(GG_FWD, GG_EPI_STORE, false, 0);
     }
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<fwd>");
@@ -2395,16 +2235,14 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_DGRAD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_DGRAD, ge, a)) {
         if (!fp8) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
-        else gq_launch((hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
+        else gq_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<dgrad>");
         return a.out_q ? gg_quantise(ctx, stream, dA, Rcap, 2 * K, offsets + E, mx, a) : MOE_OK;
     } else if (Z_saved) {
-        if (mx) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 2);
-        else if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
+        if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
         else GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 0);
     } else {
-        if (mx) GG_LAUNCH(GG_DGRAD, GG_EPI_STORE, false, 2);
-        else if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_STORE, false, 1);
+        if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_STORE, false, 1);
         else GG_LAUNCH(GG_DGRAD, GG_EPI_STORE, false, 0);
     }
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<dgrad>");
@@ -2459,7 +2297,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     a.p_scale = dc_scale;
     a.q_scale = a_scale;
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
-        if (mx || bw) gq_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
+        if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
         else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;

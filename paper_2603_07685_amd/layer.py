@@ -52,8 +52,8 @@ class LayerState:
         assert not self.gather or not (cfg.fp8 or cfg.mx or f32), "the gathered GEMMs are bf16 kernels"
         self.eq2 = bool(eq2)  # memory-efficient permutation (Sec. 4.1.2): weights applied before fc2
         self.fused_quant = None if fused_quant is None else bool(fused_quant)   # (resolved below, once fp8_wgrad is known)
-        # blockwise fp8 (default there): the SwiGLU / SwiGLU-backward epilogues also emit the 1x128 codes of their
-        # output, the next GEMM's operand (Sec. 5.4.2); off = stand-alone quantiser launches
+        # blockwise fp8 (default there): the SwiGLU / SwiGLU-backward GEMM calls also emit the 1x128 codes of their
+        # output, the next GEMM's operand (Sec. 5.4.2); off = stand-alone quantiser calls
         # (MXFP8: the 1x32 codes and the 32x1 copy for the weight gradients; row counts are on the 128-row grid there)
         self.epilogue_quant = bool(cfg.fp8 or cfg.mx) if epilogue_quant is None else bool(epilogue_quant)
         assert not self.epilogue_quant or cfg.fp8 or cfg.mx, "epilogue quantisation belongs to the one-byte recipes"
@@ -402,8 +402,8 @@ class LayerState:
         B.moe_unpermute_combine(c, self.dXp, B.BF16, self.row_of, None, self.dXs if sf else None, T, k, h, self.dX)
 
     def _fc1_fwd(self, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc, live):
-        """fc1 + SwiGLU and the quantised copies of the activation fc2 and its weight gradient read: from the GEMM's own
-        epilogue (Sec. 5.4.2) where that is built and switched on, else by quantiser launches."""
+        """fc1 + SwiGLU and the quantised copies of the activation fc2 and its weight gradient read: from the GEMM call
+        itself (Sec. 5.4.2) where that is switched on, else by quantiser calls."""
         c, eq = self.ctx, self.epilogue_quant
         if eq and self.mx:
             B.moe_grouped_gemm_fwd_quant_mx(c, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc)
