@@ -1,13 +1,13 @@
 // Grouped GEMM for the expert MLP (Sec. 2.1.4, 4.3.2), device-initiated (Sec. 4.3.7): one
 // persistent launch per call, every expert's extent is read from `offsets` on the device;
-// forward, data-gradient and weight-gradient (Sec. 4.2.3 "W/D split") in bf16 and blockwise fp8 (Sec. 5.3.2) and the
-// weight-gradient in MXFP8 (Sec. 5.3.3) are instantiations of one kernel (MXFP8 forward and data gradient: gemm_tile8.hip).
+// forward, data-gradient and weight-gradient (Sec. 4.2.3 "W/D split") in bf16 and blockwise fp8 (Sec. 5.3.2) are
+// instantiations of one kernel (MXFP8, Sec. 5.3.3: gemm_tile8.hip).
 //
 // The kernel computes OUT[i,j] = sum_c P[i,c] * Q[j,c] on a 256x256 output tile per workgroup.  Two bodies share
 // the schedule, the tile set-up, the LDS layouts and the epilogue (template parameter NW):
 //   bf16:        4 wavefronts as 2 x 2, one per SIMD with 512 registers; wave tile 128x128 = 8x8 blocks of the
 //                16x16x32 MFMA; operands staged through registers (described at the stage loop)
-//   fp8 / MXFP8: 8 wavefronts as 2 x 4; wave tile 128x64 = 4x2 blocks of the 32x32x64 MFMA; operands by DMA, the
+//   fp8:         8 wavefronts as 2 x 4; wave tile 128x64 = 4x2 blocks of the 32x32x64 MFMA; operands by DMA, the
 //                "ping-pong" schedule below
 //     forward : P = activations [rows,K]   Q = W_e [N,K]        OUT = C[rows,N]
 //     dgrad   : P = dC [rows,N]            Q = W_e as [K,N]^T   OUT = dA[rows,K]
@@ -114,8 +114,7 @@ __device__ __forceinline__ i32x8_t lds_read_tr8x32(const char* p, int second = 1
 
 // MODE: GG_FWD / GG_DGRAD / GG_WGRAD.  EPI: see enum.  OUT_F32: fp32 output (wgrad only).
 // F8: 0 = bf16 operands; 1 = E4M3 codes with fp32 block scales applied in software
-// (blockwise recipe); 2 = E4M3 codes with one E8M0 scale per 32 contraction elements, applied by the matrix instruction
-// itself (MXFP8, Sec. 5.3.3; wgrad only).
+// (blockwise recipe).
 // NW: waves per workgroup.  8 = two groups of four waves (wave tile 128 x 64) that alternate between fragment reads
 // and MFMAs, operands by global -> LDS DMA; 4 = one wave per SIMD with 512 registers (wave tile 128 x 128 as 8 x 8
 // blocks of the 16x16x32 MFMA), operands staged through registers one stage ahead, fragment reads pipelined inside
@@ -126,7 +125,6 @@ __device__ __forceinline__ i32x8_t lds_read_tr8x32(const char* p, int second = 1
 template <int MODE, int EPI, bool OUT_F32, int F8, int NW, int GATH = 0>
 __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, NW == 4 ? 1 : 2))) void gg_kernel(const gg_args a) {
     constexpr bool FP8 = F8 != 0;  // one-byte operands
-    constexpr bool MX = F8 == 2;   // hardware block scales
     static_assert(NW == 8 || (NW == 4 && !FP8), "four-wave workgroups are built for bf16 operands only");
     static_assert(GATH == 0 || (NW == 4 && (GATH == 1 || (GATH == 2 && MODE == GG_WGRAD))), "gathered operands: four-wave body; Q only in the weight gradient");
     constexpr int THREADS = NW * 64;
@@ -148,7 +146,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
     // (blockwise weight gradient: both operands carry one scale per tile row / column and stage, and the rescaling
     // needs the previous stage's too: 256 + 256 current, then 256 + 256 previous)
     constexpr bool BW_WGRAD = F8 == 1 && MODE == GG_WGRAD;
-    static_assert(F8 != 2 || MODE == GG_WGRAD, "MXFP8 forward and data gradient: gemm_tile8.hip");
     constexpr int SC_BYTES = FP8 ? (BW_WGRAD ? 4096 : 2048) : 0;
     // One LDS array: [P0 | scales0 | Q0 | P1 | scales1 | Q1 | pad].  Buffer 1 (from P1 on) doubles as the
     // staging area of the epilogue: 64 tile rows x 260 floats.
@@ -257,8 +254,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             if (MODE != GG_WGRAD) tile_start[e] = run;
             const int rows = offs[e + 1] - offs[e];
             bad |= rows < 0;
-            // MXFP8 wgrad: a 32-row scale block (and the 128-row stage) must not straddle two experts
-            // (the same for the 128-row scale blocks of the blockwise recipe)
+            // wgrad on codes: a 128-row scale block (= stage) must not straddle two experts
             if (FP8 && MODE == GG_WGRAD) bad |= (rows & 127) != 0 || (offs[e] & 127) != 0;
             if (MODE == GG_WGRAD) run += tiles_i_w * tiles_j;
             else run += rows > 0 ? ((rows + GG_BM - 1) / GG_BM) * tiles_j : 0;
@@ -344,12 +340,8 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
     //        slot = (cb / 8 ^ 4 (i >> 2)) + 2 (blk & 1) + ((i & 3) >> 1), byte (i & 1) * 8
     //   fp8  (row pitch 256 B, 128 rows): row = 64 half + 32 (blk >> 1) + 8 g + (i >> 1),
     //        slot = (cb / 16 ^ 2 (i >> 1)) + (blk & 1), byte (i & 1) * 8
-    // (MX: the scaled MFMA takes K 0..31 of a 64-step, the first scale block, from bytes 0..15 of both lane
-    // halves and K 32..63 from bytes 16..31, so a lane of half h holds K 16 h + 0..15 and 32 + 16 h + 0..15;
-    // without block scales the order inside the step does not matter and a lane holds 32 consecutive K)
-    const int tr_rowoff = MX    ? (16 * (tr_blk >> 1) + (tr_i >> 1)) * 256
-                          : FP8 ? (32 * (tr_blk >> 1) + (tr_i >> 1)) * 256
-                                : (8 * (tr_blk >> 1) + (tr_i >> 2)) * 512;
+    // (the order of the contraction inside a step does not matter: a lane holds 32 consecutive K)
+    const int tr_rowoff = FP8 ? (32 * (tr_blk >> 1) + (tr_i >> 1)) * 256 : (8 * (tr_blk >> 1) + (tr_i >> 2)) * 512;
     const int tr_low = FP8 ? (tr_blk & 1) : 2 * (tr_blk & 1) + ((tr_i & 3) >> 1);
     const int tr_xor = FP8 ? 2 * (tr_i >> 1) : 4 * (tr_i >> 2);
     const int tr_byte = (tr_i & 1) * 8;
@@ -640,26 +632,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
         // multiplied by s(kb-1) / s(kb), and by the last s in the epilogue.  The scales of block kb reach
         // LDS with the operands of stage kb (one more 4-byte-per-lane DMA by waves 0..4).
         const int CB = (c_hi - c_lo) / 128;  // contraction blocks = stages
-        if (MX) {
-            // one dword = the four E8M0 bytes (32-element blocks) of one tile row for this stage of 128 contraction
-            // elements.  Waves 0..3 fetch the 256 P rows (position layout as below), waves 4..7 the 256 Q rows:
-            // position p' = 64 (wave - 4) + lane holds Q tile row 128 (p' & 1) + (p' >> 1), so a lane finds the rows
-            // of its two column blocks in one 8-byte read.  32x1 copies: [c/128, columns] dwords, `columns` per stage.
-            if (wave < 4) {
-                const int pp = wave * 64 + lane;
-                int64_t r = (int64_t)i0 + (pp >> 7) * 128 + (pp & 3) * 32 + ((pp & 127) >> 2);
-                r = r < N ? r : N - 1;   // P tile row = output row n
-                sc_src = a.p_scale + (int64_t)(c_lo >> 7) * N + r;
-                sc_step = N;
-            } else {
-                const int pp = (wave - 4) * 64 + lane;
-                const int rho = 128 * (pp & 1) + (pp >> 1);
-                int col = (rho < 128 ? j0 : j1 - 128) + rho;  // output column k
-                col = col < K ? col : K - 1;
-                sc_src = a.q_scale + (int64_t)(c_lo >> 7) * K + col;
-                sc_step = K;
-            }
-        } else if (BW_WGRAD) {
+        if (BW_WGRAD) {
             // 128x1 scales of both operands: [c / 128, columns] floats, one row of them per stage.  Waves 0..3 fetch the
             // 256 scales of the tile's rows (= columns n of dC; position layout as in the forward kernel: a lane finds
             // its four rows in one 16-byte read), waves 4..7 the 256 of the tile's columns (= columns k of A), in
@@ -726,7 +699,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                 dma4(sc_src + (kb > 0 ? kb - 1 : 0) * sc_step, wave * 256, lds_addr(ss) + 2048);
                 return;
             }
-            if (MX || wave <= 4) {
+            if (wave <= 4) {
                 const float* src = sc_src + kb * sc_step;
                 dma4(src, wave * 256, lds_addr(ss));
             }
@@ -910,7 +883,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         if (P_CMAJ) {
-                            pf8[i] = lds_read_tr8x32(sp + p_rd[i] + half * 64 * 256, MX ? 32 : 16);
+                            pf8[i] = lds_read_tr8x32(sp + p_rd[i] + half * 64 * 256, 16);
                         } else {
                             const i32x4_t lo = *(const i32x4_t*)(sp + p_rd[i] + s0), hi = *(const i32x4_t*)(sp + p_rd[i] + s1);
                             pf8[i] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -919,7 +892,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
 #pragma unroll
                     for (int j = 0; j < 2; ++j) {
                         if (Q_CMAJ) {
-                            qf8[j] = lds_read_tr8x32(sq + q_rd[j] + half * 64 * 256, MX ? 32 : 16);
+                            qf8[j] = lds_read_tr8x32(sq + q_rd[j] + half * 64 * 256, 16);
                         } else {
                             const i32x4_t lo = *(const i32x4_t*)(sq + q_rd[j] + s0), hi = *(const i32x4_t*)(sq + q_rd[j] + s1);
                             qf8[j] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
@@ -944,7 +917,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                 }
             };
             // the MFMAs of one half-stage, with the 2 CH DMA instructions of stage kt_dma slipped in
-            int psr[4] = {127, 127, 127, 127}, qsr[2] = {127, 127};  // MX: scale bytes of the current stage
             // blockwise forward / data gradient: s(kb-1) / s(kb) of every block of accumulators for the stage being entered,
             // set in the read phase.  Where the 128 multiplies are done was measured both ways (per-slot timestamps): in
             // the read phase that phase lasts 1030 cycles against the 550 of the MFMA phase it alternates with; in front
@@ -963,11 +935,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
 #pragma unroll
                                 for (int x = 0; x < 16; ++x) acc[i][j][x] *= ratio8[i][j];
                             }
-                            // MX: the lane's 32 contraction elements are one scale block; its E8M0 byte sits in byte 0
-                            // (first half-stage) / byte 2 (second) of the pre-shifted scale registers
-                            if (!MX) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(qf8[j], pf8[i], acc[i][j], 0, 0, 0, 127, 0, 127);
-                            else if (half == 0) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(qf8[j], pf8[i], acc[i][j], 0, 0, 0, qsr[j], 0, psr[i]);
-                            else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(qf8[j], pf8[i], acc[i][j], 0, 0, 2, qsr[j], 2, psr[i]);
+                            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(qf8[j], pf8[i], acc[i][j], 0, 0, 0, 127, 0, 127);
                             pin(acc[i][j]);
                             __builtin_amdgcn_sched_barrier(0);
                             if (do_dma) issue_one(kt_dma, dp, dq, i * 2 + j);
@@ -995,16 +963,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             f32x4_t pn;
             float qn[2];
             auto read_scales = [&](const float* ss) {
-                if (MX) {
-                    const i32x4_t pw = *(const i32x4_t*)(ss + wm * 128 + fr_row * 4);
-                    const i32x2_t qw = *(const i32x2_t*)(ss + 256 + (wn * 32 + fr_row) * 2);
-                    const int sh = 8 * fr_khalf;  // this lane's 32 elements are block khalf (first half) / 2 + khalf (second)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) psr[i] = (int)((uint32_t)pw[i] >> sh);
-                    qsr[0] = (int)((uint32_t)qw.x >> sh);
-                    qsr[1] = (int)((uint32_t)qw.y >> sh);
-                    return;
-                }
                 pn = *(const f32x4_t*)(ss + wm * 128 + fr_row * 4);
                 qn[0] = ss[256];
                 qn[1] = ss[257];
@@ -1101,7 +1059,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
                 fetch(SP[s], SQ[s], half);
                 __builtin_amdgcn_sched_barrier(0);
                 if (BW_WGRAD && half == 0) rescale_w(SS[s]);
-                else if (FP8 && !MX && half == 0) rescale();  // after the fragment reads in program order: overlaps them
+                else if (FP8 && half == 0) rescale();  // after the fragment reads in program order: overlaps them
                 wait_lgkm0();
             };
             if (NW == 4) {
@@ -1648,7 +1606,7 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
 #pragma unroll
                         for (int x = 0; x < 4; ++x) {
                             v[x] = acc[i][h2][4 * g + x];
-                            if (FP8 && !MX && !BW_WGRAD) v[x] *= ps_cur[i] * qs_cur[h2];
+                            if (FP8 && !BW_WGRAD) v[x] *= ps_cur[i] * qs_cur[h2];
                         }
                         *(f32x4_t*)(stg + (wm * 32 + fr_row) * STG_PITCH + blk_col(h2) + 8 * g + 4 * fr_khalf) = v;
                     }
@@ -2296,28 +2254,25 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     }
     a.p_scale = dc_scale;
     a.q_scale = a_scale;
+    a.tile_counter = ctx->aux + MOE_AUX_TILE_COUNTER;
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
         if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
         else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;
     }
-    a.tile_counter = ctx->aux + MOE_AUX_TILE_COUNTER;
     // split contraction (bf16 operands): as many slices of partial tiles as the workspace holds behind its reserved head
     const size_t slice_bytes = (size_t)ceil_div64(N, GG_BM) * ceil_div64(K, GG_BN) * GG_BM * GG_BN * sizeof(float);
     const size_t ws_free = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;
     a.split_info = (int*)((char*)ctx->ws + MOE_WS_SPLIT_INFO);
     a.partials = (float*)((char*)ctx->ws + MOE_WS_RESERVED);
-    a.split_cap = (!mx && !bw && GG_BF16_NW == 4) ? (int)(ws_free / slice_bytes < GG_MAX_SPLIT ? ws_free / slice_bytes : GG_MAX_SPLIT) : 0;
+    a.split_cap = (!bw && GG_BF16_NW == 4) ? (int)(ws_free / slice_bytes < GG_MAX_SPLIT ? ws_free / slice_bytes : GG_MAX_SPLIT) : 0;
     if (gath == 2) {
         if (out_dt == MOE_F32) GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, true, 2);
         else GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, false, 2);
     } else if (gath == 1) {
         if (out_dt == MOE_F32) GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, true, 1);
         else GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, false, 1);
-    } else if (mx) {
-        if (out_dt == MOE_F32) GG_LAUNCH(GG_WGRAD, GG_EPI_STORE, true, 2);
-        else GG_LAUNCH(GG_WGRAD, GG_EPI_STORE, false, 2);
     } else if (bw) {
         if (out_dt == MOE_F32) GG_LAUNCH(GG_WGRAD, GG_EPI_STORE, true, 1);
         else GG_LAUNCH(GG_WGRAD, GG_EPI_STORE, false, 1);

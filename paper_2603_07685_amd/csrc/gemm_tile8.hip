@@ -24,9 +24,10 @@
 // Against eight waves in two groups that take turns reading and multiplying (us, old : this), T 16384, h 7168, f 2048, 32
 // experts, top-8: fc1 + SwiGLU 4233 with quantised copies : 3699 + 240 for the quantiser, fc2 1991 : 1864, fc2 data gradient
 // + SwiGLU backward 2625 : 2106 + 480, fc1 data gradient 3614 : 3437; the shared expert 526 : 421 + 30, 247 : 224, 331 : 273 + 50,
-// 443 : 403, its weight gradients 229 : 206, 429 : 387.  Bound now: 1.75 us per stage and tile, the matrix pipe busy about 60 % at the
-// clock the card holds under this load, operands at 37 bytes/ns and compute unit.  (The routed experts' weight gradients stay with
-// gemm.hip's kernel, which deals tiles in descending cost: 3275 : 3740 without.)
+// 443 : 403; weight gradients 1840 : 1639, 3450 : 3127, the shared expert's 229 : 206, 429 : 400.  T 8192, h 2048, f 1024, 16
+// experts, rank^-1.2: 193 : 164, 220 : 191.  Without the order of cost and the draw the routed weight gradients took 1869 and
+// 3740.  Bound now: 1.75 us per stage and tile, the matrix pipe busy about 60 % at the clock the card holds under this load,
+// operands at 37 bytes/ns and compute unit.
 #include "gemm_tile.h"
 
 #include <type_traits>
@@ -57,10 +58,12 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     constexpr int PC = BM / 32, QC = BN / 32, XC = PC + QC + SC;    // DMA instructions per wave and stage: P, Q, scales
     constexpr int NI = BM / 64, NJ = BN / 64;                       // 32-row and 32-column blocks per wave
     constexpr bool MANY = BM == 256;                                // one workgroup per compute unit, tile after tile
+    constexpr bool LPT = MANY && MODE == GG_WGRAD;
     constexpr int HB = BN / 2;                                      // SwiGLU: features per tile
     __shared__ __attribute__((aligned(1024))) char ring[2 * STAGE];
     __shared__ __attribute__((aligned(16))) float scales[4][PS + BN];
     __shared__ tile_pick_lds pick;
+    __shared__ int offs[LPT ? GG_MAX_E + 1 : 1], order[LPT ? GG_MAX_E : 1], drawn;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
@@ -80,6 +83,31 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     tile_sums<256> sums;
     if (!tile_scan(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM, MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j,
                    pick, sums)) return;
+    // Weight gradients, tile after tile: a tile costs its expert's rows, so the experts are taken in descending order of rows
+    // (rank sort, ties by index) and the list is dealt to the XCDs in chunks, in a snake; with an expert above twice the mean no
+    // deal balances, and the workgroups draw from a device counter in the same order (gemm.hip: tile_of, draw).
+    const int G = (int)gridDim.x, tpe = tiles_iw * tiles_j;
+    bool dyn = false;
+    int ticket = 0;
+    if constexpr (LPT) {
+        for (int x = tid; x <= a.E; x += 256) offs[x] = a.offsets[x];
+        __syncthreads();
+        for (int x = tid; x < a.E; x += 256) {
+            const int rows = offs[x + 1] - offs[x];
+            int rank = 0;
+            for (int o = 0; o < a.E; ++o) {
+                const int ro = offs[o + 1] - offs[o];
+                rank += ro > rows || (ro == rows && o < x);
+            }
+            order[rank] = x;
+        }
+        __syncthreads();
+        const int most = __builtin_amdgcn_readfirstlane(offs[order[0] + 1] - offs[order[0]]);
+        dyn = (int64_t)most * a.E > 2 * (int64_t)__builtin_amdgcn_readfirstlane(offs[a.E] - offs[0]);
+    }
+    auto draw = [&]() __attribute__((always_inline)) {
+        if (LPT && dyn && tid == 0) ticket = atomicAdd(a.tile_counter, 1);
+    };
     // the tile in work
     int e, u, row_lo, row_hi, ti, tj, i0, i_end, j0, c_lo, KT;
     const int CB = (MODE == GG_FWD ? K : N) / 128;          // contraction blocks (forward, data gradient)
@@ -95,8 +123,22 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     const char *p_base0, *q_base0;
     const float* sc_src[SC];
     int64_t sc_step;
-    auto set_tile = [&](int block) __attribute__((always_inline)) -> bool {
-    if (!tile_find(sums, block, pick, e, u, row_lo, row_hi)) return false;
+    auto set_tile = [&](int n) __attribute__((always_inline)) -> bool {   // this workgroup's n-th
+    if constexpr (LPT) {
+        const int x = (int)blockIdx.x & 7;
+        int t = (8 * n + ((n & 1) ? 7 - x : x)) * (G >> 3) + ((int)blockIdx.x >> 3);
+        if (dyn) {
+            if (tid == 0) drawn = ticket;
+            wait_lgkm0();
+            stage_barrier();
+            t = __builtin_amdgcn_readfirstlane(drawn);
+        }
+        if (t >= sums.total) return false;
+        u = __builtin_amdgcn_readfirstlane(t % tpe);
+        e = __builtin_amdgcn_readfirstlane(order[t / tpe]);
+        row_lo = __builtin_amdgcn_readfirstlane(offs[e]);
+        row_hi = __builtin_amdgcn_readfirstlane(offs[e + 1]);
+    } else if (!tile_find(sums, (int)blockIdx.x + n * G, pick, e, u, row_lo, row_hi)) return false;
     gt_place(u, MODE == GG_WGRAD ? tiles_iw : (row_hi - row_lo + BM - 1) / BM, tiles_j, ti, tj);
     i0 = MODE == GG_WGRAD ? ti * BM : row_lo + ti * BM;
     i_end = MODE == GG_WGRAD ? N : row_hi;
@@ -286,10 +328,11 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
 #pragma unroll
         for (int x = 0; x < XC; ++x) issue_one(s, lds0 + s * STAGE, x);
     };
-    int block = (int)blockIdx.x;
-    if (!set_tile(block)) return;
-    if (KT > 0) issue_stage(0);     // (an expert without rows: not even its scales' address is inside the tensor)
-    for (;;) {
+    draw();
+    bool more = set_tile(0);
+    if (more && KT > 0) issue_stage(0);     // (an expert without rows: not even its scales' address is inside the tensor)
+    for (int n = 1; more; ++n) {
+    draw();                                 // (collected behind the contraction)
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
         ps_cur[i] = 1.f;
@@ -368,7 +411,7 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     // a workgroup with further tiles: the next one's first stage is on its way while this one's output goes through the other
     // stage buffer
     const int e_ = e, i0_ = i0, i_end_ = i_end, j0_ = j0, tj_ = tj;
-    const bool more = MANY && set_tile(block += gridDim.x);
+    more = MANY && set_tile(n);
     if (more && KT > 0) issue_stage(0);
     gt_output<MODE, EPI, OUT_F32, BM, BN>(a, (float*)(ring + (MANY ? STAGE : 0)), e_, i0_, i_end_, j0_, tj_, tiles_j, [&](int pass, float* stg) __attribute__((always_inline)) {
         // a lane's accumulators of a block: one row (lane % 32), four groups of columns 8 g + 4 (lane / 32) .. + 3
@@ -385,9 +428,15 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
                 *(f32x4_t*)(stg + stg_at<BN>(wm * 32 + fr_row, col_of(j) + 8 * g + 4 * fr_khalf)) = v;
             }
     });
-    if (!more) return;
-    wait_lgkm0();
-    stage_barrier();            // (the next stage 1 goes where the output was staged)
+    if (more) {                 // (the next stage 1 goes where the output was staged)
+        wait_lgkm0();
+        stage_barrier();
+    }
+    }
+    // the counter goes back to zero with the last workgroup that is done with it
+    if (LPT && dyn && tid == 0 && atomicAdd(a.tile_counter + 1, 1) + 1 == G) {
+        atomicExch(a.tile_counter, 0);
+        atomicExch(a.tile_counter + 1, 0);
     }
 }
 
@@ -413,13 +462,13 @@ static void gq_call(hipStream_t s, int mode, int epi, bool out_f32, const gg_arg
     else if (epi == GG_EPI_SWIGLU_BWD) gq_go<GG_DGRAD, GG_EPI_SWIGLU_BWD, false, F8, BM, BN>(s, a, cu);
     else gq_go<GG_DGRAD, GG_EPI_STORE, false, F8, BM, BN>(s, a, cu);
 }
-// Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 256 x 256 (MXFP8; weight gradients of one expert only: the
-// tiles of several differ in cost), 0 = the 256 x 256 kernel of gemm.hip.  Decided from the call's sizes by
+// Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 256 x 256 (MXFP8), 0 = the 256 x 256
+// kernel of gemm.hip (blockwise).  Decided from the call's sizes by
 // two estimates of its time in microseconds, fitted to measured calls (MI355X; the rows of an expert are unknown on the host:
 // R is taken to hold half a 128-row tile of slack per expert, and an expert's rows to be multiples of 128):
-//   256 x 256: one workgroup per compute unit, whole rounds of tiles, a tile = per stage 1.75 (MXFP8 here), 2.1 (MXFP8 weight
-//              gradient in gemm.hip), 2.35 (blockwise) or 3.4 (blockwise weight gradient: two multiplies per accumulator and
-//              stage) + its output phase: 8 (weight gradient, blockwise: 11.5), SwiGLU 13 (blockwise 19 with quantised copies, 14
+//   256 x 256: one workgroup per compute unit, whole rounds of tiles, a tile = per stage 1.75 (MXFP8 here), 2.35
+//              (blockwise) or 3.4 (blockwise weight gradient: two multiplies per accumulator and stage) + its output phase: 8
+//              (weight gradient 10, blockwise 11.5), SwiGLU 13 (blockwise 19 with quantised copies, 14
 //              without), SwiGLU backward 38 (blockwise 57 when most units are in it at once, 35 without quantised copies)
 //   128 x 128: two workgroups per compute unit, a round = 1.5 per stage (SwiGLU 1.7; weight gradient 1.25, blockwise 2.1) + 6.5
 //              (SwiGLU backward 16); plus the quantiser's launch and its way over memory where the other kernel needs none
@@ -445,15 +494,14 @@ int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg
     const double n256 = __builtin_ceil(cols / 256) * (wg ? E * __builtin_ceil(a.N / 256.0) : row_tiles(256, 0.125));
     const double n128 = __builtin_ceil(cols / 128) * (wg ? E * __builtin_ceil(a.N / 128.0) : row_tiles(128, -0.25));
     const double r256 = __builtin_ceil(n256 / cu), r128 = n128 / (2 * cu);
-    const bool big = mx && (!wg || E == 1);
-    const double out256 = big ? (sw ? 13 : swb ? 38 : 8)
-                              : sw ? (quant ? 19 : 14) : swb ? (!quant ? 35 : 2 * n256 > cu ? 57 : 38) : wg && !mx ? 11.5 : 8;
-    const double t256 = r256 * ((big ? 1.75 : mx ? 2.1 : wg ? 3.4 : 2.35) * stages + out256);
+    const double out256 = mx ? (sw ? 13 : swb ? 38 : wg ? 10 : 8)
+                             : sw ? (quant ? 19 : 14) : swb ? (!quant ? 35 : 2 * n256 > cu ? 57 : 38) : wg ? 11.5 : 8;
+    const double t256 = r256 * ((mx ? 1.75 : wg ? 3.4 : 2.35) * stages + out256);
     const double per_stage = wg ? (mx ? 1.25 : 2.1) : sw ? 1.7 : 1.5;
     double t128 = (3 * r128 + __builtin_ceil(r128)) / 4;
     t128 = (t128 < 0.5 ? 0.5 : t128) * (per_stage * stages + (swb ? 16 : 6.5));
-    if (quant && !big) t128 += 4 + R * (sw ? a.N / 2 : 2 * a.K) * 3 / 5e6;   // (bytes at 5 TB/s)
-    if (t128 > t256) return big ? 3 : 0;
+    if (quant && !mx) t128 += 4 + R * (sw ? a.N / 2 : 2 * a.K) * 3 / 5e6;   // (bytes at 5 TB/s)
+    if (t128 > t256) return mx ? 3 : 0;
     return wg || r128 >= 1.5 ? 2 : 1;
 }
 void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a) {

@@ -37,7 +37,8 @@ BIG = [3000, 1, 0, 2300, 515]
 CASES = [(FEW, 256, 128), (EDGE, 512, 384), (WIDE, 2304, 1152), (BIG, 3328, 2176), ([4000, 3], 3840, 3840),
          ([6000, 130, 0, 900], 3840, 1152), ([6000, 130, 0, 900], 1280, 3840)]   # (more than one tile per workgroup)
 WCASES = [([128, 0, 256], 256, 128), ([0, 384, 128, 0, 1280], 640, 384), ([512] * 9 + [0], 1408, 2176), ([128], 128, 128),
-          ([3840, 256], 3840, 3840), ([4096], 4096, 7168)]
+          ([3840, 256], 3840, 3840), ([4096], 4096, 7168),
+          ([512, 1024, 0, 768, 640, 896, 512], 2048, 2304), ([5120, 128, 256, 0, 128, 384], 2048, 2048)]   # (dealt; drawn)
 
 
 def _nan(*s, dt=BF):
