@@ -35,7 +35,7 @@ def measured_traffic(workload: str, label: str):
         return None
     with open(path) as fh:
         for line in fh:
-            m = re.match(r"\s+(\S+)\s+gg_kernel<[^>]*>\s+read\s+([0-9.]+)\s+write\s+([0-9.]+)", line)
+            m = re.match(r"\s+(\S+)\s+g[gqt]_kernel<[^>]*>\s+read\s+([0-9.]+)\s+write\s+([0-9.]+)", line)
             if m and m.group(1) == label:
                 return float(m.group(2)), float(m.group(3))
     return None
@@ -390,7 +390,7 @@ def main():
         "pct_bf16_mfma_peak": round(100.0 * flops / ms / 1e9 / BF16_PEAK_TFLOPS, 2),
         "gemm_only": {"tflops": round(gemm_fl / gemm_ms / 1e9, 1),
                       "pct_peak": round(100.0 * gemm_fl / gemm_ms / 1e9 / BF16_PEAK_TFLOPS, 2)},
-        "roofline": {"bound": "mfma", "kernel": f"gg_kernel ({n_dom})", "achieved": round(achieved, 1),
+        "roofline": {"bound": "mfma", "kernel": f"{'gq' if cfg.mx else 'gg'}_kernel ({n_dom})", "achieved": round(achieved, 1),
                      "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                      "traffic": traffic, "traffic_unit": "GB per launch (HBM-side read + write, offline counters: profiles/gg_kernel_<workload>_hbm_traffic.txt)",
                      "traffic_read_write_gb": list(rw) if rw else None,

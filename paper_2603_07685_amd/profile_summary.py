@@ -20,7 +20,8 @@ import sys
 from collections import OrderedDict
 
 GIB = 1 << 30
-LEGEND = ("gg_kernel<MODE,EPI,F32,F8,NW>: MODE 0 fwd / 1 dgrad / 2 wgrad; EPI 0 store / 1 SwiGLU / 2 SwiGLU-bwd; "
+GEMMS = ("gg_kernel", "gq_kernel", "gt_kernel")
+LEGEND = ("gg_kernel<MODE,EPI,F32,F8,NW>, gq_kernel<MODE,EPI,F32,F8,BM,BN>: MODE 0 fwd / 1 dgrad / 2 wgrad; EPI 0 store / 1 SwiGLU / 2 SwiGLU-bwd; "
           "F8 0 bf16 / 1 blockwise fp8 / 2 MXFP8; NW waves per workgroup")
 
 
@@ -50,7 +51,7 @@ def _gemm_labels(bench: dict):
 
 
 def _is_site(name: str) -> bool:
-    return any(t in name for t in ("gg_kernel", "combine", "permute_rows", "quant"))
+    return any(t in name for t in (*GEMMS, "combine", "permute_rows", "quant"))
 
 
 def _last_step(rows, name_of):
@@ -101,7 +102,7 @@ def trace(d: str, bench_path: str | None = None):
         name = steps[-1][i][0]
         avg = sum(s[i][1] for s in steps) / len(steps)
         lab = ""
-        if name.startswith("gg_kernel") and gi < len(labels):
+        if name.startswith(GEMMS) and gi < len(labels):
             lab = labels[gi]
             gi += 1
         print(f"  {i:2d} {name:44s} {lab:36s} {avg:10.1f} us")
@@ -147,7 +148,7 @@ def traffic(fd: str, wd: str, bench_path: str):
     gi = 0
     for name, rd, wr in rows:
         lab = "-"
-        if name.startswith("gg_kernel") and gi < len(labels):
+        if name.startswith(GEMMS) and gi < len(labels):
             lab = labels[gi]
             gi += 1
         print(f"  {lab:36s} {name:44s} read {rd:8.3f}  write {wr:8.3f}")
@@ -164,7 +165,7 @@ def mfma(d: str, bench_path: str):
     print(f"  {'call site':36s} {'kernel':30s} {'dur_us':>8s} {'clock_GHz':>9s} {'MFMA busy / CU busy':>20s} {'vs 2.4 GHz peak':>16s}")
     gi = 0
     for v in rows:
-        if "gg_kernel" not in v["name"]:
+        if not any(t in v["name"] for t in GEMMS):
             continue
         dur = (v["e"] - v["s"]) / 1e3
         clk = v["GRBM_GUI_ACTIVE"] / 8 / (dur * 1e3)
