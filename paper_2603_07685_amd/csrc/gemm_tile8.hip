@@ -26,8 +26,8 @@
 // + SwiGLU backward 2625 : 2106 + 480, fc1 data gradient 3614 : 3437; the shared expert 526 : 421 + 30, 247 : 224, 331 : 273 + 50,
 // 443 : 403; weight gradients 1840 : 1639, 3450 : 3127, the shared expert's 229 : 206, 429 : 400.  T 8192, h 2048, f 1024, 16
 // experts, rank^-1.2: 193 : 164, 220 : 191.  Without the order of cost and the draw the routed weight gradients took 1869 and
-// 3740.  Bound now: 1.75 us per stage and tile, the matrix pipe busy about 60 % at the clock the card holds under this load,
-// operands at 37 bytes/ns and compute unit.
+// 3740.  Bound now: 1.75 us per stage and tile, the matrix pipe busy 53-70 % of the time at the 1.7-1.9 GHz the card holds
+// under this load, operands at 37 bytes/ns and compute unit.
 #include "gemm_tile.h"
 
 #include <type_traits>
