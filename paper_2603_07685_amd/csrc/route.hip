@@ -3,8 +3,8 @@
 //
 // A group of LPT lanes owns one token: 16 lanes (four tokens per wavefront) up to 256 experts, a whole wavefront above.
 // Lane l of the group holds the logits of experts l, l + LPT, l + 2 LPT, ... in registers; what the group has to agree on
-// (maximum, sum, the winner of an arg-max round) is a reduction of four DPP steps over 16 lanes (two more, through the
-// LDS crossbar, over 64).  A wavefront handles one token per group and ends.
+// (maximum, sum, the winner of an arg-max round) is a reduction of four DPP steps over 16 lanes (two more before them,
+// through the LDS crossbar, over 64).  A wavefront handles one token per group and ends.
 // Bound: vector instructions at large T (one read of the logits: 3.6 us for T 16384, E 256 at the copy rate), one
 // token's chain of reductions at small T.  Values are compared as order-preserving integers, so that an arg-max round is
 // max3 over the lane's values, four DPP maxima, and a DPP minimum over the indices that hold the maximum.
@@ -27,17 +27,18 @@ __device__ __forceinline__ double dpp(double x) {
     const uint64_t b = (uint64_t)__double_as_longlong(x);
     return __longlong_as_double((long long)(((uint64_t)dpp<CTRL>((uint32_t)(b >> 32)) << 32) | dpp<CTRL>((uint32_t)b)));
 }
-// exchange with the neighbour, the neighbouring pair, the mirrored quad of 8, the mirrored half of 16, then 16 and 32 away
+// Exchange with the lane 32 and 16 away (a whole wavefront), then 8, 4, 2 and 1 away: row_ror by 8 and by 4 (by then a row
+// repeats every 8 lanes, so that 4 to either side are the same value), quad permutations for the rest.
 template <int LPT, typename T, typename F>
 __device__ __forceinline__ T lanes_reduce(T v, F op) {
-    v = op(v, dpp<0xB1>(v));
-    v = op(v, dpp<0x4E>(v));
-    v = op(v, dpp<0x141>(v));
-    v = op(v, dpp<0x140>(v));
     if (LPT == 64) {
-        v = op(v, __shfl_xor(v, 16));
         v = op(v, __shfl_xor(v, 32));
+        v = op(v, __shfl_xor(v, 16));
     }
+    v = op(v, dpp<0x128>(v));
+    v = op(v, dpp<0x124>(v));
+    v = op(v, dpp<0x4E>(v));
+    v = op(v, dpp<0xB1>(v));
     return v;
 }
 template <int LPT> __device__ __forceinline__ float lanes_max(float v) { return lanes_reduce<LPT>(v, [](float a, float b) { return fmaxf(a, b); }); }
@@ -45,6 +46,22 @@ template <int LPT> __device__ __forceinline__ float lanes_sum(float v) { return 
 template <int LPT> __device__ __forceinline__ double lanes_sum(double v) { return lanes_reduce<LPT>(v, [](double a, double b) { return a + b; }); }
 template <int LPT> __device__ __forceinline__ uint32_t lanes_max(uint32_t v) { return lanes_reduce<LPT>(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; }); }
 template <int LPT> __device__ __forceinline__ uint32_t lanes_min(uint32_t v) { return lanes_reduce<LPT>(v, [](uint32_t a, uint32_t b) { return a < b ? a : b; }); }
+
+// Sum over a token's experts, add(j, sum) = sum + the term of expert l + LPT j.  The order of the additions is the same for
+// both layouts, that of 64 lanes: per residue of the expert modulo 64 in ascending order, then residues 32, 16, 8, 4, 2, 1
+// apart (a lane of 16 holds four residues).  A weight's last bit moves bf16 roundings all the way through a layer: it must
+// not depend on the lane layout.
+template <int LPT, int VPL, typename T, typename F>
+__device__ __forceinline__ T experts_sum(F add) {
+    T part[4] = {(T)0, (T)0, (T)0, (T)0};
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) part[LPT == 64 ? 0 : j & 3] = add(j, part[LPT == 64 ? 0 : j & 3]);
+    return lanes_sum<LPT>(LPT == 64 ? part[0] : (part[0] + part[2]) + (part[1] + part[3]));
+}
+// Sum over a token's slots, one per lane (0 in the lanes without one).  The + 0 rounds a product before it is added, as the
+// empty upper lanes of a 64-lane sum do.
+template <int LPT>
+__device__ __forceinline__ float slots_sum(float v) { return lanes_sum<LPT>(LPT == 64 ? v : v + 0.0f); }
 
 // fp32 values as unsigned integers in the same order (-0 counts as 0); every number, -inf included, is above 0, which
 // stands for "no candidate"
@@ -121,10 +138,7 @@ __global__ __launch_bounds__(1024) void route_topk_kernel(
 #pragma unroll
         for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
         mx = lanes_max<LPT>(m);
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) s += l + LPT * j < E ? expf(v[j] - mx) : 0.f;
-        den = lanes_sum<LPT>(s);
+        den = experts_sum<LPT, VPL, float>([&](int j, float s) { return s + (l + LPT * j < E ? expf(v[j] - mx) : 0.f); });
     }
     float my_logit = 0.f;
     uint32_t my_idx = 0;
@@ -138,7 +152,7 @@ __global__ __launch_bounds__(1024) void route_topk_kernel(
     }
     float p = 0.f;
     if (l < k) p = fn == MOE_SCORE_SOFTMAX ? expf(my_logit - mx) / den : 1.f / (1.f + expf(-my_logit));
-    if (norm_topk) p = p / lanes_sum<LPT>(p);
+    if (norm_topk) p = p / slots_sum<LPT>(p);
     __syncthreads();  // hist is zero
     if (l < k && t < T) {
         const int e = (int)min(my_idx, (uint32_t)E - 1);  // (NaN logits: some expert that exists)
@@ -180,13 +194,11 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
 #pragma unroll
         for (int j = 1; j < VPL; ++j) mf = fmaxf(mf, v[j]);
         const double mx = (double)lanes_max<LPT>(mf);
-        double ex[VPL], part = 0.0;
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) {
+        double ex[VPL];
+        const double den = experts_sum<LPT, VPL, double>([&](int j, double s) {
             ex[j] = l + LPT * j < E ? exp((double)v[j] - mx) : 0.0;
-            part += ex[j];
-        }
-        const double den = lanes_sum<LPT>(part);
+            return s + ex[j];
+        });
 #pragma unroll
         for (int j = 0; j < VPL; ++j) sc[j] = (float)(ex[j] / den);
     } else {
@@ -270,7 +282,7 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
         }
     }
     float p = l < k ? my_s : 0.f;
-    if (norm_topk) p = p / lanes_sum<LPT>(p);
+    if (norm_topk) p = p / slots_sum<LPT>(p);
     __syncthreads();  // hist is zero
     if (l < k && t < T) {
         const int e = (int)min(my_idx, (uint32_t)E - 1);  // (NaN logits: some expert that exists)
@@ -310,23 +322,20 @@ __global__ __launch_bounds__(256) void route_topk_bwd_kernel(
 #pragma unroll
         for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
         mx = lanes_max<LPT>(m);
-        float s = 0.f;
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) {
+        den = experts_sum<LPT, VPL, float>([&](int j, float s) {
             v[j] = l + LPT * j < E ? expf(v[j] - mx) : 0.f;
-            s += v[j];
-        }
-        den = lanes_sum<LPT>(s);
+            return s + v[j];
+        });
     }
     float q = 0.f;
     if (my_idx >= 0) q = fn == MOE_SCORE_SOFTMAX ? expf(lg - mx) / den : 1.f / (1.f + expf(-lg));
     float dq = scale * dw;
     if (norm_topk) {
-        const float D = lanes_sum<LPT>(q);
-        const float dwq = lanes_sum<LPT>(dw * q);
+        const float D = slots_sum<LPT>(q);
+        const float dwq = slots_sum<LPT>(dw * q);
         dq = my_idx >= 0 ? scale * (dw / D - dwq / (D * D)) : 0.f;
     }
-    const float dqq = lanes_sum<LPT>(dq * q);  // <dq, q>
+    const float dqq = slots_sum<LPT>(dq * q);  // <dq, q>
     // every lane collects the dq of the selected experts it owns
     float gsel[VPL];
 #pragma unroll
@@ -363,7 +372,7 @@ __global__ __launch_bounds__(256) void route_topk_bwd_kernel(
 //          = sum_t <w, p[t,:]>,      w_e = coeff E counts[e] / (T^2 k)
 //   dl[t,j] = g p_j (w_j - <w, p>) (softmax),  g (1 - sg_j) p_j (w_j - <w, p>) (sigmoid),  g = dloss
 // so both the loss and the gradient need only per-token quantities.  The per-token terms are summed in double: the
-// tokens of a workgroup in order, one partial sum per workgroup (32 tokens) into the context's workspace, and the last
+// tokens of a workgroup in order, by eights, one partial sum per workgroup (32 tokens) into the context's workspace, and the last
 // workgroup to arrive adds the partial sums in a fixed order (run-to-run identical, no floating-point atomics).
 // ---------------------------------------------------------------------------
 #define AUX_TOKENS 32  // tokens per workgroup (and 8 bytes of workspace for each)
@@ -387,33 +396,22 @@ __global__ __launch_bounds__(AUX_TOKENS * LPT > 1024 ? 1024 : AUX_TOKENS * LPT) 
 #pragma unroll
             for (int j = 0; j < VPL; ++j) old[j] = l + LPT * j < E ? dlogits[(int64_t)tr * E + l + LPT * j] : 0.f;
         }
-        float part = 0.f;
         if (fn == MOE_SCORE_SOFTMAX) {
             float m = v[0];
 #pragma unroll
             for (int j = 1; j < VPL; ++j) m = fmaxf(m, v[j]);
             m = lanes_max<LPT>(m);
 #pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-                p[j] = l + LPT * j < E ? expf(v[j] - m) : 0.f;
-                part += p[j];
-            }
+            for (int j = 0; j < VPL; ++j) p[j] = l + LPT * j < E ? expf(v[j] - m) : 0.f;
         } else {
 #pragma unroll
-            for (int j = 0; j < VPL; ++j) {
-                v[j] = l + LPT * j < E ? 1.f / (1.f + expf(-v[j])) : 0.f;
-                p[j] = v[j];
-                part += p[j];
-            }
+            for (int j = 0; j < VPL; ++j) p[j] = v[j] = l + LPT * j < E ? 1.f / (1.f + expf(-v[j])) : 0.f;
         }
-        const float inv = 1.f / lanes_sum<LPT>(part);
-        float d = 0.f;
-#pragma unroll
-        for (int j = 0; j < VPL; ++j) {
+        const float inv = 1.f / experts_sum<LPT, VPL, float>([&](int j, float s) { return s + p[j]; });
+        const float d = experts_sum<LPT, VPL, float>([&](int j, float s) {  // <w, p[t,:]>
             p[j] *= inv;
-            d += w[j] * p[j];
-        }
-        d = lanes_sum<LPT>(d);  // <w, p[t,:]>
+            return s + w[j] * p[j];
+        });
         if (l == 0) terms[i] = t < T ? (double)d : 0.0;
         if (dlogits && t < T) {
 #pragma unroll
@@ -430,7 +428,11 @@ __global__ __launch_bounds__(AUX_TOKENS * LPT > 1024 ? 1024 : AUX_TOKENS * LPT) 
     __syncthreads();
     if (threadIdx.x == 0) {
         double sum = 0.0;
-        for (int i = 0; i < AUX_TOKENS; ++i) sum += terms[i];
+        for (int i = 0; i < AUX_TOKENS; i += 8) {
+            double eight = 0.0;
+            for (int x = 0; x < 8; ++x) eight += terms[i + x];
+            sum += eight;
+        }
         if (gridDim.x == 1) *loss = (float)sum;
         else __hip_atomic_store(&partial[blockIdx.x], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

@@ -96,3 +96,38 @@ def test_aux_loss(B, ctx, oracle, T, E, fn):
         assert abs(loss.item() - ref_loss) <= 2e-6 * abs(ref_loss)
         seen.append(loss.item())
     assert len(set(seen)) == 1
+
+
+@pytest.mark.parametrize("T,E", [(37, 17), (70, 33), (301, 64), (130, 129), (515, 256)])
+@pytest.mark.parametrize("fn", [0, 1])
+def test_the_lane_layout_does_not_show_in_the_bits(B, ctx, T, E, fn):
+    """16 lanes per token (16 slots) and a whole wavefront (17 slots, the last with a gradient of zero) add in the same order:
+    weights, gradients, and the loss with 64 experts of no probability appended beyond 256 are the same bits."""
+    from gpu_util import dev
+    g = np.random.default_rng(T * E)
+    logits = g.normal(size=(T, E)).astype(np.float32)
+    d = dev(logits)
+    dw = np.zeros((T, 17), np.float32)
+    dw[:, :16] = g.normal(size=(T, 16))
+    bits = lambda t: t.cpu().numpy().view(np.int32)
+    seen = {}
+    for k in (16, 17):
+        idx, prob, counts = _out(T, E, k)
+        out = torch.empty((T, E), dtype=torch.float32, device="cuda")
+        B.moe_route_topk(ctx, d, T, E, k, fn, False, 1.5, idx, prob, counts)
+        B.moe_route_topk_bwd(ctx, d, idx, dev(dw[:, :k]), T, E, k, fn, False, 1.5, out)
+        gidx, gprob, gcounts = _out(T, E, k)
+        B.moe_route_topk_grouped(ctx, d, None, T, E, k, 1, 1, fn, False, 1.5, gidx, gprob, gcounts)
+        seen[k] = [bits(prob)[:, :16], bits(out), bits(gprob)[:, :16]]
+    for a, b in zip(seen[16], seen[17]):
+        assert np.array_equal(a, b)
+    wide = np.full((T, 320), -np.inf, np.float32)
+    wide[:, :E] = logits
+    counts = np.zeros(320, np.int32)
+    counts[:E] = g.multinomial(2 * T, np.ones(E) / E)
+    res = []
+    for e in (E, 320):
+        dl, loss = torch.empty((T, e), dtype=torch.float32, device="cuda"), torch.empty(1, dtype=torch.float32, device="cuda")
+        B.moe_aux_loss(ctx, dev(wide[:, :e]), dev(counts[:e]), T, e, 2, fn, (E if e == 320 else 320) / 256, 0.7, 0, loss, dl)
+        res.append((bits(loss), bits(dl)[:, :E]))
+    assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
