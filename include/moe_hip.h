@@ -361,7 +361,7 @@ moe_status moe_grouped_gemm_wgrad_gather(moe_ctx* ctx, void* stream, const void*
  * stores (in the GEMM's epilogue, or, small calls, by one more launch), bit for bit what moe_fp8_quantize(MOE_Q_1x128) would make of it:
  *   fwd  (epi = MOE_EPI_SWIGLU): act_q [Rcap, N/2] codes, act_q_scale [Rcap, N/256] of C_act;
  *   dgrad (Z_saved != NULL)    : dz_q  [Rcap, 2K] codes,  dz_q_scale [Rcap, 2K/128] of dZ.
- * Both NULL = the _weighted call.  Rows >= offsets[E] are not written.
+ * Both NULL = the _weighted call.  Rows outside offsets[0] .. offsets[E] - 1 are not written; refused offsets: nothing is.
  */
 moe_status moe_grouped_gemm_fwd_quant(moe_ctx* ctx, void* stream, const void* A, const void* B,
                                       const int32_t* offsets, int E, int N, int K, int64_t Rcap,
@@ -386,8 +386,8 @@ moe_status moe_grouped_gemm_dgrad_quant(moe_ctx* ctx, void* stream, const void* 
  *   q_col [Rcap, cols] codes, e8_col [Rcap/128, cols, 4] E8M0 bytes: the 32x1 copy (operand of the weight
  *         gradients); both NULL = not made.  Needs Rcap % 128 == 0 and every expert's range to start and end on a
  *         multiple of 128 rows (moe_permute with align = 128); otherwise the device error word is raised
- *         (moe_ctx_poll_error) and the outputs are undefined.
- * Rows >= offsets[E] are not written.  All device pointers; nothing is allocated.
+ *         (moe_ctx_poll_error) and nothing is written.
+ * Rows outside offsets[0] .. offsets[E] - 1 are not written; refused offsets: nothing is.  All device pointers; nothing is allocated.
  */
 moe_status moe_grouped_gemm_fwd_quant_mx(moe_ctx* ctx, void* stream, const void* A, const void* B,
                                          const int32_t* offsets, int E, int N, int K, int64_t Rcap,

@@ -257,6 +257,12 @@ __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, i
     return tile_scan(offsets, E, Rcap, dev_err, bm, mult, l, st) && tile_find(st, (int)blockIdx.x, l, e, u, row_lo, row_hi);
 }
 
+// Quantised copies of the tensor X [rows, cols] that a grouped GEMM has just stored (fp8.hip): blockwise 1x128 codes and
+// scales, or MXFP8 1x32 (and, q_col not NULL, 32x1) ones, of the rows offsets[0] .. offsets[E] - 1; nothing at all where the
+// GEMM refuses the offsets too (they fall, leave 0 .. rows, or, with q_col, lie off the 128-row grid).
+moe_status moe_quantise_live(moe_ctx* ctx, hipStream_t s, const void* X, int64_t rows, int cols, const int32_t* offsets, int E,
+                             bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col);
+
 // all-fp32 grouped GEMMs (gemm_f32.hip), reached from the public entry points with dt = MOE_F32
 moe_status moe_gg_f32_fwd(moe_ctx* ctx, hipStream_t s, const void* A, const void* B, const int32_t* offsets, int E, int N,
                           int K, int64_t Rcap, int swiglu, const float* row_prob, void* C, void* C_act);

@@ -27,15 +27,28 @@ __device__ __forceinline__ u32x2_t cvt8_e4m3(u32x4_t v, float scale) {
     return o;
 }
 
+// Rows of the copies that go with a GEMM call (moe_quantise_live): rows_dev points to the last of E + 1 offsets, and whatever
+// makes the GEMM refuse them (see tile_scan) has to stop its copies as well.  Decided alike by every workgroup, from E + 1
+// loads in flight together; every thread must call it.
+__device__ __forceinline__ bool offsets_refused(const int32_t* __restrict__ rows_dev, int E, int64_t rows, bool grid128) {
+    const int32_t* const o = rows_dev - E;
+    bool bad = o[0] < 0 || o[E] > rows;
+    for (int i = threadIdx.x; i < E; i += blockDim.x) bad |= o[i + 1] < o[i] || (grid128 && ((o[i] | o[i + 1]) & 127) != 0);
+    return __syncthreads_or(bad);
+}
+
 // ---- 1x128 ---------------------------------------------------------------------------------
+// (E > 0: the copy of a GEMM's output, see offsets_refused)
 __global__ __launch_bounds__(256) void quant_1x128_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
-                                                          const int32_t* __restrict__ rows_dev,
+                                                          const int32_t* __restrict__ rows_dev, int E,
                                                           u32x2_t* __restrict__ q, float* __restrict__ scale) {
     const int64_t live = rows_dev ? min((int64_t)*rows_dev, rows) : rows;
+    if (E > 0 && offsets_refused(rows_dev, E, rows, false)) return;
     const int bpr = cols / 128;                       // blocks per row
     const int64_t nblocks = live * bpr;
     const int sub = threadIdx.x & 15;                 // lane inside its 16-lane block group
     int64_t b = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 4;
+    if (E > 0) b += (int64_t)rows_dev[-E] * bpr;
     const int64_t stride = ((int64_t)gridDim.x * blockDim.x) >> 4;
     for (; b < nblocks; b += stride) {                // uniform inside a 16-lane group
         const int64_t vec = b * 16 + sub;             // 16-byte vector index (row-major, 16 per block)
@@ -160,7 +173,7 @@ extern "C" moe_status moe_fp8_quantize(moe_ctx* ctx, void* stream, const void* X
             int64_t grid = ceil_div64(nb * 16, 256);
             if (grid > (int64_t)cu * 32) grid = (int64_t)cu * 32;
             hipLaunchKernelGGL(quant_1x128_kernel, dim3((unsigned)grid), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
-                               rows_dev, (u32x2_t*)q, scale);
+                               rows_dev, 0, (u32x2_t*)q, scale);
             break;
         }
         case MOE_Q_128x1: {
@@ -403,11 +416,13 @@ extern "C" moe_status moe_fp8_quantize_rowcol_gather(moe_ctx* ctx, void* stream,
 //          the 1x32 copy in one pass over the input (mx_quant_rowcol_kernel).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void mx_quant_1x32_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
-                                                            const int32_t* __restrict__ rows_dev,
+                                                            const int32_t* __restrict__ rows_dev, int E,
                                                             u32x2_t* __restrict__ q, uint8_t* __restrict__ e8) {
     const int64_t live = rows_dev ? min((int64_t)*rows_dev, rows) : rows;
+    if (E > 0 && offsets_refused(rows_dev, E, rows, false)) return;
     const int64_t nvec = live * (cols / 8);            // 16-byte vectors; 4 per block, blocks never straddle rows
     int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (E > 0) v += (int64_t)rows_dev[-E] * (cols / 8);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; v < ((nvec + 3) & ~(int64_t)3); v += stride) {  // whole 4-lane groups stay together
         const bool in = v < nvec;
@@ -441,7 +456,7 @@ __device__ __forceinline__ uint32_t scale2_bf16(uint32_t w, float sc) { return p
 
 template <bool GATHER>
 __global__ __launch_bounds__(256) void mx_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
-                                                              const int32_t* __restrict__ rows_dev,
+                                                              const int32_t* __restrict__ rows_dev, int E,
                                                               const int32_t* __restrict__ src_of, uint32_t k_magic, int k_shift,
                                                               const float* __restrict__ pair_scale, int groups,
                                                               u32x2_t* __restrict__ q_row, uint32_t* __restrict__ e8_row,
@@ -496,6 +511,7 @@ __global__ __launch_bounds__(256) void mx_quant_rowcol_kernel(const u32x4_t* __r
     } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) x[i] = X[v0 + (int64_t)i * 4 * vpr];
+        if (E > 0 && (offsets_refused(rows_dev, E, rows, true) || row0 < rows_dev[-E])) return;  // (the rows are on their way meanwhile)
     }
     if (q_row) {
 #pragma unroll
@@ -555,7 +571,7 @@ __global__ __launch_bounds__(256) void mx_quant_rowcol_kernel(const u32x4_t* __r
 static moe_status mx_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who, const void* X, int64_t rows, int cols,
                                    const int32_t* rows_dev, void* q_row, uint8_t* e8_row, void* q_col, uint8_t* e8_col,
                                    const int32_t* src_of = nullptr, int k = 1, const float* pair_scale = nullptr,
-                                   int groups = 1) {
+                                   int groups = 1, int E = 0) {
     if (rows % 128 || cols % 128) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: rows and cols must be multiples of 128", who);
     if (groups < 1) groups = 1;
     const int64_t tiles_r = src_of ? (rows / 128 + groups - 1) / groups * groups : rows / 128;
@@ -563,11 +579,11 @@ static moe_status mx_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who,
     if (nblk > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: too many tiles", who);
     if (src_of)
         hipLaunchKernelGGL(mx_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
-                           rows_dev, src_of, gather_div(k).m, gather_div(k).sh, pair_scale, groups, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
+                           rows_dev, 0, src_of, gather_div(k).m, gather_div(k).sh, pair_scale, groups, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
                            (uint32_t*)e8_col);
     else
         hipLaunchKernelGGL(mx_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
-                           rows_dev, nullptr, 0, 0, nullptr, 1, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
+                           rows_dev, E, nullptr, 0, 0, nullptr, 1, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
                            (uint32_t*)e8_col);
     return MOE_OK;
 }
@@ -588,7 +604,7 @@ extern "C" moe_status moe_mx_quantize(moe_ctx* ctx, void* stream, const void* X,
             int64_t grid = ceil_div64(rows * (cols / 8), 256);
             if (grid > (int64_t)cu * 32) grid = (int64_t)cu * 32;
             hipLaunchKernelGGL(mx_quant_1x32_kernel, dim3((unsigned)grid), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
-                               rows_dev, (u32x2_t*)q, e8m0);
+                               rows_dev, 0, (u32x2_t*)q, e8m0);
             break;
         }
         case MOE_MX_32x1: {
@@ -633,5 +649,24 @@ extern "C" moe_status moe_mx_quantize_rowcol_gather(moe_ctx* ctx, void* stream, 
                                      e8m0_row, q_col, e8m0_col, src_of, k, pair_scale, groups);
     if (st != MOE_OK) return st;
     MOE_LAUNCH_CHECK(ctx, "moe_mx_quantize_rowcol_gather");
+    return MOE_OK;
+}
+
+moe_status moe_quantise_live(moe_ctx* ctx, hipStream_t s, const void* X, int64_t rows, int cols, const int32_t* offsets, int E,
+                             bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col) {
+    const char* who = "quantised copies of a grouped GEMM";
+    const int32_t* const end = offsets + E;
+    const int64_t most = (int64_t)(ctx->num_cu > 0 ? ctx->num_cu : 256) * 32, grid = ceil_div64(rows * (cols / 8), 256);
+    const dim3 g((unsigned)(grid < most ? grid : most)), b(256);
+    if (cols % 128) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: %d columns are not a multiple of 128", who, cols);
+    if (mx && q_col) {
+        const moe_status st = mx_rowcol_launch(ctx, s, who, X, rows, cols, end, q, (uint8_t*)scale, q_col, e8_col, nullptr, 1, nullptr, 1, E);
+        if (st != MOE_OK) return st;
+    } else if (mx) {
+        hipLaunchKernelGGL(mx_quant_1x32_kernel, g, b, 0, s, (const u32x4_t*)X, rows, cols, end, E, (u32x2_t*)q, (uint8_t*)scale);
+    } else {
+        hipLaunchKernelGGL(quant_1x128_kernel, g, b, 0, s, (const u32x4_t*)X, rows, cols, end, E, (u32x2_t*)q, (float*)scale);
+    }
+    MOE_LAUNCH_CHECK(ctx, who);
     return MOE_OK;
 }

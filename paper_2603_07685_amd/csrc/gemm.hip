@@ -1978,13 +1978,11 @@ static moe_status gg_mx_out_check(moe_ctx* ctx, const char* who, const gg_mx_out
     return MOE_OK;
 }
 
-// The small-tile kernels' quantised copies of a stored tensor X [live rows, cols]: the stand-alone quantisers, which produce
+// The quantised copies of the tensor X [Rcap, cols] that a kernel of gemm_tile8.hip has stored: one more launch, which gives
 // the codes and scales of the quantising epilogues.
-static moe_status gg_quantise(moe_ctx* ctx, void* stream, const void* X, int64_t rows, int cols, const int32_t* live, bool mx,
-                              const gg_args& a) {
-    if (!mx) return moe_fp8_quantize(ctx, stream, X, MOE_Q_1x128, 1, rows, cols, live, a.out_q, a.out_q_scale);
-    if (!a.out_qc) return moe_mx_quantize(ctx, stream, X, MOE_MX_1x32, 1, rows, cols, live, a.out_q, a.out_q_e8);
-    return moe_mx_quantize_rowcol(ctx, stream, X, rows, cols, live, a.out_q, a.out_q_e8, a.out_qc, a.out_qc_e8);
+static moe_status gg_quantise(moe_ctx* ctx, void* stream, const void* X, int cols, bool mx, const gg_args& a) {
+    return moe_quantise_live(ctx, (hipStream_t)stream, X, a.Rcap, cols, a.offsets, a.E, mx, a.out_q,
+                             mx ? (void*)a.out_q_e8 : (void*)a.out_q_scale, a.out_qc, a.out_qc_e8);
 }
 
 static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const void* B, const int32_t* offsets, int E, int N,
@@ -2067,7 +2065,7 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
         if (!fp8) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
         else gq_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<fwd>");
-        return a.out_q ? gg_quantise(ctx, stream, C_act, Rcap, N / 2, offsets + E, mx, a) : MOE_OK;
+        return a.out_q ? gg_quantise(ctx, stream, C_act, N / 2, mx, a) : MOE_OK;
     } else if (epi == MOE_EPI_SWIGLU) {
         if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 1);
         else GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 0);
@@ -2195,7 +2193,7 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
         if (!fp8) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
         else gq_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<dgrad>");
-        return a.out_q ? gg_quantise(ctx, stream, dA, Rcap, 2 * K, offsets + E, mx, a) : MOE_OK;
+        return a.out_q ? gg_quantise(ctx, stream, dA, 2 * K, mx, a) : MOE_OK;
     } else if (Z_saved) {
         if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
         else GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 0);
