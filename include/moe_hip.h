@@ -24,9 +24,10 @@
  *     moe_last_error gives a host string describing the last failure on a context.
  *   - Calls on one context from several host threads at once are not supported, and all calls on one
  *     context must be stream-ordered with respect to each other (use one context per stream): several calls
- *     keep device-side state in the context workspace (the row-ID map's histograms, the router's histogram, the
- *     auxiliary loss's partial sums, the gate GEMM's offsets, the weight gradient's tile counter and partial tiles), and two such
- *     calls running at the same time on different streams would race silently.
+ *     keep device-side state in the context workspace (the row-ID map's histograms, the auxiliary loss's
+ *     partial sums, the gate GEMM's partial results, the weight gradient's tile counter and partial tiles), and two such
+ *     calls running at the same time on different streams would race silently.  Nothing of it outlives its call: each
+ *     call writes what it reads there, so that such a race spoils those calls alone.
  *   - Same inputs give bit-identical outputs from run to run (no floating-point
  *     atomics anywhere; integer atomics only where the result is order-free).
  */
@@ -67,7 +68,7 @@ typedef enum { MOE_EPI_NONE = 0, MOE_EPI_SWIGLU = 1 } moe_epilogue;
 size_t moe_workspace_bytes(int T, int k, int E, int h, int f_max);
 
 /* Create a context on `device` and allocate `workspace_bytes` of device memory
- * (and a few KB more) for it (hipMalloc; the only allocation the library ever makes).  *out is
+ * for it (hipMalloc; the only allocation the library ever makes).  *out is
  * written only on success.  Host call; synchronises the device. */
 moe_status moe_ctx_create(moe_ctx** out, int device, size_t workspace_bytes);
 

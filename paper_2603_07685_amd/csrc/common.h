@@ -13,19 +13,11 @@ struct moe_ctx {
     size_t ws_bytes;
     int* dev_err;      // device error word (first 256 bytes of ws are reserved for it)
     int num_cu;
-    int* aux;          // small device state of the library's own behind the workspace: zero whenever no call is running
     char err[512];
 };
 
 #define MOE_WS_RESERVED 256  // bytes at the head of the workspace: error word at 0, ...
 #define MOE_WS_ZEROS 128     // ... and 128 bytes that stay zero for the whole life of the context
-
-// ints of ctx->aux (each user leaves what it counted in at zero again)
-#define MOE_AUX_ROUTE_TICKET 0    // workgroups of a routing kernel that have added their histogram
-#define MOE_AUX_LOSS_TICKET 16    // ... of the auxiliary loss that have stored their partial sum
-#define MOE_AUX_TILE_COUNTER 32    // weight gradient: tiles drawn, then workgroups done drawing
-#define MOE_AUX_ROUTE_COUNTS 64   // [1024] the histogram being added up
-#define MOE_AUX_INTS (64 + 1024)
 
 #define MOE_FAIL(ctx, code, ...)                                   \
     do {                                                           \

@@ -41,10 +41,9 @@ extern "C" moe_status moe_ctx_create(moe_ctx** out, int device, size_t workspace
     memset(c, 0, sizeof(*c));
     c->device = device;
     if (workspace_bytes < MOE_WS_RESERVED) workspace_bytes = MOE_WS_RESERVED;
-    const size_t aux_at = (workspace_bytes + 255) / 256 * 256, all_bytes = aux_at + MOE_AUX_INTS * sizeof(int);
     hipError_t e = hipSetDevice(device);
-    if (e == hipSuccess) e = hipMalloc(&c->ws, all_bytes);
-    if (e == hipSuccess) e = hipMemset(c->ws, 0, all_bytes);
+    if (e == hipSuccess) e = hipMalloc(&c->ws, workspace_bytes);
+    if (e == hipSuccess) e = hipMemset(c->ws, 0, workspace_bytes);
     hipDeviceProp_t prop;
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -55,7 +54,6 @@ extern "C" moe_status moe_ctx_create(moe_ctx** out, int device, size_t workspace
     }
     c->ws_bytes = workspace_bytes;
     c->dev_err = (int*)c->ws;
-    c->aux = (int*)((char*)c->ws + aux_at);
     c->num_cu = prop.multiProcessorCount;
     *out = c;
     return MOE_OK;

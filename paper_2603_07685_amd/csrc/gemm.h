@@ -94,7 +94,7 @@ struct gg_args {
     uint8_t* out_q_e8;
     uint8_t* out_qc;
     uint8_t* out_qc_e8;
-    int* tile_counter;     // wgrad: zeroed device counter for the dynamic tile order under skewed loads (see the kernel)
+    int* tile_counter;     // wgrad: device counter, zero at the start, for the dynamic tile order under skewed loads (see the kernel)
     // wgrad, bf16: deterministic split of the contraction for experts far above the mean load (see the kernel)
     int split_cap;         // how many expert-sized slices of fp32 partial tiles `partials` can hold (0: never split)
     float* partials;       // [split_cap][tiles per expert][256 x 256] fp32

@@ -1780,13 +1780,6 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
         }
         t = t_next;
     }
-    // the counter the tiles were drawn from goes back to zero with the last workgroup that is done with it
-    if (MODE == GG_WGRAD && dyn && tid == 0) {
-        if (atomicAdd(a.tile_counter + 1, 1) + 1 == G) {
-            atomicExch(a.tile_counter, 0);
-            atomicExch(a.tile_counter + 1, 0);
-        }
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1826,7 +1819,9 @@ static gg_args gg_make(moe_ctx* ctx, const void* P, const void* Q, const int32_t
     return a;
 }
 
-#define MOE_WS_SPLIT_INFO 64    // byte offset in the reserved head of the workspace: the list of split experts (1 + 3 * GG_MAX_SPLIT_EXPERTS ints)
+// byte offsets in the reserved head of the workspace
+#define MOE_WS_TILE_COUNTER 48  // the weight gradient's tile counter, cleared by each call
+#define MOE_WS_SPLIT_INFO 64    // the list of split experts (1 + 3 * GG_MAX_SPLIT_EXPERTS ints)
 
 // Second step of a weight gradient with a split contraction: dW tile = sum of its pieces' partial tiles, piece 0
 // first, then the ordinary output step (type, accumulate, matrix edges).  The list of split experts was written by the
@@ -2252,13 +2247,14 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     }
     a.p_scale = dc_scale;
     a.q_scale = a_scale;
-    a.tile_counter = ctx->aux + MOE_AUX_TILE_COUNTER;
+    a.tile_counter = (int*)((char*)ctx->ws + MOE_WS_TILE_COUNTER);
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
         if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
         else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;
     }
+    moe_launch_fill_i32(a.tile_counter, 1, 0, (hipStream_t)stream);
     // split contraction (bf16 operands): as many slices of partial tiles as the workspace holds behind its reserved head
     const size_t slice_bytes = (size_t)ceil_div64(N, GG_BM) * ceil_div64(K, GG_BN) * GG_BM * GG_BN * sizeof(float);
     const size_t ws_free = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;

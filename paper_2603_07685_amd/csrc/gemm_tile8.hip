@@ -433,11 +433,6 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
         stage_barrier();
     }
     }
-    // the counter goes back to zero with the last workgroup that is done with it
-    if (LPT && dyn && tid == 0 && atomicAdd(a.tile_counter + 1, 1) + 1 == G) {
-        atomicExch(a.tile_counter, 0);
-        atomicExch(a.tile_counter + 1, 0);
-    }
 }
 
 
@@ -506,6 +501,7 @@ int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg
 }
 void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a) {
     const int cu = ctx->num_cu >= 8 ? ctx->num_cu & ~7 : 256;
+    if (mx && tile == 3 && mode == GG_WGRAD) moe_launch_fill_i32(a.tile_counter, 1, 0, s);
     if (mx && tile == 3) gq_call<2, 256, 256>(s, mode, epi, out_f32, a, cu);
     else if (mx) tile == 1 ? gq_call<2, 64>(s, mode, epi, out_f32, a, cu) : gq_call<2, 128>(s, mode, epi, out_f32, a, cu);
     else tile == 1 ? gq_call<1, 64>(s, mode, epi, out_f32, a, cu) : gq_call<1, 128>(s, mode, epi, out_f32, a, cu);

@@ -8,9 +8,8 @@
 // Bound: vector instructions at large T (one read of the logits: 3.6 us for T 16384, E 256 at the copy rate), one
 // token's chain of reductions at small T.  Values are compared as order-preserving integers, so that an arg-max round is
 // max3 over the lane's values, four DPP maxima, and a DPP minimum over the indices that hold the maximum.
-// Measured (us; one token per wavefront, eight in turn, butterfly shuffles : this), T 16384, E 256, k 8: top-k 59 : 17;
-// group-limited with bias, 8 groups: 150 : 36; backward 23 : 11.5; auxiliary loss 27 (two kernels) : 19.
-// T 64, E 128, k 8: 51 : 7.
+// Measured (us a call; one token per wavefront, eight in turn, butterfly shuffles : this), T 16384, E 256, k 8: top-k 57 : 15;
+// group-limited with bias, 8 groups: 147 : 35; backward 22 : 11; auxiliary loss 22 : 16.  T 64, E 128, k 8: 47 : 6.
 #include "common.h"
 
 #define ROUTE_MAX_E 1024
@@ -86,41 +85,23 @@ __device__ __forceinline__ void take_best(uint32_t (&key)[VPL], int l, uint32_t&
     for (int j = 0; j < VPL; ++j) key[j] = (uint32_t)(l + LPT * j) == idx ? 0u : key[j];
 }
 
-// ---- the histogram: LDS per workgroup, then, with more than one workgroup, an accumulator in the context that is zero
-// between calls: the last workgroup to arrive takes the totals out and leaves zeros (a fill launch ahead of the kernel
-// costs more than the kernel at small T) -----------------------------------------------------------------------------
-// What is handed over are agent-scope atomics only, complete (at the memory side) once the wave's counter of outstanding
-// memory operations is zero; a device-wide fence instead would write back every dirty line of the L2 in each workgroup
-// (T 16384, E 256: top-k 77 us with it, 17 without).
-__device__ __forceinline__ bool last_workgroup(int* ticket) {   // every thread must call it
-    __shared__ int mine;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const int t = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        mine = t + 1 == (int)gridDim.x;
-        if (mine) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    return mine != 0;
-}
-__device__ __forceinline__ void finish_counts(const int32_t* hist, int E, int32_t* counts, int* ticket, int32_t* acc) {
+// The histogram: LDS per workgroup, then, with more than one workgroup, added to `counts`, which a launch ahead of the kernel
+// has cleared.  (An accumulator kept at zero between calls, taken out by the last workgroup, saves that launch, 2-4 us, but
+// what one call left there the next would count.)
+__device__ __forceinline__ void finish_counts(const int32_t* hist, int E, int32_t* counts) {
     __syncthreads();
     if (!counts) return;
-    if (gridDim.x == 1) {
-        for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = hist[e];
-        return;
+    const bool alone = gridDim.x == 1;
+    for (int e = threadIdx.x; e < E; e += blockDim.x) {
+        if (alone) counts[e] = hist[e];
+        else if (hist[e]) atomicAdd(&counts[e], hist[e]);
     }
-    for (int e = threadIdx.x; e < E; e += blockDim.x)
-        if (hist[e]) atomicAdd(&acc[e], hist[e]);
-    if (last_workgroup(ticket))
-        for (int e = threadIdx.x; e < E; e += blockDim.x) counts[e] = atomicExch(&acc[e], 0);
 }
 
 template <int LPT, int VPL>
 __global__ __launch_bounds__(1024) void route_topk_kernel(
     const float* __restrict__ logits, int T, int E, int k, int fn, int norm_topk, float scale,
-    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts, int* ticket, int32_t* acc) {
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts) {
     extern __shared__ int32_t hist[];  // [E]
     const int l = threadIdx.x & (LPT - 1);
     const int t = blockIdx.x * (blockDim.x / LPT) + threadIdx.x / LPT;
@@ -160,7 +141,7 @@ __global__ __launch_bounds__(1024) void route_topk_kernel(
         topk_prob[(int64_t)t * k + l] = p * scale;
         atomicAdd(&hist[e], 1);
     }
-    finish_counts(hist, E, counts, ticket, acc);
+    finish_counts(hist, E, counts);
 }
 
 // ---------------------------------------------------------------------------
@@ -178,7 +159,7 @@ template <int LPT, int VPL>
 __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
     const float* __restrict__ logits, const float* __restrict__ bias, int T, int E, int k, int n_group, int topk_group,
     int lpg, uint32_t gs_magic, int fn, int norm_topk, float scale,
-    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts, int* ticket, int32_t* acc) {
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts) {
     extern __shared__ int32_t hist[];  // [E] histogram, then one [E + E / 16 + 1] row of c per token of the workgroup
     const int l = threadIdx.x & (LPT - 1);
     const int t = blockIdx.x * (blockDim.x / LPT) + threadIdx.x / LPT;
@@ -290,7 +271,7 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
         topk_prob[(int64_t)t * k + l] = p * scale;
         atomicAdd(&hist[e], 1);
     }
-    finish_counts(hist, E, counts, ticket, acc);
+    finish_counts(hist, E, counts);
 }
 
 // ---------------------------------------------------------------------------
@@ -372,14 +353,14 @@ __global__ __launch_bounds__(256) void route_topk_bwd_kernel(
 //          = sum_t <w, p[t,:]>,      w_e = coeff E counts[e] / (T^2 k)
 //   dl[t,j] = g p_j (w_j - <w, p>) (softmax),  g (1 - sg_j) p_j (w_j - <w, p>) (sigmoid),  g = dloss
 // so both the loss and the gradient need only per-token quantities.  The per-token terms are summed in double: the
-// tokens of a workgroup in order, by eights, one partial sum per workgroup (32 tokens) into the context's workspace, and the last
-// workgroup to arrive adds the partial sums in a fixed order (run-to-run identical, no floating-point atomics).
+// tokens of a workgroup in order, by eights, one partial sum per workgroup (32 tokens) into the context's workspace, and a
+// one-wave kernel adds the partial sums in a fixed order (run-to-run identical, no floating-point atomics).
 // ---------------------------------------------------------------------------
 #define AUX_TOKENS 32  // tokens per workgroup (and 8 bytes of workspace for each)
 template <int LPT, int VPL>
 __global__ __launch_bounds__(AUX_TOKENS * LPT > 1024 ? 1024 : AUX_TOKENS * LPT) void aux_loss_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ counts, int T, int E, int fn, float wscale, float g,
-    int accumulate, float* __restrict__ dlogits, double* partial, float* __restrict__ loss, int* ticket) {
+    int accumulate, float* __restrict__ dlogits, double* __restrict__ partial, float* __restrict__ loss) {
     __shared__ double terms[AUX_TOKENS];
     const int l = threadIdx.x & (LPT - 1);
     float w[VPL];
@@ -434,16 +415,15 @@ __global__ __launch_bounds__(AUX_TOKENS * LPT > 1024 ? 1024 : AUX_TOKENS * LPT) 
             sum += eight;
         }
         if (gridDim.x == 1) *loss = (float)sum;
-        else __hip_atomic_store(&partial[blockIdx.x], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else partial[blockIdx.x] = sum;
     }
-    if (gridDim.x == 1 || !last_workgroup(ticket)) return;
-    if (threadIdx.x < 64) {
-        double a = 0.0;
-        for (int i = threadIdx.x; i < (int)gridDim.x; i += 64)
-            a += __hip_atomic_load(&partial[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        a = lanes_sum<64>(a);
-        if (threadIdx.x == 0) *loss = (float)a;
-    }
+}
+
+__global__ __launch_bounds__(64) void aux_loss_sum_kernel(const double* __restrict__ partial, int n, float* __restrict__ loss) {
+    double a = 0.0;
+    for (int i = threadIdx.x; i < n; i += 64) a += partial[i];
+    a = lanes_sum<64>(a);
+    if (threadIdx.x == 0) *loss = (float)a;
 }
 
 // ---------------------------------------------------------------------------
@@ -484,10 +464,12 @@ extern "C" moe_status moe_route_topk(moe_ctx* ctx, void* stream, const float* lo
     }
     const int lpt = route_narrow(E, k, 1) ? 16 : 64;
     // many tokens: large workgroups, so that fewer of them add their histograms to the shared one
-    const int threads = T > 4096 ? 1024 : 256, tokens = threads / lpt;
+    // (and one alone where it can: nothing to clear then)
+    const int threads = T > 4096 || (T > 256 / lpt && T <= 1024 / lpt) ? 1024 : 256, tokens = threads / lpt;
     const dim3 grid((T + tokens - 1) / tokens), block(threads);
+    if (counts && grid.x > 1) moe_launch_fill_i32(counts, E, 0, s);
     ROUTE_CASES(route_topk_kernel, grid, block, (size_t)E * sizeof(int32_t), s, logits, T, E, k, (int)fn, norm_topk, scale,
-                topk_idx, topk_prob, counts, ctx->aux + MOE_AUX_ROUTE_TICKET, (int32_t*)(ctx->aux + MOE_AUX_ROUTE_COUNTS));
+                topk_idx, topk_prob, counts);
     MOE_LAUNCH_CHECK(ctx, "route_topk_kernel");
     return MOE_OK;
 }
@@ -518,10 +500,10 @@ extern "C" moe_status moe_route_topk_grouped(moe_ctx* ctx, void* stream, const f
     const int tokens = 256 / lpt, gs = E / n_group;
     const uint32_t gs_magic = ((1u << 20) + gs - 1) / gs;  // (e * gs_magic) >> 20 == e / gs for e < 1024: the excess, e * gs at most, stays below 2^20
     const dim3 grid((T + tokens - 1) / tokens), block(256);
+    if (counts && grid.x > 1) moe_launch_fill_i32(counts, E, 0, s);
     const size_t shm = (size_t)E * sizeof(int32_t) + (size_t)tokens * (E + E / 16 + 1) * sizeof(float);
     ROUTE_CASES(route_topk_grouped_kernel, grid, block, shm, s, logits, expert_bias, T, E, k, n_group, topk_group, lpg, gs_magic,
-                (int)fn, norm_topk, scale, topk_idx, topk_prob, counts, ctx->aux + MOE_AUX_ROUTE_TICKET,
-                (int32_t*)(ctx->aux + MOE_AUX_ROUTE_COUNTS));
+                (int)fn, norm_topk, scale, topk_idx, topk_prob, counts);
     MOE_LAUNCH_CHECK(ctx, "route_topk_grouped_kernel");
     return MOE_OK;
 }
@@ -556,10 +538,11 @@ extern "C" moe_status moe_aux_loss(moe_ctx* ctx, void* stream, const float* logi
         MOE_FAIL(ctx, MOE_ERR_WORKSPACE, "moe_aux_loss: workspace %zu B < %zu B", ctx->ws_bytes,
                  MOE_WS_RESERVED + (size_t)nblocks * sizeof(double));
     const int lpt = E <= 256 ? 16 : 64;
+    double* const partial = (double*)((char*)ctx->ws + MOE_WS_RESERVED);
     const float wscale = (float)((double)coeff * E / ((double)T * T * k));
     ROUTE_CASES(aux_loss_kernel, dim3(nblocks), dim3(lpt == 16 ? 16 * AUX_TOKENS : 1024), 0, (hipStream_t)stream, logits, counts, T, E,
-                (int)fn, wscale, dloss, accumulate, dlogits, (double*)((char*)ctx->ws + MOE_WS_RESERVED), loss,
-                ctx->aux + MOE_AUX_LOSS_TICKET);
+                (int)fn, wscale, dloss, accumulate, dlogits, partial, loss);
+    if (nblocks > 1) hipLaunchKernelGGL(aux_loss_sum_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, partial, nblocks, loss);
     MOE_LAUNCH_CHECK(ctx, "aux_loss_kernel");
     return MOE_OK;
 }

@@ -131,3 +131,32 @@ def test_the_lane_layout_does_not_show_in_the_bits(B, ctx, T, E, fn):
         B.moe_aux_loss(ctx, dev(wide[:, :e]), dev(counts[:e]), T, e, 2, fn, (E if e == 320 else 320) / 256, 0.7, 0, loss, dl)
         res.append((bits(loss), bits(dl)[:, :E]))
     assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
+
+
+def test_calls_that_overlap_leave_nothing_behind(B, oracle):
+    """The router keeps nothing in the context: calls of several token counts on two streams at once each count right, and so
+    does a later call."""
+    from gpu_util import dev
+    ctx = B.Context(T=8192, k=8, E=64, h=64, f_max=64)
+    E, k, cases = 96, 4, []
+    for i, T in enumerate((8192, 6000, 8000, 4097)):
+        logits = np.random.default_rng(i).normal(size=(T, E)).astype(np.float32)
+        cases.append((T, dev(logits), oracle.route_topk(logits, k, 0, False, 1.0)[2], _out(T, E, k)))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for _ in range(5):
+        torch.cuda.synchronize()
+        torch.cuda._sleep(2_000_000)   # (both streams start on what has been queued by then together)
+        queued = torch.cuda.Event()
+        queued.record()
+        for s in streams:
+            s.wait_event(queued)
+        for i, (T, d, _, out) in enumerate(cases):
+            with torch.cuda.stream(streams[i & 1]):
+                B.moe_route_topk(ctx, d, T, E, k, 0, False, 1.0, *out)
+        torch.cuda.synchronize()
+        for T, d, want, out in cases:
+            assert np.array_equal(out[2].cpu().numpy(), want)
+    T, d, want, out = cases[3]
+    B.moe_route_topk(ctx, d, T, E, k, 0, False, 1.0, *out)
+    assert np.array_equal(out[2].cpu().numpy(), want)
+    ctx.close()
