@@ -246,8 +246,68 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             tile_start[rank] = e;
         }
     }
-    if (SPLITK) __syncthreads();  // (thread 0 walks the sorted experts below)
-    if (tid == 0) {
+    if (SPLITK) {
+        // Deterministic split of the contraction (Sec. 4.3.1 names the imbalance it answers).  Under a skewed load
+        // one tile of the largest expert can be most of a workgroup's share; such experts are cut into pieces of at most
+        // `lim` rows (whole stages), each piece is a work item of its own that leaves its 256 x 256 result as an fp32
+        // partial tile in the workspace, and a second kernel adds the pieces of a tile in increasing order: the same sums
+        // in the same order whatever the timing.  Decided here, from the offsets alone and identically in every thread of
+        // every workgroup: the largest experts, those above twice the mean and above lim, while the workspace has slices
+        // left.  A piece costs a partial tile's way to memory and back, so lim is as large as the draw can balance: a third
+        // of a workgroup's share of the call (rows times tiles, over the workgroups), or the mean where that is more.
+        // T 1999, k 4, h 2880, f 1472, 24 experts (12 row tiles' worth of experts per workgroup): fc1 gradient 334 us + 153 us
+        // of second pass with pieces of the mean, 334 + 5 now; T 16384, k 8, h 4096, f 1536, 16 experts, rank^-1.2:
+        // 2472 + 205 : 2434 + 28.
+        // (In parallel over the experts, and the 64-bit divisions only under skew.  With one thread walking them, T 16384, k 8,
+        // h 512, f 512, 128 even experts: 167 us a call against 157; T 4096, k 8, h 1024, f 256, 64 experts: 61.5 against 53.5.)
+        bool off = tid == 0 && (offs[0] < 0 || offs[E] > a.Rcap);
+        for (int e = tid; e < E; e += THREADS) off |= offs[e + 1] < offs[e];
+        const bool bad = __syncthreads_or(off);   // (the sorted experts are there then, too)
+        const int tpe = tiles_i_w * tiles_j;
+        const int64_t rows_all = offs[E] - offs[0];
+        auto rows_of = [&](int i) {   // of the i-th largest expert
+            const int ee = tile_start[i];
+            return offs[ee + 1] - offs[ee];
+        };
+        int pieces[GG_MAX_SPLIT_EXPERTS], slice0[GG_MAX_SPLIT_EXPERTS], used = 0, nsplit = 0;
+#pragma unroll
+        for (int i = 0; i < GG_MAX_SPLIT_EXPERTS; ++i) pieces[i] = 1, slice0[i] = 0;
+        if (!bad && a.split_cap >= 2 && (int64_t)rows_of(0) * E > 2 * rows_all) {
+            const int64_t third = rows_all * tpe / (3 * (int64_t)gridDim.x), avg = rows_all / E;
+            const int lim = (int)((max(min(max(third, avg), rows_all), (int64_t)1) + 127) / 128 * 128);
+#pragma unroll
+            for (int i = 0; i < GG_MAX_SPLIT_EXPERTS; ++i) {
+                const int rows = i < E ? rows_of(i) : 0;
+                const int n = min((rows + lim - 1) / lim, a.split_cap - used);
+                if (nsplit == i && rows > 2 * avg && rows > lim && n >= 2) {
+                    pieces[i] = n;
+                    slice0[i] = used;
+                    used += n;
+                    ++nsplit;
+                    if (blockIdx.x == 0 && tid == 0) {
+                        a.split_info[1 + 3 * i] = tile_start[i];
+                        a.split_info[2 + 3 * i] = n;
+                        a.split_info[3 + 3 * i] = slice0[i];
+                    }
+                }
+            }
+        }
+        for (int x = tid; x <= E; x += THREADS) {
+            int before = x, sp = 1;
+#pragma unroll
+            for (int i = 0; i < GG_MAX_SPLIT_EXPERTS; ++i) {
+                before += i < x ? pieces[i] - 1 : 0;
+                sp = i == x ? pieces[i] | (slice0[i] << 8) : sp;
+            }
+            item_start[x] = before * tpe;
+            if (x < E) split_of[x] = sp;
+            else tile_start[E] = bad ? 0 : before * tpe;   // inconsistent offsets: touch no tensor memory, raise the error word
+        }
+        if (blockIdx.x == 0 && tid == 0) {
+            a.split_info[0] = bad ? 0 : nsplit;
+            if (bad) atomicExch(a.dev_err, 1);
+        }
+    } else if (tid == 0) {
         int run = 0;
         bool bad = offs[0] < 0 || offs[E] > a.Rcap;
         for (int e = 0; e < E; ++e) {
@@ -261,57 +321,9 @@ __global__ __launch_bounds__(NW * 64, 1) __attribute__((amdgpu_waves_per_eu(1, N
             if (GATE) run *= a.split_cap;
         }
         tile_start[E] = run;
-        if (SPLITK) {
-            // Deterministic split of the contraction (Sec. 4.3.1 names the imbalance it answers).  Under a skewed load
-            // one tile of the largest expert can be most of a workgroup's share; such experts are cut into pieces of
-            // about the mean expert's row count (whole stages), each piece is a work item of its own that leaves its
-            // 256 x 256 result as an fp32 partial tile in the workspace, and a second kernel adds the pieces of a tile
-            // in increasing order: the same sums in the same order whatever the timing.  Decided here, from the
-            // offsets alone and identically in every workgroup: experts in descending size, those above twice the mean,
-            // into pieces of at most `lim` rows, while the workspace has slices left.  A piece costs a partial tile's
-            // way to memory and back, so lim is as large as the draw can balance: a third of a workgroup's share of the
-            // call (rows times tiles, over the workgroups), or the mean where that is more.  T 1999, k 4, h 2880, f 1472,
-            // 24 experts (12 row tiles' worth of experts per workgroup): fc1 gradient 334 us + 153 us of second pass with
-            // pieces of the mean, 334 + 5 now; T 16384, k 8, h 4096, f 1536, 16 experts, rank^-1.2: 2472 + 205 : 2434 + 28.
-            const int tpe = tiles_i_w * tiles_j;
-            const int64_t rows_all = offs[E] - offs[0];
-            const int emax = tile_start[0];
-            const bool skew = !bad && a.split_cap >= 2 && (int64_t)(offs[emax + 1] - offs[emax]) * E > 2 * rows_all;
-            const int64_t third = rows_all * tpe / (3 * (int64_t)gridDim.x), avg = rows_all / E;
-            const int64_t most = rows_all > 0 ? rows_all : 1;
-            const int lim = (int)((max(min(max(third, avg), most), (int64_t)1) + 127) / 128 * 128);
-            int used = 0, nsplit = 0, items = 0;
-            for (int i = 0; i < E; ++i) {
-                const int ee = tile_start[i];
-                const int rows = offs[ee + 1] - offs[ee];
-                int pieces = 1;
-                if (skew && rows > 2 * avg && rows > lim && nsplit < GG_MAX_SPLIT_EXPERTS) {
-                    pieces = min((rows + lim - 1) / lim, a.split_cap - used);
-                    if (pieces < 2) pieces = 1;
-                }
-                item_start[i] = items;
-                split_of[i] = pieces | (used << 8);
-                if (pieces > 1) {
-                    if (blockIdx.x == 0) {
-                        a.split_info[1 + 3 * nsplit] = ee;
-                        a.split_info[2 + 3 * nsplit] = pieces;
-                        a.split_info[3 + 3 * nsplit] = used;
-                    }
-                    used += pieces;
-                    ++nsplit;
-                }
-                items += pieces * tpe;
-            }
-            item_start[E] = items;
-            if (blockIdx.x == 0) a.split_info[0] = nsplit;
-            tile_start[E] = items;
-        }
         if (bad) {  // inconsistent offsets: touch no tensor memory, raise the error word
             tile_start[E] = 0;
-            if (blockIdx.x == 0) {
-                atomicExch(a.dev_err, 1);
-                if (SPLITK) a.split_info[0] = 0;
-            }
+            if (blockIdx.x == 0) atomicExch(a.dev_err, 1);
         }
     }
     __syncthreads();
