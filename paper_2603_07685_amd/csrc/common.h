@@ -152,8 +152,10 @@ __device__ __forceinline__ float bf16_absmax_finish(uint32_t m) {
 // finds its tile in the list of all experts' tiles, expert by expert: mult * ceil(rows / bm) of them each, or mult if
 // bm = 0.  u = the tile's number inside its expert.  A parallel prefix sum: one pass of loads and two barriers whatever E
 // is.  Workgroups land on the 8 XCDs round-robin; each XCD gets a contiguous run of the tiles that exist (the grid is an
-// upper bound, rounded up to a multiple of 8), so that neighbours share their operands in its L2.  Returns false
+// upper bound, rounded up to a multiple of 8), so that neighbours share their operands in its L2.  With bm = 0, lim > 0 cuts
+// experts of more than lim rows into split_pieces pieces of mult tiles each.  Returns false
 // (uniformly) if there is nothing to do.  Every thread of the workgroup must call it.
+__device__ __forceinline__ int split_pieces(int rows, int lim) { return rows > lim ? (rows - 1) / lim + 1 : 1; }
 struct tile_pick_lds {
     int wave_sum[16];
     int wave_bad[16];
@@ -169,7 +171,7 @@ struct tile_sums {
 };
 template <int THREADS>
 __device__ __forceinline__ bool tile_scan(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
-                                          int mult, tile_pick_lds& l, tile_sums<THREADS>& st) {
+                                          int mult, tile_pick_lds& l, tile_sums<THREADS>& st, int lim = 0) {
     constexpr int PER = tile_sums<THREADS>::PER;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto& o = st.o;
@@ -186,8 +188,13 @@ __device__ __forceinline__ bool tile_scan(const int32_t* __restrict__ offsets, i
         const int rows = o[x + 1] - o[x];
         bad |= rows < 0;
         cnt[x] = mult * (bm ? (rows > 0 ? (rows + bm - 1) / bm : 0) : (tid * PER + x < E ? 1 : 0));
-        n += cnt[x];
     }
+    if (lim > 0) {   // (uniform: the divisions stay out of the calls that cut nothing)
+#pragma unroll
+        for (int x = 0; x < PER; ++x) cnt[x] *= split_pieces(o[x + 1] - o[x], lim);
+    }
+#pragma unroll
+    for (int x = 0; x < PER; ++x) n += cnt[x];
     int incl = n;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {

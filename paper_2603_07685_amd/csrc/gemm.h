@@ -95,9 +95,9 @@ struct gg_args {
     uint8_t* out_qc;
     uint8_t* out_qc_e8;
     int* tile_counter;     // wgrad: device counter, zero at the start, for the dynamic tile order under skewed loads (see the kernel)
-    // wgrad, bf16: deterministic split of the contraction for experts far above the mean load (see the kernel)
-    int split_cap;         // how many expert-sized slices of fp32 partial tiles `partials` can hold (0: never split)
-    float* partials;       // [split_cap][tiles per expert][256 x 256] fp32
+    // wgrad, bf16: deterministic split of the contraction for experts far above the mean load (see the kernels)
+    int split_cap;         // how many expert-sized slices of fp32 partial results `partials` can hold (0: never split)
+    float* partials;       // [split_cap] slices: 256 x 256 kernel [tiles per expert][256 x 256], small tiles [N][K]
     int* split_info;       // [1 + 3 * GG_MAX_SPLIT_EXPERTS]: count, then (expert, pieces, first slice) for the reduce kernel
     float* dprob_part;     // eq. (2), dgrad SWIGLU_BWD: [Rcap, 2 ceil(K/256)] partial <dA, act(Z)> per row, two per column tile
     // Permutation fused into the operand fetch (Sec. 4.3.3; GATH variants): the gathered operand (P or Q) points to
@@ -116,6 +116,8 @@ struct gg_args {
 // Small-tile kernels for bf16 operands (gemm_tile.hip).  gt_tile: which of them serves a call (0: none, the 256 x 256
 // kernel of gemm.hip is the better one); gt_launch: run it.
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a);
+// Rows from which on a weight gradient on small tiles may split its contraction (set split_cap and partials)
+#define GT_SPLIT_ROWS 24576
 void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
 // the same for one-byte operands (gemm_tile8.hip); `quant`: the call also asks for quantised copies of its output
 int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg_args& a);

@@ -2260,7 +2260,11 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     a.p_scale = dc_scale;
     a.q_scale = a_scale;
     a.tile_counter = (int*)((char*)ctx->ws + MOE_WS_TILE_COUNTER);
+    const size_t ws_free = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;
+    a.partials = (float*)((char*)ctx->ws + MOE_WS_RESERVED);
+    auto slices = [&](size_t bytes) { return (int)(ws_free / bytes < GG_MAX_SPLIT ? ws_free / bytes : GG_MAX_SPLIT); };
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
+        if (!mx && !bw && Rcap > GT_SPLIT_ROWS) a.split_cap = slices((size_t)N * K * sizeof(float));
         if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
         else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
@@ -2269,10 +2273,8 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     moe_launch_fill_i32(a.tile_counter, 1, 0, (hipStream_t)stream);
     // split contraction (bf16 operands): as many slices of partial tiles as the workspace holds behind its reserved head
     const size_t slice_bytes = (size_t)ceil_div64(N, GG_BM) * ceil_div64(K, GG_BN) * GG_BM * GG_BN * sizeof(float);
-    const size_t ws_free = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;
     a.split_info = (int*)((char*)ctx->ws + MOE_WS_SPLIT_INFO);
-    a.partials = (float*)((char*)ctx->ws + MOE_WS_RESERVED);
-    a.split_cap = (!bw && GG_BF16_NW == 4) ? (int)(ws_free / slice_bytes < GG_MAX_SPLIT ? ws_free / slice_bytes : GG_MAX_SPLIT) : 0;
+    a.split_cap = (!bw && GG_BF16_NW == 4) ? slices(slice_bytes) : 0;
     if (gath == 2) {
         if (out_dt == MOE_F32) GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, true, 2);
         else GG_LAUNCH_G(GG_WGRAD, GG_EPI_STORE, false, 2);

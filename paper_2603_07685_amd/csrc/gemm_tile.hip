@@ -23,8 +23,21 @@
 // workgroup (decoding, 32 rows on each of 16 experts, 403 MB of fc1 weights: 92 us against 98, 4.4 TB/s).
 #include "gemm_tile.h"
 
-template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF>
+// Weight gradients of many rows: an expert of more than split_limit rows is cut into pieces of at most that many, each with its
+// own tiles, which leave their results as fp32 in a slice of the workspace; gt_add_kernel adds an expert's slices in order.
+// One workgroup would otherwise walk all its rows (0.54 us per 64; the 256 x 256 kernel splits too).  The limit is the
+// smallest with which the pieces of any load fit the slices: with R <= n lim, the m experts above lim have at most
+// n - 1 + m <= 2 n - 2 pieces.  Measured (us a call, 256 x 256 kernel, whole : pieces): T 16384, k 8, h 256, f 256, 32 experts, one
+// with half of the rows 317, 560 : 198; with 95 % 444, 1059 : 228; even 111, 47 : 49; T 8192, k 8, 64 experts, half 252, 283 : 105.
+__device__ __forceinline__ int split_limit(const int32_t* __restrict__ offsets, int E, int cap) {
+    if (cap < 2) return 0;
+    const int rows = offsets[E] - offsets[0], n = cap / 2 + 1;
+    return max((int)(((int64_t)rows + n * 64 - 1) / (n * 64)) * 64, 2048);   // (small results: not worth cutting)
+}
+
+template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF, bool SPLIT>
 __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
+    static_assert(!SPLIT || MODE == GG_WGRAD, "the weight gradient's contraction is the one whose length depends on the load");
     static_assert(GATH == 0 || GATH == 1 || (GATH == 2 && MODE == GG_WGRAD), "Q is gathered in the weight gradient only");
     constexpr bool P_CMAJ = MODE == GG_WGRAD, Q_CMAJ = MODE != GG_FWD;
     constexpr int P_BYTES = BM * 128, STAGE = P_BYTES + GT_BN * 128;
@@ -46,8 +59,33 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
     const int tiles_iw = (N + BM - 1) / BM;             // wgrad
 
     int e, u, row_lo, row_hi;
-    if (!tile_pick<256>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM,
-                        MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, e, u, row_lo, row_hi)) return;
+    const int lim = SPLIT ? split_limit(a.offsets, a.E, a.split_cap) : 0;
+    tile_sums<256> sums;
+    if (!tile_scan<256>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM,
+                        MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, sums, lim)) return;
+    __shared__ int slices_before;
+    if (SPLIT && tid == 0) slices_before = 0;
+    if (!tile_find(sums, (int)blockIdx.x, pick, e, u, row_lo, row_hi)) return;
+    int slice = -1;   // >= 0: a piece, its place among the partial results
+    if (SPLIT) {
+        const int pieces = __builtin_amdgcn_readfirstlane(split_pieces(row_hi - row_lo, lim));
+        if (pieces > 1) {
+            int n = 0;
+#pragma unroll
+            for (int x = 0; x < tile_sums<256>::PER; ++x) {
+                const int p = split_pieces(sums.o[x + 1] - sums.o[x], lim);
+                n += tid * tile_sums<256>::PER + x < e && p > 1 ? p : 0;
+            }
+            if (n) atomicAdd(&slices_before, n);
+            __syncthreads();
+            const int tpe = tiles_iw * tiles_j, piece = __builtin_amdgcn_readfirstlane(u / tpe);
+            const int len = ((row_hi - row_lo + pieces - 1) / pieces + 63) / 64 * 64;   // (whole stages; none is empty)
+            slice = __builtin_amdgcn_readfirstlane(slices_before) + piece;
+            u -= piece * tpe;
+            row_lo += piece * len;
+            row_hi = min(row_lo + len, row_hi);
+        }
+    }
     int ti, tj;
     {
         const int tiles_i = MODE == GG_WGRAD ? tiles_iw : (row_hi - row_lo + BM - 1) / BM;
@@ -232,14 +270,69 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
     wait_lgkm0();
     stage_barrier();
 
-    gt_output<MODE, EPI, OUT_F32, BM>(a, (float*)ring, e, i0, i_end, j0, tj, tiles_j, [&](int ps, float* stg) {
+    auto stage = [&](int ps, float* stg) {
         // a lane's accumulators of a block: one row (l16), columns 4 kq .. 4 kq + 3
 #pragma unroll
         for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 *(f32x4_t*)(stg + (wm * 32 + 16 * i2 + l16) * STG_PITCH + col_of(j) + 4 * kq) = acc[2 * ps + i2][j];
-    });
+    };
+    if (SPLIT && slice >= 0) {   // (a slice is laid out as one expert's fp32 result)
+        gg_args part = a;
+        part.out = a.partials;
+        part.accumulate = 0;
+        gt_output<MODE, EPI, SPLIT, BM>(part, (float*)ring, slice, i0, i_end, j0, tj, tiles_j, stage);
+        return;
+    }
+    gt_output<MODE, EPI, OUT_F32, BM>(a, (float*)ring, e, i0, i_end, j0, tj, tiles_j, stage);
+}
+
+// Second step of a weight gradient with pieces: every workgroup finds the split experts in the offsets (at most four) and goes
+// over its share of their results, piece 0 first.  Bound: HBM, a slice read per piece; without a split expert, one look.
+template <bool OUT_F32>
+__global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
+    __shared__ int at[8], rows_at[8], count;
+    const int lim = split_limit(a.offsets, a.E, a.split_cap);   // (> 0: launched with split_cap >= 2)
+    if (threadIdx.x == 0) count = 0;
+    bool bad = a.offsets[0] < 0 || a.offsets[a.E] > a.Rcap;
+    for (int e = threadIdx.x; e < a.E; e += 256) bad |= a.offsets[e + 1] < a.offsets[e];
+    if (__syncthreads_or(bad)) return;   // (as the first step did)
+    for (int e = threadIdx.x; e < a.E; e += 256) {
+        const int rows = a.offsets[e + 1] - a.offsets[e];
+        if (split_pieces(rows, lim) > 1) {
+            const int i = atomicAdd(&count, 1);
+            at[i] = e;
+            rows_at[i] = rows;
+        }
+    }
+    __syncthreads();
+    const int64_t n4 = (int64_t)a.N * a.K / 4;
+    for (int i = 0; i < count; ++i) {
+        int before = 0;
+        for (int j = 0; j < count; ++j) before += at[j] < at[i] ? split_pieces(rows_at[j], lim) : 0;
+        const int pieces = split_pieces(rows_at[i], lim);
+        const f32x4_t* const src = (const f32x4_t*)a.partials + before * n4;
+        for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < n4; x += (int64_t)gridDim.x * 256) {
+            f32x4_t v = src[x];
+            for (int p = 1; p < pieces; ++p) v += src[p * n4 + x];
+            if (OUT_F32) {
+                f32x4_t* const o = (f32x4_t*)a.out + at[i] * n4 + x;
+                if (a.accumulate) v += *o;
+                *o = v;
+            } else {
+                bf16_t* const o = (bf16_t*)a.out + (at[i] * n4 + x) * 4;
+                float t[4] = {v[0], v[1], v[2], v[3]};
+                if (a.accumulate) {
+                    float old[4];
+                    ld4_bf16(o, old);
+#pragma unroll
+                    for (int y = 0; y < 4; ++y) t[y] += old[y];
+                }
+                st4_bf16(o, t);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -258,6 +351,8 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
 //   T 4096 h 512 f 512 E 16 k 4     56 : 43      T 4096 h 2048 f 1024 E 8 k 2     122 : 113
 //   T 2048 h 2048 f 1024 E 8 k 2    65 : 74      T 1024 h 4096 f 1536 E 16 k 8    222 : 284  (fc2 dgrad of the former 72 : 36)
 //   T 8192 h 1024 f 1024 E 16 k 4  200 : 230     T 64 h 7168 f 2048 E 32 k 8      429 : 312  (fc2 274 : 168)
+// These are scattered loads.  One that fills whole 256-row tiles exactly is not told apart and can lose (T 4096 h 2048 f 1024
+// E 8 k 2, 1024 rows each, plain fc1 forward 60 : 67; any other load there 93 : 82).  Skewed weight gradients: split_limit.
 // Few rows per expert (on average at most 48): the third buffer (T 64 h 4096 f 14336 E 8 k 2: 464 : 330 against 363 with two
 // buffers and 359 with 128 x 128).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill the chip's two workgroups per
 // unit (T 256 h 128 f 256: fc2 dgrad 6.9 against 9.5; T 4096 h 512 f 512: 27 against 34).
@@ -281,11 +376,11 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     return r128 < 1 ? 1 : 2;
 }
 
-template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF>
+template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF, bool SPLIT = false>
 static void gt_go(hipStream_t s, const gg_args& a) {
     const int64_t cols = EPI == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(MODE == GG_FWD ? a.N : a.K, GT_BN);
-    const int64_t n = cols * (MODE == GG_WGRAD ? a.E * ceil_div64(a.N, BM) : ceil_div64(a.Rcap, BM) + a.E);
-    hipLaunchKernelGGL((gt_kernel<MODE, EPI, F32, GATH, BM, NBUF>), dim3((unsigned)(ceil_div64(n, 8) * 8)), dim3(256), 0, s, a);
+    const int64_t n = cols * (MODE == GG_WGRAD ? (a.E + (SPLIT ? a.split_cap : 0)) * ceil_div64(a.N, BM) : ceil_div64(a.Rcap, BM) + a.E);
+    hipLaunchKernelGGL((gt_kernel<MODE, EPI, F32, GATH, BM, NBUF, SPLIT>), dim3((unsigned)(ceil_div64(n, 8) * 8)), dim3(256), 0, s, a);
 }
 template <int MODE, int EPI, int GATH>
 static void gt_rows(hipStream_t s, int tile, const gg_args& a) {
@@ -293,16 +388,21 @@ static void gt_rows(hipStream_t s, int tile, const gg_args& a) {
     else if (tile == 2) gt_go<MODE, EPI, false, GATH, 128, 2>(s, a);
     else gt_go<MODE, EPI, false, GATH, 64, 3>(s, a);
 }
-template <bool F32>
+// (a kernel of its own for calls that may split: the others are 5 % faster at their smallest without the choice in them)
+template <bool F32, bool SPLIT>
 static void gt_wgrad(hipStream_t s, int gath, const gg_args& a) {
-    if (gath == 1) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 1, 128, 2>(s, a);
-    else if (gath == 2) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 2, 128, 2>(s, a);
-    else gt_go<GG_WGRAD, GG_EPI_STORE, F32, 0, 128, 2>(s, a);
+    if (gath == 1) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 1, 128, 2, SPLIT>(s, a);
+    else if (gath == 2) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 2, 128, 2, SPLIT>(s, a);
+    else gt_go<GG_WGRAD, GG_EPI_STORE, F32, 0, 128, 2, SPLIT>(s, a);
+    if (SPLIT) {
+        const int64_t blocks = ceil_div64((int64_t)a.N * a.K / 4, 256);
+        hipLaunchKernelGGL(gt_add_kernel<F32>, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, a);
+    }
 }
 void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     if (mode == GG_WGRAD) {
-        if (out_f32) gt_wgrad<true>(s, gath, a);
-        else gt_wgrad<false>(s, gath, a);
+        if (a.split_cap >= 2) out_f32 ? gt_wgrad<true, true>(s, gath, a) : gt_wgrad<false, true>(s, gath, a);
+        else out_f32 ? gt_wgrad<true, false>(s, gath, a) : gt_wgrad<false, false>(s, gath, a);
     } else if (mode == GG_FWD) {
         if (epi == GG_EPI_SWIGLU) gath ? gt_rows<GG_FWD, GG_EPI_SWIGLU, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_SWIGLU, 0>(s, tile, a);
         else gath ? gt_rows<GG_FWD, GG_EPI_STORE, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_STORE, 0>(s, tile, a);
