@@ -2336,7 +2336,7 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
     int64_t pieces = cu / tiles;
     if (pieces > h / 64 / GATE_MIN_STAGES) pieces = h / 64 / GATE_MIN_STAGES;
     if (pieces > (int64_t)(room / one)) pieces = (int64_t)(room / one);
-    if (pieces < 2) pieces = 1;
+    if (pieces < 2 || GG_BF16_NW != 4) pieces = 1;   // (the four-wave body's output step is the one that knows of pieces)
     a.split_cap = (int)pieces;
     if (pieces > 1) a.out = (char*)ctx->ws + MOE_WS_RESERVED;
     GG_LAUNCH(GG_FWD, GG_EPI_STORE, true, 0);
