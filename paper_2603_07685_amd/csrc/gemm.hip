@@ -2307,8 +2307,9 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
 // output (the router works on fp32 logits, Sec. 5.1).  One group of T rows through the forward kernel with the
 // fp32 store.  With E <= 256 there is one column tile, so T / 256 workgroups have a tile (a quarter of the chip at
 // T = 16384): the contraction is cut into as many pieces as fill the compute units, each a work item that leaves
-// an fp32 partial result in the context's workspace, and a second kernel adds the pieces in order.  A piece keeps at
-// least 8 stages (1.45 us each), less than which does not pay for the second launch and the partial results' way.
+// an fp32 partial result in the context's workspace, and a second kernel adds the pieces in order.  A piece has at
+// least 8 stages (1.45 us each; the last one what is left), less than which does not pay for the second launch and the
+// partial results' way.
 // T 16384, E 256, h 7168 (64 tiles, 112 stages): one piece 176 us + 5 for a launch that wrote the group's offsets; four
 // pieces 73 + 13 for the sum.  T 2048, E 64, h 4096: 75 + 5 : 21 + 4.  Bound now: HBM (X once, 235 MB, and the partial results
 // out and in, 134 MB) and the 28 stages of a piece (41 us at the rate operands reach a compute unit).
@@ -2336,6 +2337,10 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
     int64_t pieces = cu / tiles;
     if (pieces > h / 64 / GATE_MIN_STAGES) pieces = h / 64 / GATE_MIN_STAGES;
     if (pieces > (int64_t)(room / one)) pieces = (int64_t)(room / one);
+    if (pieces > 1) {   // (pieces of whole stages may need fewer: 81 stages in 10 pieces of 9 would leave the tenth empty)
+        const int64_t stages = h / 64, each = (stages + pieces - 1) / pieces;
+        pieces = (stages + each - 1) / each;
+    }
     if (pieces < 2 || GG_BF16_NW != 4) pieces = 1;   // (the four-wave body's output step is the one that knows of pieces)
     a.split_cap = (int)pieces;
     if (pieces > 1) a.out = (char*)ctx->ws + MOE_WS_RESERVED;

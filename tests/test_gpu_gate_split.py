@@ -16,7 +16,8 @@ def B():
 
 
 @pytest.mark.parametrize("T,E,h", [(1, 8, 64), (255, 16, 960), (256, 256, 1024), (257, 264, 1088), (700, 8, 4160),
-                                   (3000, 40, 2624), (20000, 512, 1152), (66000, 256, 1024)])
+                                   (3000, 40, 2624), (20000, 512, 1152), (66000, 256, 1024),
+                                   (300, 64, 5184), (300, 64, 5760), (520, 72, 6720)])   # (as many pieces as have stages)
 @pytest.mark.parametrize("room", [True, False])
 def test_gate_gemm(B, T, E, h, room):
     ctx = B.Context(T, 1, E, h, max(E, 8)) if room else B.Context(1, 1, 1, 0, 0)
