@@ -5,19 +5,21 @@ include/moe_hip.h.  Tensors are torch CUDA tensors used as device memory; the
 current torch stream is passed as the HIP stream.  Nothing here computes: if
 the library is missing the import of `lib()` raises, there is no fallback.
 The entry points of a step are called through csrc/pycall.cpp, which converts
-the arguments in native code; the others through ctypes.
+the arguments in native code; the others through ctypes, and all of them where
+that module, which is built against the installed torch, does not load.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 
 import torch
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("MOE_HIP_LIB") or os.path.join(_PKG, "libmoe_hip.so")
 _lib = None
-_native = None   # the module built from csrc/pycall.cpp; set by lib(), so before any Context exists
+_native = None   # the module built from csrc/pycall.cpp, or _Ctypes; set by lib(), so before any Context exists
 
 BF16, FP8_E4M3, F32, MXFP8_E4M3 = 0, 1, 2, 3
 SOFTMAX, SIGMOID = 0, 1
@@ -98,12 +100,37 @@ def lib() -> C.CDLL:
     return _lib
 
 
+class _Ctypes:
+    """The entry points with the arguments of the native module's functions, converted by ctypes."""
+
+    def __init__(self, L):
+        self._lib = L
+
+    def __getattr__(self, name):
+        f = getattr(self._lib, name)
+        kinds = f.argtypes[2:]
+
+        def call(ctx, *args):
+            if len(args) != len(kinds):
+                raise TypeError(f"{name}: {len(kinds) + 1} arguments expected, {len(args) + 1} given")
+            try:
+                return f(ctx, _stream(), *[_ptr(a) if t is _vp else a for t, a in zip(kinds, args)])
+            except C.ArgumentError as e:
+                raise TypeError(f"{name}: {e}") from e
+
+        setattr(self, name, call)
+        return call
+
+
 def _load_native(L):
     global _native
     try:
         from . import _pycall
     except ImportError as e:
-        raise MoeError(f"_pycall.so is not built or does not load ({e}): run `python -m paper_2603_07685_amd.build` first") from e
+        warnings.warn(f"_pycall.so is not built or does not load ({e}): calls go through ctypes, 8-9 us of host time each more; "
+                      "`python -m paper_2603_07685_amd.build` builds it", RuntimeWarning, stacklevel=3)
+        _native = _Ctypes(L)
+        return
     _pycall.init({name: C.cast(getattr(L, name), _vp).value for name in EXPORTS}, _ptr)
     _native = _pycall
 

@@ -34,6 +34,40 @@ def test_host_tensors_and_wrong_types_are_refused(B):
         B.moe_gate_gemm(_Ctx, [1, 2], None, 1, 8, 64, None)
 
 
+def test_the_c_library_suffices():
+    """Without the native module (built against one torch) the library loads all the same, with a warning, and a call's
+    arguments meet the same refusals."""
+    import subprocess
+    import sys
+    code = """
+import sys, warnings
+sys.modules['paper_2603_07685_amd._pycall'] = None      # (an import of it fails)
+import pytest, torch
+from paper_2603_07685_amd import binding as B
+with pytest.warns(RuntimeWarning, match='ctypes'):
+    L = B.lib()
+assert L.moe_workspace_bytes(256, 2, 8, 128, 256) > 0
+B._stream = lambda: 0
+class Ctx:
+    _addr = None
+    def check(st, what):
+        raise B.MoeError(what, st)
+t = torch.zeros(8, 64)
+with pytest.raises(AssertionError):
+    B.moe_gate_gemm(Ctx, t, None, 1, 8, 64, None)
+with pytest.raises(TypeError):
+    B.moe_gate_gemm(Ctx, None, None, 1.0, 8, 64, None)
+with pytest.raises(TypeError):
+    B._native.moe_gate_gemm(None, None, None, 1, 8, 64)
+for name in B.EXPORTS:
+    if hasattr(B, name) and name not in ('moe_workspace_bytes', 'moe_permute_static'):
+        assert callable(getattr(B._native, name)), name
+with pytest.raises(B.MoeError):
+    B.moe_gate_gemm(Ctx, None, None, 1, 8, 64, None)
+"""
+    subprocess.run([sys.executable, "-c", code], check=True, timeout=300)
+
+
 class _Sub(torch.Tensor):
     pass
 
@@ -70,3 +104,21 @@ def test_pointers_stream_and_status(B):
     ctx.close()
     with pytest.raises(B.MoeError):
         B.moe_gate_gemm(ctx, X, W, T, E, h, out)
+
+
+@pytest.mark.gpu
+def test_through_ctypes(B, monkeypatch):
+    """A layer's step with ctypes conversions gives the bits of the native module's."""
+    from paper_2603_07685_amd import layer, workloads as wl
+    cfg = wl.CONFIGS["C1"]
+    hin = layer.host_inputs(cfg, shared_f=64)
+    seen = []
+    for native in (B._native, B._Ctypes(B.lib())):
+        monkeypatch.setattr(B, "_native", native)
+        st = layer.LayerState(cfg, hin, shared_f=64)
+        st.step()
+        torch.cuda.synchronize()
+        assert st.ctx.poll_error() == 0
+        seen.append([t.clone() for t in (st.Y, st.dX, st.dW1, st.dW2, st.dprob)])
+    for a, b in zip(*seen):
+        assert torch.equal(a, b)
