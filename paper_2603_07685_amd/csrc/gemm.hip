@@ -2353,3 +2353,20 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<gate>");
     return MOE_OK;
 }
+
+// Which kernel serves a grouped GEMM of these sizes on a GPU of num_cu compute units: 0 the 256 x 256 kernel of this file, 1 .. 3
+// as gt_tile and gq_tile say; fp32: 64 or 128.  Host only, and no part of the library's interface: the tests choose their
+// sizes with it.  mode, epi: GG_*; quant: the call asks for quantised copies.
+extern "C" int gg_kernel_choice(int num_cu, int mode, int epi, int dt, int quant, int E, int N, int K, long long Rcap) {
+    moe_ctx ctx;
+    memset(&ctx, 0, sizeof(ctx));
+    ctx.num_cu = num_cu;
+    gg_args a;
+    memset(&a, 0, sizeof(a));
+    a.E = E;
+    a.N = N;
+    a.K = K;
+    a.Rcap = Rcap;
+    if (dt == MOE_F32) return moe_gg_f32_tile(num_cu, mode == GG_WGRAD, E, N, mode == GG_FWD ? N : K, Rcap);
+    return dt == MOE_BF16 ? gt_tile(&ctx, mode, epi, a) : gq_tile(&ctx, mode, epi, dt == MOE_MXFP8_E4M3, quant != 0, a);
+}

@@ -11,7 +11,7 @@
 // per stage: a stage is BT/32 squared blocks x 4 MFMAs of 32 cycles per wave against (BT = 128) 16 KB of operands, so
 // registers hold the next stage's operands while two LDS buffers alternate, one barrier per stage, and the loads have a
 // whole stage (2048 cycles at BT = 128) to arrive.  BT = 64 trades operand reuse for four times as many workgroups where
-// the larger tile would leave compute units idle (gf_tile below).
+// the larger tile would leave compute units idle (moe_gg_f32_tile below).
 // LDS: an operand whose contraction index is contiguous in memory is kept [row][16] with a pitch of 20 floats, one
 // 16-byte read giving a lane contraction elements 4 g .. 4 g + 3 (g = lane / 16; MFMA step j takes element j of every
 // lane, the order inside a stage is free); the other kind is kept [16][column] with a pitch of BT + 4 floats, read
@@ -237,17 +237,17 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
 // T 256, h 128, f 256: 106 us against 178; T 2048, h 1024, f 512: 537 against 665; T 4096, h 1024, f 512: 906 against 1042;
 // T 8192, h 1024, f 1024 (8 tiles per unit in fc1): 3.04 ms against 3.05; T 8192, h 2048, f 2048: 11.4 against 10.7;
 // T 8192, h 4096, f 2048: 22.6 against 20.7 ms (119 TFLOP/s).
-static int gf_tile(const moe_ctx* ctx, int mode, const gf_args& a, int out_cols) {
+int moe_gg_f32_tile(int num_cu, bool wgrad, int E, int N, int out_cols, int64_t Rcap) {
     const int64_t cols = ceil_div64(out_cols, 128);
-    const int64_t tiles = mode == GF_WGRAD ? (int64_t)a.E * ceil_div64(a.N, 128) * cols : ceil_div64(a.Rcap, 128) * cols;
-    return tiles >= 8 * (int64_t)(ctx->num_cu > 0 ? ctx->num_cu : 256) ? 128 : 64;
+    const int64_t tiles = wgrad ? (int64_t)E * ceil_div64(N, 128) * cols : ceil_div64(Rcap, 128) * cols;
+    return tiles >= 8 * (int64_t)(num_cu > 0 ? num_cu : 256) ? 128 : 64;
 }
 
 template <int MODE, int EPI>
 static moe_status gf_launch(moe_ctx* ctx, hipStream_t s, const char* who, const gf_args& a) {
     if (a.E > F32_MAX_E) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: E > %d", who, F32_MAX_E);
     const int out_cols = EPI == GF_SWIGLU ? a.N : (MODE == GF_FWD ? a.N : a.K);
-    const int bt = gf_tile(ctx, MODE, a, out_cols);
+    const int bt = moe_gg_f32_tile(ctx->num_cu, MODE == GF_WGRAD, a.E, a.N, out_cols, a.Rcap);
     const int64_t tiles_j = EPI == GF_SWIGLU ? ceil_div64(a.N / 2, bt / 2) : ceil_div64(out_cols, bt);
     // (every expert may end in a partly filled row tile)
     const int64_t grid = ceil_div64(tiles_j * (MODE == GF_WGRAD ? a.E * ceil_div64(a.N, bt) : ceil_div64(a.Rcap, bt) + a.E), 8) * 8;

@@ -243,8 +243,8 @@ def test_full_size_sampled(oracle, name, variant):
 def test_full_size_gathered_operands_bit_identical(name, variant, eq2):
     """The permute's row move fused into the GEMMs (no Xp; with eq. (2) no dO): at the benchmark sizes, in the launch
     configuration bench.py times, every tensor of the step equals, bit for bit, that of the path with the stand-alone
-    mover, which test_full_size_sampled holds against the oracle.  (hot / Zipf loads: the weight gradients split
-    their contraction and hand tiles out dynamically.)"""
+    mover, which test_full_size_sampled holds against the oracle.  (hot / Zipf loads: the weight gradients hand
+    tiles out dynamically.)"""
     from paper_2603_07685_amd import layer as L
     from paper_2603_07685_amd import workloads as wl
     cfg = wl.CONFIGS[name]

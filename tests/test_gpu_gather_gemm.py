@@ -130,7 +130,7 @@ def test_dgrad_gather(B, ctx, oracle, counts, align, T, k, N, f):
     assert_close(host_f64(dA1[:R]), dAref, "dA")
 
 
-WG_MAPS = MAPS + [([6000, 300, 257, 0, 700, 64, 1, 130], 1, 2000, 4)]     # the last one splits its contraction
+WG_MAPS = MAPS + [([6000, 300, 257, 0, 700, 64, 1, 130], 1, 2000, 4)]     # the last one: one expert far above the others
 
 
 @pytest.mark.parametrize("counts,align,T,k", WG_MAPS)
@@ -138,7 +138,7 @@ WG_MAPS = MAPS + [([6000, 300, 257, 0, 700, 64, 1, 130], 1, 2000, 4)]     # the 
 @pytest.mark.parametrize("out_f32", [False, True])
 def test_wgrad_gather(B, ctx, oracle, counts, align, T, k, N, K, out_f32):
     """Either operand of the weight gradient through the map (A: the fc1 gradient reads X; dC: under eq. (2) the fc2
-    gradient reads dY), with accumulation, on balanced and on skewed loads (split contraction)."""
+    gradient reads dY), with accumulation, on balanced and on skewed loads."""
     from gpu_util import dev, dev_bf16, host_f64, assert_close, F32_REG
     from paper_2603_07685_amd import workloads as wl
     E = len(counts)

@@ -266,10 +266,10 @@ def test_grouped_gemm_wgrad(B, ctx, oracle, counts, N, K, out_f32):
 @pytest.mark.parametrize("counts", [[6000, 300, 257, 0, 700, 64, 1, 130], [9000, 5000, 100, 100, 100, 100, 100, 100, 100, 100]])
 @pytest.mark.parametrize("out_f32", [False, True])
 def test_grouped_gemm_wgrad_split_contraction(B, oracle, counts, out_f32):
-    """Skewed loads: the contraction of experts far above the mean is split into pieces whose fp32 partial tiles are
-    added in a fixed order by a second kernel.  Against the oracle (every element, every row), bit-identical from run
-    to run, accumulate on top, and the same call on a context whose workspace has no room for partial tiles (no
-    split) must agree with the oracle as well."""
+    """Skewed loads at sizes that the small tiles serve whole (they split from 24576 rows on; contractions that are split:
+    test_gpu_wgrad_split.py).  Against the oracle (every element, every row), bit-identical from run to run, accumulate on
+    top, and the same call on a context whose workspace has no room for partial results must agree with the oracle as
+    well."""
     from gpu_util import dev, dev_bf16, host_f64, assert_close, F32_REG
     from paper_2603_07685_amd import workloads as wl
     E = len(counts)

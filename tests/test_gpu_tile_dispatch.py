@@ -1,6 +1,7 @@
 """GPU parity of the bf16 grouped GEMMs on either side of the choice between the small-tile kernels and the 256 x 256 one:
-few rows per expert (64 x 128 tiles, three stage buffers), few tiles (64 x 128), more (128 x 128), many (256 x 256, with a
-split contraction under a skewed load).  Row counts around the tile edges, column counts off the tile grid, one-row and
+few rows per expert (64 x 128 tiles, three stage buffers), few tiles (64 x 128; the weight gradients 128 x 128), many (256 x 256, with a
+split contraction under a skewed load).  (Which kernel a size selects is asked, and every kernel reached, in test_gpu_gemm_variants.py;
+ragged split contractions are in test_gpu_wgrad_split.py.)  Row counts around the tile edges, column counts off the tile grid, one-row and
 empty experts, the row map, routing weights.  Every element against float64, within one bf16 rounding of the result plus
 the error bound of an fp32 sum in any order, (n + 2) 2^-24 sum |a||b|."""
 import numpy as np
