@@ -5,6 +5,9 @@
     python -m paper_2603_07685_amd.profile_summary mfma    DIR BENCH_JSON        SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES GRBM_GUI_ACTIVE pass
     python -m paper_2603_07685_amd.profile_summary moves   TRACE_DIR FETCH_DIR WRITE_DIR BENCH_JSON   data-movement kernels
 
+    python -m paper_2603_07685_amd.profile_summary kernels TRACE_DIR PMC_DIR PASSES   every kernel of PASSES equal passes of any program;
+                                       PMC_DIR: SQ_VALU_MFMA_BUSY_CYCLES SQ_BUSY_CU_CYCLES SQ_LDS_IDX_ACTIVE SQ_LDS_BANK_CONFLICT
+
 DIR is the -d directory of a `rocprofv3 ... --output-format csv -- python3 bench.py ...` run; BENCH_JSON the JSON line
 bench.py printed in that run (its "kernels" keys, in call order, label the call sites).  Only parsing and arithmetic on
 the profiler's numbers happen here; nothing is measured and nothing of the layer is computed.
@@ -20,8 +23,8 @@ import sys
 from collections import OrderedDict
 
 GIB = 1 << 30
-GEMMS = ("gg_kernel", "gq_kernel", "gt_kernel")
-LEGEND = ("gg_kernel<MODE,EPI,F32,F8,NW>, gq_kernel<MODE,EPI,F32,F8,BM,BN>: MODE 0 fwd / 1 dgrad / 2 wgrad; EPI 0 store / 1 SwiGLU / 2 SwiGLU-bwd; "
+GEMMS = ("gg_kernel", "gq_kernel", "gt_kernel", "gf_kernel")
+LEGEND = ("gg_kernel<MODE,EPI,F32,F8,NW,GATH>, gq_kernel<MODE,EPI,F32,F8,BM,BN>, gt_kernel<MODE,EPI,F32,GATH,BM,NBUF,SPLIT> (bf16), gf_kernel<MODE,EPI,BT,VEC> (fp32): MODE 0 fwd / 1 dgrad / 2 wgrad; EPI 0 store / 1 SwiGLU / 2 SwiGLU-bwd; "
           "F8 0 bf16 / 1 blockwise fp8 / 2 MXFP8; NW waves per workgroup")
 
 
@@ -211,6 +214,30 @@ def moves(td: str, fd: str, wd: str, bench_path: str):
         print(f"{lab:20s} {name:30s} {avg:8.1f} {alg_gb:8.3f} {m:8.3f} {alg_gb / avg * 1e6:9.0f} {alg_gb / avg * 1e6 / 80:8.1f}% {m / avg * 1e6:10.0f}")
 
 
+def kernels(td: str, pd: str, passes: str):
+    n = int(passes)
+    times, counts = OrderedDict(), {}
+    for r in sorted(_csv(td, "kernel_trace.csv"), key=lambda r: int(r["Start_Timestamp"])):
+        times.setdefault(_short(r["Kernel_Name"]), []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3)
+    for r in _csv(pd, "counter_collection.csv"):
+        counts.setdefault(_short(r["Kernel_Name"]), {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
+    print("# " + LEGEND)
+    print("# us: average of a launch;  of a CU's busy cycles: matrix pipes busy (SQ_VALU_MFMA_BUSY_CYCLES / 4 SQ_BUSY_CU_CYCLES), LDS instructions")
+    print("# (SQ_LDS_IDX_ACTIVE) and, of those LDS cycles, bank conflicts (SQ_LDS_BANK_CONFLICT)")
+    print(f"  {'kernel':58s} {'per pass':>8s} {'us':>9s} {'matrix':>7s} {'LDS':>6s} {'conflicts':>9s}")
+    total = 0.0
+    for name, t in times.items():
+        if len(t) < n or len(t) % n:       # (what prepares the inputs)
+            continue
+        total += sum(t) / n
+        c = {k: sum(v) for k, v in counts.get(name, {}).items()}
+        busy, lds = c.get("SQ_BUSY_CU_CYCLES", 0.0), c.get("SQ_LDS_IDX_ACTIVE", 0.0)
+        pct = lambda a, b: f"{100 * a / b:5.1f}%" if b else "    - "
+        print(f"  {name:58s} {len(t) // n:8d} {sum(t) / len(t):9.1f} {pct(c.get('SQ_VALU_MFMA_BUSY_CYCLES', 0.0), 4 * busy):>7s} "
+              f"{pct(lds, busy):>6s} {pct(c.get('SQ_LDS_BANK_CONFLICT', 0.0), lds):>9s}")
+    print(f"  sum of the kernels of a pass: {total:.1f} us")
+
+
 if __name__ == "__main__":
     cmd, args = sys.argv[1], sys.argv[2:]
-    {"trace": trace, "traffic": traffic, "mfma": mfma, "moves": moves}[cmd](*args)
+    {"trace": trace, "traffic": traffic, "mfma": mfma, "moves": moves, "kernels": kernels}[cmd](*args)
