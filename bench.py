@@ -77,7 +77,7 @@ def parse():
     ap.add_argument("--bf16-wgrad", action="store_true",
                     help="blockwise fp8 workloads: weight gradients from the bf16 tensors instead of the 128x1 E4M3 copies")
     ap.add_argument("--no-epilogue-quant", action="store_true",
-                    help="one-byte recipes: quantise A and dZ with stand-alone quantiser launches instead of in the GEMM epilogues")
+                    help="one-byte recipes: quantise A and dZ by stand-alone quantiser calls instead of with the GEMM calls")
     ap.add_argument("--gather", action="store_true",
                     help="bf16 workloads: no permuted copy of the tokens (with --eq2: nor of dY); the GEMMs that would read it "
                          "fetch the rows of X / dY through the row map")

@@ -273,9 +273,10 @@ moe_status moe_grouped_gemm_dgrad(moe_ctx* ctx, void* stream, const void* dC, co
  *        `offsets`; an expert with no rows gets dB_e = 0 (accumulate = 0) or is
  *        left as it is (accumulate != 0: dB += ...).  out_dt: MOE_BF16 or MOE_F32.
  *        Under a skewed load (largest expert above twice the mean; decided on the device from
- *        `offsets`) the tiles are handed out through a counter in the context's reserved workspace
- *        and, for bf16 operands, the contraction of every expert above twice the mean is split into
- *        up to 8 pieces whose fp32 partial tiles go to the workspace and are added in piece order by
+ *        `offsets`) the tiles of large calls are handed out through a counter in the context's reserved
+ *        workspace, which the call clears, and, for bf16 operands, the contraction of experts far above the
+ *        others (so far that handing out whole tiles does not balance them) is split, into 8 pieces in all at
+ *        most, whose fp32 partial results go to the workspace and are added in piece order by
  *        a second kernel of the same call.  Which workgroup computes what varies from run to run,
  *        what is added to what, and in which order, does not: results are bit-identical run to
  *        run.  wgrad calls on one context must not overlap in time.

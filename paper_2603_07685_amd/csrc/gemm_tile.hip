@@ -5,7 +5,7 @@
 // Same operation, operand layouts and LDS swizzles as there: OUT[i,j] = sum_c P[i,c] * Q[j,c], the contraction in stages
 // of 64 elements (128 bytes of a row: whole cache lines), row-major operands read with ds_read_b128, contraction-major
 // ones with the transposing ds_read_b64_tr_b16.  The contraction order inside a result is that kernel's too, so the two
-// give the same bits.
+// give the same bits (dprob's partial sums, which group other columns, aside).
 //
 // A 256-thread workgroup computes one BM x 128 tile (BM = 64 or 128), four waves as 2 x 2, wave tile BM/2 x 64 in 16 x 16
 // blocks; operands come by global -> LDS DMA into a ring of NBUF stage buffers, NBUF - 1 stages ahead of their use, awaited
@@ -14,7 +14,7 @@
 //
 // Bound: the fixed cost around a short contraction (finding the tile, the first operands' latency, the output: about 5 us)
 // and the rate at which a compute unit's L1 takes lines from the L2 (35-45 bytes per ns here, in the 256 x 256 kernel too;
-// the matrix pipes are 34 % busy, the LDS 17 %).  What helped is waves: NBUF = 2 keeps two (BM = 128) or three (64)
+// the matrix pipes are 13-36 % busy over the calls of T 2048, h 1024, f 512 and T 1999, h 2880, f 1472, the LDS 12-29 %).  What helped is waves: NBUF = 2 keeps two (BM = 128) or three (64)
 // workgroups on a compute unit, which cover each other's waits; with a ring of four stages and one workgroup, the same
 // bytes ahead, a call takes 1.25-1.5 times as long (fc1 forward, T 2048, h 1024, f 512, 8 experts, top-2: 24 us against
 // 33, BM = 128).  A persistent form, whose operand stream runs on across tiles, was no faster (27 us) and its static share

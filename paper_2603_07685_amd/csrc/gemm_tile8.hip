@@ -4,7 +4,7 @@
 //
 // A workgroup computes one BM x BN tile with its waves as 2 x 2, wave tile BM/2 x BN/2 in 32 x 32 blocks of
 // v_mfma_scale_f32_32x32x64_f8f6f4: fragments, contraction order and the software rescaling of the blockwise
-// recipe are those of gemm.hip's kernel, so the two give the same bits.  A stage is 128 contraction elements (128 bytes of a
+// recipe are those of gemm.hip's kernel, so all of them give the same bits.  A stage is 128 contraction elements (128 bytes of a
 // row), two MFMA steps of 64; operands come by DMA into two stage buffers, the scales of a stage (a dword per row and column)
 // into a ring of four, because the blockwise weight gradient needs the previous stage's beside the current.
 // The quantising epilogues are not built here: their 1 x 128 blocks span two small tiles; the caller runs the quantiser on the
@@ -21,13 +21,14 @@
 // the first step), and the refill is spread over the rest of the stage: an even flow is what matters (all 18 DMA instructions
 // of a wave in the second step: 5-7 % slower, bunched in its first half: 9 % slower; where exactly they lie, below 1 %).  The next
 // tile's first stage is under way during the output phase, which is staged through the other buffer.
-// Against eight waves in two groups that take turns reading and multiplying (us, old : this), T 16384, h 7168, f 2048, 32
-// experts, top-8: fc1 + SwiGLU 4233 with quantised copies : 3699 + 240 for the quantiser, fc2 1991 : 1864, fc2 data gradient
-// + SwiGLU backward 2625 : 2106 + 480, fc1 data gradient 3614 : 3437; the shared expert 526 : 421 + 30, 247 : 224, 331 : 273 + 50,
-// 443 : 403; weight gradients 1840 : 1639, 3450 : 3127, the shared expert's 229 : 206, 429 : 400.  T 8192, h 2048, f 1024, 16
-// experts, rank^-1.2: 193 : 164, 220 : 191.  Without the order of cost and the draw the routed weight gradients took 1869 and
-// 3740.  Bound now: 1.75 us per stage and tile, the matrix pipe busy 53-70 % of the time at the 1.7-1.9 GHz the card holds
-// under this load, operands at 37 bytes/ns and compute unit.
+// Against eight waves in two groups that take turns reading and multiplying, with the copies in their output phase (us, old :
+// this, profiled steps), T 16384, h 7168, f 2048, 32 experts, top-8: fc1 + SwiGLU with quantised copies 4153 : 3733 + 207 for the
+// quantiser, fc2 2006 : 1909, fc2 data gradient + SwiGLU backward with copies 2665 : 2180 + 443, fc1 data gradient 3595 : 3452; the
+// shared expert 525 : 426 + 34, 247 : 224, 331 : 270 + 62, 433 : 397; weight gradients 1787 : 1611, 3279 : 3063, the shared
+// expert's 226 : 203, 427 : 390.  T 8192, h 2048, f 1024, 16 experts, rank^-1.2: 193 : 164, 220 : 191.  Without the order of cost
+// and the draw the routed weight gradients took 1869 and 3740.  Bound now: 1.75 us per stage and tile; the matrix pipe is busy
+// 46-66 % of the time in forward and data-gradient calls and 65-83 % in weight gradients, at the 1.75-2.0 GHz the card holds
+// under this load; operands at 37 bytes/ns and compute unit.
 #include "gemm_tile.h"
 
 #include <type_traits>

@@ -3,7 +3,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
-// moe_permute: one wave ranks PERMUTE_CHUNK consecutive (token, slot) pairs; the
+// moe_permute: a workgroup ranks PERMUTE_CHUNK consecutive (token, slot) pairs; the
 // workspace holds one per-expert histogram per chunk (int32 [chunks, E]).
 #define PERMUTE_CHUNK 1024
 

@@ -506,7 +506,7 @@ static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int
     const int nchunks = (int)moe_permute_chunks(pairs), nbits = bits_for(E);
     // One workgroup while its serial share is cheaper than three launches, kernel times alone: E 32, k 4, T 256: 4.5 us
     // against 7.5; T 1024: 6.5 against 9.2; T 2048 (the most it takes): 9.2 against 9.3, and two launches fewer.  Up to 512
-    // experts (64 KB of LDS counters).
+    // experts (36 KB of LDS counters).
     if (pairs <= PERMUTE_ONE_PAIRS && E <= 512 && Rcap - pairs <= PERMUTE_ONE_FREE) {
         hipLaunchKernelGGL(permute_one_kernel, dim3(1), dim3(1024), (size_t)(18 * E + 2) * sizeof(int32_t), s, idx, (int)pairs, E,
                            nbits, align, Rcap, row_of, src_of, offsets, counts);
