@@ -271,6 +271,10 @@ moe_status moe_gg_f32_dgrad(moe_ctx* ctx, hipStream_t s, const void* dC, const v
 moe_status moe_gg_f32_wgrad(moe_ctx* ctx, hipStream_t s, const void* A, const void* dC, const int32_t* offsets, int E, int N,
                             int K, int64_t Rcap, int accumulate, void* dB);
 
+// gate GEMM of small calls (gate.hip): the best of its tiles with an estimate of its time, and the launch
+int moe_gate_tile(int num_cu, int T, int E, int h, double* us);
+void moe_gate_launch(hipStream_t s, int tile, const void* X, const void* W, int T, int E, int h, float* out);
+
 // message buffer (512 bytes, one per host thread) of the calls that take no context; moe_last_error(NULL) returns it
 char* moe_ctxless_error();
 

@@ -2342,6 +2342,17 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
         pieces = (stages + each - 1) / each;
     }
     if (pieces < 2 || GG_BF16_NW != 4) pieces = 1;   // (the four-wave body's output step is the one that knows of pieces)
+    // Which kernel: this one's time from its stages, the launches and the bytes of X and of the partial results (16384, 256, 7168:
+    // 86 measured, 79 by this; 4096, 256, 7168: 39.5, 37; 2048, 64, 4096: 25, 27), the other's from its tiles
+    double us = 0;
+    const int tile = moe_gate_tile((int)cu, T, E, h, &us);
+    const double bytes = 2.0 * T * h + (pieces > 1 ? 8.0 * pieces * T * E : 0.0);
+    const double rounds = __builtin_ceil((double)tiles * pieces / cu);
+    if (tile >= 0 && us < 14 + rounds * 1.45 * (double)ceil_div64(h / 64, pieces) + bytes / 15e6) {
+        moe_gate_launch((hipStream_t)stream, tile, X, Wr, T, E, h, logits);
+        MOE_LAUNCH_CHECK(ctx, "gate_kernel");
+        return MOE_OK;
+    }
     a.split_cap = (int)pieces;
     if (pieces > 1) a.out = (char*)ctx->ws + MOE_WS_RESERVED;
     GG_LAUNCH(GG_FWD, GG_EPI_STORE, true, 0);
