@@ -36,15 +36,15 @@ __device__ __forceinline__ int split_limit(const int32_t* __restrict__ offsets, 
 }
 
 template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF, bool SPLIT>
-__global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
+__global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
     static_assert(!SPLIT || MODE == GG_WGRAD, "the weight gradient's contraction is the one whose length depends on the load");
     static_assert(GATH == 0 || GATH == 1 || (GATH == 2 && MODE == GG_WGRAD), "Q is gathered in the weight gradient only");
     constexpr bool P_CMAJ = MODE == GG_WGRAD, Q_CMAJ = MODE != GG_FWD;
     constexpr int P_BYTES = BM * 128, STAGE = P_BYTES + GT_BN * 128;
     constexpr int PC = BM / 32, QC = 4;                 // 1 KB DMA chunks per wave, operand and stage
     constexpr int NI = BM / 32;                         // 16-row blocks per wave
-    static_assert(NBUF * STAGE >= 64 * STG_PITCH * 4, "the output phase stages 64 rows in the ring");
-    __shared__ __attribute__((aligned(1024))) char ring[NBUF * STAGE];
+    constexpr int STAGED = 64 * STG_PITCH * 4;          // (the output phase stages 64 rows in the ring)
+    __shared__ __attribute__((aligned(1024))) char ring[NBUF * STAGE > STAGED ? NBUF * STAGE : STAGED];
     __shared__ tile_pick_lds pick;
     // weight gradient with a gathered operand: byte offsets of the rows of two blocks of 16 stages (see rows_in)
     constexpr bool G_CM = GATH != 0 && MODE == GG_WGRAD;
@@ -61,11 +61,29 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
     int e, u, row_lo, row_hi;
     const int lim = SPLIT ? split_limit(a.offsets, a.E, a.split_cap) : 0;
     tile_sums<256> sums;
-    if (!tile_scan<256>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM,
-                        MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, sums, lim)) return;
     __shared__ int slices_before;
-    if (SPLIT && tid == 0) slices_before = 0;
-    if (!tile_find(sums, (int)blockIdx.x, pick, e, u, row_lo, row_hi)) return;
+    // A weight gradient without pieces has the same number of tiles for every expert: its tile is found without a sum over the
+    // experts.  The check of all offsets goes on while the first operands are on their way (from rows made safe by
+    // clamping), and is asked for its answer at the first barrier.
+    constexpr bool EVEN = MODE == GG_WGRAD && !SPLIT;
+    bool bad = false;
+    if (EVEN) {
+        const int tpe = tiles_iw * tiles_j, total = a.E * tpe, run = (total + 7) >> 3, at = (int)blockIdx.x >> 3;
+        const int unit = ((int)blockIdx.x & 7) * run + at;
+        if (at >= run || unit >= total) return;
+        e = unit / tpe;
+        u = unit - e * tpe;
+        row_lo = min(max(__builtin_amdgcn_readfirstlane(a.offsets[e]), 0), (int)a.Rcap);
+        row_hi = min(max(__builtin_amdgcn_readfirstlane(a.offsets[e + 1]), row_lo), (int)a.Rcap);
+        for (int x = tid; x < a.E; x += 256) bad |= a.offsets[x + 1] < a.offsets[x];
+        bad |= a.offsets[0] < 0 || a.offsets[a.E] > a.Rcap;
+        pick.wave_bad[wave] = __builtin_amdgcn_ballot_w64(bad) != 0;
+    } else {
+        if (!tile_scan<256>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM,
+                            MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, sums, lim)) return;
+        if (SPLIT && tid == 0) slices_before = 0;
+        if (!tile_find(sums, (int)blockIdx.x, pick, e, u, row_lo, row_hi)) return;
+    }
     int slice = -1;   // >= 0: a piece, its place among the partial results
     if (SPLIT) {
         const int pieces = __builtin_amdgcn_readfirstlane(split_pieces(row_hi - row_lo, lim));
@@ -236,35 +254,65 @@ __global__ __launch_bounds__(256, NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_ke
             }
     };
     wait_vm<(NBUF - 1) * (PC + QC)>();
+    wait_lgkm0();
     stage_barrier();
+    if (EVEN && (pick.wave_bad[0] | pick.wave_bad[1] | pick.wave_bad[2] | pick.wave_bad[3])) {
+        wait_vm0();                                         // (nothing may land in this LDS once it is someone else's)
+        if (blockIdx.x == 0 && tid == 0) atomicExch(a.dev_err, 1);
+        return;
+    }
+    if constexpr (NBUF == 1) {
+        // One buffer, for contractions of a stage or two: what counts is a third workgroup per compute unit.  Both steps'
+        // fragments leave the buffer, then the next stage's transfers run beside the MFMAs.
+        for (int s = 0; s < KT; ++s) {
+            if (s) {
+                wait_vm0();
+                stage_barrier();
+            }
 #pragma unroll
-    for (int r = 0; r < NR; ++r) read_one(0, ring, 0, r);
-    int buf = 0;
-    for (int s = 0; s < KT; ++s) {
-        const char* const t0 = ring + buf * STAGE;
-        const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
-        const char* const t1 = ring + nbuf * STAGE;
-        step(0, [&](int m) {
+            for (int r = 0; r < 2 * NR; ++r) read_one(r / NR, ring, r / NR, r % NR);
+            if (s + 1 < KT) {
+                wait_lgkm0();
+                stage_barrier();
+                describe(s + 1);
+                g_rows(s + 1);
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (r * (NM - 2) / NR == m) read_one(1, t0, 1, r);
-            if (m == NM - 2) describe(s + NBUF);
-            if (m == NM - 1) g_rows(s + NBUF);
-        });
-        wait_vm<(NBUF - 2) * (PC + QC)>();
-        wait_lgkm0();
-        stage_barrier();
-        step(1, [&](int m) {
+                for (int x = 0; x < PC + QC; ++x) issue_one(lds0, x);
+                if (G_CM && ((s + 1) & 15) == 8) rows_in(((s + 1) >> 4) + 1);
+            }
+            step(0, [](int) {});
+            step(1, [](int) {});
+        }
+    } else {
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (r * (NM - 2) / NR == m) read_one(0, t1, 0, r);
+        for (int r = 0; r < NR; ++r) read_one(0, ring, 0, r);
+        int buf = 0;
+        for (int s = 0; s < KT; ++s) {
+            const char* const t0 = ring + buf * STAGE;
+            const int nbuf = buf + 1 == NBUF ? 0 : buf + 1;
+            const char* const t1 = ring + nbuf * STAGE;
+            step(0, [&](int m) {
 #pragma unroll
-            for (int x = 0; x < PC + QC; ++x)
-                if (x * NM / (PC + QC) == m) issue_one(lds0 + buf * STAGE, x);
-        });
-        // (the half written here was last read 8 stages ago, and is read from 8 stages on)
-        if (G_CM && ((s + NBUF) & 15) == 8 && s + NBUF < KT) rows_in(((s + NBUF) >> 4) + 1);
-        buf = nbuf;
+                for (int r = 0; r < NR; ++r)
+                    if (r * (NM - 2) / NR == m) read_one(1, t0, 1, r);
+                if (m == NM - 2) describe(s + NBUF);
+                if (m == NM - 1) g_rows(s + NBUF);
+            });
+            wait_vm<(NBUF - 2) * (PC + QC)>();
+            wait_lgkm0();
+            stage_barrier();
+            step(1, [&](int m) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (r * (NM - 2) / NR == m) read_one(0, t1, 0, r);
+#pragma unroll
+                for (int x = 0; x < PC + QC; ++x)
+                    if (x * NM / (PC + QC) == m) issue_one(lds0 + buf * STAGE, x);
+            });
+            // (the half written here was last read 8 stages ago, and is read from 8 stages on)
+            if (G_CM && ((s + NBUF) & 15) == 8 && s + NBUF < KT) rows_in(((s + NBUF) >> 4) + 1);
+            buf = nbuf;
+        }
     }
     wait_vm0();        // (the stages past the end: their zeros must not land in the staging area)
     wait_lgkm0();
@@ -354,8 +402,12 @@ __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
 // These are scattered loads.  One that fills whole 256-row tiles exactly is not told apart and can lose (T 4096 h 2048 f 1024
 // E 8 k 2, 1024 rows each, plain fc1 forward 60 : 67; any other load there 93 : 82).  Skewed weight gradients: split_limit.
 // Few rows per expert (on average at most 48): the third buffer (T 64 h 4096 f 14336 E 8 k 2: 464 : 330 against 363 with two
-// buffers and 359 with 128 x 128).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill the chip's two workgroups per
-// unit (T 256 h 128 f 256: fc2 dgrad 6.9 against 9.5; T 4096 h 512 f 512: 27 against 34).
+// buffers and 359 with 128 x 128).  The same where the 64 x 128 tiles are at most two per unit, so that a third workgroup would
+// find no work (fc1, fc2, fc2 dgrad, fc1 dgrad, two buffers : three: T 256 h 1024 f 704 E 16 k 4 18.0 : 15.4, 12.3 : 9.7, 14.6 :
+// 12.2, 15.6 : 11.4; T 400 h 512 f 512 E 8 k 2 10.9 : 8.6, 7.7 : 6.2, 10.2 : 9.1, 11.8 : 9.1; but at 2.25 per unit, T 2048 h 1024
+// f 512 E 8 k 2, 21.8 : 23.8, 12.2 : 14.1, 18.2 : 21.0).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill the chip's two workgroups per
+// unit (T 256 h 128 f 256: fc2 dgrad 6.9 against 9.5; T 4096 h 512 f 512: 27 against 34); SwiGLU backward, whose output
+// phase is long, up to one and a half times that (T 3000 h 512 f 1536 E 12 k 2 34 : 28.5; T 4096 h 512 f 512 E 8 k 4 32 : 27).
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
     const double E = a.E, R = (double)a.Rcap, one = E < R ? E : R;
@@ -372,8 +424,19 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     const double t128 = (r128 + __builtin_ceil(r128)) * (0.62 * stages + 4);
     if (t128 > (mode == GG_WGRAD ? 1.1 : 1.0) * t256) return 0;   // (weight gradients of a few stages are better than the estimate)
     if (mode == GG_WGRAD) return 2;
-    if (R <= 48 * E) return 3;
-    return r128 < 1 ? 1 : 2;
+    const double n64 = __builtin_ceil(cols / 128) * row_tiles(64);
+    if (R <= 48 * E || n64 <= 2 * cu) return 3;
+    return r128 < (epi == GG_EPI_SWIGLU_BWD ? 1.5 : 1) ? 1 : 2;
+}
+
+// Weight gradients of more than two tiles per unit and short contractions, mostly output: one buffer, three workgroups per
+// unit (fc2, fc1; two buffers : one; h 3072 f 1024 E 32, T 128 k 4 75 : 59, 143 : 109; h 4096 f 1536 E 16, T 64 k 8 63 : 45, 127 : 93;
+// h 1024 f 704 E 16 k 4, T 256 13.8 : 10.8, 19.1 : 15.3, T 1024 19.3 : 17.0, 28.2 : 24.1).  A hot expert's workgroups walk their
+// rows at half the pace then, hence the bound on the rows (rank^-1.2 loads, h 512 f 512 E 64 k 4: T 1024 h 2048 E 16 73 : 72, T 2048
+// 42 : 46, 49 : 46, T 4096 72 : 82, 74 : 79).
+static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
+    const int64_t tiles = a.E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
+    return tiles > 2 * cu && a.Rcap <= 256 * (int64_t)a.E && a.Rcap <= 6144;
 }
 
 template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF, bool SPLIT = false>
@@ -389,20 +452,21 @@ static void gt_rows(hipStream_t s, int tile, const gg_args& a) {
     else gt_go<MODE, EPI, false, GATH, 64, 3>(s, a);
 }
 // (a kernel of its own for calls that may split: the others are 5 % faster at their smallest without the choice in them)
-template <bool F32, bool SPLIT>
+template <bool F32, bool SPLIT, int NBUF>
 static void gt_wgrad(hipStream_t s, int gath, const gg_args& a) {
-    if (gath == 1) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 1, 128, 2, SPLIT>(s, a);
-    else if (gath == 2) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 2, 128, 2, SPLIT>(s, a);
-    else gt_go<GG_WGRAD, GG_EPI_STORE, F32, 0, 128, 2, SPLIT>(s, a);
+    if (gath == 1) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 1, 128, NBUF, SPLIT>(s, a);
+    else if (gath == 2) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 2, 128, NBUF, SPLIT>(s, a);
+    else gt_go<GG_WGRAD, GG_EPI_STORE, F32, 0, 128, NBUF, SPLIT>(s, a);
     if (SPLIT) {
         const int64_t blocks = ceil_div64((int64_t)a.N * a.K / 4, 256);
         hipLaunchKernelGGL(gt_add_kernel<F32>, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, a);
     }
 }
-void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
+void gt_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     if (mode == GG_WGRAD) {
-        if (a.split_cap >= 2) out_f32 ? gt_wgrad<true, true>(s, gath, a) : gt_wgrad<false, true>(s, gath, a);
-        else out_f32 ? gt_wgrad<true, false>(s, gath, a) : gt_wgrad<false, false>(s, gath, a);
+        if (a.split_cap >= 2) out_f32 ? gt_wgrad<true, true, 2>(s, gath, a) : gt_wgrad<false, true, 2>(s, gath, a);
+        else if (gt_one_buffer(ctx, a)) out_f32 ? gt_wgrad<true, false, 1>(s, gath, a) : gt_wgrad<false, false, 1>(s, gath, a);
+        else out_f32 ? gt_wgrad<true, false, 2>(s, gath, a) : gt_wgrad<false, false, 2>(s, gath, a);
     } else if (mode == GG_FWD) {
         if (epi == GG_EPI_SWIGLU) gath ? gt_rows<GG_FWD, GG_EPI_SWIGLU, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_SWIGLU, 0>(s, tile, a);
         else gath ? gt_rows<GG_FWD, GG_EPI_STORE, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_STORE, 0>(s, tile, a);
