@@ -10,6 +10,8 @@
 // max3 over the lane's values, four DPP maxima, and a DPP minimum over the indices that hold the maximum.
 // Measured (us a call; one token per wavefront, eight in turn, butterfly shuffles : this), T 16384, E 256, k 8: top-k 57 : 15;
 // group-limited with bias, 8 groups: 147 : 35; backward 22 : 11; auxiliary loss 22 : 16.  T 64, E 128, k 8: 47 : 6.
+// The group-limited kernel then: 35 -> 25 with the groups' best two met in registers instead of scans through LDS, a slot's score read
+// back from LDS instead of picked out of 16 registers per round, and half as many workgroups adding their histograms.
 #include "common.h"
 
 #define ROUTE_MAX_E 1024
@@ -156,7 +158,7 @@ __global__ __launch_bounds__(1024) void route_topk_kernel(
 // every lpg-th member.
 // ---------------------------------------------------------------------------
 template <int LPT, int VPL>
-__global__ __launch_bounds__(256) void route_topk_grouped_kernel(
+__global__ __launch_bounds__(512) void route_topk_grouped_kernel(
     const float* __restrict__ logits, const float* __restrict__ bias, int T, int E, int k, int n_group, int topk_group,
     int lpg, uint32_t gs_magic, int fn, int norm_topk, float scale,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_prob, int32_t* __restrict__ counts) {
@@ -186,6 +188,10 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
 #pragma unroll
         for (int j = 0; j < VPL; ++j) sc[j] = (float)(1.0 / (1.0 + exp(-(double)v[j])));
     }
+    // Groups of whole rows of lanes (16 members, or a multiple) whose best one or two count: a lane's members of a group are
+    // neighbours in its registers, and the two largest of 16 lanes meet in four exchanges.  Other groups meet through LDS
+    // (by_lds), which otherwise keeps the scores for the lanes that will hold a slot.
+    const bool in_regs = LPT == 16 && m <= 2 && (gs & 15) == 0, by_lds = n_group > 1 && !in_regs;
     float* const cw = (float*)(hist + E) + (threadIdx.x / LPT) * (E + E / 16 + 1);
     auto at = [](int e) { return e + (e >> 4); };  // (a float of padding every 16 keeps the groups on different banks)
 #pragma unroll
@@ -193,17 +199,46 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
         const int e = l + LPT * j;
         const float c = (bias && e < E) ? sc[j] + bias[e] : sc[j];
         key[j] = e < E ? order_key(c) : 0u;
-        if (n_group > 1 && e < E) cw[at(e)] = c;
+        if (e < E) cw[at(e)] = by_lds ? c : sc[j];
     }
 
     // ---- groups to keep ----
     if (n_group > 1) {
+        const int g = l / lpg, sub = l & (lpg - 1);
+        uint32_t gkey = 0;
+        float gsum = 0.f;
+        if (in_regs) {
+            uint32_t hi = 0, lo = 0;
+            const int per = gs >> 4;
+            int grp = 0, left = per;
+#pragma unroll
+            for (int j = 0; j < VPL; ++j) {
+                // (a NaN counts for nothing here; numbers' keys run from that of -inf to that of inf)
+                const uint32_t x = key[j] - 0x007fffffu <= 0xff800000u - 0x007fffffu ? key[j] : 0u;
+                lo = max(lo, min(hi, x));
+                hi = max(hi, x);
+                if (--left == 0) {                          // (uniform)
+                    uint32_t h2 = hi, l2 = lo;
+                    auto meet = [&](uint32_t oh, uint32_t ol) {
+                        l2 = max(min(h2, oh), max(l2, ol));
+                        h2 = max(h2, oh);
+                    };
+                    meet(dpp<0x128>(h2), dpp<0x128>(l2));
+                    meet(dpp<0x124>(h2), dpp<0x124>(l2));
+                    meet(dpp<0x4E>(h2), dpp<0x4E>(l2));
+                    meet(dpp<0xB1>(h2), dpp<0xB1>(l2));
+                    const float sum = m == 1 ? key_value(h2) : key_value(h2) + key_value(l2);
+                    gsum = grp == g ? sum : gsum;
+                    ++grp;
+                    left = per;
+                    hi = lo = 0;
+                }
+            }
+        } else {
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // (a token's lanes are of one wavefront: program order suffices)
         // sum of the m largest c of the lane's group, largest first; round r takes the best element that comes after
         // round r - 1's pick in (value desc, index asc) order
-        const int g = l / lpg, sub = l & (lpg - 1);
-        uint32_t gkey = 0;
-        float gsum = 0.f, pv = INFINITY;
+        float pv = INFINITY;
         int pi = -1;
         for (int r = 0; r < m; ++r) {
             uint32_t bk = 0, bi = 0x7fffffff;
@@ -227,6 +262,7 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
             pv = key_value(bk);
             pi = (int)bi;
             gsum = r == 0 ? pv : gsum + pv;
+        }
         }
         if (g < n_group) gkey = order_key(gsum);
         bool kept = false;
@@ -253,14 +289,18 @@ __global__ __launch_bounds__(256) void route_topk_grouped_kernel(
     for (int it = 0; it < k; ++it) {
         uint32_t best, idx;
         take_best<LPT, VPL>(key, l, best, idx);
-        uint32_t sv = 0;  // the winner's unbiased score, from the lane that holds it
+        if (by_lds) {
+            uint32_t sv = 0;  // the winner's unbiased score, from the lane that holds it
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) sv = (uint32_t)(l + LPT * j) == idx ? __float_as_uint(sc[j]) : sv;
-        sv = lanes_max<LPT>(sv);  // (scores are not negative: their bits order like the values, the other lanes hold 0)
-        if (l == it) {
-            my_s = __uint_as_float(sv);
-            my_idx = idx;
+            for (int j = 0; j < VPL; ++j) sv = (uint32_t)(l + LPT * j) == idx ? __float_as_uint(sc[j]) : sv;
+            sv = lanes_max<LPT>(sv);  // (scores are not negative: their bits order like the values, the other lanes hold 0)
+            if (l == it) my_s = __uint_as_float(sv);
         }
+        if (l == it) my_idx = idx;
+    }
+    if (!by_lds) {
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        my_s = cw[at((int)min(my_idx, (uint32_t)E - 1))];
     }
     float p = l < k ? my_s : 0.f;
     if (norm_topk) p = p / slots_sum<LPT>(p);
@@ -317,15 +357,20 @@ __global__ __launch_bounds__(256) void route_topk_bwd_kernel(
         dq = my_idx >= 0 ? scale * (dw / D - dwq / (D * D)) : 0.f;
     }
     const float dqq = slots_sum<LPT>(dq * q);  // <dq, q>
-    // every lane collects the dq of the selected experts it owns
-    float gsel[VPL];
+    // every lane collects the dq of the selected experts it owns, and (sigmoid) their scores: the other experts' gradient is
+    // zero, so that k scores of a token are computed and not E
+    float gsel[VPL], ssel[VPL];
 #pragma unroll
-    for (int j = 0; j < VPL; ++j) gsel[j] = 0.f;
+    for (int j = 0; j < VPL; ++j) gsel[j] = ssel[j] = 0.f;
     for (int s = 0; s < k; ++s) {
         const int e = __shfl(my_idx, s, LPT);
-        const float d = __shfl(dq, s, LPT);
+        const float d = __shfl(dq, s, LPT), qs = __shfl(q, s, LPT);
 #pragma unroll
-        for (int j = 0; j < VPL; ++j) gsel[j] += e == l + LPT * j ? d : 0.f;
+        for (int j = 0; j < VPL; ++j) {
+            const bool mine = e == l + LPT * j;
+            gsel[j] += mine ? d : 0.f;
+            ssel[j] = mine ? qs : ssel[j];
+        }
     }
     if (t >= T) return;
     float* o = dlogits + (int64_t)t * E;
@@ -337,8 +382,7 @@ __global__ __launch_bounds__(256) void route_topk_bwd_kernel(
             if (fn == MOE_SCORE_SOFTMAX) {
                 r = v[j] / den * (gsel[j] - dqq);
             } else {
-                const float sg = 1.f / (1.f + expf(-v[j]));
-                r = gsel[j] * sg * (1.f - sg);
+                r = v[j] != v[j] ? v[j] : gsel[j] * ssel[j] * (1.f - ssel[j]);   // (a NaN logit: NaN, selected or not)
             }
             o[e] = r;
         }
@@ -421,7 +465,13 @@ __global__ __launch_bounds__(AUX_TOKENS * LPT > 1024 ? 1024 : AUX_TOKENS * LPT) 
 
 __global__ __launch_bounds__(64) void aux_loss_sum_kernel(const double* __restrict__ partial, int n, float* __restrict__ loss) {
     double a = 0.0;
-    for (int i = threadIdx.x; i < n; i += 64) a += partial[i];
+    for (int i = threadIdx.x; i < n; i += 512) {   // (eight loads in flight; the order of the additions is i's)
+        double v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = i + 64 * x < n ? partial[i + 64 * x] : 0.0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) a += v[x];
+    }
     a = lanes_sum<64>(a);
     if (threadIdx.x == 0) *loss = (float)a;
 }
@@ -497,9 +547,10 @@ extern "C" moe_status moe_route_topk_grouped(moe_ctx* ctx, void* stream, const f
     const int lpt = route_narrow(E, k, n_group) ? 16 : 64;
     int lpg = lpt;  // lanes per group: the largest power of two with room for all groups
     while (lpg > 1 && lpg * n_group > lpt) lpg >>= 1;
-    const int tokens = 256 / lpt, gs = E / n_group;
+    // (many tokens: as moe_route_topk, with 35 KB of LDS at 256 experts)
+    const int threads = lpt == 16 && T > 4096 ? 512 : 256, tokens = threads / lpt, gs = E / n_group;
     const uint32_t gs_magic = ((1u << 20) + gs - 1) / gs;  // (e * gs_magic) >> 20 == e / gs for e < 1024: the excess, e * gs at most, stays below 2^20
-    const dim3 grid((T + tokens - 1) / tokens), block(256);
+    const dim3 grid((T + tokens - 1) / tokens), block(threads);
     if (counts && grid.x > 1) moe_launch_fill_i32(counts, E, 0, s);
     const size_t shm = (size_t)E * sizeof(int32_t) + (size_t)tokens * (E + E / 16 + 1) * sizeof(float);
     ROUTE_CASES(route_topk_grouped_kernel, grid, block, shm, s, logits, expert_bias, T, E, k, n_group, topk_group, lpg, gs_magic,
