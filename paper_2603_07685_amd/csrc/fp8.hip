@@ -8,8 +8,15 @@
 //   1x128   : 16 lanes own one block (8 elements per lane), amax by butterfly over those 16 lanes.
 //   128x1   : a wave owns a 128-row x 512-column panel, 8 columns per lane; first pass keeps the running
 //             column amax in registers, second pass re-reads the panel (from L2) and converts.
-//   128x128 : a 256-thread workgroup owns one block, 64 elements per thread held in registers.
+//   128x128 : a 512-thread workgroup owns one block, 32 elements per thread held in registers.
 #include "common.h"
+
+// Threads per 128 x 128 tile of the two-copy quantiser and the weight quantiser, 2048 / this 16-byte pieces per lane.  At 256 a call
+// of few tiles was bound by one lane's chain of eight pieces and sixteen divisions; at 1024 every lane's share of the column scales
+// outweighs its pieces.  Measured (us, 256 threads with every lane dividing : 512 and one division pair per column), T 1024 h 512 f 256 E 8
+// k 4: tokens and p * dY through the row map 13.8, 13.1 : 9.2, 9.3, X and dY 11.0, 10.9 : 7.2, 6.8, columns only 6.1 : 5.0, weights 6.1,
+// 5.3, 5.0 : 5.1, 4.2, 4.2; T 8192 h 1024 f 512 E 8 k 2: 27.6, 15.2 : 25.1, 13.0; T 16384 h 4096 k 4 unchanged.
+#define QUANT_THREADS 512
 
 __device__ __forceinline__ float amax8(u32x4_t v) {
     float m = fabsf(bf16_lo(v.x));
@@ -124,31 +131,34 @@ __global__ __launch_bounds__(256) void quant_128x1_kernel(const u32x4_t* __restr
 
 // ---- 128x128 -------------------------------------------------------------------------------
 // grid = groups * (rows/128) * (cols/128) workgroups of 256 threads
-__global__ __launch_bounds__(256) void quant_128x128_kernel(const u32x4_t* __restrict__ W, int rows, int cols,
+__global__ __launch_bounds__(QUANT_THREADS) void quant_128x128_kernel(const u32x4_t* __restrict__ W, int rows, int cols,
                                                             u32x2_t* __restrict__ q, float* __restrict__ scale) {
-    __shared__ float part[4];
+    constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RP = 128 / PIECES;   // per lane; waves; rows of a pass
+    __shared__ float part[NW];
     const int nbr = rows / 128, nbc = cols / 128;
     const int b = blockIdx.x;
     const int g = b / (nbr * nbc), rb = (b / nbc) % nbr, cb = b % nbc;
     const int vpr = cols / 8;
-    const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;   // 16 rows x 16 vectors per pass
+    const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;   // RP rows x 16 vectors per pass
     const int64_t base = ((int64_t)g * rows + rb * 128) * vpr + cb * 16 + tc;
-    u32x4_t v[8];
+    u32x4_t v[PIECES];
     float m = 0.f;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) {
-        v[it] = W[base + (int64_t)(it * 16 + tr) * vpr];
+    for (int it = 0; it < PIECES; ++it) {
+        v[it] = W[base + (int64_t)(it * RP + tr) * vpr];
         m = fmaxf(m, amax8(v[it]));
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
     __syncthreads();
-    m = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+    m = part[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m = fmaxf(m, part[w]);
     const float s = block_scale(m);
     if (threadIdx.x == 0) scale[b] = s;
 #pragma unroll
-    for (int it = 0; it < 8; ++it) q[base + (int64_t)(it * 16 + tr) * vpr] = cvt8_e4m3(v[it], s);
+    for (int it = 0; it < PIECES; ++it) q[base + (int64_t)(it * RP + tr) * vpr] = cvt8_e4m3(v[it], s);
 }
 
 static moe_status fp8_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who, const void* X, int64_t rows, int cols,
@@ -197,7 +207,7 @@ extern "C" moe_status moe_fp8_quantize(moe_ctx* ctx, void* stream, const void* X
             if (rows_dev) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_fp8_quantize(128x128): rows_dev is not used for weights");
             const int64_t nb = (int64_t)groups * (rows / 128) * (cols / 128);
             if (nb > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_fp8_quantize(128x128): too many blocks");
-            hipLaunchKernelGGL(quant_128x128_kernel, dim3((unsigned)nb), dim3(256), 0, s, (const u32x4_t*)X, (int)rows, cols,
+            hipLaunchKernelGGL(quant_128x128_kernel, dim3((unsigned)nb), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, (int)rows, cols,
                                (u32x2_t*)q, scale);
             break;
         }
@@ -211,12 +221,12 @@ extern "C" moe_status moe_fp8_quantize(moe_ctx* ctx, void* stream, const void* X
 // ---------------------------------------------------------------------------
 // Blockwise recipe, row- and column-wise copies in one pass (Sec. 5.3.3: a tensor that two GEMMs read with different
 // contraction dimensions is quantised once per direction; Sec. 5.4.2: one grouped launch; Sec. 5.4.1: padding and
-// the permutation fused in).  A 256-thread workgroup owns a tile of 128 rows x 128 columns: exactly one 1x128 block
-// of each of its rows and one 128x1 block of each of its columns.  Wave w owns rows 32 w .. 32 w + 31; a lane reads
-// eight 16-byte pieces: piece i is row 32 w + 4 i + lane / 16, columns 8 (lane % 16) .. + 7.
+// the permutation fused in).  A 512-thread workgroup owns a tile of 128 rows x 128 columns: exactly one 1x128 block
+// of each of its rows and one 128x1 block of each of its columns.  Wave w owns rows 16 w .. 16 w + 15; a lane reads
+// four 16-byte pieces: piece i is row 16 w + 4 i + lane / 16, columns 8 (lane % 16) .. + 7.
 //   row-wise : the block is the 16 lanes of one piece (four butterfly steps);
-//   col-wise : the block is the same element of the lane's 8 pieces, of the 4 lanes 16 apart and of the 4 waves
-//              (maxima meet in LDS).
+//   col-wise : the block is the same element of the lane's 4 pieces, of the 4 lanes 16 apart and of the 8 waves
+//              (maxima meet in LDS, where one thread per column forms the scale).
 // Either copy may be switched off (q_row or q_col NULL).  GATHER: row r of the input is pair_scale[s] * X[s / k, :]
 // rounded to bf16 (no scale, no rounding when pair_scale is NULL) with s = src_of[r], zero where s < 0.
 // Scales and codes are formed exactly as in the single-direction kernels above (amax / 448, fp32 division,
@@ -235,13 +245,15 @@ static inline gather_div_t gather_div(int k) {
 __device__ __forceinline__ uint32_t scale2_bf16_bw(uint32_t w, float sc) { return pack_bf16(sc * bf16_lo(w), sc * bf16_hi(w)); }
 
 template <bool GATHER>
-__global__ __launch_bounds__(256) void fp8_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
+__global__ __launch_bounds__(QUANT_THREADS) void fp8_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
                                                                const int32_t* __restrict__ rows_dev,
                                                                const int32_t* __restrict__ src_of, uint32_t k_magic, int k_shift,
                                                                const float* __restrict__ pair_scale, int groups,
                                                                u32x2_t* __restrict__ q_row, float* __restrict__ s_row,
                                                                u32x2_t* __restrict__ q_col, float* __restrict__ s_col) {
-    __shared__ float cmax[4][128];
+    constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RW = 4 * PIECES;   // per lane; waves; rows of a wave
+    __shared__ float cmax[NW][128];
+    __shared__ __attribute__((aligned(16))) float cscale[128], crcp[128];
     const int64_t live = rows_dev ? min((int64_t)*rows_dev, rows) : rows;
     const int ctiles = cols / 128;
     int64_t rt = blockIdx.x / ctiles;
@@ -254,46 +266,46 @@ __global__ __launch_bounds__(256) void fp8_quant_rowcol_kernel(const u32x4_t* __
     if (row0 >= live || row0 >= rows) return;  // uniform over the workgroup
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int vpr = cols / 8;
-    const int64_t v0 = (row0 + wave * 32 + (lane >> 4)) * vpr + ct * 16 + (lane & 15);
-    u32x4_t x[8];
+    const int64_t v0 = (row0 + wave * RW + (lane >> 4)) * vpr + ct * 16 + (lane & 15);
+    u32x4_t x[PIECES];
     if (GATHER) {
-        // Three passes, so that the eight map entries, then the eight rows, then the eight weights are each in
-        // flight together (one pass per piece would chain sixteen memory latencies per lane), and no branch: a lane
+        // Three passes, so that the map entries, then the rows, then the weights of a lane are each in
+        // flight together (one pass per piece would chain the memory latencies), and no branch: a lane
         // whose row is padding reads 16 aligned bytes of this tile's 512 bytes of map entries instead, which always
         // exist, and drops them.
         const void* const spare = (const void*)(((uintptr_t)(src_of + row0) + 15) & ~(uintptr_t)15);
-        int32_t sidx[8];
+        int32_t sidx[PIECES];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sidx[i] = src_of[row0 + wave * 32 + 4 * i + (lane >> 4)];
+        for (int i = 0; i < PIECES; ++i) sidx[i] = src_of[row0 + wave * RW + 4 * i + (lane >> 4)];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             const int64_t tok = (int64_t)(((uint64_t)(uint32_t)sidx[i] * k_magic) >> k_shift);  // sidx / k (gather_div)
             uint64_t live_at = (uint64_t)(X + (tok * vpr + ct * 16 + (lane & 15)));
             asm volatile("" : "+v"(live_at));  // (formed for every lane: a select then, not a branch around the multiplications)
             x[i] = *(const u32x4_t*)(sidx[i] >= 0 ? live_at : (uint64_t)spare);
         }
         if (pair_scale) {
-            float psc[8];
+            float psc[PIECES];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) psc[i] = *(sidx[i] >= 0 ? pair_scale + sidx[i] : (const float*)spare);
+            for (int i = 0; i < PIECES; ++i) psc[i] = *(sidx[i] >= 0 ? pair_scale + sidx[i] : (const float*)spare);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < PIECES; ++i)
                 x[i] = u32x4_t{scale2_bf16_bw(x[i].x, psc[i]), scale2_bf16_bw(x[i].y, psc[i]), scale2_bf16_bw(x[i].z, psc[i]),
                                scale2_bf16_bw(x[i].w, psc[i])};
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < PIECES; ++i)
             if (sidx[i] < 0) x[i] = u32x4_t{0, 0, 0, 0};
     } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = X[v0 + (int64_t)i * 4 * vpr];
+        for (int i = 0; i < PIECES; ++i) x[i] = X[v0 + (int64_t)i * 4 * vpr];
     }
     if (q_col) {  // (first: the other waves' maxima are on their way while this wave converts its rows)
         float m[8];
 #pragma unroll
         for (int c = 0; c < 8; ++c) m[c] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             m[0] = fmaxf(m[0], fabsf(bf16_lo(x[i].x))); m[1] = fmaxf(m[1], fabsf(bf16_hi(x[i].x)));
             m[2] = fmaxf(m[2], fabsf(bf16_lo(x[i].y))); m[3] = fmaxf(m[3], fabsf(bf16_hi(x[i].y)));
             m[4] = fmaxf(m[4], fabsf(bf16_lo(x[i].z))); m[5] = fmaxf(m[5], fabsf(bf16_hi(x[i].z)));
@@ -308,34 +320,41 @@ __global__ __launch_bounds__(256) void fp8_quant_rowcol_kernel(const u32x4_t* __
     }
     if (q_row) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             float m = amax8(x[i]);
 #pragma unroll
             for (int o = 8; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
             const float sc = block_scale(m);
             q_row[v0 + (int64_t)i * 4 * vpr] = cvt8_e4m3(x[i], sc);
-            if ((lane & 15) == 0) s_row[(row0 + wave * 32 + 4 * i + (lane >> 4)) * ctiles + ct] = sc;
+            if ((lane & 15) == 0) s_row[(row0 + wave * RW + 4 * i + (lane >> 4)) * ctiles + ct] = sc;
         }
     }
     if (q_col) {
+        // (a column's two divisions by one thread, not by every lane that has a piece of it)
+        __syncthreads();
+        if (threadIdx.x < 128) {
+            const int c = threadIdx.x;
+            float m = cmax[0][c];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) m = fmaxf(m, cmax[w][c]);
+            const float one = block_scale(m);
+            s_col[rt * cols + ct * 128 + c] = one;
+            cscale[c] = one;
+            crcp[c] = 1.0f / one;
+        }
         __syncthreads();
         float sc[8], rc[8];
         bool fast = true;
         const int cb = 8 * (lane & 15);
+        *(f32x4_t*)sc = *(const f32x4_t*)(cscale + cb);
+        *(f32x4_t*)(sc + 4) = *(const f32x4_t*)(cscale + cb + 4);
+        *(f32x4_t*)rc = *(const f32x4_t*)(crcp + cb);
+        *(f32x4_t*)(rc + 4) = *(const f32x4_t*)(crcp + cb + 4);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            sc[c] = block_scale(fmaxf(fmaxf(cmax[0][cb + c], cmax[1][cb + c]), fmaxf(cmax[2][cb + c], cmax[3][cb + c])));
-            rc[c] = 1.0f / sc[c];
-            fast &= quant_fast_ok(sc[c]);
-        }
+        for (int c = 0; c < 8; ++c) fast &= quant_fast_ok(sc[c]);
         fast = quant_fast_all(fast);   // (see quant_div: one division per column block instead of one per element)
-        if (wave == 0 && lane < 16) {
-            f32x4_t* sd = (f32x4_t*)(s_col + rt * cols + ct * 128 + cb);
-            sd[0] = f32x4_t{sc[0], sc[1], sc[2], sc[3]};
-            sd[1] = f32x4_t{sc[4], sc[5], sc[6], sc[7]};
-        }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             float v[8] = {bf16_lo(x[i].x), bf16_hi(x[i].x), bf16_lo(x[i].y), bf16_hi(x[i].y),
                           bf16_lo(x[i].z), bf16_hi(x[i].z), bf16_lo(x[i].w), bf16_hi(x[i].w)};
             if (fast) {
@@ -368,11 +387,11 @@ static moe_status fp8_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who
     const int64_t nblk = tiles_r * (cols / 128);
     if (nblk > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: too many tiles", who);
     if (src_of)
-        hipLaunchKernelGGL(fp8_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
+        hipLaunchKernelGGL(fp8_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
                            rows_dev, src_of, gather_div(k).m, gather_div(k).sh, pair_scale, groups, (u32x2_t*)q_row, s_row,
                            (u32x2_t*)q_col, s_col);
     else
-        hipLaunchKernelGGL(fp8_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
+        hipLaunchKernelGGL(fp8_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
                            rows_dev, nullptr, 0, 0, nullptr, 1, (u32x2_t*)q_row, s_row, (u32x2_t*)q_col, s_col);
     return MOE_OK;
 }

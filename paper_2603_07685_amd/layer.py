@@ -56,6 +56,9 @@ class LayerState:
         # output, the next GEMM's operand (Sec. 5.4.2); off = stand-alone quantiser calls
         # (MXFP8: the 1x32 codes and the 32x1 copy for the weight gradients; row counts are on the 128-row grid there)
         self.epilogue_quant = bool(cfg.fp8 or cfg.mx) if epilogue_quant is None else bool(epilogue_quant)
+        # blockwise calls of few rows are served by small tiles, where the copies are a launch of their own anyway: unless the
+        # caller asks, both copies of A and dZ then come from one launch of the two-copy quantiser (the same bits)
+        self.epilogue_rows = 16384 if epilogue_quant is None and not cfg.mx else 0
         assert not self.epilogue_quant or cfg.fp8 or cfg.mx, "epilogue quantisation belongs to the one-byte recipes"
         # blockwise fp8 (default there): the weight gradients also run on E4M3 codes, quantised 128x1 down the token
         # dimension inside each expert's 128-aligned row range (Sec. 5.3.2, 5.4.1); off = weight gradients from the
@@ -404,7 +407,7 @@ class LayerState:
     def _fc1_fwd(self, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc, live):
         """fc1 + SwiGLU and the quantised copies of the activation fc2 and its weight gradient read: from the GEMM call
         itself (Sec. 5.4.2) where that is switched on, else by quantiser calls."""
-        c, eq = self.ctx, self.epilogue_quant
+        c, eq = self.ctx, self.epilogue_quant and not (self.fp8_wgrad and rows <= self.epilogue_rows)
         if eq and self.mx:
             B.moe_grouped_gemm_fwd_quant_mx(c, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc)
             return
@@ -417,7 +420,7 @@ class LayerState:
 
     def _fc2_dgrad(self, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part, qdZ, sdZ, qdZc, sdZc, live):
         """fc2 data gradient + SwiGLU backward and the quantised copies of dZ, as in _fc1_fwd."""
-        c, eq = self.ctx, self.epilogue_quant
+        c, eq = self.ctx, self.epilogue_quant and not (self.fp8_wgrad and rows <= self.epilogue_rows)
         if eq and self.mx:
             B.moe_grouped_gemm_dgrad_quant_mx(c, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part,
                                               qdZ, sdZ, qdZc, sdZc)
