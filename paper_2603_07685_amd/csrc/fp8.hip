@@ -11,11 +11,13 @@
 //   128x128 : a 512-thread workgroup owns one block, 32 elements per thread held in registers.
 #include "common.h"
 
-// Threads per 128 x 128 tile of the two-copy quantiser and the weight quantiser, 2048 / this 16-byte pieces per lane.  At 256 a call
+// Threads per 128 x 128 tile of the two-copy quantisers and the weight quantiser, 2048 / this 16-byte pieces per lane.  At 256 a call
 // of few tiles was bound by one lane's chain of eight pieces and sixteen divisions; at 1024 every lane's share of the column scales
 // outweighs its pieces.  Measured (us, 256 threads with every lane dividing : 512 and one division pair per column), T 1024 h 512 f 256 E 8
 // k 4: tokens and p * dY through the row map 13.8, 13.1 : 9.2, 9.3, X and dY 11.0, 10.9 : 7.2, 6.8, columns only 6.1 : 5.0, weights 6.1,
-// 5.3, 5.0 : 5.1, 4.2, 4.2; T 8192 h 1024 f 512 E 8 k 2: 27.6, 15.2 : 25.1, 13.0; T 16384 h 4096 k 4 unchanged.
+// 5.3, 5.0 : 5.1, 4.2, 4.2; T 8192 h 1024 f 512 E 8 k 2: 27.6, 15.2 : 25.1, 13.0; T 16384 h 4096 k 4 unchanged.  MXFP8 (256 : 512), T 256
+// h 512 f 256 E 8 k 2 7.6, 7.9 : 6.3, 6.9; T 16384 h 7168 f 2048 E 32 k 8: weights 793, 376 : 739, 365, tokens and p * dY 740, 764 : 675, 715,
+// A and dZ 208, 438 : 198, 412.
 #define QUANT_THREADS 512
 
 __device__ __forceinline__ float amax8(u32x4_t v) {
@@ -460,12 +462,13 @@ __global__ __launch_bounds__(256) void mx_quant_1x32_kernel(const u32x4_t* __res
     }
 }
 
-// Row- and column-wise copies in one pass (either may be switched off).  A 256-thread workgroup owns a tile of
-// 128 rows x 128 columns; wave w owns its rows 32 w .. 32 w + 31, i.e. one 32-row block of every column.  A lane
-// reads eight 16-byte pieces: piece i is row 4 i + lane / 16, columns 8 (lane % 16) .. + 7.
+// Row- and column-wise copies in one pass (either may be switched off).  A 512-thread workgroup owns a tile of
+// 128 rows x 128 columns; wave w owns its rows 16 w .. 16 w + 15, i.e. half a 32-row block of every column.  A lane
+// reads four 16-byte pieces: piece i is row 4 i + lane / 16, columns 8 (lane % 16) .. + 7.
 //   row-wise  : a 1x32 block is 4 adjacent lanes of one piece (two butterfly steps);
-//   col-wise  : a 32x1 block is the same element of the lane's 8 pieces and of the 4 lanes 16 apart.
-// The column scales of the four waves meet in LDS and leave as one dword per column:
+//   col-wise  : a 32x1 block is the same element of the lane's 4 pieces, of the 4 lanes 16 apart and of two waves (maxima meet
+//               in LDS, where one thread per block forms the exponent).
+// The column scales of a tile leave as one dword per column:
 // e8_col[(row / 128) * cols + col] holds the four 32-row blocks of rows 128 (row / 128) .. + 127, the unit in
 // which the GEMMs walk a contraction over rows.
 // GATHER: the input is not stored in row order: row r of it is pair_scale[s] * X[s / k, :] rounded to bf16
@@ -474,12 +477,16 @@ __global__ __launch_bounds__(256) void mx_quant_1x32_kernel(const u32x4_t* __res
 __device__ __forceinline__ uint32_t scale2_bf16(uint32_t w, float sc) { return pack_bf16(sc * bf16_lo(w), sc * bf16_hi(w)); }
 
 template <bool GATHER>
-__global__ __launch_bounds__(256) void mx_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
+__global__ __launch_bounds__(QUANT_THREADS) void mx_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
                                                               const int32_t* __restrict__ rows_dev, int E,
                                                               const int32_t* __restrict__ src_of, uint32_t k_magic, int k_shift,
                                                               const float* __restrict__ pair_scale, int groups,
                                                               u32x2_t* __restrict__ q_row, uint32_t* __restrict__ e8_row,
                                                               u32x2_t* __restrict__ q_col, uint32_t* __restrict__ e8_col) {
+    constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RW = 4 * PIECES;   // per lane; waves; rows of a wave
+    static_assert(QUANT_THREADS == 512, "a thread per column and 32-row block");
+    __shared__ float cmax[NW][128];
+    __shared__ __attribute__((aligned(16))) float cscale[4][128];
     __shared__ uint8_t sc[4][128];
     const int64_t live = rows_dev ? min((int64_t)*rows_dev, rows) : rows;
     const int ctiles = cols / 128;
@@ -497,44 +504,62 @@ __global__ __launch_bounds__(256) void mx_quant_rowcol_kernel(const u32x4_t* __r
     if (row0 >= live || row0 >= rows) return;  // uniform over the workgroup
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int vpr = cols / 8;                                       // 16-byte pieces per row
-    const int64_t v0 = (row0 + wave * 32 + (lane >> 4)) * vpr + ct * 16 + (lane & 15);
-    u32x4_t x[8];
+    const int64_t v0 = (row0 + wave * RW + (lane >> 4)) * vpr + ct * 16 + (lane & 15);
+    u32x4_t x[PIECES];
     if (GATHER) {
-        // Three passes, so that the eight map entries, then the eight rows, then the eight weights are each in
-        // flight together (one pass per piece would chain sixteen memory latencies per lane), and no branch: a lane
+        // Three passes, so that the map entries, then the rows, then the weights of a lane are each in
+        // flight together (one pass per piece would chain the memory latencies), and no branch: a lane
         // whose row is padding reads 16 aligned bytes of this tile's 512 bytes of map entries instead, which always
         // exist, and drops them.
         const void* const spare = (const void*)(((uintptr_t)(src_of + row0) + 15) & ~(uintptr_t)15);
-        int32_t sidx[8];
+        int32_t sidx[PIECES];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sidx[i] = src_of[row0 + wave * 32 + 4 * i + (lane >> 4)];
+        for (int i = 0; i < PIECES; ++i) sidx[i] = src_of[row0 + wave * RW + 4 * i + (lane >> 4)];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             const int64_t tok = (int64_t)(((uint64_t)(uint32_t)sidx[i] * k_magic) >> k_shift);  // sidx / k (gather_div)
             uint64_t live_at = (uint64_t)(X + (tok * vpr + ct * 16 + (lane & 15)));
             asm volatile("" : "+v"(live_at));  // (formed for every lane: a select then, not a branch around the multiplications)
             x[i] = *(const u32x4_t*)(sidx[i] >= 0 ? live_at : (uint64_t)spare);
         }
         if (pair_scale) {
-            float psc[8];
+            float psc[PIECES];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) psc[i] = *(sidx[i] >= 0 ? pair_scale + sidx[i] : (const float*)spare);
+            for (int i = 0; i < PIECES; ++i) psc[i] = *(sidx[i] >= 0 ? pair_scale + sidx[i] : (const float*)spare);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < PIECES; ++i)
                 x[i] = u32x4_t{scale2_bf16(x[i].x, psc[i]), scale2_bf16(x[i].y, psc[i]), scale2_bf16(x[i].z, psc[i]),
                                scale2_bf16(x[i].w, psc[i])};
         }
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < PIECES; ++i)
             if (sidx[i] < 0) x[i] = u32x4_t{0, 0, 0, 0};
     } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = X[v0 + (int64_t)i * 4 * vpr];
+        for (int i = 0; i < PIECES; ++i) x[i] = X[v0 + (int64_t)i * 4 * vpr];
         if (E > 0 && (offsets_refused(rows_dev, E, rows, true) || row0 < rows_dev[-E])) return;  // (the rows are on their way meanwhile)
+    }
+    if (q_col) {
+        float m[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) m[c] = 0.f;
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) {
+            m[0] = fmaxf(m[0], fabsf(bf16_lo(x[i].x))); m[1] = fmaxf(m[1], fabsf(bf16_hi(x[i].x)));
+            m[2] = fmaxf(m[2], fabsf(bf16_lo(x[i].y))); m[3] = fmaxf(m[3], fabsf(bf16_hi(x[i].y)));
+            m[4] = fmaxf(m[4], fabsf(bf16_lo(x[i].z))); m[5] = fmaxf(m[5], fabsf(bf16_hi(x[i].z)));
+            m[6] = fmaxf(m[6], fabsf(bf16_lo(x[i].w))); m[7] = fmaxf(m[7], fabsf(bf16_hi(x[i].w)));
+        }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            m[c] = fmaxf(m[c], __shfl_xor(m[c], 16));
+            m[c] = fmaxf(m[c], __shfl_xor(m[c], 32));
+            if (lane < 16) cmax[wave][8 * lane + c] = m[c];
+        }
     }
     if (q_row) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             float m = amax8(x[i]);
             m = fmaxf(m, __shfl_xor(m, 1));
             m = fmaxf(m, __shfl_xor(m, 2));
@@ -547,38 +572,27 @@ __global__ __launch_bounds__(256) void mx_quant_rowcol_kernel(const u32x4_t* __r
             const int b = e + 127, base = lane & 48;
             const uint32_t w = (uint32_t)__shfl(b, base) | ((uint32_t)__shfl(b, base + 4) << 8) |
                                ((uint32_t)__shfl(b, base + 8) << 16) | ((uint32_t)__shfl(b, base + 12) << 24);
-            if ((lane & 15) == 0) e8_row[((row0 + wave * 32 + 4 * i + (lane >> 4)) * (cols / 32) + ct * 4) >> 2] = w;
+            if ((lane & 15) == 0) e8_row[((row0 + wave * RW + 4 * i + (lane >> 4)) * (cols / 32) + ct * 4) >> 2] = w;
         }
     }
     if (q_col) {
-        float m[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) m[c] = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            m[0] = fmaxf(m[0], fabsf(bf16_lo(x[i].x))); m[1] = fmaxf(m[1], fabsf(bf16_hi(x[i].x)));
-            m[2] = fmaxf(m[2], fabsf(bf16_lo(x[i].y))); m[3] = fmaxf(m[3], fabsf(bf16_hi(x[i].y)));
-            m[4] = fmaxf(m[4], fabsf(bf16_lo(x[i].z))); m[5] = fmaxf(m[5], fabsf(bf16_hi(x[i].z)));
-            m[6] = fmaxf(m[6], fabsf(bf16_lo(x[i].w))); m[7] = fmaxf(m[7], fabsf(bf16_hi(x[i].w)));
+        __syncthreads();
+        {   // (a 32-row block is two waves' rows; its exponent is formed by one thread)
+            const int blk = threadIdx.x >> 7, c = threadIdx.x & 127;
+            const int e = mx_exponent(fmaxf(cmax[2 * blk][c], cmax[2 * blk + 1][c]));
+            sc[blk][c] = (uint8_t)(e + 127);
+            cscale[blk][c] = mx_scale_f32(e);
         }
-        int e[8];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            m[c] = fmaxf(m[c], __shfl_xor(m[c], 16));
-            m[c] = fmaxf(m[c], __shfl_xor(m[c], 32));
-            e[c] = mx_exponent(m[c]);
-            if (lane < 16) sc[wave][8 * lane + c] = (uint8_t)(e[c] + 127);
-        }
+        __syncthreads();
         float sf[8];
+        *(f32x4_t*)sf = *(const f32x4_t*)(cscale[wave >> 1] + 8 * (lane & 15));
+        *(f32x4_t*)(sf + 4) = *(const f32x4_t*)(cscale[wave >> 1] + 8 * (lane & 15) + 4);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) sf[c] = mx_scale_f32(e[c]);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < PIECES; ++i) {
             const u32x2_t o = {mx_cvt4_bf16_each(x[i].x, x[i].y, sf[0], sf[1], sf[2], sf[3]),
                                mx_cvt4_bf16_each(x[i].z, x[i].w, sf[4], sf[5], sf[6], sf[7])};
             q_col[v0 + (int64_t)i * 4 * vpr] = o;
         }
-        __syncthreads();
         if (threadIdx.x < 128) {
             const int c = threadIdx.x;
             e8_col[rt * cols + ct * 128 + c] = (uint32_t)sc[0][c] | ((uint32_t)sc[1][c] << 8) | ((uint32_t)sc[2][c] << 16) |
@@ -597,11 +611,11 @@ static moe_status mx_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who,
     const int64_t nblk = tiles_r * (cols / 128);
     if (nblk > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: too many tiles", who);
     if (src_of)
-        hipLaunchKernelGGL(mx_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
+        hipLaunchKernelGGL(mx_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
                            rows_dev, 0, src_of, gather_div(k).m, gather_div(k).sh, pair_scale, groups, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
                            (uint32_t*)e8_col);
     else
-        hipLaunchKernelGGL(mx_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(256), 0, s, (const u32x4_t*)X, rows, cols,
+        hipLaunchKernelGGL(mx_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
                            rows_dev, E, nullptr, 0, 0, nullptr, 1, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
                            (uint32_t*)e8_col);
     return MOE_OK;
