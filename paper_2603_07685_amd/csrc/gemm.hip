@@ -2311,7 +2311,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
 // least 8 stages (1.45 us each; the last one what is left), less than which does not pay for the second launch and the
 // partial results' way.
 // T 16384, E 256, h 7168 (64 tiles, 112 stages): one piece 176 us + 5 for a launch that wrote the group's offsets; four
-// pieces 73 + 13 for the sum.  T 2048, E 64, h 4096: 75 + 5 : 21 + 4.  Bound now: HBM (X once, 235 MB, and the partial results
+// pieces 73 + 13 for the sum.  (Smaller calls: gate_kernel, one launch, below.)  Bound now: HBM (X once, 235 MB, and the partial results
 // out and in, 134 MB) and the 28 stages of a piece (41 us at the rate operands reach a compute unit).
 // ---------------------------------------------------------------------------
 #define GATE_MIN_STAGES 8

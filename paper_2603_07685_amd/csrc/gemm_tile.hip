@@ -19,8 +19,10 @@
 // bytes ahead, a call takes 1.25-1.5 times as long (fc1 forward, T 2048, h 1024, f 512, 8 experts, top-2: 24 us against
 // 33, BM = 128).  A persistent form, whose operand stream runs on across tiles, was no faster (27 us) and its static share
 // of the tiles made it slower where there are many (BM = 64, 24 experts, 8000 rows: 309 us against 251).
-// Where the rows of an expert fit one tile and the call streams the weights, a third buffer is worth more than the third
-// workgroup (decoding, 32 rows on each of 16 experts, 403 MB of fc1 weights: 92 us against 98, 4.4 TB/s).
+// Where the rows of an expert fit one tile and the call streams the weights, or the tiles leave at most two to a unit, a third
+// buffer is worth more than the third workgroup (decoding, 32 rows on each of 16 experts, 403 MB of fc1 weights: 92 us against
+// 98, 4.4 TB/s).  The other way round, weight gradients of a few stages and many tiles are mostly output: one buffer, no operand
+// ahead, and three workgroups to a unit (gt_one_buffer).
 #include "gemm_tile.h"
 
 // Weight gradients of many rows: an expert of more than split_limit rows is cut into pieces of at most that many, each with its
