@@ -57,7 +57,9 @@ class LayerState:
         # (MXFP8: the 1x32 codes and the 32x1 copy for the weight gradients; row counts are on the 128-row grid there)
         self.epilogue_quant = bool(cfg.fp8 or cfg.mx) if epilogue_quant is None else bool(epilogue_quant)
         # blockwise calls of few rows are served by small tiles, where the copies are a launch of their own anyway: unless the
-        # caller asks, both copies of A and dZ then come from one launch of the two-copy quantiser (the same bits)
+        # caller asks, both copies of A and dZ then come from one launch of the two-copy quantiser (the same bits).
+        # A step, us, epilogue : one launch: T 256 h 512 f 256 E 8 k 2 97 : 95; T 1024 h 1024 f 768 E 16 k 4 222 : 212; T 3072 h 2048
+        # f 1024 E 16 k 4 (14336 rows) 694 : 680
         self.epilogue_rows = 16384 if epilogue_quant is None and not cfg.mx else 0
         assert not self.epilogue_quant or cfg.fp8 or cfg.mx, "epilogue quantisation belongs to the one-byte recipes"
         # blockwise fp8 (default there): the weight gradients also run on E4M3 codes, quantised 128x1 down the token
