@@ -56,11 +56,13 @@ class LayerState:
         # output, the next GEMM's operand (Sec. 5.4.2); off = stand-alone quantiser calls
         # (MXFP8: the 1x32 codes and the 32x1 copy for the weight gradients; row counts are on the 128-row grid there)
         self.epilogue_quant = bool(cfg.fp8 or cfg.mx) if epilogue_quant is None else bool(epilogue_quant)
-        # blockwise calls of few rows are served by small tiles, where the copies are a launch of their own anyway: unless the
-        # caller asks, both copies of A and dZ then come from one launch of the two-copy quantiser (the same bits).
+        # blockwise calls: unless the caller asks, both copies of A and dZ come from one launch of the two-copy quantiser (the same
+        # bits): small tiles need a launch for the copies anyway, and the large ones' epilogue is vector-ALU-bound.  The line is
+        # the largest capacity measured.
         # A step, us, epilogue : one launch: T 256 h 512 f 256 E 8 k 2 97 : 95; T 1024 h 1024 f 768 E 16 k 4 222 : 212; T 3072 h 2048
-        # f 1024 E 16 k 4 (14336 rows) 694 : 680
-        self.epilogue_rows = 16384 if epilogue_quant is None and not cfg.mx else 0
+        # f 1024 E 16 k 4 (14336 rows) 694 : 680; T 16384, k 4 h 1024 f 512 E 16 1049 : 1010, k 8 h 2048 f 768 E 32 (135168 rows)
+        # 3869 : 3734, k 8 h 4096 f 1536 E 16 11445 : 11145, k 8 h 7168 f 2048 E 32 24592 : 24502
+        self.epilogue_rows = 135168 if epilogue_quant is None and not cfg.mx else 0
         assert not self.epilogue_quant or cfg.fp8 or cfg.mx, "epilogue quantisation belongs to the one-byte recipes"
         # blockwise fp8 (default there): the weight gradients also run on E4M3 codes, quantised 128x1 down the token
         # dimension inside each expert's 128-aligned row range (Sec. 5.3.2, 5.4.1); off = weight gradients from the
