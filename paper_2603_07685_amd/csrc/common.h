@@ -263,7 +263,7 @@ moe_status moe_quantise_live(moe_ctx* ctx, hipStream_t s, const void* X, int64_t
                              bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col);
 
 // all-fp32 grouped GEMMs (gemm_f32.hip), reached from the public entry points with dt = MOE_F32
-int moe_gg_f32_tile(int num_cu, bool wgrad, int E, int N, int out_cols, int64_t Rcap);   // 64 or 128
+int moe_gg_f32_choice(int num_cu, int mode, int epi, int E, int N, int K, int64_t Rcap);   // the kernel: 64 or 128 (tile of gf_kernel), 3 (gs_kernel)
 moe_status moe_gg_f32_fwd(moe_ctx* ctx, hipStream_t s, const void* A, const void* B, const int32_t* offsets, int E, int N,
                           int K, int64_t Rcap, int swiglu, const float* row_prob, void* C, void* C_act);
 moe_status moe_gg_f32_dgrad(moe_ctx* ctx, hipStream_t s, const void* dC, const void* B, const int32_t* offsets, int E, int N,

@@ -118,7 +118,7 @@ struct gg_args {
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a);
 // Rows from which on a weight gradient on small tiles may split its contraction (set split_cap and partials)
 #define GT_SPLIT_ROWS 24576
-void gt_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
+void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
 // the same for one-byte operands (gemm_tile8.hip); `quant`: the call also asks for quantised copies of its output
 int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg_args& a);
 void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a);

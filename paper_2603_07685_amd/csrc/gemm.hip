@@ -1944,7 +1944,7 @@ extern "C" moe_status moe_grouped_gemm_fwd_gather(moe_ctx* ctx, void* stream, co
     a.out_act = (bf16_t*)C_act;
     a.row_prob = row_prob;
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
-    if (const int tile = gt_tile(ctx, GG_FWD, ge, a)) gt_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, 1, tile, a);
+    if (const int tile = gt_tile(ctx, GG_FWD, ge, a)) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 1, tile, a);
     else if (epi == MOE_EPI_SWIGLU) GG_LAUNCH_G(GG_FWD, GG_EPI_SWIGLU, false, 1);
     else GG_LAUNCH_G(GG_FWD, GG_EPI_STORE, false, 1);
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<fwd, gather>");
@@ -2069,7 +2069,7 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
     }
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_FWD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_FWD, ge, a)) {
-        if (!fp8) gt_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
+        if (!fp8) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
         else gq_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<fwd>");
         return a.out_q ? gg_quantise(ctx, stream, C_act, N / 2, mx, a) : MOE_OK;
@@ -2103,7 +2103,7 @@ extern "C" moe_status moe_grouped_gemm_dgrad_gather(moe_ctx* ctx, void* stream, 
     a.row_prob = row_prob;
     a.dprob_part = dprob_part;
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
-    if (const int tile = gt_tile(ctx, GG_DGRAD, ge, a)) gt_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, 1, tile, a);
+    if (const int tile = gt_tile(ctx, GG_DGRAD, ge, a)) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 1, tile, a);
     else if (Z_saved) GG_LAUNCH_G(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
     else GG_LAUNCH_G(GG_DGRAD, GG_EPI_STORE, false, 1);
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<dgrad, gather>");
@@ -2197,7 +2197,7 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
     }
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_DGRAD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_DGRAD, ge, a)) {
-        if (!fp8) gt_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
+        if (!fp8) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
         else gq_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<dgrad>");
         return a.out_q ? gg_quantise(ctx, stream, dA, 2 * K, mx, a) : MOE_OK;
@@ -2266,7 +2266,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
         if (!mx && !bw && Rcap > GT_SPLIT_ROWS) a.split_cap = slices((size_t)N * K * sizeof(float));
         if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
-        else gt_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
+        else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;
     }
@@ -2323,6 +2323,27 @@ __global__ __launch_bounds__(256) void gate_add_kernel(const f32x4_t* __restrict
     }
 }
 
+// A gate call's kernel: a tile of gate_kernel, or (-1) the 256 x 256 one with the contraction in `pieces`, as many as `room` bytes hold
+static int gate_choose(int64_t cu, int T, int E, int h, size_t room, int64_t& pieces) {
+    const int64_t tiles = ceil_div64(T, GG_BM) * ceil_div64(E, GG_BN);
+    const size_t one = (size_t)T * E * sizeof(float);
+    pieces = cu / tiles;
+    if (pieces > h / 64 / GATE_MIN_STAGES) pieces = h / 64 / GATE_MIN_STAGES;
+    if (pieces > (int64_t)(room / one)) pieces = (int64_t)(room / one);
+    if (pieces > 1) {   // (pieces of whole stages may need fewer: 81 stages in 10 pieces of 9 would leave the tenth empty)
+        const int64_t stages = h / 64, each = (stages + pieces - 1) / pieces;
+        pieces = (stages + each - 1) / each;
+    }
+    if (pieces < 2 || GG_BF16_NW != 4) pieces = 1;   // (the four-wave body's output step is the one that knows of pieces)
+    // This one's time from its stages, the launches and the bytes of X and of the partial results (16384, 256, 7168:
+    // 86 measured, 79 by this; 4096, 256, 7168: 39.5, 37; 2048, 64, 4096: 25, 27), the other's from its tiles
+    double us = 0;
+    const int tile = moe_gate_tile((int)cu, T, E, h, &us);
+    const double bytes = 2.0 * T * h + (pieces > 1 ? 8.0 * pieces * T * E : 0.0);
+    const double rounds = __builtin_ceil((double)tiles * pieces / cu);
+    return tile >= 0 && us < 14 + rounds * 1.45 * (double)ceil_div64(h / 64, pieces) + bytes / 15e6 ? tile : -1;
+}
+
 extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, const void* Wr, int T, int E, int h,
                                     float* logits) {
     if (!ctx) return MOE_ERR_ARG;
@@ -2332,23 +2353,10 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
     if (st != MOE_OK) return st;
     if (h % 64) MOE_FAIL(ctx, MOE_ERR_UNSUPPORTED, "moe_gate_gemm: h=%d must be a multiple of 64", h);
     gg_args a = gg_make(ctx, X, Wr, nullptr, 1, E, h, T, logits);
-    const int64_t tiles = ceil_div64(T, GG_BM) * ceil_div64(E, GG_BN), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
-    const size_t one = (size_t)T * E * sizeof(float), room = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;
-    int64_t pieces = cu / tiles;
-    if (pieces > h / 64 / GATE_MIN_STAGES) pieces = h / 64 / GATE_MIN_STAGES;
-    if (pieces > (int64_t)(room / one)) pieces = (int64_t)(room / one);
-    if (pieces > 1) {   // (pieces of whole stages may need fewer: 81 stages in 10 pieces of 9 would leave the tenth empty)
-        const int64_t stages = h / 64, each = (stages + pieces - 1) / pieces;
-        pieces = (stages + each - 1) / each;
-    }
-    if (pieces < 2 || GG_BF16_NW != 4) pieces = 1;   // (the four-wave body's output step is the one that knows of pieces)
-    // Which kernel: this one's time from its stages, the launches and the bytes of X and of the partial results (16384, 256, 7168:
-    // 86 measured, 79 by this; 4096, 256, 7168: 39.5, 37; 2048, 64, 4096: 25, 27), the other's from its tiles
-    double us = 0;
-    const int tile = moe_gate_tile((int)cu, T, E, h, &us);
-    const double bytes = 2.0 * T * h + (pieces > 1 ? 8.0 * pieces * T * E : 0.0);
-    const double rounds = __builtin_ceil((double)tiles * pieces / cu);
-    if (tile >= 0 && us < 14 + rounds * 1.45 * (double)ceil_div64(h / 64, pieces) + bytes / 15e6) {
+    const size_t room = ctx->ws_bytes > MOE_WS_RESERVED ? ctx->ws_bytes - MOE_WS_RESERVED : 0;
+    int64_t pieces;
+    const int tile = gate_choose(ctx->num_cu > 0 ? ctx->num_cu : 256, T, E, h, room, pieces);
+    if (tile >= 0) {
         moe_gate_launch((hipStream_t)stream, tile, X, Wr, T, E, h, logits);
         MOE_LAUNCH_CHECK(ctx, "gate_kernel");
         return MOE_OK;
@@ -2365,9 +2373,9 @@ extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, c
     return MOE_OK;
 }
 
-// Which kernel serves a grouped GEMM of these sizes on a GPU of num_cu compute units: 0 the 256 x 256 kernel of this file, 1 .. 3
-// as gt_tile and gq_tile say; fp32: 64 or 128.  Host only, and no part of the library's interface: the tests choose their
-// sizes with it.  mode, epi: GG_*; quant: the call asks for quantised copies.
+// Which kernel serves a grouped GEMM of these sizes on a GPU of num_cu compute units: 0 the 256 x 256 kernel of this file, 1 .. 4
+// as gt_tile and gq_tile say; fp32: 64 or 128 gf_kernel on that tile, 3 gs_kernel.  Host only, and no part of the library's interface:
+// the tests choose their sizes with it.  mode, epi: GG_*; quant: the call asks for quantised copies.
 extern "C" int gg_kernel_choice(int num_cu, int mode, int epi, int dt, int quant, int E, int N, int K, long long Rcap) {
     moe_ctx ctx;
     memset(&ctx, 0, sizeof(ctx));
@@ -2378,6 +2386,11 @@ extern "C" int gg_kernel_choice(int num_cu, int mode, int epi, int dt, int quant
     a.N = N;
     a.K = K;
     a.Rcap = Rcap;
-    if (dt == MOE_F32) return moe_gg_f32_tile(num_cu, mode == GG_WGRAD, E, N, mode == GG_FWD ? N : K, Rcap);
+    if (dt == MOE_F32) return moe_gg_f32_choice(num_cu, mode, epi, E, N, K, Rcap);
     return dt == MOE_BF16 ? gt_tile(&ctx, mode, epi, a) : gq_tile(&ctx, mode, epi, dt == MOE_MXFP8_E4M3, quant != 0, a);
+}
+// The same for a gate call in a context with ws_bytes of workspace: gate_choose's answer
+extern "C" int gg_gate_choice(int num_cu, int T, int E, int h, size_t ws_bytes) {
+    int64_t pieces;
+    return gate_choose(num_cu, T, E, h, ws_bytes > MOE_WS_RESERVED ? ws_bytes - MOE_WS_RESERVED : 0, pieces);
 }

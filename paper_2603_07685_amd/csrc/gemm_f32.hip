@@ -14,7 +14,7 @@
 // per stage: a stage is BT/32 squared blocks x 4 MFMAs of 32 cycles per wave against (BT = 128) 16 KB of operands, so
 // registers hold the next stage's operands while two LDS buffers alternate, one barrier per stage, and the loads have a
 // whole stage (2048 cycles at BT = 128) to arrive.  BT = 64 trades operand reuse for four times as many workgroups where
-// the larger tile would leave compute units idle (moe_gg_f32_tile below).
+// the larger tile would leave compute units idle (gf_tile below).
 // LDS: an operand whose contraction index is contiguous in memory is kept [row][16] with a pitch of 20 floats, one
 // 16-byte read giving a lane contraction elements 4 g .. 4 g + 3 (g = lane / 16; MFMA step j takes element j of every
 // lane, the order inside a stage is free); the other kind is kept [16][column] with a pitch of BT + 4 floats, read
@@ -622,11 +622,14 @@ __global__ __launch_bounds__(F32_THREADS, BM == 64 ? 2 : 1) void gs_kernel(const
 // T 256, h 128, f 256: 106 us against 178; T 2048, h 1024, f 512: 537 against 665; T 4096, h 1024, f 512: 906 against 1042;
 // (all calls on gf_kernel) T 8192, h 1024, f 1024 (8 tiles per unit in fc1): 3.04 ms against 3.05; T 8192, h 2048, f 2048: 11.4 against 10.7;
 // T 8192, h 4096, f 2048: 22.6 against 20.7 ms (119 TFLOP/s).
-int moe_gg_f32_tile(int num_cu, bool wgrad, int E, int N, int out_cols, int64_t Rcap) {
+static int gf_tile(int num_cu, bool wgrad, int E, int N, int out_cols, int64_t Rcap) {
     const int64_t cols = ceil_div64(out_cols, 128);
     const int64_t tiles = wgrad ? (int64_t)E * ceil_div64(N, 128) * cols : ceil_div64(Rcap, 128) * cols;
     return tiles >= 8 * (int64_t)(num_cu > 0 ? num_cu : 256) ? 128 : 64;
 }
+
+// rows of 16-byte pieces
+static bool gf_vec(int epi, int N, int K) { return N % 4 == 0 && K % 4 == 0 && (epi != GF_SWIGLU || N % 8 == 0); }
 
 // Which kernel: the split needs enough work per workgroup and workgroups for most of the compute units.  Measured (us, gf : gs):
 //   forward / data gradient: 64 x 128 tiles for 0.6 of the units and a contraction of 320 (SwiGLU backward 512).  128 tiles: T 300
@@ -646,17 +649,28 @@ static bool gs_serves(int num_cu, int mode, int epi, const gf_args& a) {
     return tiles >= 0.6 * cu && c >= (epi == GF_SWIGLU_BWD ? 512 : 320);
 }
 
+// 64 or 128: gf_kernel on tiles of that size; 3: gs_kernel (bases, too, on 16 bytes then)
+int moe_gg_f32_choice(int num_cu, int mode, int epi, int E, int N, int K, int64_t Rcap) {
+    gf_args a = {};
+    a.E = E;
+    a.N = N;
+    a.K = K;
+    a.Rcap = Rcap;
+    if (gf_vec(epi, N, K) && gs_serves(num_cu, mode, epi, a)) return 3;
+    return gf_tile(num_cu, mode == GF_WGRAD, E, N, mode == GF_FWD ? N : K, Rcap);
+}
+
 template <int MODE, int EPI>
 static moe_status gf_launch(moe_ctx* ctx, hipStream_t s, const char* who, const gf_args& a) {
     if (a.E > F32_MAX_E) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: E > %d", who, F32_MAX_E);
     const int out_cols = EPI == GF_SWIGLU ? a.N : (MODE == GF_FWD ? a.N : a.K);
-    const int bt = moe_gg_f32_tile(ctx->num_cu, MODE == GF_WGRAD, a.E, a.N, out_cols, a.Rcap);
+    const int bt = gf_tile(ctx->num_cu, MODE == GF_WGRAD, a.E, a.N, out_cols, a.Rcap);
     const int64_t tiles_j = EPI == GF_SWIGLU ? ceil_div64(a.N / 2, bt / 2) : ceil_div64(out_cols, bt);
     // (every expert may end in a partly filled row tile)
     const int64_t grid = ceil_div64(tiles_j * (MODE == GF_WGRAD ? a.E * ceil_div64(a.N, bt) : ceil_div64(a.Rcap, bt) + a.E), 8) * 8;
     if (grid > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: problem too large for the fp32 path", who);
     const uintptr_t bits = (uintptr_t)a.P | (uintptr_t)a.Q | (uintptr_t)a.out | (uintptr_t)a.out_act | (uintptr_t)a.Zsaved;
-    const bool vec = a.N % 4 == 0 && a.K % 4 == 0 && (EPI != GF_SWIGLU || a.N % 8 == 0) && bits % 16 == 0;
+    const bool vec = gf_vec(EPI, a.N, a.K) && bits % 16 == 0;
     const dim3 g((unsigned)grid), b(F32_THREADS);
     constexpr int GS_BM = MODE == GF_WGRAD ? 128 : 64;
     if (vec && gs_serves(ctx->num_cu, MODE, EPI, a)) {

@@ -388,8 +388,18 @@ __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 0 = the 256 x 256
-// kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted to measured calls
+// Weight gradients of more than two tiles per unit and short contractions, mostly output: one buffer, three workgroups per
+// unit (fc2, fc1; two buffers : one; h 3072 f 1024 E 32, T 128 k 4 75 : 59, 143 : 109; h 4096 f 1536 E 16, T 64 k 8 63 : 45, 127 : 93;
+// h 1024 f 704 E 16 k 4, T 256 13.8 : 10.8, 19.1 : 15.3, T 1024 19.3 : 17.0, 28.2 : 24.1).  A hot expert's workgroups walk their
+// rows at half the pace then, hence the bound on the rows (rank^-1.2 loads, h 512 f 512 E 64 k 4: T 1024 h 2048 E 16 73 : 72, T 2048
+// 42 : 46, 49 : 46, T 4096 72 : 82, 74 : 79).
+static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
+    const int64_t tiles = a.E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
+    return tiles > 2 * cu && a.Rcap <= 256 * (int64_t)a.E && a.Rcap <= 6144;
+}
+
+// Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 4 = 128 x 128 on one
+// (gt_one_buffer), 0 = the 256 x 256 kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted to measured calls
 // (MI355X, bf16; rows of an expert unknown on the host, so each of several is given half a partly filled row tile, and at
 // least one tile):
 //   256 x 256: one workgroup per compute unit, whole rounds of tiles (a tenth of one over is not rounded up: it comes from
@@ -425,20 +435,10 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     const double t256 = r256 * (1.5 * stages + (epi == GG_EPI_SWIGLU_BWD ? 35 : 15)) + (mode == GG_WGRAD ? 6 : 0);
     const double t128 = (r128 + __builtin_ceil(r128)) * (0.62 * stages + 4);
     if (t128 > (mode == GG_WGRAD ? 1.1 : 1.0) * t256) return 0;   // (weight gradients of a few stages are better than the estimate)
-    if (mode == GG_WGRAD) return 2;
+    if (mode == GG_WGRAD) return gt_one_buffer(ctx, a) ? 4 : 2;
     const double n64 = __builtin_ceil(cols / 128) * row_tiles(64);
     if (R <= 48 * E || n64 <= 2 * cu) return 3;
     return r128 < (epi == GG_EPI_SWIGLU_BWD ? 1.5 : 1) ? 1 : 2;
-}
-
-// Weight gradients of more than two tiles per unit and short contractions, mostly output: one buffer, three workgroups per
-// unit (fc2, fc1; two buffers : one; h 3072 f 1024 E 32, T 128 k 4 75 : 59, 143 : 109; h 4096 f 1536 E 16, T 64 k 8 63 : 45, 127 : 93;
-// h 1024 f 704 E 16 k 4, T 256 13.8 : 10.8, 19.1 : 15.3, T 1024 19.3 : 17.0, 28.2 : 24.1).  A hot expert's workgroups walk their
-// rows at half the pace then, hence the bound on the rows (rank^-1.2 loads, h 512 f 512 E 64 k 4: T 1024 h 2048 E 16 73 : 72, T 2048
-// 42 : 46, 49 : 46, T 4096 72 : 82, 74 : 79).
-static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
-    const int64_t tiles = a.E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
-    return tiles > 2 * cu && a.Rcap <= 256 * (int64_t)a.E && a.Rcap <= 6144;
 }
 
 template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF, bool SPLIT = false>
@@ -464,10 +464,10 @@ static void gt_wgrad(hipStream_t s, int gath, const gg_args& a) {
         hipLaunchKernelGGL(gt_add_kernel<F32>, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, a);
     }
 }
-void gt_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
+void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     if (mode == GG_WGRAD) {
         if (a.split_cap >= 2) out_f32 ? gt_wgrad<true, true, 2>(s, gath, a) : gt_wgrad<false, true, 2>(s, gath, a);
-        else if (gt_one_buffer(ctx, a)) out_f32 ? gt_wgrad<true, false, 1>(s, gath, a) : gt_wgrad<false, false, 1>(s, gath, a);
+        else if (tile == 4) out_f32 ? gt_wgrad<true, false, 1>(s, gath, a) : gt_wgrad<false, false, 1>(s, gath, a);
         else out_f32 ? gt_wgrad<true, false, 2>(s, gath, a) : gt_wgrad<false, false, 2>(s, gath, a);
     } else if (mode == GG_FWD) {
         if (epi == GG_EPI_SWIGLU) gath ? gt_rows<GG_FWD, GG_EPI_SWIGLU, 1>(s, tile, a) : gt_rows<GG_FWD, GG_EPI_SWIGLU, 0>(s, tile, a);

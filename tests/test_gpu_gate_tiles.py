@@ -9,13 +9,17 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
-@pytest.mark.parametrize("T,E,h", [(17, 8, 64), (33, 24, 192), (300, 200, 4160),       # 16 x 16
-                                   (499, 248, 7168), (1000, 128, 2112),                # 32 x 16
-                                   (4000, 40, 2048), (3971, 40, 1984),                 # 32 x 32
-                                   (16384, 32, 512), (16001, 24, 576),                 # 64 x 32
-                                   (8000, 104, 512), (7999, 104, 448), (15991, 64, 4096),   # 64 x 64
-                                   (16383, 128, 448), (16001, 248, 1088),              # 64 x 128
-                                   (2048, 256, 7168), (4100, 248, 6720)])              # 256 x 256, pieces
+# T, E, h by the number of the tile that takes them (-1: the 256 x 256 kernel, in pieces)
+SIZES = {0: [(17, 8, 64), (33, 24, 192), (300, 200, 4160)],                  # 16 x 16
+         1: [(499, 248, 7168), (1000, 128, 2112)],                           # 32 x 16
+         2: [(4000, 40, 2048), (3971, 40, 1984)],                            # 32 x 32
+         3: [(16384, 32, 512), (16001, 24, 576)],                            # 64 x 32
+         4: [(8000, 104, 512), (7999, 104, 448), (15991, 64, 4096)],         # 64 x 64
+         5: [(16383, 128, 448), (16001, 248, 1088)],                         # 64 x 128
+         -1: [(2048, 256, 7168), (4100, 248, 6720)]}
+
+
+@pytest.mark.parametrize("T,E,h", sum(SIZES.values(), []))
 def test_gate_gemm_tiles(T, E, h):
     from paper_2603_07685_amd import binding as B
     ctx = B.Context(T, 1, E, h, max(E, 8))

@@ -1,7 +1,7 @@
 """Every kernel behind the grouped-GEMM calls on the same rows.  Which one serves a call follows from its sizes, the row capacity
 among them, so a call whose rows lie in a larger tensor runs on another kernel: all of them have to give the same bits (they add
-a result's products in the same order), leave what lies behind the rows alone, and lie within the rounding of the output type of
-64-bit sums.  The library is asked which kernel a capacity selects; where its rules change so that one is no longer reached, the
+a result's products in the same order; the fp32 kernel that splits its operands into bf16 parts does not, and is held to the 64-bit sums
+alone), leave what lies behind the rows alone, and lie within the rounding of the output type of 64-bit sums.  The library is asked which kernel a capacity selects; where its rules change so that one is no longer reached, the
 tests fail instead of testing less."""
 import ctypes
 
@@ -23,7 +23,7 @@ ROWS = {
     ("bf16", FWD, SWIGLU, 336, 192): (FEW, {0, 1, 2, 3}),
     ("bf16", DGRAD, STORE, 192, 264): (FEW, {0, 1, 2, 3}),
     ("bf16", DGRAD, SWIGLU_BWD, 2944, 264): (FEW, {0, 1, 2, 3}),
-    ("bf16", WGRAD, STORE, 1016, 1000): ([70, 0, 150, 1, 64, 90, 129, 40, 100, 100, 63, 150, 60, 80, 110, 33], {0, 2}),   # (none above
+    ("bf16", WGRAD, STORE, 1016, 1000): ([70, 0, 150, 1, 64, 90, 129, 40, 100, 100, 63, 150, 60, 80, 110, 33], {0, 2, 4}),   # (none above
     # twice the mean: those the 256 x 256 kernel would cut)
     ("fp8", FWD, STORE, 768, 256): (SIX, {0, 1, 2}),
     ("fp8", FWD, SWIGLU, 768, 768): (SIX, {0, 1, 2}),
@@ -45,11 +45,12 @@ ROWS = {
     ("f32", DGRAD, SWIGLU_BWD, 99, 259): (SIX, {64, 128}),
     ("f32", WGRAD, STORE, 300, 260): (SIX, {64}),
     ("f32", WGRAD, STORE, 299, 259): (SIX, {64}),
-    ("f32", WGRAD, STORE, 1916, 1660): (SIX + [3] * 6, {128}),
+    ("f32", WGRAD, STORE, 1916, 1660): (SIX + [3] * 6, {3, 128}),
     ("f32", WGRAD, STORE, 1915, 1659): (SIX + [3] * 6, {128}),
 }
 CASES = sorted(ROWS)
 DT = {"bf16": 0, "fp8": 1, "f32": 2, "mx": 3}
+PARTS = 3   # fp32: the kernel on bf16 parts
 
 
 def _lib():
@@ -78,6 +79,26 @@ def test_every_kernel_is_reached(case):
     assert set(_capacities(case, 0)) == ROWS[case][1]
     if case[0] in ("fp8", "mx") and case[2] != STORE:
         assert set(_capacities(case, 1)) == ROWS[case][1]
+
+
+def test_other_tests_sizes_reach_their_kernels():
+    """The tests of single kernels take sizes that those kernels serve."""
+    import test_gpu_f32_split
+    import test_gpu_gate_tiles
+    import test_gpu_wgrad_single
+    f = _lib()
+    for counts, N, K in test_gpu_f32_split.CASES:
+        for mode, epi in ((FWD, STORE), (FWD, SWIGLU), (DGRAD, STORE), (DGRAD, SWIGLU_BWD), (WGRAD, STORE)):
+            assert f(256, mode, epi, DT["f32"], 0, len(counts), N, K, sum(counts) + 3) == PARTS, (counts, N, K, mode, epi)
+    for counts, N, K in test_gpu_wgrad_single.CASES:
+        assert f(256, WGRAD, STORE, DT["bf16"], 0, len(counts), N, K, sum(counts) + 9) == 4, (counts, N, K)
+    from paper_2603_07685_amd import build
+    lib = ctypes.CDLL(build.LIB)
+    lib.gg_gate_choice.argtypes = [ctypes.c_int] * 4 + [ctypes.c_size_t]
+    lib.moe_workspace_bytes.restype = ctypes.c_size_t
+    for tile, sizes in test_gpu_gate_tiles.SIZES.items():
+        for T, E, h in sizes:
+            assert lib.gg_gate_choice(256, T, E, h, lib.moe_workspace_bytes(T, 1, E, h, max(E, 8))) == tile, (T, E, h)
 
 
 @pytest.fixture(scope="module")
@@ -282,12 +303,16 @@ def test_all_kernels_agree(B, ctx, case, gather):
         res = {t: _run(B, ctx, d, r, gather, out_f32) for t, r in caps.items()}
         torch.cuda.synchronize()
         assert ctx.poll_error() == 0
-        first = res[min(res)]
+        first = res[min(t for t in res if dt != "f32" or t != PARTS)]
         bound = 2e-6 * np.sqrt(max(d.counts)) if out_f32 and dt == "bf16" else BOUND[dt]
-        for got, ref in zip(first, _reference(d, gather)):
-            g = got.double().sum(1) if ref.dim() == 1 else got.double()
-            assert ((g - ref).norm() / ref.norm()).item() <= (4 * BOUND[dt] if ref.dim() == 1 else bound)
+        refs = _reference(d, gather)
+        for outs in [first] + ([res[PARTS]] if dt == "f32" and PARTS in res else []):
+            for got, ref in zip(outs, refs):
+                g = got.double().sum(1) if ref.dim() == 1 else got.double()
+                assert ((g - ref).norm() / ref.norm()).item() <= (4 * BOUND[dt] if ref.dim() == 1 else bound)
         for t, outs in res.items():
+            if dt == "f32" and t == PARTS:
+                continue
             for i, (a, b) in enumerate(zip(first, outs)):
                 if a.dtype == F32 and mode == DGRAD and i == 1 and a.shape[1] == 2 * ((K + 255) // 256):
                     # partial <dA, act> of a row: other groups of columns, the same fp32 terms
