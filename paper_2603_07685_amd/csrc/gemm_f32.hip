@@ -264,10 +264,13 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
 // ---------------------------------------------------------------------------
 // The same GEMMs on the bf16 matrix instruction, without losing a bit of the operands: every fp32 element is the sum of
 // three bf16 numbers, x = hi + mid + lo (each the remainder rounded to 8 bits), and a product of two elements is the sum of
-// the nine products of their parts, each exact in the matrix unit.  Six are taken; the other three (lo mid, mid lo, lo lo)
-// are together at most 2^-23 of the product of the magnitudes, in the mean 2^-26, where one rounding of the sum is 2^-24 of the sum so far and
-// there are hundreds (contractions of up to GS_FULL stages take all nine).  Sums in fp32, in the matrix unit's four roundings
-// per 32 elements instead of 32: against 64 bits the layer below has 3.6e-7 relative error, 8.7e-7 on the fp32 instruction.
+// the nine products of their parts, each exact in the matrix unit.  Eight are taken; the ninth, lo lo, is at most 2^-34 of the
+// product, where a rounding of the sum is 2^-24 of the sum so far.  (lo mid and mid lo are up to 2^-24 of it together, and count where
+// few terms of a sum are not zero.)  Sums in fp32, in the matrix unit's four roundings per 32 elements instead of 32.  Error against 64
+// bits in units of 2^-24 sum |ab|, root mean square and largest of some million sums, fp32 instruction : six products : these
+// eight; one term that is not zero 0.425 : 0.436 : 0.425, 1.00 : 1.71 : 1.01; two 0.44 : 0.37 : 0.36, 1.99 : 2.9 : 2.6 (the unit drops what
+// lies below the last place of the larger product); four 0.45 : 0.30 : 0.29, 3.6 : 3.2 : 3.2; 32 0.47 : 0.20 : 0.20, 6.0 : 3.4 : 3.4.  The
+// layer below: 8.7e-7 relative error on the fp32 instruction, 3.5e-7 here.
 //
 // BM x 128 tiles (BM = 64; weight gradients 128, whose contraction-major rows then fill 256-byte bank lines), four waves as
 // 2 x 2, stages of 32 contraction elements.  Global loads run two to three stages ahead into registers; each element is split
@@ -275,13 +278,13 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
 // one barrier per stage.  What shaped it: a vector instruction issues for free beside a 32 x 32 x 16 MFMA up to about five
 // (16 x 16 x 32: two), if it does not wait for the one before it (8 cycles there); v_dot2_f32_bf16, which would give a
 // remainder in one instruction, shares the matrix pipe and doubled the time of a stage.
-// Bound: per 128 x 128 x 32 stage and unit 1.45 us, of which the MFMAs alone are 0.88 at the clock the card holds, loads add
-// 0.3, splitting 0.25; 6 us around a tile.  Measured (us a call, gf_kernel : this), T 2048, h 1024, f 512, 8 experts, top-2: fc1 + SwiGLU 113 : 88, fc2 61 :
-// 50, weight gradients 54, 99 : 41, 74 (rank^-1.2 loads 151, 291 : 95, 179), fc2 data gradient + SwiGLU backward 74 : 63,
-// fc1 data gradient 110 : 89; the step 507 -> 405.
+// Bound: the MFMAs of eight products, 1.17 us per 128 x 128 x 32 stage and unit at the clock the card holds, with loads and splitting
+// mostly beside them; 6 us around a tile.  Measured (us a call, gf_kernel : six products : these eight), T 2048, h 1024, f 512, 8
+// experts, top-2: fc1 + SwiGLU 104 : 84 : 92, fc2 55 : 45 : 48, weight gradients 72, 141 : 47, 92 : 50, 97 (rank^-1.2 loads 132, 260 : 76,
+// 149 : 82, 162), fc2 data gradient + SwiGLU backward 70 : 57 : 60, fc1 data gradient 101 : 83 : 91; the
+// step 504 : 408 : 434.
 // ---------------------------------------------------------------------------
 #define GS_BN 128
-#define GS_FULL 8   // contractions of at most this many stages (of 32) take all nine products
 
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x8_t __attribute__((ext_vector_type(8)));
@@ -515,11 +518,11 @@ __global__ __launch_bounds__(F32_THREADS, BM == 64 ? 2 : 1) void gs_kernel(const
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
     };
-    const bool full = KT <= GS_FULL;
     auto stage = [&](int s, auto parity) __attribute__((always_inline)) {
         constexpr int b = decltype(parity)::value;          // s & 1: this stage's buffer, the set of the loads in flight
-        // work between the MFMAs of the first five products: the splitting of stage s + 1 and the loads of stage s + 3
-        constexpr int W = PIECES * (UNITS + 1), M = 5 * NM;
+        // work between the MFMAs of the first seven products (weight gradients: six, 3 % faster there, 2 % slower elsewhere): the
+        // splitting of stage s + 1 and the loads of stage s + 3
+        constexpr int W = PIECES * (UNITS + 1), M = (MODE == GF_WGRAD ? 6 : 7) * NM;
         auto work = [&](int m) __attribute__((always_inline)) {
 #pragma unroll
             for (int w = 0; w < W; ++w)
@@ -544,11 +547,8 @@ __global__ __launch_bounds__(F32_THREADS, BM == 64 ? 2 : 1) void gs_kernel(const
         products(2, 0, [&](int m) __attribute__((always_inline)) { reads_p(m, b, 0); work(2 * NM + m); });
         products(0, 0, [&](int m) __attribute__((always_inline)) { reads_q(m, b, 2); work(3 * NM + m); });
         products(0, 1, [&](int m) __attribute__((always_inline)) { work(4 * NM + m); });
-        if (full) {
-            products(2, 2, [](int) {});
-            products(2, 1, [](int) {});
-            products(1, 2, [](int) {});
-        }
+        products(2, 1, [&](int m) __attribute__((always_inline)) { work(5 * NM + m); });
+        products(1, 2, [&](int m) __attribute__((always_inline)) { work(6 * NM + m); });
         barrier();                                          // stage s + 1 is in its buffer, this one's has been read
         products(0, 2, [&](int m) __attribute__((always_inline)) { reads_p(m, b ^ 1, 1); reads_q(m, b ^ 1, 1); });
     };
@@ -631,22 +631,30 @@ static int gf_tile(int num_cu, bool wgrad, int E, int N, int out_cols, int64_t R
 // rows of 16-byte pieces
 static bool gf_vec(int epi, int N, int K) { return N % 4 == 0 && K % 4 == 0 && (epi != GF_SWIGLU || N % 8 == 0); }
 
-// Which kernel: the split needs enough work per workgroup and workgroups for most of the compute units.  Measured (us, gf : gs):
+// Which kernel: the split needs enough work per workgroup, workgroups for most of the compute units, and columns that fill its
+// wider tiles.  Measured (us, gf : gs):
 //   forward / data gradient: 64 x 128 tiles for 0.6 of the units and a contraction of 320 (SwiGLU backward 512).  128 tiles: T 300
-//     h 256 f 512 E 16 k 2 14 : 17, T 100 h 2048 f 1024 E 8 k 2 77 : 79; 156: T 1000 h 512 f 256 E 32 k 4 fc2 dgrad 31 : 28;
-//     512: T 30 h 1024 f 4096 E 8 k 2 92 : 71.  Contraction 320: T 2000 f 704 E 8 k 4 92 : 73 (fc2 dgrad there, 320: 57 : 60); 256:
-//     T 8192 h 192 E 8 k 4 45 : 52.
-//   weight gradient: 128 x 128 tiles that fill their last round to three quarters (T 4096 h 1024 f 1536 E 4 k 1, 384 tiles 144 : 127, 768
-//     274 : 200; T 2000 h 320 f 704, 144 tiles 54 : 59, 264 92 : 112) and 384 rows per expert in the mean (125: 20 : 24, 34 : 41).
+//     h 256 f 512 E 16 k 2 fc2 dgrad 13 : 16, T 100 h 2048 f 1024 E 8 k 2 61 : 70; 158: T 1000 h 512 f 256 E 32 k 4 fc2 dgrad 30 : 26;
+//     320: T 30 h 1024 f 4096 E 8 k 2 80 : 59.  Contraction 320: T 2000 f 704 E 8 k 4 82 : 68 (fc2 dgrad there, 320: 51 : 55); 256:
+//     T 8192 h 192 f 256 E 8 k 4 fc2 41 : 44.
+//   weight gradient: 128 x 128 tiles that fill their rounds to three quarters (T 4096 h 1024 f 1536 E 4 k 1, 384 tiles 196 : 170; T 2048
+//     h 768 f 512 E 8 k 2, 192 57 : 51; T 2000 h 320 f 704 E 8 k 4, 144 84 : 88, 264 148 : 176), from 32 experts on, the largest of which is
+//     further above the mean and sets the time of a round, to seven eighths (192 tiles: T 8192 h 384 f 128 E 64 k 4 45 : 54, T 8192 h 512
+//     f 192 E 32 k 2 45 : 54), and 384 rows per expert in the mean (T 3072 h 512 f 512 E 16 k 2 49 : 45, T 2048 33.8 : 34.5).
+//   columns (and the weight gradient's rows) whose 64-wide tiles cover at least 0.8 of what the 128-wide ones do: 192 of 256 T 8192
+//     h 192 f 256 E 8 k 4 fc1 dgrad 74 : 84, E 64 weight gradients 45, 72 : 56, 84; 320 of 384 T 4096 h 320 f 512 E 16 k 4 fc2 64 : 58,
+//     weight gradients 107, 159 : 99, 144.
 static bool gs_serves(int num_cu, int mode, int epi, const gf_args& a) {
     const double cu = num_cu > 0 ? num_cu : 256;
+    auto cover = [](int64_t cols, int bn) { return (double)ceil_div64(cols, bn / 2) / (2 * ceil_div64(cols, bn)); };
     if (mode == GF_WGRAD) {
         const double n = (double)a.E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128), rounds = __builtin_ceil(n / cu);
-        return (double)a.Rcap >= 384.0 * a.E && n >= 0.75 * cu * rounds;
+        return (double)a.Rcap >= 384.0 * a.E && n >= (a.E < 32 ? 0.75 : 0.875) * cu * rounds && cover(a.N, 128) * cover(a.K, 128) >= 0.8;
     }
-    const int64_t tiles = (ceil_div64(a.Rcap, 64) + a.E / 2) * (epi == GF_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(mode == GF_FWD ? a.N : a.K, GS_BN));
-    const int64_t c = mode == GF_FWD ? a.K : a.N;
-    return tiles >= 0.6 * cu && c >= (epi == GF_SWIGLU_BWD ? 512 : 320);
+    const int64_t cols = epi == GF_SWIGLU ? a.N / 2 : mode == GF_FWD ? a.N : a.K, c = mode == GF_FWD ? a.K : a.N;
+    const int bn = epi == GF_SWIGLU ? 64 : GS_BN;
+    const int64_t tiles = (ceil_div64(a.Rcap, 64) + a.E / 2) * ceil_div64(cols, bn);
+    return tiles >= 0.6 * cu && c >= (epi == GF_SWIGLU_BWD ? 512 : 320) && cover(cols, bn) >= 0.8;
 }
 
 // 64 or 128: gf_kernel on tiles of that size; 3: gs_kernel (bases, too, on 16 bytes then)
