@@ -389,13 +389,18 @@ __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
 // host side
 // ---------------------------------------------------------------------------
 // Weight gradients of more than two tiles per unit and short contractions, mostly output: one buffer, three workgroups per
-// unit (fc2, fc1; two buffers : one; h 3072 f 1024 E 32, T 128 k 4 75 : 59, 143 : 109; h 4096 f 1536 E 16, T 64 k 8 63 : 45, 127 : 93;
-// h 1024 f 704 E 16 k 4, T 256 13.8 : 10.8, 19.1 : 15.3, T 1024 19.3 : 17.0, 28.2 : 24.1).  A hot expert's workgroups walk their
-// rows at half the pace then, hence the bound on the rows (rank^-1.2 loads, h 512 f 512 E 64 k 4: T 1024 h 2048 E 16 73 : 72, T 2048
-// 42 : 46, 49 : 46, T 4096 72 : 82, 74 : 79).
+// unit (fc2, fc1; two buffers : one; h 3072 f 1024 E 32, T 128 k 4 75 : 59, 143 : 109; h 4096 f 1536 E 16, T 64 k 8 63 : 45, 127 : 93).
+// A hot expert's workgroups walk their rows at half the pace then, which the host cannot see; it shows once that walk is long beside
+// the output of all tiles.  Hence at most 160 rows in all for every tile per unit: up to there no load was slower, also with 95 % of
+// the rows on one expert; at 192 one such was (512 x 512 of 40 experts, 9.4 : 9.9), from 256 on most.  Two buffers : one, equal loads |
+// half on one expert | 95 %, R rows in all (per tile and unit), N x K of E experts: 512 x 512 of 64, R 512 (128) 13 : 11 | 13 : 10 | 12 : 10, R 1024 (256) 13 : 11 | 14 : 11 |
+// 14 : 16, R 4096 (1024) 14 : 12 | 23 : 27 | 39 : 46; 768 x 512 of 24, R 320 (142) 10 : 8 | 10 : 8 | 10 : 8.4, R 864 (384) 10 : 8 |
+// 10 : 9 | 11.5 : 12.4; 2048 x 1024 of 8, R 512 (128) 14 : 12 | 16 : 14 | 22 : 21, R 1024 (256) 15 : 13 | 22 : 21 | 32 : 33.5, R 2048 (512) 18 : 17 |
+// 32 : 34 | 51 : 56; 1024 x 1024 of 64, R 2304 (144) 38 : 27 | 50 : 38 | 61 : 48.  (256 rows per expert and 6144 in all are the most that
+// was measured.)
 static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
     const int64_t tiles = a.E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
-    return tiles > 2 * cu && a.Rcap <= 256 * (int64_t)a.E && a.Rcap <= 6144;
+    return tiles > 2 * cu && a.Rcap * cu <= 160 * tiles && a.Rcap <= 256 * (int64_t)a.E && a.Rcap <= 6144;
 }
 
 // Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 4 = 128 x 128 on one

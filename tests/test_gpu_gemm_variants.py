@@ -23,7 +23,7 @@ ROWS = {
     ("bf16", FWD, SWIGLU, 336, 192): (FEW, {0, 1, 2, 3}),
     ("bf16", DGRAD, STORE, 192, 264): (FEW, {0, 1, 2, 3}),
     ("bf16", DGRAD, SWIGLU_BWD, 2944, 264): (FEW, {0, 1, 2, 3}),
-    ("bf16", WGRAD, STORE, 1016, 1000): ([70, 0, 150, 1, 64, 90, 129, 40, 100, 100, 63, 150, 60, 80, 110, 33], {0, 2, 4}),   # (none above
+    ("bf16", WGRAD, STORE, 1528, 1512): ([70, 0, 150, 1, 64, 90, 129, 40, 100, 100, 63, 150, 60, 80, 110, 33], {0, 2, 4}),   # (none above
     # twice the mean: those the 256 x 256 kernel would cut)
     ("fp8", FWD, STORE, 768, 256): (SIX, {0, 1, 2}),
     ("fp8", FWD, SWIGLU, 768, 768): (SIX, {0, 1, 2}),
