@@ -77,7 +77,9 @@ def parse():
     ap.add_argument("--bf16-wgrad", action="store_true",
                     help="blockwise fp8 workloads: weight gradients from the bf16 tensors instead of the 128x1 E4M3 copies")
     ap.add_argument("--no-epilogue-quant", action="store_true",
-                    help="one-byte recipes: quantise A and dZ by stand-alone quantiser calls instead of with the GEMM calls")
+                    help="one-byte recipes: quantise A and dZ by quantiser calls (blockwise with one-byte weight gradients: the default)")
+    ap.add_argument("--epilogue-quant", action="store_true",
+                    help="one-byte recipes: quantise A and dZ with the GEMM calls (MXFP8, and blockwise with --bf16-wgrad: the default)")
     ap.add_argument("--gather", action="store_true",
                     help="bf16 workloads: no permuted copy of the tokens (with --eq2: nor of dY); the GEMMs that would read it "
                          "fetch the rows of X / dY through the row map")
@@ -85,7 +87,10 @@ def parse():
                     help="only the timed step and the box reference (profiler runs: no second pass with gathered operands)")
     ap.add_argument("--eq2", action="store_true",
                     help="memory-efficient permutation: routing weights applied in the fc1 epilogue, plain-sum combine")
-    return ap.parse_args()
+    args = ap.parse_args()
+    if args.epilogue_quant and args.no_epilogue_quant:
+        ap.error("--epilogue-quant and --no-epilogue-quant exclude each other")
+    return args
 
 
 def describe_call(name, args, st):
@@ -314,7 +319,7 @@ def main():
     hin = L.host_inputs(cfg) if small else None
     st = L.LayerState(cfg, hin, variant=args.variant, wgrad_f32=args.wgrad_f32, eq2=args.eq2,
                       fp8_wgrad=False if args.bf16_wgrad else None,
-                      epilogue_quant=False if args.no_epilogue_quant else None, gather=args.gather)
+                      epilogue_quant=False if args.no_epilogue_quant else True if args.epilogue_quant else None, gather=args.gather)
 
     # one plain device copy of known size, outside the timed region: the reference dispatch the HBM byte
     # counters (FETCH_SIZE / WRITE_SIZE) of a profiler run are scaled by

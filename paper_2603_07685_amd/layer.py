@@ -52,24 +52,22 @@ class LayerState:
         assert not self.gather or not (cfg.fp8 or cfg.mx or f32), "the gathered GEMMs are bf16 kernels"
         self.eq2 = bool(eq2)  # memory-efficient permutation (Sec. 4.1.2): weights applied before fc2
         self.fused_quant = None if fused_quant is None else bool(fused_quant)   # (resolved below, once fp8_wgrad is known)
-        # blockwise fp8 (default there): the SwiGLU / SwiGLU-backward GEMM calls also emit the 1x128 codes of their
-        # output, the next GEMM's operand (Sec. 5.4.2); off = stand-alone quantiser calls
-        # (MXFP8: the 1x32 codes and the 32x1 copy for the weight gradients; row counts are on the 128-row grid there)
-        self.epilogue_quant = bool(cfg.fp8 or cfg.mx) if epilogue_quant is None else bool(epilogue_quant)
-        # blockwise calls: unless the caller asks, both copies of A and dZ come from one launch of the two-copy quantiser (the same
-        # bits): small tiles need a launch for the copies anyway, and the large ones' epilogue is vector-ALU-bound.  The line is
-        # the largest capacity measured.
-        # A step, us, epilogue : one launch: T 256 h 512 f 256 E 8 k 2 97 : 95; T 1024 h 1024 f 768 E 16 k 4 222 : 212; T 3072 h 2048
-        # f 1024 E 16 k 4 (14336 rows) 694 : 680; T 16384, k 4 h 1024 f 512 E 16 1049 : 1010, k 8 h 2048 f 768 E 32 (135168 rows)
-        # 3869 : 3734, k 8 h 4096 f 1536 E 16 11445 : 11145, k 8 h 7168 f 2048 E 32 24592 : 24502
-        self.epilogue_rows = 135168 if epilogue_quant is None and not cfg.mx else 0
-        assert not self.epilogue_quant or cfg.fp8 or cfg.mx, "epilogue quantisation belongs to the one-byte recipes"
         # blockwise fp8 (default there): the weight gradients also run on E4M3 codes, quantised 128x1 down the token
         # dimension inside each expert's 128-aligned row range (Sec. 5.3.2, 5.4.1); off = weight gradients from the
         # bf16 tensors.  (MXFP8 always runs them on its 32x1 copies.)
         self.fp8_wgrad = (bool(cfg.fp8) and not cfg.mx) if fp8_wgrad is None else bool(fp8_wgrad)
         assert not self.fp8_wgrad or (cfg.fp8 and not cfg.mx and cfg.align % 128 == 0), \
             "blockwise fp8 weight gradients need the blockwise config with experts padded to 128 rows"
+        # Quantised copies of A and dZ.  On: the SwiGLU / SwiGLU-backward GEMM calls emit them (Sec. 5.4.2), blockwise the 1x128 codes of
+        # the next GEMM, MXFP8 the 1x32 codes and the 32x1 copy for the weight gradients (row counts are on the 128-row grid
+        # there).  Off: quantiser calls.  Blockwise with one-byte weight gradients, where two copies are needed, one launch of the
+        # two-copy quantiser is the default, the same bits: small tiles need a launch for the copies anyway, and the large ones'
+        # epilogue is vector-ALU-bound.  No size was found where the epilogue wins.  A step, us, epilogue : one launch: T 256 h 512
+        # f 256 E 8 k 2 97 : 95; T 3072 h 2048 f 1024 E 16 k 4 694 : 680; T 16384, k 8 (h, f, E) 2048 768 32 3988 : 3861, 64 4192 : 4058,
+        # 4096 1536 64 13344 : 13086, 7168 2048 32 26023 : 25751, 64 28023 : 27644; T 32768 k 8 4096 1536 32 23965 : 23361, 7168
+        # 2048 32 49633 : 49210, 1024 4096 16 19838 : 18800; T 131072 k 4 1024 512 16 7610 : 7187.
+        self.epilogue_quant = bool(cfg.mx or (cfg.fp8 and not self.fp8_wgrad)) if epilogue_quant is None else bool(epilogue_quant)
+        assert not self.epilogue_quant or cfg.fp8 or cfg.mx, "epilogue quantisation belongs to the one-byte recipes"
         # one-byte recipes whose weight gradients run on one-byte operands too: the permuted tokens and the combine's
         # backward are quantised straight from X / dY through the row map, in both directions, padding included
         # (Sec. 5.4.1, 5.4.2); Xp and dO are never stored in bf16
@@ -353,7 +351,6 @@ class LayerState:
         if self.eq2:
             B.moe_gather_row_prob(c, self.topk_prob, self.src_of, Rcap, self.row_prob)
             row_prob = self.row_prob
-        eq = self.epilogue_quant
         self._fc1_fwd(self.qXp, self.qW1, self.offsets, E, 2 * f, h, Rcap, self.sXp, self.sW1, row_prob, self.Z, self.A,
                       self.qA, self.sA, self.qAc, self.sAc, self.live_rows)
         B.moe_grouped_gemm_fwd(c, self.qA, self.qW2, self.offsets, E, h, f, Rcap, F8, B.EPI_NONE,
@@ -411,7 +408,7 @@ class LayerState:
     def _fc1_fwd(self, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc, live):
         """fc1 + SwiGLU and the quantised copies of the activation fc2 and its weight gradient read: from the GEMM call
         itself (Sec. 5.4.2) where that is switched on, else by quantiser calls."""
-        c, eq = self.ctx, self.epilogue_quant and not (self.fp8_wgrad and rows <= self.epilogue_rows)
+        c, eq = self.ctx, self.epilogue_quant
         if eq and self.mx:
             B.moe_grouped_gemm_fwd_quant_mx(c, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc)
             return
@@ -424,7 +421,7 @@ class LayerState:
 
     def _fc2_dgrad(self, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part, qdZ, sdZ, qdZc, sdZc, live):
         """fc2 data gradient + SwiGLU backward and the quantised copies of dZ, as in _fc1_fwd."""
-        c, eq = self.ctx, self.epilogue_quant and not (self.fp8_wgrad and rows <= self.epilogue_rows)
+        c, eq = self.ctx, self.epilogue_quant
         if eq and self.mx:
             B.moe_grouped_gemm_dgrad_quant_mx(c, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part,
                                               qdZ, sdZ, qdZc, sdZc)
