@@ -6,10 +6,10 @@
 // bytes of a row; a chunk's two steps of 32 share its cache lines), and the waves' sums meet in LDS and are added in order.
 // Nothing is staged, so nothing is waited for but the loads themselves; AHEAD chunks per wave are in flight.
 // Bound: the rate at which a compute unit takes these 64-byte row pieces, 38 bytes per ns, over (16 MB + 16 NB) rows of 2 h bytes
-// per tile; hence the choice of tile by gate_tiles below.  Measured (us, 256 x 256 kernel with its second launch : this),
+// per tile; hence the choice of tile by moe_gate_tile below.  Measured (us, 256 x 256 kernel with its second launch : this),
 // T, E, h: 512, 48, 960 23.6 : 3.8; 64, 128, 4096 19.6 : 8.9; 512, 256, 7168 32 : 21; 2048, 64, 4096 25 : 13; 4000, 40, 2048
 // 24 : 9.4; 16384, 32, 512 19 : 5.9; 16384, 64, 4096 39 : 34; 16384, 256, 1024 41 : 32; but 2048, 256, 7168 36 : 40 and 16384,
-// 256, 7168 86 : 156.
+// 256, 7168 86 : 156, 16384, 128, 7168 61 : 81, 8192, 64, 7168 33 : 42.
 #include "common.h"
 
 template <int MB, int NB, int WAVES, int AHEAD>
@@ -88,8 +88,9 @@ static void gate_go(hipStream_t s, const void* X, const void* W, int T, int E, i
     hipLaunchKernelGGL((gate_kernel<MB, NB, WAVES, AHEAD>), dim3((unsigned)(ceil_div64(n, 8) * 8)), dim3(WAVES * 64), 0, s, (const char*)X,
                        (const char*)W, T, E, h, (int)tj, (int)n, out);
 }
-// The best tile's number, and its time in microseconds: 2 + the bytes of a compute unit's tiles at 38 per ns, a started round
-// counted half (within 15 % of 19 measured sizes but the largest, 25 % low there)
+// The best tile's number, and its time in microseconds: 2.1 + the bytes of a compute unit's tiles at 38.8 per ns, a started round
+// counted half, + X and the logits at 15.5 TB/s (what memory adds to the units' own rate).  Between 31 % low and 14 % high of 135 measured
+// sizes, 7 % in the root mean square.
 static const int GATE_TILES[6][2] = {{16, 16}, {32, 16}, {32, 32}, {64, 32}, {64, 64}, {64, 128}};
 int moe_gate_tile(int num_cu, int T, int E, int h, double* us) {
     int best = -1;
@@ -97,7 +98,7 @@ int moe_gate_tile(int num_cu, int T, int E, int h, double* us) {
         const int64_t n = ceil_div64(T, GATE_TILES[x][0]) * ceil_div64(E, GATE_TILES[x][1]);
         double r = (double)n / num_cu;
         r = r < 1 ? 1 : (r + __builtin_ceil(r)) / 2;
-        const double t = 2 + r * (GATE_TILES[x][0] + GATE_TILES[x][1]) * 2.0 * h / 38e3;
+        const double t = 2.1 + r * (GATE_TILES[x][0] + GATE_TILES[x][1]) * 2.0 * h / 38.8e3 + (2.0 * T * h + 4.0 * T * E) / 15.5e6;
         if (n <= 0x7ffffff0 && (best < 0 || t < *us)) {
             best = x;
             *us = t;

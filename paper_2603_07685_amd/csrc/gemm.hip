@@ -2335,13 +2335,17 @@ static int gate_choose(int64_t cu, int T, int E, int h, size_t room, int64_t& pi
         pieces = (stages + each - 1) / each;
     }
     if (pieces < 2 || GG_BF16_NW != 4) pieces = 1;   // (the four-wave body's output step is the one that knows of pieces)
-    // This one's time from its stages, the launches and the bytes of X and of the partial results (16384, 256, 7168:
-    // 86 measured, 79 by this; 4096, 256, 7168: 39.5, 37; 2048, 64, 4096: 25, 27), the other's from its tiles
+    // This one's time from its stages (shorter with fewer columns of W), the launches and the bytes of X and of the partial results;
+    // the other's from its tiles.  Fitted to 135 sizes (T 16 .. 65536, E 8 .. 512, h 64 .. 7168; X from memory) to 9 and 7 % in the
+    // root mean square, this one's then taken 6 % higher: of those sizes the choice loses most at 12288, 64, 4096 (gate_kernel : this
+    // 35.1 : 33.1), 8192, 128, 4096 (32.6 : 31.0) and 8192, 32, 7168 (33.9 : 32.7).  (Without the columns' share here and the bytes there
+    // 16384, 128, 7168, 81 : 61, 8192, 64, 7168, 42 : 33, and 12288, 128, 4096, 48 : 37, were left to gate_kernel.)
     double us = 0;
     const int tile = moe_gate_tile((int)cu, T, E, h, &us);
     const double bytes = 2.0 * T * h + (pieces > 1 ? 8.0 * pieces * T * E : 0.0);
     const double rounds = __builtin_ceil((double)tiles * pieces / cu);
-    return tile >= 0 && us < 14 + rounds * 1.45 * (double)ceil_div64(h / 64, pieces) + bytes / 15e6 ? tile : -1;
+    const double stage = 0.48 + 0.9 * (E < GG_BN ? E : GG_BN) / GG_BN;
+    return tile >= 0 && us < (pieces > 1 ? 14.8 : 11) + rounds * stage * (double)ceil_div64(h / 64, pieces) + bytes / 10.3e6 ? tile : -1;
 }
 
 extern "C" moe_status moe_gate_gemm(moe_ctx* ctx, void* stream, const void* X, const void* Wr, int T, int E, int h,

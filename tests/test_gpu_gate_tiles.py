@@ -16,7 +16,7 @@ SIZES = {0: [(17, 8, 64), (33, 24, 192), (300, 200, 4160)],                  # 1
          3: [(16384, 32, 512), (16001, 24, 576)],                            # 64 x 32
          4: [(8000, 104, 512), (7999, 104, 448), (15991, 64, 4096)],         # 64 x 64
          5: [(16383, 128, 448), (16001, 248, 1088)],                         # 64 x 128
-         -1: [(2048, 256, 7168), (4100, 248, 6720)]}
+         -1: [(2048, 256, 7168), (4100, 248, 6720), (16384, 128, 7168), (8192, 64, 7168), (12283, 120, 4096)]}
 
 
 @pytest.mark.parametrize("T,E,h", sum(SIZES.values(), []))
