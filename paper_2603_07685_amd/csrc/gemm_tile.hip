@@ -424,7 +424,9 @@ static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
 // 12.2, 15.6 : 11.4; T 400 h 512 f 512 E 8 k 2 10.9 : 8.6, 7.7 : 6.2, 10.2 : 9.1, 11.8 : 9.1; but at 2.25 per unit, T 2048 h 1024
 // f 512 E 8 k 2, 21.8 : 23.8, 12.2 : 14.1, 18.2 : 21.0).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill the chip's two workgroups per
 // unit (T 256 h 128 f 256: fc2 dgrad 6.9 against 9.5; T 4096 h 512 f 512: 27 against 34); SwiGLU backward, whose output
-// phase is long, up to one and a half times that (T 3000 h 512 f 1536 E 12 k 2 34 : 28.5; T 4096 h 512 f 512 E 8 k 4 32 : 27).
+// phase is long, up to one and a half times that if the contraction is not (128 x 128 : 64 x 128, T 3000 h 512 f 1536 E 12 k 2 34 : 28.5,
+// T 4096 h 512 f 512 E 8 k 4 32 : 27, T 4008 h 1536 f 2048 E 17 52 : 48; but h 3264 f 640 E 51, 10230 rows, equal loads 83 : 116, scattered
+// 119 : 115).
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
     const double E = a.E, R = (double)a.Rcap, one = E < R ? E : R;
@@ -443,7 +445,7 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     if (mode == GG_WGRAD) return gt_one_buffer(ctx, a) ? 4 : 2;
     const double n64 = __builtin_ceil(cols / 128) * row_tiles(64);
     if (R <= 48 * E || n64 <= 2 * cu) return 3;
-    return r128 < (epi == GG_EPI_SWIGLU_BWD ? 1.5 : 1) ? 1 : 2;
+    return r128 < (epi == GG_EPI_SWIGLU_BWD && stages <= 24 ? 1.5 : 1) ? 1 : 2;
 }
 
 template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF, bool SPLIT = false>

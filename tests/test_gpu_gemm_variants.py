@@ -81,6 +81,14 @@ def test_every_kernel_is_reached(case):
         assert set(_capacities(case, 1)) == ROWS[case][1]
 
 
+def test_swiglu_backward_tiles():
+    """More 128 x 128 tiles than the chip holds at a time: 64 x 128 ones if the contraction is short beside the output phase."""
+    f = _lib()
+    for E, N, K, R, tile in ((12, 512, 1536, 6000, 1), (8, 512, 512, 16384, 1), (17, 1536, 2048, 4008, 1), (51, 3264, 640, 10230, 2),
+                             (32, 4096, 1024, 6144, 2), (16, 2048, 768, 10240, 2)):
+        assert f(256, DGRAD, SWIGLU_BWD, DT["bf16"], 0, E, N, K, R) == tile, (E, N, K, R)
+
+
 def test_other_tests_sizes_reach_their_kernels():
     """The tests of single kernels take sizes that those kernels serve."""
     import test_gpu_f32_split
