@@ -132,7 +132,7 @@ __global__ __launch_bounds__(256) void quant_128x1_kernel(const u32x4_t* __restr
 }
 
 // ---- 128x128 -------------------------------------------------------------------------------
-// grid = groups * (rows/128) * (cols/128) workgroups of 256 threads
+// grid = groups * (rows/128) * (cols/128) workgroups of QUANT_THREADS
 __global__ __launch_bounds__(QUANT_THREADS) void quant_128x128_kernel(const u32x4_t* __restrict__ W, int rows, int cols,
                                                             u32x2_t* __restrict__ q, float* __restrict__ scale) {
     constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RP = 128 / PIECES;   // per lane; waves; rows of a pass
