@@ -238,8 +238,9 @@ moe_status moe_permute_static(void* stream, const void* X, moe_dtype dt,
  * wgrad contracts over the expert's rows, any count.  N, K <= 2^24 and N*K <= 2^31 elements per
  * expert (32-bit offsets inside one expert's weights).  Sizes outside these limits
  * return MOE_ERR_UNSUPPORTED and touch nothing.  dt = MOE_F32: every operand and result is fp32
- * (fp32 accumulation in increasing contraction index; wgrad needs out_dt = MOE_F32; any N, K >= 1);
- * a plain one-thread-per-output path for parity runs at the 1e-5 level on small layers, not tuned.
+ * (wgrad needs out_dt = MOE_F32; any N, K >= 1).  fp32 accumulation in an order that follows from the sizes and the
+ * operands' alignment; a product enters it exactly, or as the sum of eight products of bf16 parts of its factors that
+ * is within 2^-33 of it (infinities, NaN and magnitudes that the parts cannot hold: as in fp32 arithmetic).
  * dt = MOE_MXFP8_E4M3 (Sec. 5.3.3) is described with moe_mx_quantize below; all three calls take
  * both one-byte types.
  *
