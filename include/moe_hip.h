@@ -76,6 +76,18 @@ moe_status moe_ctx_create(moe_ctx** out, int device, size_t workspace_bytes);
  * must have finished.  NULL is accepted. */
 moe_status moe_ctx_destroy(moe_ctx* ctx);
 
+/*
+ * A batch: a second handle on ctx (same device, same workspace) for calls that do not depend on each other, so that small
+ * ones share a launch: a layer's weight and data gradient, or the routed and the shared experts' calls.  A grouped GEMM called
+ * with the batch as its context is checked as ever, and either launched at once or kept until moe_batch_end, which launches what is
+ * kept on the stream each call was given, in no particular order; every other call is launched at once.  Results are those
+ * of the same calls on ctx, bit for bit.  Until moe_batch_end returns, the operands of the calls must stay valid, none may
+ * read or write what another of them writes, and no other work that uses them may be enqueued.
+ * launch = 0: the kept calls are dropped instead (a call of the batch has failed).  A batch can be used again after moe_batch_end.
+ * It is destroyed by moe_ctx_destroy, before ctx.  Both calls are host-only but for the launches. */
+moe_status moe_batch_create(moe_ctx* ctx, moe_ctx** out);
+moe_status moe_batch_end(moe_ctx* batch, void* stream, int launch);
+
 /* Host string for the last error recorded on ctx ("" if none); owned by ctx.  ctx = NULL: the message of the
  * calling host thread's last failed call that takes no context (moe_permute_static). */
 const char* moe_last_error(const moe_ctx* ctx);

@@ -39,6 +39,7 @@ EXPORTS = [
     "moe_grouped_gemm_fwd_quant_mx", "moe_grouped_gemm_dgrad_quant_mx", "moe_gate_gemm", "moe_permute_static",
     "moe_fp8_quantize_rowcol", "moe_fp8_quantize_rowcol_gather",
     "moe_grouped_gemm_fwd_gather", "moe_grouped_gemm_dgrad_gather", "moe_grouped_gemm_wgrad_gather",
+    "moe_batch_create", "moe_batch_end",
 ]
 
 _vp, _i, _i64, _f = C.c_void_p, C.c_int, C.c_int64, C.c_float
@@ -63,6 +64,8 @@ def lib() -> C.CDLL:
         L.moe_last_error.restype = C.c_char_p
         L.moe_last_error.argtypes = [_vp]
         L.moe_ctx_poll_error.argtypes = [_vp, _vp, C.POINTER(_i)]
+        L.moe_batch_create.argtypes = [_vp, C.POINTER(_vp)]
+        L.moe_batch_end.argtypes = [_vp, _vp, _i]
         L.moe_route_topk.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, _f, _vp, _vp, _vp]
         L.moe_permute.argtypes = [_vp, _vp, _vp, _i, _vp, _i, _i, _i, _i, _i, _vp, _i64, _vp, _vp, _vp, _vp]
         L.moe_permute_static.argtypes = [_vp, _vp, _i, _vp, _i, _i, _i, _i, _i, _vp, _i64, _vp, _vp, _vp, _vp]
@@ -178,6 +181,30 @@ class Context:
             self.close()
         except Exception:
             pass
+
+
+class Batch(Context):
+    """A Context's handle for calls that do not depend on each other (moe_batch_create): `with batch as b:` around them, b in
+    the Context's place.  At the end what was kept is launched, or, after an exception, dropped."""
+
+    def __init__(self, ctx):
+        h_ = _vp()
+        ctx.check(lib().moe_batch_create(ctx.h, C.byref(h_)), "moe_batch_create")
+        self.parent, self.bytes = ctx, ctx.bytes   # (the workspace is the parent's)
+        self.h = h_
+        self._addr = h_.value
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, exc, value, trace):
+        moe_batch_end(self, exc is None)
+
+
+def moe_batch_end(batch, launch=True):
+    st = _native.moe_batch_end(batch._addr, int(launch))
+    if st:
+        batch.check(st, "moe_batch_end")
 
 
 def moe_workspace_bytes(T, k, E, h, f_max):

@@ -13,6 +13,7 @@ struct moe_ctx {
     size_t ws_bytes;
     int* dev_err;      // device error word (first 256 bytes of ws are reserved for it)
     int num_cu;
+    struct moe_batch* batch;   // a batch (moe_batch_create): its recorded calls, and the workspace is its parent's; else NULL
     char err[512];
 };
 
@@ -171,7 +172,7 @@ struct tile_sums {
 };
 template <int THREADS>
 __device__ __forceinline__ bool tile_scan(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
-                                          int mult, tile_pick_lds& l, tile_sums<THREADS>& st, int lim = 0) {
+                                          int mult, tile_pick_lds& l, tile_sums<THREADS>& st, bool first_block, int lim = 0) {
     constexpr int PER = tile_sums<THREADS>::PER;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     auto& o = st.o;
@@ -213,7 +214,7 @@ __device__ __forceinline__ bool tile_scan(const int32_t* __restrict__ offsets, i
         wrong |= l.wave_bad[w];
     }
     if (wrong) {
-        if (blockIdx.x == 0 && tid == 0) atomicExch(dev_err, 1);
+        if (first_block && tid == 0) atomicExch(dev_err, 1);
         return false;
     }
     st.n = n;
@@ -253,7 +254,7 @@ template <int THREADS>
 __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
                                           int mult, tile_pick_lds& l, int& e, int& u, int& row_lo, int& row_hi) {
     tile_sums<THREADS> st;
-    return tile_scan(offsets, E, Rcap, dev_err, bm, mult, l, st) && tile_find(st, (int)blockIdx.x, l, e, u, row_lo, row_hi);
+    return tile_scan(offsets, E, Rcap, dev_err, bm, mult, l, st, blockIdx.x == 0) && tile_find(st, (int)blockIdx.x, l, e, u, row_lo, row_hi);
 }
 
 // Quantised copies of the tensor X [rows, cols] that a grouped GEMM has just stored (fp8.hip): blockwise 1x128 codes and

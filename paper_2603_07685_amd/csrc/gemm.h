@@ -119,6 +119,22 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a);
 // Rows from which on a weight gradient on small tiles may split its contraction (set split_cap and partials)
 #define GT_SPLIT_ROWS 24576
 void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
+// Calls of a batch that wait for its end: gt_submit records a call, or launches it where the context is no batch or the call is none
+// of the small ones; gt_flush launches the recorded ones, up to GT_JOBS of them together.
+#define GT_JOBS 4
+struct gt_job {
+    hipStream_t s;
+    int mode, epi, gath, tile;
+    bool f32, done;
+    gg_args a;
+};
+#define MOE_BATCH_MAX 16
+struct moe_batch {
+    gt_job gt[MOE_BATCH_MAX];
+    int n_gt;
+};
+void gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
+void gt_flush(gt_job* jobs, int n);
 // the same for one-byte operands (gemm_tile8.hip); `quant`: the call also asks for quantised copies of its output
 int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg_args& a);
 void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a);

@@ -1944,7 +1944,7 @@ extern "C" moe_status moe_grouped_gemm_fwd_gather(moe_ctx* ctx, void* stream, co
     a.out_act = (bf16_t*)C_act;
     a.row_prob = row_prob;
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
-    if (const int tile = gt_tile(ctx, GG_FWD, ge, a)) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 1, tile, a);
+    if (const int tile = gt_tile(ctx, GG_FWD, ge, a)) gt_submit(ctx, (hipStream_t)stream, GG_FWD, ge, false, 1, tile, a);
     else if (epi == MOE_EPI_SWIGLU) GG_LAUNCH_G(GG_FWD, GG_EPI_SWIGLU, false, 1);
     else GG_LAUNCH_G(GG_FWD, GG_EPI_STORE, false, 1);
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<fwd, gather>");
@@ -2069,7 +2069,7 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
     }
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_FWD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_FWD, ge, a)) {
-        if (!fp8) gt_launch((hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
+        if (!fp8) gt_submit(ctx, (hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
         else gq_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<fwd>");
         return a.out_q ? gg_quantise(ctx, stream, C_act, N / 2, mx, a) : MOE_OK;
@@ -2103,7 +2103,7 @@ extern "C" moe_status moe_grouped_gemm_dgrad_gather(moe_ctx* ctx, void* stream, 
     a.row_prob = row_prob;
     a.dprob_part = dprob_part;
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
-    if (const int tile = gt_tile(ctx, GG_DGRAD, ge, a)) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 1, tile, a);
+    if (const int tile = gt_tile(ctx, GG_DGRAD, ge, a)) gt_submit(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, 1, tile, a);
     else if (Z_saved) GG_LAUNCH_G(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
     else GG_LAUNCH_G(GG_DGRAD, GG_EPI_STORE, false, 1);
     MOE_LAUNCH_CHECK(ctx, "gg_kernel<dgrad, gather>");
@@ -2197,7 +2197,7 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
     }
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_DGRAD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_DGRAD, ge, a)) {
-        if (!fp8) gt_launch((hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
+        if (!fp8) gt_submit(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
         else gq_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<dgrad>");
         return a.out_q ? gg_quantise(ctx, stream, dA, 2 * K, mx, a) : MOE_OK;
@@ -2266,7 +2266,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
         if (!mx && !bw && Rcap > GT_SPLIT_ROWS) a.split_cap = slices((size_t)N * K * sizeof(float));
         if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
-        else gt_launch((hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
+        else gt_submit(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;
     }

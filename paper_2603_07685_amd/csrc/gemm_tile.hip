@@ -37,20 +37,32 @@ __device__ __forceinline__ int split_limit(const int32_t* __restrict__ offsets, 
     return max((int)(((int64_t)rows + n * 64 - 1) / (n * 64)) * 64, 2048);   // (small results: not worth cutting)
 }
 
+// The LDS of a workgroup
+template <int MODE, int GATH, int BM, int NBUF>
+struct gt_lds {
+    static constexpr int STAGE = (BM + GT_BN) * 128;
+    static constexpr int STAGED = 64 * STG_PITCH * 4;    // (the output phase stages 64 rows in the ring)
+    __attribute__((aligned(1024))) char ring[NBUF * STAGE > STAGED ? NBUF * STAGE : STAGED];
+    tile_pick_lds pick;
+    // weight gradient with a gathered operand: byte offsets of the rows of two blocks of 16 stages (see rows_in)
+    uint32_t rows_at[GATH != 0 && MODE == GG_WGRAD ? 2048 : 1];
+    int slices_before;
+};
+// GATH: 0 no gathered operand, 1 P, 2 Q (weight gradient), 3 P if the call has a map (row-major P).
+// `block`: the workgroup's place among those of its call
 template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF, bool SPLIT>
-__global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
+__device__ __forceinline__ void gt_body(const gg_args& a, gt_lds<MODE, GATH, BM, NBUF>& lds, const int block) {
     static_assert(!SPLIT || MODE == GG_WGRAD, "the weight gradient's contraction is the one whose length depends on the load");
-    static_assert(GATH == 0 || GATH == 1 || (GATH == 2 && MODE == GG_WGRAD), "Q is gathered in the weight gradient only");
+    static_assert(GATH == 2 ? MODE == GG_WGRAD : GATH != 3 || MODE != GG_WGRAD, "Q is gathered in the weight gradient only");
     constexpr bool P_CMAJ = MODE == GG_WGRAD, Q_CMAJ = MODE != GG_FWD;
     constexpr int P_BYTES = BM * 128, STAGE = P_BYTES + GT_BN * 128;
     constexpr int PC = BM / 32, QC = 4;                 // 1 KB DMA chunks per wave, operand and stage
     constexpr int NI = BM / 32;                         // 16-row blocks per wave
-    constexpr int STAGED = 64 * STG_PITCH * 4;          // (the output phase stages 64 rows in the ring)
-    __shared__ __attribute__((aligned(1024))) char ring[NBUF * STAGE > STAGED ? NBUF * STAGE : STAGED];
-    __shared__ tile_pick_lds pick;
-    // weight gradient with a gathered operand: byte offsets of the rows of two blocks of 16 stages (see rows_in)
+    char* const ring = lds.ring;
+    tile_pick_lds& pick = lds.pick;
+    uint32_t* const rows_at = lds.rows_at;
     constexpr bool G_CM = GATH != 0 && MODE == GG_WGRAD;
-    __shared__ uint32_t rows_at[G_CM ? 2048 : 1];
+    const bool gath_p = GATH == 1 || (GATH == 3 && a.g_src_of);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
@@ -63,15 +75,14 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
     int e, u, row_lo, row_hi;
     const int lim = SPLIT ? split_limit(a.offsets, a.E, a.split_cap) : 0;
     tile_sums<256> sums;
-    __shared__ int slices_before;
     // A weight gradient without pieces has the same number of tiles for every expert: its tile is found without a sum over the
     // experts.  The check of all offsets goes on while the first operands are on their way (from rows made safe by
     // clamping), and is asked for its answer at the first barrier.
     constexpr bool EVEN = MODE == GG_WGRAD && !SPLIT;
     bool bad = false;
     if (EVEN) {
-        const int tpe = tiles_iw * tiles_j, total = a.E * tpe, run = (total + 7) >> 3, at = (int)blockIdx.x >> 3;
-        const int unit = ((int)blockIdx.x & 7) * run + at;
+        const int tpe = tiles_iw * tiles_j, total = a.E * tpe, run = (total + 7) >> 3, at = block >> 3;
+        const int unit = (block & 7) * run + at;
         if (at >= run || unit >= total) return;
         e = unit / tpe;
         u = unit - e * tpe;
@@ -82,9 +93,9 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
         pick.wave_bad[wave] = __builtin_amdgcn_ballot_w64(bad) != 0;
     } else {
         if (!tile_scan<256>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM,
-                            MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, sums, lim)) return;
-        if (SPLIT && tid == 0) slices_before = 0;
-        if (!tile_find(sums, (int)blockIdx.x, pick, e, u, row_lo, row_hi)) return;
+                            MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, sums, block == 0, lim)) return;
+        if (SPLIT && tid == 0) lds.slices_before = 0;
+        if (!tile_find(sums, block, pick, e, u, row_lo, row_hi)) return;
     }
     int slice = -1;   // >= 0: a piece, its place among the partial results
     if (SPLIT) {
@@ -96,11 +107,11 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
                 const int p = split_pieces(sums.o[x + 1] - sums.o[x], lim);
                 n += tid * tile_sums<256>::PER + x < e && p > 1 ? p : 0;
             }
-            if (n) atomicAdd(&slices_before, n);
+            if (n) atomicAdd(&lds.slices_before, n);
             __syncthreads();
             const int tpe = tiles_iw * tiles_j, piece = __builtin_amdgcn_readfirstlane(u / tpe);
             const int len = ((row_hi - row_lo + pieces - 1) / pieces + 63) / 64 * 64;   // (whole stages; none is empty)
-            slice = __builtin_amdgcn_readfirstlane(slices_before) + piece;
+            slice = __builtin_amdgcn_readfirstlane(lds.slices_before) + piece;
             u -= piece * tpe;
             row_lo += piece * len;
             row_hi = min(row_lo + len, row_hi);
@@ -135,7 +146,7 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
             po[i] = (uint32_t)((GATH == 1 ? 0 : row * ldp) + i0 + slot * 8) * 2u;
         } else {
             const int row = c * 8 + (lane >> 3), slot = (lane & 7) ^ KM_SWZ(row);
-            if (GATH == 1) {
+            if (gath_p) {
                 const int s = i0 + row < i_end ? a.g_src_of[i0 + row] : -1;
                 const uint32_t tok = __umulhi(2u * (uint32_t)s + 1u, a.g_magic);  // s / g_k
                 po[i] = s >= 0 ? tok * (uint32_t)(ldp * 2) + slot * 16 : GG_NO_ROW;
@@ -157,11 +168,11 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
         }
     }
     // base and byte count of each operand at stage s (past the last stage: nothing, the buffer fills with zeros)
-    const char* const p_base0 = GATH == 1 ? (const char*)a.P
+    const char* const p_base0 = gath_p ? (const char*)a.P
                                           : (const char*)a.P + (int64_t)(P_CMAJ ? c_lo : i0) * ldp * 2;
     const char* const q_base0 = GATH == 2 ? (const char*)a.Q : MODE == GG_WGRAD ? (const char*)a.Q + (int64_t)c_lo * K * 2
                                                  : (const char*)a.Q + (int64_t)e * N * K * 2;
-    const uint32_t p_all = GATH == 1 ? (uint32_t)a.g_T * (uint32_t)(ldp * 2) : (uint32_t)min(BM, i_end - i0) * (uint32_t)(ldp * 2);
+    const uint32_t p_all = gath_p ? (uint32_t)a.g_T * (uint32_t)(ldp * 2) : (uint32_t)min(BM, i_end - i0) * (uint32_t)(ldp * 2);
     const uint32_t q_all = GATH == 2 ? (uint32_t)a.g_T * (uint32_t)(K * 2) : (uint32_t)N * (uint32_t)(K * 2);
     auto make = [](const char* base, uint32_t bytes) {
         const uint64_t b = (uint64_t)base;
@@ -260,7 +271,7 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
     stage_barrier();
     if (EVEN && (pick.wave_bad[0] | pick.wave_bad[1] | pick.wave_bad[2] | pick.wave_bad[3])) {
         wait_vm0();                                         // (nothing may land in this LDS once it is someone else's)
-        if (blockIdx.x == 0 && tid == 0) atomicExch(a.dev_err, 1);
+        if (block == 0 && tid == 0) atomicExch(a.dev_err, 1);
         return;
     }
     if constexpr (NBUF == 1) {
@@ -336,6 +347,45 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
         return;
     }
     gt_output<MODE, EPI, OUT_F32, BM>(a, (float*)ring, e, i0, i_end, j0, tj, tiles_j, stage);
+}
+template <int MODE, int EPI, bool OUT_F32, int GATH, int BM, int NBUF, bool SPLIT>
+__global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2) : 2) void gt_kernel(const gg_args a) {
+    __shared__ gt_lds<MODE, GATH, BM, NBUF> lds;
+    gt_body<MODE, EPI, OUT_F32, GATH, BM, NBUF, SPLIT>(a, lds, (int)blockIdx.x);
+}
+
+// Independent calls in one launch: the workgroups of call x are start[x] .. start[x + 1] - 1 (multiples of 8: the XCDs' shares of a
+// call stay).  Small calls leave compute units idle in their start, their output phase and the last of their rounds, and each
+// launch costs about 2 us behind another; together they fill each other's gaps.  A step, us, one launch each : together: T 256 h 128
+// f 256 E 8 k 2 52.8 : 45.1; T 377 h 2240 f 512 E 8 k 2 130 : 106; T 7394 h 128 f 192 E 24 125 : 104; with a shared expert T 27 h 576 f 512
+// E 7 k 2 105 : 60, T 873 h 896 f 2688 E 12 k 2 342 : 300.  Data gradients go first: their tiles take longer.
+struct gt_jobs {
+    gg_args a[GT_JOBS];
+    int start[GT_JOBS + 1];
+};
+__device__ __forceinline__ int gt_job_of(const gt_jobs& m, int block) {
+    int j = 0;
+#pragma unroll
+    for (int x = 1; x < GT_JOBS; ++x) j += block >= m.start[x];
+    return j;
+}
+// forward calls with one epilogue
+template <int EPI, int BM, int NBUF>
+__global__ __launch_bounds__(256, NBUF == 2 && BM == 64 ? 3 : 2) void gt_fwd_jobs_kernel(const gt_jobs m) {
+    __shared__ gt_lds<GG_FWD, 3, BM, NBUF> lds;
+    const int j = gt_job_of(m, (int)blockIdx.x);
+    gt_body<GG_FWD, EPI, false, 3, BM, NBUF, false>(m.a[j], lds, (int)blockIdx.x - m.start[j]);
+}
+// data gradients with one epilogue (calls 0, 1) and weight gradients (2, 3)
+template <int EPI, int BM, int NBUF, bool F32, int WGATH, int WBUF>
+__global__ __launch_bounds__(256, 2) void gt_bwd_jobs_kernel(const gt_jobs m) {
+    __shared__ union {
+        gt_lds<GG_DGRAD, 3, BM, NBUF> d;
+        gt_lds<GG_WGRAD, WGATH, 128, WBUF> w;
+    } lds;
+    const int j = gt_job_of(m, (int)blockIdx.x), block = (int)blockIdx.x - m.start[j];
+    if (j < 2) gt_body<GG_DGRAD, EPI, false, 3, BM, NBUF, false>(m.a[j], lds.d, block);
+    else gt_body<GG_WGRAD, GG_EPI_STORE, F32, WGATH, 128, WBUF, false>(m.a[j], lds.w, block);
 }
 
 // Second step of a weight gradient with pieces: every workgroup finds the split experts in the offsets (at most four) and goes
@@ -448,11 +498,15 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     return r128 < (epi == GG_EPI_SWIGLU_BWD && stages <= 24 ? 1.5 : 1) ? 1 : 2;
 }
 
+// (a multiple of 8: every XCD gets as many workgroups of a call)
+static int64_t gt_blocks(int mode, int epi, int bm, const gg_args& a) {
+    const int64_t cols = epi == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(mode == GG_FWD ? a.N : a.K, GT_BN);
+    const int64_t n = cols * (mode == GG_WGRAD ? (a.E + a.split_cap) * ceil_div64(a.N, bm) : ceil_div64(a.Rcap, bm) + a.E);
+    return ceil_div64(n, 8) * 8;
+}
 template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF, bool SPLIT = false>
 static void gt_go(hipStream_t s, const gg_args& a) {
-    const int64_t cols = EPI == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(MODE == GG_FWD ? a.N : a.K, GT_BN);
-    const int64_t n = cols * (MODE == GG_WGRAD ? (a.E + (SPLIT ? a.split_cap : 0)) * ceil_div64(a.N, BM) : ceil_div64(a.Rcap, BM) + a.E);
-    hipLaunchKernelGGL((gt_kernel<MODE, EPI, F32, GATH, BM, NBUF, SPLIT>), dim3((unsigned)(ceil_div64(n, 8) * 8)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((gt_kernel<MODE, EPI, F32, GATH, BM, NBUF, SPLIT>), dim3((unsigned)gt_blocks(MODE, EPI, BM, a)), dim3(256), 0, s, a);
 }
 template <int MODE, int EPI, int GATH>
 static void gt_rows(hipStream_t s, int tile, const gg_args& a) {
@@ -483,4 +537,97 @@ void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int til
         if (epi == GG_EPI_SWIGLU_BWD) gath ? gt_rows<GG_DGRAD, GG_EPI_SWIGLU_BWD, 1>(s, tile, a) : gt_rows<GG_DGRAD, GG_EPI_SWIGLU_BWD, 0>(s, tile, a);
         else gath ? gt_rows<GG_DGRAD, GG_EPI_STORE, 1>(s, tile, a) : gt_rows<GG_DGRAD, GG_EPI_STORE, 0>(s, tile, a);
     }
+}
+
+// ---- calls of a batch (see moe_batch_create) ----
+template <int EPI>
+static void gt_fwd_jobs(hipStream_t s, int tile, int64_t n, const gt_jobs& m) {
+    const dim3 grid((unsigned)n), block(256);
+    if (tile == 1) hipLaunchKernelGGL((gt_fwd_jobs_kernel<EPI, 64, 2>), grid, block, 0, s, m);
+    else if (tile == 2) hipLaunchKernelGGL((gt_fwd_jobs_kernel<EPI, 128, 2>), grid, block, 0, s, m);
+    else hipLaunchKernelGGL((gt_fwd_jobs_kernel<EPI, 64, 3>), grid, block, 0, s, m);
+}
+template <int EPI, bool F32, int WGATH>
+static void gt_bwd_jobs(hipStream_t s, int tile, int wtile, int64_t n, const gt_jobs& m) {
+    const dim3 grid((unsigned)n), block(256);
+    if (wtile == 4) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 1>), grid, block, 0, s, m);
+    else if (tile == 1) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 2, F32, WGATH, 2>), grid, block, 0, s, m);
+    else hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 2>), grid, block, 0, s, m);
+}
+void gt_flush(gt_job* jobs, int n) {
+    for (int i = 0; i < n; ++i) {
+        gt_job& first = jobs[i];
+        if (first.done) continue;
+        // the calls that can go with this one: same stream; forward calls of one epilogue, or data gradients of one epilogue and
+        // weight gradients of one output type and gathered operand
+        gt_job* take[GT_JOBS] = {};
+        int tile = 0, wtile = 0, count = 0;
+        const gt_job *d = nullptr, *w = nullptr;
+        for (int x = i; x < n; ++x) {
+            gt_job& j = jobs[x];
+            if (j.done || j.s != first.s || (j.mode == GG_FWD) != (first.mode == GG_FWD)) continue;
+            int at;
+            if (j.mode == GG_FWD) {
+                if (j.epi != first.epi) continue;
+                at = count;
+            } else if (j.mode == GG_DGRAD) {
+                if (d ? j.epi != d->epi : w && w->gath == (j.epi == GG_EPI_SWIGLU_BWD ? 2 : 1)) continue;
+                at = take[0] ? 1 : 0;
+            } else {
+                if (w ? j.f32 != w->f32 || j.gath != w->gath : d && j.gath == (d->epi == GG_EPI_SWIGLU_BWD ? 2 : 1)) continue;
+                at = take[2] ? 3 : 2;
+            }
+            if (at >= GT_JOBS || take[at]) continue;
+            if (j.mode == GG_DGRAD && !d) d = &j;
+            if (j.mode == GG_WGRAD && !w) w = &j;
+            if (j.mode == GG_WGRAD ? !wtile : !tile) (j.mode == GG_WGRAD ? wtile : tile) = j.tile;
+            take[at] = &j;
+            ++count;
+        }
+        if (count == 1) {
+            gt_launch(first.s, first.mode, first.epi, first.f32, first.gath, first.tile, first.a);
+            first.done = true;
+            continue;
+        }
+        gt_jobs m;
+        memset(&m, 0, sizeof(m));
+        int64_t at = 0;
+        for (int x = 0; x < GT_JOBS; ++x) {
+            m.start[x] = (int)at;
+            if (!take[x]) continue;
+            const gt_job& j = *take[x];
+            m.a[x] = j.a;
+            at += gt_blocks(j.mode, j.epi, j.mode == GG_WGRAD || tile == 2 ? 128 : 64, j.a);
+            take[x]->done = true;
+        }
+        m.start[GT_JOBS] = (int)at;
+        if (first.mode == GG_FWD) {
+            first.epi == GG_EPI_SWIGLU ? gt_fwd_jobs<GG_EPI_SWIGLU>(first.s, tile, at, m) : gt_fwd_jobs<GG_EPI_STORE>(first.s, tile, at, m);
+        } else {
+            const bool f32 = w && w->f32;
+            const int g = w ? w->gath : 0;
+            if (d ? d->epi == GG_EPI_SWIGLU_BWD : g == 1) {
+                if (g) f32 ? gt_bwd_jobs<GG_EPI_SWIGLU_BWD, true, 1>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_SWIGLU_BWD, false, 1>(first.s, tile, wtile, at, m);
+                else f32 ? gt_bwd_jobs<GG_EPI_SWIGLU_BWD, true, 0>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_SWIGLU_BWD, false, 0>(first.s, tile, wtile, at, m);
+            } else {
+                if (g) f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 2>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_STORE, false, 2>(first.s, tile, wtile, at, m);
+                else f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 0>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_STORE, false, 0>(first.s, tile, wtile, at, m);
+            }
+        }
+    }
+}
+void gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
+    moe_batch* const b = ctx->batch;
+    const int64_t cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
+    // Not kept: data gradients on 128-row tiles and weight gradients in pieces, which fill the chip by themselves; weight gradients on
+    // one buffer of more than eight tiles per unit, which live off three workgroups to a unit, one more than beside a data
+    // gradient (a step, us, alone : together: T 112 h 5504 f 1152 E 57 k 4, 86 tiles per unit, 1433 : 1545; T 262 h 5696 f 704 E 16 k 2,
+    // 17 per unit, 422 : 435; T 2541 h 1088 f 384 E 54, 6 per unit, 171 : 157).
+    if (!b || a.split_cap >= 2 || (mode == GG_DGRAD && tile == 2) || (tile == 4 && gt_blocks(mode, epi, 128, a) > 8 * cu))
+        return gt_launch(s, mode, epi, out_f32, gath, tile, a);
+    if (b->n_gt == MOE_BATCH_MAX) {
+        gt_flush(b->gt, b->n_gt);
+        b->n_gt = 0;
+    }
+    b->gt[b->n_gt++] = {s, mode, epi, gath, tile, out_f32, false, a};
 }

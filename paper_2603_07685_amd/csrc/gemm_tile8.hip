@@ -83,7 +83,7 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     }
     tile_sums<256> sums;
     if (!tile_scan(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM, MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j,
-                   pick, sums)) return;
+                   pick, sums, blockIdx.x == 0)) return;
     // Weight gradients, tile after tile: a tile costs its expert's rows, so the experts are taken in descending order of rows
     // (rank sort, ties by index) and the list is dealt to the XCDs in chunks, in a snake; with an expert above twice the mean no
     // deal balances, and the workgroups draw from a device counter in the same order (gemm.hip: tile_of, draw).

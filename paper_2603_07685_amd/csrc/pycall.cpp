@@ -97,7 +97,7 @@ PyObject* run(moe_status (*f)(moe_ctx*, void*, A...), PyObject* const* args, Py_
     X(moe_grouped_gemm_dgrad_quant) X(moe_grouped_gemm_dgrad_quant_mx) X(moe_grouped_gemm_dgrad_gather)                    \
     X(moe_grouped_gemm_wgrad) X(moe_grouped_gemm_wgrad_gather) X(moe_unpermute_combine) X(moe_unpermute_combine_bwd)       \
     X(moe_gather_row_prob) X(moe_scatter_row_dprob) X(moe_fp8_quantize) X(moe_fp8_quantize_rowcol)                         \
-    X(moe_fp8_quantize_rowcol_gather) X(moe_mx_quantize) X(moe_mx_quantize_rowcol) X(moe_mx_quantize_rowcol_gather)
+    X(moe_fp8_quantize_rowcol_gather) X(moe_mx_quantize) X(moe_mx_quantize_rowcol) X(moe_mx_quantize_rowcol_gather) X(moe_batch_end)
 
 #define DEFINE(name)                                                              \
     decltype(&::name) fn_##name = nullptr;                                        \

@@ -83,6 +83,7 @@ class LayerState:
             Rcap = (Rcap + 127) // 128 * 128
         self.Rcap = Rcap
         self.ctx = B.Context(T, k, max(E, cfg.E_router), h, max(f, sf))
+        self.batch = B.Batch(self.ctx)   # for GEMM calls that do not depend on each other: small ones share a launch
         # all-fp32 run (small layers, host inputs): every tensor and every call in fp32, for parity at the 1e-5 level
         self.f32 = bool(f32)
         assert not self.f32 or (hin is not None and not cfg.fp8 and not cfg.mx and not self.eq2), \
@@ -268,19 +269,22 @@ class LayerState:
         if self.eq2:  # eq. (2): A = p * silu(gate) * up, plain-sum combine
             B.moe_gather_row_prob(c, self.topk_prob, self.src_of, Rcap, self.row_prob)
             row_prob = self.row_prob
-        if self.gather:
-            B.moe_grouped_gemm_fwd_gather(c, self.X, T, self.src_of, k, self.W1, self.offsets, E, 2 * f, h, Rcap,
-                                          B.EPI_SWIGLU, row_prob, self.Z, self.A)
-        else:
-            B.moe_grouped_gemm_fwd_weighted(c, self.Xp, self.W1, self.offsets, E, 2 * f, h, Rcap, self.dt, B.EPI_SWIGLU,
-                                            None, None, row_prob, self.Z, self.A)
-        B.moe_grouped_gemm_fwd(c, self.A, self.W2, self.offsets, E, h, f, Rcap, self.dt, B.EPI_NONE,
-                               None, None, self.O, None)
-        if sf:
-            B.moe_grouped_gemm_fwd(c, self.X, self.Ws1, self.off_shared, 1, 2 * sf, h, T, self.dt, B.EPI_SWIGLU,
-                                   None, None, self.Zs, self.As)
-            B.moe_grouped_gemm_fwd(c, self.As, self.Ws2, self.off_shared, 1, h, sf, T, self.dt, B.EPI_NONE,
-                                   None, None, self.S, None)
+        with self.batch as b:
+            if self.gather:
+                B.moe_grouped_gemm_fwd_gather(b, self.X, T, self.src_of, k, self.W1, self.offsets, E, 2 * f, h, Rcap,
+                                              B.EPI_SWIGLU, row_prob, self.Z, self.A)
+            else:
+                B.moe_grouped_gemm_fwd_weighted(b, self.Xp, self.W1, self.offsets, E, 2 * f, h, Rcap, self.dt, B.EPI_SWIGLU,
+                                                None, None, row_prob, self.Z, self.A)
+            if sf:
+                B.moe_grouped_gemm_fwd(b, self.X, self.Ws1, self.off_shared, 1, 2 * sf, h, T, self.dt, B.EPI_SWIGLU,
+                                       None, None, self.Zs, self.As)
+        with self.batch as b:
+            B.moe_grouped_gemm_fwd(b, self.A, self.W2, self.offsets, E, h, f, Rcap, self.dt, B.EPI_NONE,
+                                   None, None, self.O, None)
+            if sf:
+                B.moe_grouped_gemm_fwd(b, self.As, self.Ws2, self.off_shared, 1, h, sf, T, self.dt, B.EPI_NONE,
+                                       None, None, self.S, None)
         B.moe_unpermute_combine(c, self.O, self.dt, self.row_of, None if self.eq2 else self.topk_prob,
                                 self.S if sf else None, T, k, h, self.Y)
 
@@ -288,44 +292,47 @@ class LayerState:
     def _backward_bf16(self):
         c, cfg = self.ctx, self.cfg
         T, k, E, h, f, sf, Rcap = cfg.T, cfg.k, cfg.E, cfg.h, cfg.f, self.sf, self.Rcap
-        wdt = self.wgrad_dt
-        if self.eq2 and self.gather:
-            # dO would be plain copies of dY: both fc2 gradients fetch the rows of dY through the map instead
-            B.moe_grouped_gemm_wgrad_gather(c, self.A, self.dY, B.GATHER_DC, T, self.src_of, k, self.offsets, E, h, f, Rcap,
-                                            0, wdt, self.dW2)
-            B.moe_grouped_gemm_dgrad_gather(c, self.dY, T, self.src_of, k, self.W2, self.offsets, E, h, f, Rcap, self.Z,
-                                            self.row_prob, self.dZ, self.dprob_part)
+        wdt, o1 = self.wgrad_dt, self.off_shared if sf else None
+        if not (self.eq2 and self.gather):
+            # (eq. (2): dO = plain copies of dY, no weight, O is not read)
+            B.moe_unpermute_combine_bwd(c, self.dY, None if self.eq2 else self.O, self.dt, self.row_of, self.src_of,
+                                        None if self.eq2 else self.topk_prob, T, k, h, Rcap, self.dO,
+                                        None if self.eq2 else self.dprob)
+        with self.batch as b:
+            if self.eq2 and self.gather:
+                # dO would be plain copies of dY: both fc2 gradients fetch the rows of dY through the map instead
+                B.moe_grouped_gemm_wgrad_gather(b, self.A, self.dY, B.GATHER_DC, T, self.src_of, k, self.offsets, E, h, f, Rcap,
+                                                0, wdt, self.dW2)
+                B.moe_grouped_gemm_dgrad_gather(b, self.dY, T, self.src_of, k, self.W2, self.offsets, E, h, f, Rcap, self.Z,
+                                                self.row_prob, self.dZ, self.dprob_part)
+            elif self.eq2:
+                # dprob comes out of the fc2 data gradient
+                B.moe_grouped_gemm_wgrad(b, self.A, self.dO, self.offsets, E, h, f, Rcap, self.dt, None, None, 0, wdt,
+                                         self.dW2)
+                B.moe_grouped_gemm_dgrad_weighted(b, self.dO, self.W2, self.offsets, E, h, f, Rcap, self.dt, self.Z, None,
+                                                  None, self.row_prob, self.dZ, self.dprob_part)
+            else:
+                B.moe_grouped_gemm_wgrad(b, self.A, self.dO, self.offsets, E, h, f, Rcap, self.dt, None, None, 0, wdt,
+                                         self.dW2)
+                B.moe_grouped_gemm_dgrad(b, self.dO, self.W2, self.offsets, E, h, f, Rcap, self.dt, self.Z, None, None,
+                                         self.dZ)
+            if sf:
+                B.moe_grouped_gemm_wgrad(b, self.As, self.dY, o1, 1, h, sf, T, self.dt, None, None, 0, wdt, self.dWs2)
+                B.moe_grouped_gemm_dgrad(b, self.dY, self.Ws2, o1, 1, h, sf, T, self.dt, self.Zs, None, None, self.dZs)
+        if self.eq2:
             B.moe_scatter_row_dprob(c, self.dprob_part, self.dprob_parts, self.row_of, T, k, self.dprob)
-        elif self.eq2:
-            # dO = plain copies of dY (no weight, O is not read); dprob comes out of the fc2 data gradient
-            B.moe_unpermute_combine_bwd(c, self.dY, None, self.dt, self.row_of, self.src_of, None,
-                                        T, k, h, Rcap, self.dO, None)
-            B.moe_grouped_gemm_wgrad(c, self.A, self.dO, self.offsets, E, h, f, Rcap, self.dt, None, None, 0, wdt,
-                                     self.dW2)
-            B.moe_grouped_gemm_dgrad_weighted(c, self.dO, self.W2, self.offsets, E, h, f, Rcap, self.dt, self.Z, None,
-                                              None, self.row_prob, self.dZ, self.dprob_part)
-            B.moe_scatter_row_dprob(c, self.dprob_part, self.dprob_parts, self.row_of, T, k, self.dprob)
-        else:
-            B.moe_unpermute_combine_bwd(c, self.dY, self.O, self.dt, self.row_of, self.src_of, self.topk_prob,
-                                        T, k, h, Rcap, self.dO, self.dprob)
-            B.moe_grouped_gemm_wgrad(c, self.A, self.dO, self.offsets, E, h, f, Rcap, self.dt, None, None, 0, wdt,
-                                     self.dW2)
-            B.moe_grouped_gemm_dgrad(c, self.dO, self.W2, self.offsets, E, h, f, Rcap, self.dt, self.Z, None, None,
-                                     self.dZ)
-        if self.gather:
-            B.moe_grouped_gemm_wgrad_gather(c, self.X, self.dZ, B.GATHER_A, T, self.src_of, k, self.offsets, E, 2 * f, h,
-                                            Rcap, 0, wdt, self.dW1)
-        else:
-            B.moe_grouped_gemm_wgrad(c, self.Xp, self.dZ, self.offsets, E, 2 * f, h, Rcap, self.dt, None, None, 0, wdt,
-                                     self.dW1)
-        B.moe_grouped_gemm_dgrad(c, self.dZ, self.W1, self.offsets, E, 2 * f, h, Rcap, self.dt, None, None, None,
-                                 self.dXp)
-        if sf:
-            o1 = self.off_shared
-            B.moe_grouped_gemm_wgrad(c, self.As, self.dY, o1, 1, h, sf, T, self.dt, None, None, 0, wdt, self.dWs2)
-            B.moe_grouped_gemm_dgrad(c, self.dY, self.Ws2, o1, 1, h, sf, T, self.dt, self.Zs, None, None, self.dZs)
-            B.moe_grouped_gemm_wgrad(c, self.X, self.dZs, o1, 1, 2 * sf, h, T, self.dt, None, None, 0, wdt, self.dWs1)
-            B.moe_grouped_gemm_dgrad(c, self.dZs, self.Ws1, o1, 1, 2 * sf, h, T, self.dt, None, None, None, self.dXs)
+        with self.batch as b:
+            if self.gather:
+                B.moe_grouped_gemm_wgrad_gather(b, self.X, self.dZ, B.GATHER_A, T, self.src_of, k, self.offsets, E, 2 * f, h,
+                                                Rcap, 0, wdt, self.dW1)
+            else:
+                B.moe_grouped_gemm_wgrad(b, self.Xp, self.dZ, self.offsets, E, 2 * f, h, Rcap, self.dt, None, None, 0, wdt,
+                                         self.dW1)
+            B.moe_grouped_gemm_dgrad(b, self.dZ, self.W1, self.offsets, E, 2 * f, h, Rcap, self.dt, None, None, None,
+                                     self.dXp)
+            if sf:
+                B.moe_grouped_gemm_wgrad(b, self.X, self.dZs, o1, 1, 2 * sf, h, T, self.dt, None, None, 0, wdt, self.dWs1)
+                B.moe_grouped_gemm_dgrad(b, self.dZs, self.Ws1, o1, 1, 2 * sf, h, T, self.dt, None, None, None, self.dXs)
         # dX[t] = sum of the k permuted-row gradients (+ the shared expert's dX): the plain-sum unpermute
         B.moe_unpermute_combine(c, self.dXp, self.dt, self.row_of, None, self.dXs if sf else None, T, k, h, self.dX)
 

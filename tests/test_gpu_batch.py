@@ -1,0 +1,128 @@
+"""Calls of a batch (moe_batch_create) against the same calls on their context, bit for bit: every kernel that serves several
+calls in one launch, with uneven numbers of them, and what a batch promises beside the results."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+class _Alone:
+    """In the batch's place: every call on the context itself."""
+
+    def __init__(self, ctx):
+        self.ctx = ctx
+
+    def __enter__(self):
+        return self.ctx
+
+    def __exit__(self, *exc):
+        pass
+
+
+# sizes: tiles of 64 rows with two and three stage buffers, weight gradients on one and two, a routed and a shared expert of unlike
+# sizes, calls that are launched at once beside ones that are kept, ragged columns
+SIZES = [
+    dict(T=96, h=128, f=64, E=4, k=2, sf=64),
+    dict(T=1000, h=448, f=320, E=6, k=2, sf=192),
+    dict(T=64, h=576, f=384, E=48, k=4, sf=1024),       # (one stage buffer for the routed weight gradients)
+    dict(T=2048, h=1024, f=512, E=8, k=2, sf=512),
+    dict(T=700, h=2048, f=1536, E=5, k=4, sf=192),      # (routed calls beyond the small tiles)
+]
+
+
+def _layers(size, shared, **kw):
+    from paper_2603_07685_amd import layer as L
+    from paper_2603_07685_amd import workloads as wl
+    recipe = kw.pop("recipe", "bf16")
+    cfg = wl.MoEConfig("batch", T=size["T"], h=size["h"], f=size["f"], E=size["E"], k=size["k"], E_router=size["E"],
+                       score=wl.SOFTMAX, norm_topk=False, load="router", shared_f=size["sf"] if shared else 0,
+                       fp8=recipe == "fp8", mx=recipe == "mxfp8", align=1 if recipe in ("bf16", "fp32") else 128, seed=5)
+    hin = L.host_inputs(cfg) if recipe == "fp32" else None
+    pair = [L.LayerState(cfg, hin, f32=recipe == "fp32", **kw) for _ in range(2)]
+    pair[1].batch = _Alone(pair[1].ctx)
+    return pair
+
+
+OUT = ("Y", "A", "Z", "O", "dX", "dZ", "dW1", "dW2", "dprob")
+SHARED = ("S", "As", "Zs", "dZs", "dXs", "dWs1", "dWs2")
+
+
+def _compare(pair, shared):
+    for st in pair:
+        for n in OUT + (SHARED if shared else ()):
+            getattr(st, n).zero_()
+        st.step()
+    torch.cuda.synchronize()
+    a, b = pair
+    assert a.ctx.poll_error() == 0 and b.ctx.poll_error() == 0
+    for n in OUT + (SHARED if shared else ()):
+        assert torch.equal(getattr(a, n), getattr(b, n)), n
+
+
+@pytest.mark.parametrize("size", range(len(SIZES)))
+@pytest.mark.parametrize("kw", [{}, dict(wgrad_f32=True), dict(gather=True), dict(eq2=True), dict(eq2=True, gather=True, wgrad_f32=True)],
+                         ids=lambda kw: "+".join(kw) or "plain")
+@pytest.mark.parametrize("shared", [False, True])
+def test_layer_is_that_of_single_calls(size, kw, shared):
+    _compare(_layers(SIZES[size], shared, **kw), shared)
+
+
+def test_what_is_kept_and_what_is_not():
+    """Kept calls are launched at the end and not before, more of them than a batch holds are launched on the way, dropped ones never."""
+    from paper_2603_07685_amd import binding as B
+    T, K, N, n = 256, 128, 256, 21
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    A = torch.randn((T, K), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((n, N, K), generator=g, device="cuda").to(torch.bfloat16)
+    off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    ctx = B.Context(T, 1, 1, K, N)
+    batch = B.Batch(ctx)
+    want, got = (torch.full((n, T, N), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2))
+
+    def calls(c, out):
+        for i in range(n):
+            B.moe_grouped_gemm_fwd(c, A, W[i], off, 1, N, K, T, B.BF16, B.EPI_NONE, None, None, out[i], None)
+
+    calls(ctx, want)
+    with batch as b:
+        calls(b, got)
+        torch.cuda.synchronize()
+        assert (got[-1] == 7).all()
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    got.fill_(7.0)
+    with pytest.raises(B.MoeError):
+        with batch as b:
+            B.moe_grouped_gemm_fwd(b, A, W[0], off, 1, N, K, T, B.BF16, B.EPI_NONE, None, None, got[0], None)
+            B.moe_grouped_gemm_fwd(b, A, W[1], off, 1, N, 7, T, B.BF16, B.EPI_NONE, None, None, got[1], None)
+    with batch as b:
+        B.moe_grouped_gemm_fwd(b, A, W[2], off, 1, N, K, T, B.BF16, B.EPI_NONE, None, None, got[2], None)
+    torch.cuda.synchronize()
+    assert (got[0] == 7).all() and (got[1] == 7).all() and torch.equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("at", [0, 1, 2])
+def test_offsets_of_any_call_are_checked(at):
+    """Offsets that fall: the error word is set and that call writes nothing, wherever it stands in the launch; the others are served."""
+    from paper_2603_07685_amd import binding as B
+    T, K, N = 192, 128, 256
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    A = torch.randn((T, K), generator=g, device="cuda").to(torch.bfloat16)
+    dC = torch.randn((T, N), generator=g, device="cuda").to(torch.bfloat16)
+    W = torch.randn((2, N, K), generator=g, device="cuda").to(torch.bfloat16)
+    good = torch.tensor([0, 64, T], dtype=torch.int32, device="cuda")
+    bad = torch.tensor([0, 128, 64], dtype=torch.int32, device="cuda")
+    ctx = B.Context(T, 1, 2, K, N)
+    dA = torch.full((2, T, K), 7.0, dtype=torch.bfloat16, device="cuda")
+    dW = torch.full((2, N, K), 7.0, dtype=torch.bfloat16, device="cuda")
+    with B.Batch(ctx) as b:
+        for i in range(2):
+            B.moe_grouped_gemm_dgrad(b, dC, W, bad if at == i else good, 2, N, K, T, B.BF16, None, None, None, dA[i])
+        B.moe_grouped_gemm_wgrad(b, A, dC, bad if at == 2 else good, 2, N, K, T, B.BF16, None, None, 0, B.BF16, dW)
+    torch.cuda.synchronize()
+    assert ctx.poll_error() == 1
+    for i, t in enumerate((dA[0], dA[1], dW)):
+        assert bool((t == 7).all()) == (i == at), i
