@@ -1,0 +1,104 @@
+// Batches: a second handle on a context that keeps small calls and launches several of them together at its end (host code; the
+// kernels are beside those that serve single calls).
+#include <new>
+
+#include "gemm.h"
+
+extern "C" moe_status moe_batch_create(moe_ctx* ctx, moe_ctx** out) {
+    if (!ctx || !out) return MOE_ERR_ARG;
+    if (ctx->batch) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_batch_create: a batch has no batches of its own");
+    moe_ctx* c = new (std::nothrow) moe_ctx(*ctx);
+    moe_batch* b = c ? new (std::nothrow) moe_batch() : nullptr;
+    if (!b) {
+        delete c;
+        MOE_FAIL(ctx, MOE_ERR_HIP, "moe_batch_create: no host memory");
+    }
+    c->batch = b;
+    c->err[0] = 0;
+    *out = c;
+    return MOE_OK;
+}
+
+extern "C" moe_status moe_batch_end(moe_ctx* batch, void* stream, int launch) {
+    if (!batch) return MOE_ERR_ARG;
+    (void)stream;   // (each call has its own)
+    moe_batch* const b = batch->batch;
+    if (!b) MOE_FAIL(batch, MOE_ERR_ARG, "moe_batch_end: not a batch");
+    if (launch) batch_flush(b);
+    b->n_gemm = b->n_quant = 0;
+    MOE_LAUNCH_CHECK(batch, "calls of a batch");
+    return MOE_OK;
+}
+
+void batch_gemm(moe_batch* b, const gemm_job& j) {
+    if (b->n_gemm == MOE_BATCH_MAX) batch_flush(b);
+    b->gemm[b->n_gemm++] = j;
+}
+
+static void launch_alone(const gemm_job& j) {
+    if (j.kind == JOB_BF16) gt_launch(j.s, j.mode, j.epi, j.f32, j.gath, j.tile, j.a);
+    else gq_launch(nullptr, j.s, j.mode, j.epi, j.f32, j.kind == JOB_MX, j.tile, j.a);
+}
+
+// The calls that go with the first one left: of its kind and stream; forward calls of one epilogue, or data gradients of one epilogue
+// and weight gradients of one output type and gathered operand (as many kinds of a kernel as a layer has use for: beside SwiGLU's
+// backward, fc2, a weight gradient may gather dC, beside the plain data gradient, fc1, A).
+static void gemm_flush(gemm_job* jobs, int n) {
+    auto fits = [](int epi, int gath) { return gath == 0 || gath == (epi == GG_EPI_SWIGLU_BWD ? 1 : 2); };
+    for (int i = 0; i < n; ++i) {
+        const gemm_job& first = jobs[i];
+        if (first.done) continue;
+        gemm_job* take[GT_JOBS] = {};
+        const gemm_job *d = nullptr, *w = nullptr;   // the first data and weight gradient
+        const bool fwd = first.mode == GG_FWD;
+        int count = 0;
+        for (int x = i; x < n; ++x) {
+            gemm_job& j = jobs[x];
+            if (j.done || j.s != first.s || j.kind != first.kind || (j.mode == GG_FWD) != fwd) continue;
+            int at = count;
+            if (fwd) {
+                if (j.epi != first.epi) continue;
+            } else if (j.mode == GG_DGRAD) {
+                if (d ? j.epi != d->epi : w && !fits(j.epi, w->gath)) continue;
+                at = d ? 1 : 0;
+            } else {
+                if (w ? j.f32 != w->f32 || j.gath != w->gath : d && !fits(d->epi, j.gath)) continue;
+                at = w ? 3 : 2;
+            }
+            if (at >= GT_JOBS || take[at]) continue;
+            if (j.mode == GG_DGRAD && !d) d = &j;
+            if (j.mode == GG_WGRAD && !w) w = &j;
+            take[at] = &j;
+            ++count;
+        }
+        for (gemm_job* j : take)
+            if (j) j->done = true;
+        if (count == 1) {
+            launch_alone(first);
+            continue;
+        }
+        // the first call's tiles serve all of a mode
+        const int tile = fwd ? first.tile : d ? d->tile : 3, wtile = w ? w->tile : 2;
+        gt_jobs m;
+        memset(&m, 0, sizeof(m));
+        int64_t at = 0;
+        for (int x = 0; x < GT_JOBS; ++x) {
+            m.start[x] = (int)at;
+            if (!take[x]) continue;
+            const gemm_job& j = *take[x];
+            m.a[x] = j.a;
+            const int bm = j.mode == GG_WGRAD || tile == 2 ? 128 : 64;
+            at += j.kind == JOB_BF16 ? gt_blocks(j.mode, j.epi, bm, j.a) : gq_blocks(j.mode, j.epi, bm, j.a);
+        }
+        m.start[GT_JOBS] = (int)at;
+        const int epi = fwd ? first.epi : d ? d->epi : w->gath == 1 ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
+        if (first.kind == JOB_BF16) gt_launch_jobs(first.s, fwd, epi, w && w->f32, w ? w->gath : 0, tile, wtile, m);
+        else gq_launch_jobs(first.s, first.kind == JOB_MX, fwd, epi, w && w->f32, tile, m);
+    }
+}
+
+void batch_flush(moe_batch* b) {
+    gemm_flush(b->gemm, b->n_gemm);
+    quant_flush(b->quant, b->n_quant);
+    b->n_gemm = b->n_quant = 0;
+}

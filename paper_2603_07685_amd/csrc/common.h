@@ -259,9 +259,10 @@ __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, i
 
 // Quantised copies of the tensor X [rows, cols] that a grouped GEMM has just stored (fp8.hip): blockwise 1x128 codes and
 // scales, or MXFP8 1x32 (and, q_col not NULL, 32x1) ones, of the rows offsets[0] .. offsets[E] - 1; nothing at all where the
-// GEMM refuses the offsets too (they fall, leave 0 .. rows, or, with q_col, lie off the 128-row grid).
+// GEMM refuses the offsets too (they fall, leave 0 .. rows, or, with q_col, lie off the 128-row grid).  `after`: the GEMM is kept in
+// ctx's batch (only a two-copy MXFP8 call can be), and so the copies have to be.
 moe_status moe_quantise_live(moe_ctx* ctx, hipStream_t s, const void* X, int64_t rows, int cols, const int32_t* offsets, int E,
-                             bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col);
+                             bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col, bool after);
 
 // all-fp32 grouped GEMMs (gemm_f32.hip), reached from the public entry points with dt = MOE_F32
 int moe_gg_f32_choice(int num_cu, int mode, int epi, int E, int N, int K, int64_t Rcap);   // the kernel: 64 or 128 (tile of gf_kernel), 3 (gs_kernel)

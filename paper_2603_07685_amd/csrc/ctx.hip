@@ -68,32 +68,6 @@ extern "C" moe_status moe_ctx_destroy(moe_ctx* ctx) {
     return e == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-extern "C" moe_status moe_batch_create(moe_ctx* ctx, moe_ctx** out) {
-    if (!ctx || !out) return MOE_ERR_ARG;
-    if (ctx->batch) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_batch_create: a batch has no batches of its own");
-    moe_ctx* c = new (std::nothrow) moe_ctx(*ctx);
-    moe_batch* b = c ? new (std::nothrow) moe_batch() : nullptr;
-    if (!b) {
-        delete c;
-        MOE_FAIL(ctx, MOE_ERR_HIP, "moe_batch_create: no host memory");
-    }
-    c->batch = b;
-    c->err[0] = 0;
-    *out = c;
-    return MOE_OK;
-}
-
-extern "C" moe_status moe_batch_end(moe_ctx* batch, void* stream, int launch) {
-    if (!batch) return MOE_ERR_ARG;
-    (void)stream;
-    moe_batch* const b = batch->batch;
-    if (!b) MOE_FAIL(batch, MOE_ERR_ARG, "moe_batch_end: not a batch");
-    if (launch) gt_flush(b->gt, b->n_gt);
-    b->n_gt = 0;
-    MOE_LAUNCH_CHECK(batch, "calls of a batch");
-    return MOE_OK;
-}
-
 static thread_local char ctxless_err[512];
 char* moe_ctxless_error() { return ctxless_err; }
 

@@ -9,7 +9,7 @@
 //   128x1   : a wave owns a 128-row x 512-column panel, 8 columns per lane; first pass keeps the running
 //             column amax in registers, second pass re-reads the panel (from L2) and converts.
 //   128x128 : a 512-thread workgroup owns one block, 32 elements per thread held in registers.
-#include "common.h"
+#include "gemm.h"
 
 // Threads per 128 x 128 tile of the two-copy quantisers and the weight quantiser, 2048 / this 16-byte pieces per lane.  At 256 a call
 // of few tiles was bound by one lane's chain of eight pieces and sixteen divisions; at 1024 every lane's share of the column scales
@@ -19,6 +19,9 @@
 // h 512 f 256 E 8 k 2 7.6, 7.9 : 6.3, 6.9; T 16384 h 7168 f 2048 E 32 k 8: weights 793, 376 : 739, 365, tokens and p * dY 740, 764 : 675, 715,
 // A and dZ 208, 438 : 198, 412.
 #define QUANT_THREADS 512
+
+// Calls of a batch: up to this many tiles are kept (four per compute unit and more: a launch of its own costs little)
+#define QUANT_KEEP 4096
 
 __device__ __forceinline__ float amax8(u32x4_t v) {
     float m = fabsf(bf16_lo(v.x));
@@ -133,12 +136,26 @@ __global__ __launch_bounds__(256) void quant_128x1_kernel(const u32x4_t* __restr
 
 // ---- 128x128 -------------------------------------------------------------------------------
 // grid = groups * (rows/128) * (cols/128) workgroups of QUANT_THREADS
-__global__ __launch_bounds__(QUANT_THREADS) void quant_128x128_kernel(const u32x4_t* __restrict__ W, int rows, int cols,
-                                                            u32x2_t* __restrict__ q, float* __restrict__ scale) {
+struct quant_lds {
+    union {
+        float part[32];
+        struct {
+            float cmax[16][128];
+            __attribute__((aligned(16))) float cscale[4][128];
+            __attribute__((aligned(16))) float crcp[128];
+            uint8_t sc[4][128];
+        };
+    };
+};
+__device__ __forceinline__ void quant_128x128_body(const quant_args& a, quant_lds& lds, int block) {
+    const u32x4_t* const __restrict__ W = a.X;
+    u32x2_t* const __restrict__ q = a.q_row;
+    float* const __restrict__ scale = (float*)a.s_row;
+    float* const part = lds.part;
+    const int rows = (int)a.rows, cols = a.cols;
     constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RP = 128 / PIECES;   // per lane; waves; rows of a pass
-    __shared__ float part[NW];
     const int nbr = rows / 128, nbc = cols / 128;
-    const int b = blockIdx.x;
+    const int b = block;
     const int g = b / (nbr * nbc), rb = (b / nbc) % nbr, cb = b % nbc;
     const int vpr = cols / 8;
     const int tr = threadIdx.x >> 4, tc = threadIdx.x & 15;   // RP rows x 16 vectors per pass
@@ -161,6 +178,44 @@ __global__ __launch_bounds__(QUANT_THREADS) void quant_128x128_kernel(const u32x
     if (threadIdx.x == 0) scale[b] = s;
 #pragma unroll
     for (int it = 0; it < PIECES; ++it) q[base + (int64_t)(it * RP + tr) * vpr] = cvt8_e4m3(v[it], s);
+}
+__global__ __launch_bounds__(QUANT_THREADS) void quant_128x128_kernel(const quant_args a) {
+    __shared__ quant_lds lds;
+    quant_128x128_body(a, lds, (int)blockIdx.x);
+}
+
+// floor(s / k) for a map entry 0 <= s < 2^31 as one widening multiplication (division by an invariant integer,
+// rounded-up constant): with l = ceil(log2 k) and m = ceil(2^(31 + l) / k) <= 2^32 - 1, (s * m) >> (31 + l) == s / k
+// for every such s, and the product stays below 2^63.
+struct gather_div_t { uint32_t m; int sh; };
+static inline gather_div_t gather_div(int k) {
+    int l = 0;
+    while ((1 << l) < k) ++l;
+    return gather_div_t{(uint32_t)(((1ull << (31 + l)) + (uint64_t)k - 1) / (uint64_t)k), 31 + l};
+}
+static quant_args quant_make(int kind, const void* X, int64_t rows, int cols, const int32_t* rows_dev, void* q_row, void* s_row,
+                             void* q_col, void* s_col, int64_t blocks) {
+    quant_args a;
+    memset(&a, 0, sizeof(a));
+    a.kind = kind;
+    a.X = (const u32x4_t*)X;
+    a.rows = rows;
+    a.cols = cols;
+    a.rows_dev = rows_dev;
+    a.q_row = (u32x2_t*)q_row;
+    a.s_row = s_row;
+    a.q_col = (u32x2_t*)q_col;
+    a.s_col = s_col;
+    a.groups = 1;
+    a.blocks = blocks;
+    return a;
+}
+static void quant_gather(quant_args& a, const int32_t* src_of, int k, const float* pair_scale, int groups) {
+    a.src_of = src_of;
+    a.k_magic = gather_div(k).m;
+    a.k_shift = gather_div(k).sh;
+    a.pair_scale = pair_scale;
+    a.groups = groups;
 }
 
 static moe_status fp8_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who, const void* X, int64_t rows, int cols,
@@ -209,8 +264,8 @@ extern "C" moe_status moe_fp8_quantize(moe_ctx* ctx, void* stream, const void* X
             if (rows_dev) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_fp8_quantize(128x128): rows_dev is not used for weights");
             const int64_t nb = (int64_t)groups * (rows / 128) * (cols / 128);
             if (nb > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "moe_fp8_quantize(128x128): too many blocks");
-            hipLaunchKernelGGL(quant_128x128_kernel, dim3((unsigned)nb), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, (int)rows, cols,
-                               (u32x2_t*)q, scale);
+            quant_args a = quant_make(QUANT_WEIGHTS, X, rows, cols, nullptr, q, scale, nullptr, nullptr, nb);
+            quant_submit(ctx, s, a, false);
             break;
         }
         default:
@@ -234,32 +289,25 @@ extern "C" moe_status moe_fp8_quantize(moe_ctx* ctx, void* stream, const void* X
 // Scales and codes are formed exactly as in the single-direction kernels above (amax / 448, fp32 division,
 // hardware conversion), so both copies are bit-identical to theirs.
 // ---------------------------------------------------------------------------
-// floor(s / k) for a map entry 0 <= s < 2^31 as one widening multiplication (division by an invariant integer,
-// rounded-up constant): with l = ceil(log2 k) and m = ceil(2^(31 + l) / k) <= 2^32 - 1, (s * m) >> (31 + l) == s / k
-// for every such s, and the product stays below 2^63.
-struct gather_div_t { uint32_t m; int sh; };
-static inline gather_div_t gather_div(int k) {
-    int l = 0;
-    while ((1 << l) < k) ++l;
-    return gather_div_t{(uint32_t)(((1ull << (31 + l)) + (uint64_t)k - 1) / (uint64_t)k), 31 + l};
-}
-
 __device__ __forceinline__ uint32_t scale2_bf16_bw(uint32_t w, float sc) { return pack_bf16(sc * bf16_lo(w), sc * bf16_hi(w)); }
 
 template <bool GATHER>
-__global__ __launch_bounds__(QUANT_THREADS) void fp8_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
-                                                               const int32_t* __restrict__ rows_dev,
-                                                               const int32_t* __restrict__ src_of, uint32_t k_magic, int k_shift,
-                                                               const float* __restrict__ pair_scale, int groups,
-                                                               u32x2_t* __restrict__ q_row, float* __restrict__ s_row,
-                                                               u32x2_t* __restrict__ q_col, float* __restrict__ s_col) {
+__device__ __forceinline__ void fp8_rowcol_body(const quant_args& a, quant_lds& lds, int block) {
+    const u32x4_t* const __restrict__ X = a.X;
+    const int64_t rows = a.rows;
+    const int cols = a.cols, groups = a.groups, k_shift = a.k_shift;
+    const uint32_t k_magic = a.k_magic;
+    const int32_t *const __restrict__ rows_dev = a.rows_dev, *const __restrict__ src_of = a.src_of;
+    const float* const __restrict__ pair_scale = a.pair_scale;
+    u32x2_t *const __restrict__ q_row = a.q_row, *const __restrict__ q_col = a.q_col;
+    float *const __restrict__ s_row = (float*)a.s_row, *const __restrict__ s_col = (float*)a.s_col;
+    auto& cmax = lds.cmax;
+    float *const cscale = lds.cscale[0], *const crcp = lds.crcp;
     constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RW = 4 * PIECES;   // per lane; waves; rows of a wave
-    __shared__ float cmax[NW][128];
-    __shared__ __attribute__((aligned(16))) float cscale[128], crcp[128];
     const int64_t live = rows_dev ? min((int64_t)*rows_dev, rows) : rows;
     const int ctiles = cols / 128;
-    int64_t rt = blockIdx.x / ctiles;
-    const int ct = blockIdx.x % ctiles;
+    int64_t rt = block / ctiles;
+    const int ct = block % ctiles;
     if (GATHER && groups > 1) {  // row tiles expert-interleaved: the k copies of a token are read close together in time
         const int64_t S = (rows / 128 + groups - 1) / groups;
         rt = (rt % groups) * S + rt / groups;
@@ -377,6 +425,11 @@ __global__ __launch_bounds__(QUANT_THREADS) void fp8_quant_rowcol_kernel(const u
         }
     }
 }
+template <bool GATHER>
+__global__ __launch_bounds__(QUANT_THREADS) void fp8_quant_rowcol_kernel(const quant_args a) {
+    __shared__ quant_lds lds;
+    fp8_rowcol_body<GATHER>(a, lds, (int)blockIdx.x);
+}
 
 static moe_status fp8_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who, const void* X, int64_t rows, int cols,
                                     const int32_t* rows_dev, void* q_row, float* s_row, void* q_col, float* s_col,
@@ -388,13 +441,9 @@ static moe_status fp8_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who
     const int64_t tiles_r = src_of ? (rows / 128 + groups - 1) / groups * groups : rows / 128;
     const int64_t nblk = tiles_r * (cols / 128);
     if (nblk > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: too many tiles", who);
-    if (src_of)
-        hipLaunchKernelGGL(fp8_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
-                           rows_dev, src_of, gather_div(k).m, gather_div(k).sh, pair_scale, groups, (u32x2_t*)q_row, s_row,
-                           (u32x2_t*)q_col, s_col);
-    else
-        hipLaunchKernelGGL(fp8_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
-                           rows_dev, nullptr, 0, 0, nullptr, 1, (u32x2_t*)q_row, s_row, (u32x2_t*)q_col, s_col);
+    quant_args a = quant_make(src_of ? QUANT_FP8_GATHER : QUANT_FP8, X, rows, cols, rows_dev, q_row, s_row, q_col, s_col, nblk);
+    if (src_of) quant_gather(a, src_of, k, pair_scale, groups);
+    quant_submit(ctx, s, a, false);
     return MOE_OK;
 }
 
@@ -477,21 +526,24 @@ __global__ __launch_bounds__(256) void mx_quant_1x32_kernel(const u32x4_t* __res
 __device__ __forceinline__ uint32_t scale2_bf16(uint32_t w, float sc) { return pack_bf16(sc * bf16_lo(w), sc * bf16_hi(w)); }
 
 template <bool GATHER>
-__global__ __launch_bounds__(QUANT_THREADS) void mx_quant_rowcol_kernel(const u32x4_t* __restrict__ X, int64_t rows, int cols,
-                                                              const int32_t* __restrict__ rows_dev, int E,
-                                                              const int32_t* __restrict__ src_of, uint32_t k_magic, int k_shift,
-                                                              const float* __restrict__ pair_scale, int groups,
-                                                              u32x2_t* __restrict__ q_row, uint32_t* __restrict__ e8_row,
-                                                              u32x2_t* __restrict__ q_col, uint32_t* __restrict__ e8_col) {
-    constexpr int PIECES = 2048 / QUANT_THREADS, NW = 32 / PIECES, RW = 4 * PIECES;   // per lane; waves; rows of a wave
+__device__ __forceinline__ void mx_rowcol_body(const quant_args& a, quant_lds& lds, int block) {
+    const u32x4_t* const __restrict__ X = a.X;
+    const int64_t rows = a.rows;
+    const int cols = a.cols, groups = a.groups, k_shift = a.k_shift, E = a.E;
+    const uint32_t k_magic = a.k_magic;
+    const int32_t *const __restrict__ rows_dev = a.rows_dev, *const __restrict__ src_of = a.src_of;
+    const float* const __restrict__ pair_scale = a.pair_scale;
+    u32x2_t *const __restrict__ q_row = a.q_row, *const __restrict__ q_col = a.q_col;
+    uint32_t *const __restrict__ e8_row = (uint32_t*)a.s_row, *const __restrict__ e8_col = (uint32_t*)a.s_col;
+    auto& cmax = lds.cmax;
+    auto& cscale = lds.cscale;
+    auto& sc = lds.sc;
+    constexpr int PIECES = 2048 / QUANT_THREADS, RW = 4 * PIECES;   // per lane; rows of a wave
     static_assert(QUANT_THREADS == 512, "a thread per column and 32-row block");
-    __shared__ float cmax[NW][128];
-    __shared__ __attribute__((aligned(16))) float cscale[4][128];
-    __shared__ uint8_t sc[4][128];
     const int64_t live = rows_dev ? min((int64_t)*rows_dev, rows) : rows;
     const int ctiles = cols / 128;
-    int64_t rt = blockIdx.x / ctiles;
-    const int ct = blockIdx.x % ctiles;
+    int64_t rt = block / ctiles;
+    const int ct = block % ctiles;
     if (GATHER && groups > 1) {
         // Visit the row tiles expert-interleaved: with `groups` experts of roughly equal extent, consecutive
         // workgroups take the same relative position in different experts, which (stable order inside an expert)
@@ -600,24 +652,86 @@ __global__ __launch_bounds__(QUANT_THREADS) void mx_quant_rowcol_kernel(const u3
         }
     }
 }
+template <bool GATHER>
+__global__ __launch_bounds__(QUANT_THREADS) void mx_quant_rowcol_kernel(const quant_args a) {
+    __shared__ quant_lds lds;
+    mx_rowcol_body<GATHER>(a, lds, (int)blockIdx.x);
+}
+
+// Independent calls of one recipe in one launch (a batch's), in the order of the calls
+template <bool MX>
+__global__ __launch_bounds__(QUANT_THREADS) void quant_jobs_kernel(const quant_jobs m) {
+    __shared__ quant_lds lds;
+    int j = 0;
+#pragma unroll
+    for (int x = 1; x < QUANT_JOBS; ++x) j += (int)blockIdx.x >= m.start[x];
+    const quant_args& a = m.a[j];
+    const int block = (int)blockIdx.x - m.start[j];
+    if constexpr (MX) {
+        if (a.kind == QUANT_MX_GATHER) mx_rowcol_body<true>(a, lds, block);
+        else mx_rowcol_body<false>(a, lds, block);
+    } else {
+        if (a.kind == QUANT_FP8_GATHER) fp8_rowcol_body<true>(a, lds, block);
+        else if (a.kind == QUANT_FP8) fp8_rowcol_body<false>(a, lds, block);
+        else quant_128x128_body(a, lds, block);
+    }
+}
+
+static void quant_launch(hipStream_t s, const quant_args& a) {
+    const dim3 grid((unsigned)a.blocks), block(QUANT_THREADS);
+    switch (a.kind) {
+        case QUANT_WEIGHTS: hipLaunchKernelGGL(quant_128x128_kernel, grid, block, 0, s, a); break;
+        case QUANT_FP8: hipLaunchKernelGGL(fp8_quant_rowcol_kernel<false>, grid, block, 0, s, a); break;
+        case QUANT_FP8_GATHER: hipLaunchKernelGGL(fp8_quant_rowcol_kernel<true>, grid, block, 0, s, a); break;
+        case QUANT_MX: hipLaunchKernelGGL(mx_quant_rowcol_kernel<false>, grid, block, 0, s, a); break;
+        default: hipLaunchKernelGGL(mx_quant_rowcol_kernel<true>, grid, block, 0, s, a); break;
+    }
+}
+void quant_submit(moe_ctx* ctx, hipStream_t s, const quant_args& a, bool after) {
+    moe_batch* const b = ctx->batch;
+    if (!b || (!after && a.blocks > QUANT_KEEP)) return quant_launch(s, a);
+    if (b->n_quant == MOE_BATCH_MAX) batch_flush(b);
+    b->quant[b->n_quant++] = {s, false, a};
+}
+void quant_flush(quant_job* jobs, int n) {
+    for (int i = 0; i < n; ++i) {
+        if (jobs[i].done) continue;
+        quant_jobs m;
+        memset(&m, 0, sizeof(m));
+        const bool mx = jobs[i].a.kind >= QUANT_MX;
+        int count = 0;
+        int64_t at = 0;
+        for (int x = i; x < n && count < QUANT_JOBS; ++x) {
+            quant_job& j = jobs[x];
+            if (j.done || j.s != jobs[i].s || (j.a.kind >= QUANT_MX) != mx || (count && at + j.a.blocks > QUANT_JOBS * QUANT_KEEP)) continue;
+            m.a[count] = j.a;
+            m.start[count++] = (int)at;
+            at += j.a.blocks;
+            j.done = true;
+        }
+        if (count == 1) {
+            quant_launch(jobs[i].s, m.a[0]);
+            continue;
+        }
+        for (int x = count; x <= QUANT_JOBS; ++x) m.start[x] = (int)at;
+        if (mx) hipLaunchKernelGGL(quant_jobs_kernel<true>, dim3((unsigned)at), dim3(QUANT_THREADS), 0, jobs[i].s, m);
+        else hipLaunchKernelGGL(quant_jobs_kernel<false>, dim3((unsigned)at), dim3(QUANT_THREADS), 0, jobs[i].s, m);
+    }
+}
 
 static moe_status mx_rowcol_launch(moe_ctx* ctx, hipStream_t s, const char* who, const void* X, int64_t rows, int cols,
                                    const int32_t* rows_dev, void* q_row, uint8_t* e8_row, void* q_col, uint8_t* e8_col,
                                    const int32_t* src_of = nullptr, int k = 1, const float* pair_scale = nullptr,
-                                   int groups = 1, int E = 0) {
+                                   int groups = 1, int E = 0, bool after = false) {
     if (rows % 128 || cols % 128) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: rows and cols must be multiples of 128", who);
     if (groups < 1) groups = 1;
     const int64_t tiles_r = src_of ? (rows / 128 + groups - 1) / groups * groups : rows / 128;
     const int64_t nblk = tiles_r * (cols / 128);
     if (nblk > 0x7fffffffLL) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: too many tiles", who);
-    if (src_of)
-        hipLaunchKernelGGL(mx_quant_rowcol_kernel<true>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
-                           rows_dev, 0, src_of, gather_div(k).m, gather_div(k).sh, pair_scale, groups, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
-                           (uint32_t*)e8_col);
-    else
-        hipLaunchKernelGGL(mx_quant_rowcol_kernel<false>, dim3((unsigned)nblk), dim3(QUANT_THREADS), 0, s, (const u32x4_t*)X, rows, cols,
-                           rows_dev, E, nullptr, 0, 0, nullptr, 1, (u32x2_t*)q_row, (uint32_t*)e8_row, (u32x2_t*)q_col,
-                           (uint32_t*)e8_col);
+    quant_args a = quant_make(src_of ? QUANT_MX_GATHER : QUANT_MX, X, rows, cols, rows_dev, q_row, e8_row, q_col, e8_col, nblk);
+    if (src_of) quant_gather(a, src_of, k, pair_scale, groups);
+    a.E = E;
+    quant_submit(ctx, s, a, after);
     return MOE_OK;
 }
 
@@ -686,14 +800,14 @@ extern "C" moe_status moe_mx_quantize_rowcol_gather(moe_ctx* ctx, void* stream, 
 }
 
 moe_status moe_quantise_live(moe_ctx* ctx, hipStream_t s, const void* X, int64_t rows, int cols, const int32_t* offsets, int E,
-                             bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col) {
+                             bool mx, void* q, void* scale, void* q_col, uint8_t* e8_col, bool after) {
     const char* who = "quantised copies of a grouped GEMM";
     const int32_t* const end = offsets + E;
     const int64_t most = (int64_t)(ctx->num_cu > 0 ? ctx->num_cu : 256) * 32, grid = ceil_div64(rows * (cols / 8), 256);
     const dim3 g((unsigned)(grid < most ? grid : most)), b(256);
     if (cols % 128) MOE_FAIL(ctx, MOE_ERR_ARG, "%s: %d columns are not a multiple of 128", who, cols);
     if (mx && q_col) {
-        const moe_status st = mx_rowcol_launch(ctx, s, who, X, rows, cols, end, q, (uint8_t*)scale, q_col, e8_col, nullptr, 1, nullptr, 1, E);
+        const moe_status st = mx_rowcol_launch(ctx, s, who, X, rows, cols, end, q, (uint8_t*)scale, q_col, e8_col, nullptr, 1, nullptr, 1, E, after);
         if (st != MOE_OK) return st;
     } else if (mx) {
         hipLaunchKernelGGL(mx_quant_1x32_kernel, g, b, 0, s, (const u32x4_t*)X, rows, cols, end, E, (u32x2_t*)q, (uint8_t*)scale);

@@ -119,22 +119,62 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a);
 // Rows from which on a weight gradient on small tiles may split its contraction (set split_cap and partials)
 #define GT_SPLIT_ROWS 24576
 void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
-// Calls of a batch that wait for its end: gt_submit records a call, or launches it where the context is no batch or the call is none
-// of the small ones; gt_flush launches the recorded ones, up to GT_JOBS of them together.
-#define GT_JOBS 4
-struct gt_job {
-    hipStream_t s;
-    int mode, epi, gath, tile;
-    bool f32, done;
-    gg_args a;
-};
-#define MOE_BATCH_MAX 16
-struct moe_batch {
-    gt_job gt[MOE_BATCH_MAX];
-    int n_gt;
-};
-void gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
-void gt_flush(gt_job* jobs, int n);
 // the same for one-byte operands (gemm_tile8.hip); `quant`: the call also asks for quantised copies of its output
 int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg_args& a);
 void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a);
+
+// ---- batches (moe_batch_create; batch.hip): calls kept until the batch's end, launched together ----
+// Up to four grouped GEMMs of a launch: the workgroups of call x are start[x] .. start[x + 1] - 1, multiples of 8 of them, so
+// that the XCDs' shares of a call stay.  Forward calls from 0 on; or data gradients 0 and 1, weight gradients 2 and 3.
+#define GT_JOBS 4
+struct gt_jobs {
+    gg_args a[GT_JOBS];
+    int start[GT_JOBS + 1];
+};
+enum { JOB_BF16 = 0, JOB_FP8 = 1, JOB_MX = 2 };
+struct gemm_job {
+    hipStream_t s;
+    int mode, epi, gath, tile, kind;
+    bool f32, done;
+    gg_args a;
+};
+// a call of the tile quantisers (fp8.hip), and up to six of a launch, in the order of the calls
+enum { QUANT_WEIGHTS = 0, QUANT_FP8 = 1, QUANT_FP8_GATHER = 2, QUANT_MX = 3, QUANT_MX_GATHER = 4 };
+struct quant_args {
+    int kind, cols, E, groups, k_shift;
+    uint32_t k_magic;
+    const u32x4_t* X;
+    int64_t rows, blocks;
+    const int32_t *rows_dev, *src_of;
+    const float* pair_scale;
+    u32x2_t *q_row, *q_col;
+    void *s_row, *s_col;
+};
+#define QUANT_JOBS 6
+struct quant_jobs {
+    quant_args a[QUANT_JOBS];
+    int start[QUANT_JOBS + 1];
+};
+struct quant_job {
+    hipStream_t s;
+    bool done;
+    quant_args a;
+};
+#define MOE_BATCH_MAX 16
+struct moe_batch {
+    gemm_job gemm[MOE_BATCH_MAX];
+    quant_job quant[MOE_BATCH_MAX];   // (launched behind the GEMMs: among them the quantised copies of their outputs)
+    int n_gemm, n_quant;
+};
+void batch_flush(moe_batch* b);
+void batch_gemm(moe_batch* b, const gemm_job& j);
+// gt_submit, gq_submit: launch a call, or keep it in the context's batch (true)
+bool gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
+bool gq_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a);
+int64_t gt_blocks(int mode, int epi, int bm, const gg_args& a);
+int64_t gq_blocks(int mode, int epi, int bm, const gg_args& a);
+void gt_launch_jobs(hipStream_t s, bool fwd, int epi, bool f32, int wgath, int tile, int wtile, const gt_jobs& m);
+void gq_launch_jobs(hipStream_t s, bool mx, bool fwd, int epi, bool f32, int tile, const gt_jobs& m);
+// after: the copies of a kept GEMM's output
+void quant_submit(moe_ctx* ctx, hipStream_t s, const quant_args& a, bool after);
+void quant_flush(quant_job* jobs, int n);

@@ -1987,9 +1987,9 @@ static moe_status gg_mx_out_check(moe_ctx* ctx, const char* who, const gg_mx_out
 
 // The quantised copies of the tensor X [Rcap, cols] that a kernel of gemm_tile8.hip has stored: one more launch, which gives
 // the codes and scales of the quantising epilogues.
-static moe_status gg_quantise(moe_ctx* ctx, void* stream, const void* X, int cols, bool mx, const gg_args& a) {
+static moe_status gg_quantise(moe_ctx* ctx, void* stream, const void* X, int cols, bool mx, const gg_args& a, bool kept) {
     return moe_quantise_live(ctx, (hipStream_t)stream, X, a.Rcap, cols, a.offsets, a.E, mx, a.out_q,
-                             mx ? (void*)a.out_q_e8 : (void*)a.out_q_scale, a.out_qc, a.out_qc_e8);
+                             mx ? (void*)a.out_q_e8 : (void*)a.out_q_scale, a.out_qc, a.out_qc_e8, kept);
 }
 
 static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const void* B, const int32_t* offsets, int E, int N,
@@ -2069,10 +2069,10 @@ static moe_status gg_fwd_all(moe_ctx* ctx, void* stream, const void* A, const vo
     }
     const int ge = epi == MOE_EPI_SWIGLU ? GG_EPI_SWIGLU : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_FWD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_FWD, ge, a)) {
-        if (!fp8) gt_submit(ctx, (hipStream_t)stream, GG_FWD, ge, false, 0, tile, a);
-        else gq_launch(ctx, (hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
+        const bool kept = !fp8 ? gt_submit(ctx, (hipStream_t)stream, GG_FWD, ge, false, 0, tile, a)
+                               : gq_submit(ctx, (hipStream_t)stream, GG_FWD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<fwd>");
-        return a.out_q ? gg_quantise(ctx, stream, C_act, N / 2, mx, a) : MOE_OK;
+        return a.out_q ? gg_quantise(ctx, stream, C_act, N / 2, mx, a, kept) : MOE_OK;
     } else if (epi == MOE_EPI_SWIGLU) {
         if (fp8) GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 1);
         else GG_LAUNCH(GG_FWD, GG_EPI_SWIGLU, false, 0);
@@ -2197,10 +2197,10 @@ static moe_status gg_dgrad_all(moe_ctx* ctx, void* stream, const void* dC, const
     }
     const int ge = Z_saved ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
     if (const int tile = fp8 ? gq_tile(ctx, GG_DGRAD, ge, mx, a.out_q != nullptr, a) : gt_tile(ctx, GG_DGRAD, ge, a)) {
-        if (!fp8) gt_submit(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a);
-        else gq_launch(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
+        const bool kept = !fp8 ? gt_submit(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, 0, tile, a)
+                               : gq_submit(ctx, (hipStream_t)stream, GG_DGRAD, ge, false, mx, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<dgrad>");
-        return a.out_q ? gg_quantise(ctx, stream, dA, 2 * K, mx, a) : MOE_OK;
+        return a.out_q ? gg_quantise(ctx, stream, dA, 2 * K, mx, a, kept) : MOE_OK;
     } else if (Z_saved) {
         if (fp8) GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 1);
         else GG_LAUNCH(GG_DGRAD, GG_EPI_SWIGLU_BWD, false, 0);
@@ -2265,7 +2265,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     auto slices = [&](size_t bytes) { return (int)(ws_free / bytes < GG_MAX_SPLIT ? ws_free / bytes : GG_MAX_SPLIT); };
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
         if (!mx && !bw && Rcap > GT_SPLIT_ROWS) a.split_cap = slices((size_t)N * K * sizeof(float));
-        if (mx || bw) gq_launch(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
+        if (mx || bw) gq_submit(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
         else gt_submit(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");
         return MOE_OK;

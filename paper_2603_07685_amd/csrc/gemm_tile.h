@@ -155,3 +155,10 @@ __device__ __forceinline__ void gt_output(const gg_args& a, float* const stg, in
         }
     }
 }
+
+__device__ __forceinline__ int gt_job_of(const gt_jobs& m, int block) {
+    int j = 0;
+#pragma unroll
+    for (int x = 1; x < GT_JOBS; ++x) j += block >= m.start[x];
+    return j;
+}

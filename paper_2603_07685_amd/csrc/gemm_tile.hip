@@ -354,21 +354,10 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
     gt_body<MODE, EPI, OUT_F32, GATH, BM, NBUF, SPLIT>(a, lds, (int)blockIdx.x);
 }
 
-// Independent calls in one launch: the workgroups of call x are start[x] .. start[x + 1] - 1 (multiples of 8: the XCDs' shares of a
-// call stay).  Small calls leave compute units idle in their start, their output phase and the last of their rounds, and each
+// Independent calls in one launch.  Small calls leave compute units idle in their start, their output phase and the last of their rounds, and each
 // launch costs about 2 us behind another; together they fill each other's gaps.  A step, us, one launch each : together: T 256 h 128
 // f 256 E 8 k 2 52.8 : 45.1; T 377 h 2240 f 512 E 8 k 2 130 : 106; T 7394 h 128 f 192 E 24 125 : 104; with a shared expert T 27 h 576 f 512
 // E 7 k 2 105 : 60, T 873 h 896 f 2688 E 12 k 2 342 : 300.  Data gradients go first: their tiles take longer.
-struct gt_jobs {
-    gg_args a[GT_JOBS];
-    int start[GT_JOBS + 1];
-};
-__device__ __forceinline__ int gt_job_of(const gt_jobs& m, int block) {
-    int j = 0;
-#pragma unroll
-    for (int x = 1; x < GT_JOBS; ++x) j += block >= m.start[x];
-    return j;
-}
 // forward calls with one epilogue
 template <int EPI, int BM, int NBUF>
 __global__ __launch_bounds__(256, NBUF == 2 && BM == 64 ? 3 : 2) void gt_fwd_jobs_kernel(const gt_jobs m) {
@@ -499,7 +488,7 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
 }
 
 // (a multiple of 8: every XCD gets as many workgroups of a call)
-static int64_t gt_blocks(int mode, int epi, int bm, const gg_args& a) {
+int64_t gt_blocks(int mode, int epi, int bm, const gg_args& a) {
     const int64_t cols = epi == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(mode == GG_FWD ? a.N : a.K, GT_BN);
     const int64_t n = cols * (mode == GG_WGRAD ? (a.E + a.split_cap) * ceil_div64(a.N, bm) : ceil_div64(a.Rcap, bm) + a.E);
     return ceil_div64(n, 8) * 8;
@@ -554,80 +543,28 @@ static void gt_bwd_jobs(hipStream_t s, int tile, int wtile, int64_t n, const gt_
     else if (tile == 1) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 2, F32, WGATH, 2>), grid, block, 0, s, m);
     else hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 2>), grid, block, 0, s, m);
 }
-void gt_flush(gt_job* jobs, int n) {
-    for (int i = 0; i < n; ++i) {
-        gt_job& first = jobs[i];
-        if (first.done) continue;
-        // the calls that can go with this one: same stream; forward calls of one epilogue, or data gradients of one epilogue and
-        // weight gradients of one output type and gathered operand
-        gt_job* take[GT_JOBS] = {};
-        int tile = 0, wtile = 0, count = 0;
-        const gt_job *d = nullptr, *w = nullptr;
-        for (int x = i; x < n; ++x) {
-            gt_job& j = jobs[x];
-            if (j.done || j.s != first.s || (j.mode == GG_FWD) != (first.mode == GG_FWD)) continue;
-            int at;
-            if (j.mode == GG_FWD) {
-                if (j.epi != first.epi) continue;
-                at = count;
-            } else if (j.mode == GG_DGRAD) {
-                if (d ? j.epi != d->epi : w && w->gath == (j.epi == GG_EPI_SWIGLU_BWD ? 2 : 1)) continue;
-                at = take[0] ? 1 : 0;
-            } else {
-                if (w ? j.f32 != w->f32 || j.gath != w->gath : d && j.gath == (d->epi == GG_EPI_SWIGLU_BWD ? 2 : 1)) continue;
-                at = take[2] ? 3 : 2;
-            }
-            if (at >= GT_JOBS || take[at]) continue;
-            if (j.mode == GG_DGRAD && !d) d = &j;
-            if (j.mode == GG_WGRAD && !w) w = &j;
-            if (j.mode == GG_WGRAD ? !wtile : !tile) (j.mode == GG_WGRAD ? wtile : tile) = j.tile;
-            take[at] = &j;
-            ++count;
-        }
-        if (count == 1) {
-            gt_launch(first.s, first.mode, first.epi, first.f32, first.gath, first.tile, first.a);
-            first.done = true;
-            continue;
-        }
-        gt_jobs m;
-        memset(&m, 0, sizeof(m));
-        int64_t at = 0;
-        for (int x = 0; x < GT_JOBS; ++x) {
-            m.start[x] = (int)at;
-            if (!take[x]) continue;
-            const gt_job& j = *take[x];
-            m.a[x] = j.a;
-            at += gt_blocks(j.mode, j.epi, j.mode == GG_WGRAD || tile == 2 ? 128 : 64, j.a);
-            take[x]->done = true;
-        }
-        m.start[GT_JOBS] = (int)at;
-        if (first.mode == GG_FWD) {
-            first.epi == GG_EPI_SWIGLU ? gt_fwd_jobs<GG_EPI_SWIGLU>(first.s, tile, at, m) : gt_fwd_jobs<GG_EPI_STORE>(first.s, tile, at, m);
-        } else {
-            const bool f32 = w && w->f32;
-            const int g = w ? w->gath : 0;
-            if (d ? d->epi == GG_EPI_SWIGLU_BWD : g == 1) {
-                if (g) f32 ? gt_bwd_jobs<GG_EPI_SWIGLU_BWD, true, 1>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_SWIGLU_BWD, false, 1>(first.s, tile, wtile, at, m);
-                else f32 ? gt_bwd_jobs<GG_EPI_SWIGLU_BWD, true, 0>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_SWIGLU_BWD, false, 0>(first.s, tile, wtile, at, m);
-            } else {
-                if (g) f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 2>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_STORE, false, 2>(first.s, tile, wtile, at, m);
-                else f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 0>(first.s, tile, wtile, at, m) : gt_bwd_jobs<GG_EPI_STORE, false, 0>(first.s, tile, wtile, at, m);
-            }
-        }
+void gt_launch_jobs(hipStream_t s, bool fwd, int epi, bool f32, int wgath, int tile, int wtile, const gt_jobs& m) {
+    const int64_t n = m.start[GT_JOBS];
+    if (fwd) {
+        epi == GG_EPI_SWIGLU ? gt_fwd_jobs<GG_EPI_SWIGLU>(s, tile, n, m) : gt_fwd_jobs<GG_EPI_STORE>(s, tile, n, m);
+    } else if (epi == GG_EPI_SWIGLU_BWD) {
+        if (wgath) f32 ? gt_bwd_jobs<GG_EPI_SWIGLU_BWD, true, 1>(s, tile, wtile, n, m) : gt_bwd_jobs<GG_EPI_SWIGLU_BWD, false, 1>(s, tile, wtile, n, m);
+        else f32 ? gt_bwd_jobs<GG_EPI_SWIGLU_BWD, true, 0>(s, tile, wtile, n, m) : gt_bwd_jobs<GG_EPI_SWIGLU_BWD, false, 0>(s, tile, wtile, n, m);
+    } else {
+        if (wgath) f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 2>(s, tile, wtile, n, m) : gt_bwd_jobs<GG_EPI_STORE, false, 2>(s, tile, wtile, n, m);
+        else f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 0>(s, tile, wtile, n, m) : gt_bwd_jobs<GG_EPI_STORE, false, 0>(s, tile, wtile, n, m);
     }
 }
-void gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
-    moe_batch* const b = ctx->batch;
+// Calls that a batch does not keep: data gradients on 128-row tiles and weight gradients in pieces, which fill the chip by
+// themselves; weight gradients on one buffer of more than eight tiles per unit, which live off three workgroups to a unit, one
+// more than beside a data gradient (a step, us, alone : together: T 112 h 5504 f 1152 E 57 k 4, 86 tiles per unit, 1433 : 1545; T 262
+// h 5696 f 704 E 16 k 2, 17 per unit, 422 : 435; T 2541 h 1088 f 384 E 54, 6 per unit, 171 : 157).
+bool gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     const int64_t cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
-    // Not kept: data gradients on 128-row tiles and weight gradients in pieces, which fill the chip by themselves; weight gradients on
-    // one buffer of more than eight tiles per unit, which live off three workgroups to a unit, one more than beside a data
-    // gradient (a step, us, alone : together: T 112 h 5504 f 1152 E 57 k 4, 86 tiles per unit, 1433 : 1545; T 262 h 5696 f 704 E 16 k 2,
-    // 17 per unit, 422 : 435; T 2541 h 1088 f 384 E 54, 6 per unit, 171 : 157).
-    if (!b || a.split_cap >= 2 || (mode == GG_DGRAD && tile == 2) || (tile == 4 && gt_blocks(mode, epi, 128, a) > 8 * cu))
-        return gt_launch(s, mode, epi, out_f32, gath, tile, a);
-    if (b->n_gt == MOE_BATCH_MAX) {
-        gt_flush(b->gt, b->n_gt);
-        b->n_gt = 0;
+    if (ctx->batch && a.split_cap < 2 && !(mode == GG_DGRAD && tile == 2) && !(tile == 4 && gt_blocks(mode, epi, 128, a) > 8 * cu)) {
+        batch_gemm(ctx->batch, {s, mode, epi, gath, tile, JOB_BF16, out_f32, false, a});
+        return true;
     }
-    b->gt[b->n_gt++] = {s, mode, epi, gath, tile, out_f32, false, a};
+    gt_launch(s, mode, epi, out_f32, gath, tile, a);
+    return false;
 }

@@ -50,21 +50,31 @@ __device__ __forceinline__ i32x8_t read_tr8x32_pitch(const char* p, int second) 
 }
 
 // F8: 1 = blockwise (fp32 block scales applied to the accumulators), 2 = MXFP8 (E8M0 scales, by the matrix instruction)
+// The LDS of a workgroup: two stage buffers, a ring of four stages' scales (P's from 0 on, Q's from GQ_PS(BM) on), and the rest.
+// (Arrays of their own rather than one struct: with the ring's addresses behind others' the 256 x 256 kernels need up to 8 more
+// registers, and spill.)
+#define GQ_PS(BM) ((BM) < 128 ? 128 : (BM))
+template <bool LPT>
+struct gq_lds {
+    tile_pick_lds pick;
+    int offs[LPT ? GG_MAX_E + 1 : 1], order[LPT ? GG_MAX_E : 1], drawn;
+};
+// block, G: the workgroup's place among the G of its call
 template <int MODE, int EPI, bool OUT_F32, int F8, int BM, int BN>
-__global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kernel(const gg_args a) {
+__device__ __forceinline__ void gq_body(const gg_args& a, char* const ring, float (*const scales)[GQ_PS(BM) + BN],
+                                        gq_lds<BM == 256 && MODE == GG_WGRAD>& lds, const int block, const int G) {
     constexpr bool MX = F8 == 2, P_CMAJ = MODE == GG_WGRAD, Q_CMAJ = MODE != GG_FWD, BW_WGRAD = F8 == 1 && MODE == GG_WGRAD;
     static_assert(MODE != GG_WGRAD || BM >= 128, "contraction-major tiles have rows of 128 or 256 bytes");
     constexpr int P_BYTES = BM * 128, STAGE = P_BYTES + BN * 128;
-    constexpr int PS = BM < 128 ? 128 : BM, SC = (PS + BN) / 256;   // scales of a stage: P's from 0 on, Q's from PS on
+    constexpr int PS = GQ_PS(BM), SC = (PS + BN) / 256;
     constexpr int PC = BM / 32, QC = BN / 32, XC = PC + QC + SC;    // DMA instructions per wave and stage: P, Q, scales
     constexpr int NI = BM / 64, NJ = BN / 64;                       // 32-row and 32-column blocks per wave
     constexpr bool MANY = BM == 256;                                // one workgroup per compute unit, tile after tile
     constexpr bool LPT = MANY && MODE == GG_WGRAD;
     constexpr int HB = BN / 2;                                      // SwiGLU: features per tile
-    __shared__ __attribute__((aligned(1024))) char ring[2 * STAGE];
-    __shared__ __attribute__((aligned(16))) float scales[4][PS + BN];
-    __shared__ tile_pick_lds pick;
-    __shared__ int offs[LPT ? GG_MAX_E + 1 : 1], order[LPT ? GG_MAX_E : 1], drawn;
+    tile_pick_lds& pick = lds.pick;
+    int *const offs = lds.offs, *const order = lds.order;
+    int& drawn = lds.drawn;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 1, wn = wave & 1;
@@ -77,17 +87,17 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
         bool off_grid = false;
         for (int e = tid; e <= a.E; e += 256) off_grid |= (a.offsets[e] & 127) != 0;
         if (__syncthreads_or(off_grid)) {
-            if (blockIdx.x == 0 && tid == 0) atomicExch(a.dev_err, 1);
+            if (block == 0 && tid == 0) atomicExch(a.dev_err, 1);
             return;
         }
     }
     tile_sums<256> sums;
     if (!tile_scan(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GG_WGRAD ? 0 : BM, MODE == GG_WGRAD ? tiles_iw * tiles_j : tiles_j,
-                   pick, sums, blockIdx.x == 0)) return;
+                   pick, sums, block == 0)) return;
     // Weight gradients, tile after tile: a tile costs its expert's rows, so the experts are taken in descending order of rows
     // (rank sort, ties by index) and the list is dealt to the XCDs in chunks, in a snake; with an expert above twice the mean no
     // deal balances, and the workgroups draw from a device counter in the same order (gemm.hip: tile_of, draw).
-    const int G = (int)gridDim.x, tpe = tiles_iw * tiles_j;
+    const int tpe = tiles_iw * tiles_j;
     bool dyn = false;
     int ticket = 0;
     if constexpr (LPT) {
@@ -126,8 +136,8 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     int64_t sc_step;
     auto set_tile = [&](int n) __attribute__((always_inline)) -> bool {   // this workgroup's n-th
     if constexpr (LPT) {
-        const int x = (int)blockIdx.x & 7;
-        int t = (8 * n + ((n & 1) ? 7 - x : x)) * (G >> 3) + ((int)blockIdx.x >> 3);
+        const int x = block & 7;
+        int t = (8 * n + ((n & 1) ? 7 - x : x)) * (G >> 3) + (block >> 3);
         if (dyn) {
             if (tid == 0) drawn = ticket;
             wait_lgkm0();
@@ -139,7 +149,7 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
         e = __builtin_amdgcn_readfirstlane(order[t / tpe]);
         row_lo = __builtin_amdgcn_readfirstlane(offs[e]);
         row_hi = __builtin_amdgcn_readfirstlane(offs[e + 1]);
-    } else if (!tile_find(sums, (int)blockIdx.x + n * G, pick, e, u, row_lo, row_hi)) return false;
+    } else if (!tile_find(sums, block + n * G, pick, e, u, row_lo, row_hi)) return false;
     gt_place(u, MODE == GG_WGRAD ? tiles_iw : (row_hi - row_lo + BM - 1) / BM, tiles_j, ti, tj);
     i0 = MODE == GG_WGRAD ? ti * BM : row_lo + ti * BM;
     i_end = MODE == GG_WGRAD ? N : row_hi;
@@ -435,15 +445,43 @@ __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kern
     }
     }
 }
-
+template <int MODE, int EPI, bool OUT_F32, int F8, int BM, int BN>
+__global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void gq_kernel(const gg_args a) {
+    __shared__ __attribute__((aligned(1024))) char ring[2 * (BM + BN) * 128];
+    __shared__ __attribute__((aligned(16))) float scales[4][GQ_PS(BM) + BN];
+    __shared__ gq_lds<BM == 256 && MODE == GG_WGRAD> lds;
+    gq_body<MODE, EPI, OUT_F32, F8, BM, BN>(a, ring, scales, lds, (int)blockIdx.x, (int)gridDim.x);
+}
+// Independent calls in one launch (gemm_tile.hip: gt_fwd_jobs_kernel, gt_bwd_jobs_kernel)
+template <int EPI, int F8, int BM>
+__global__ __launch_bounds__(256, BM == 64 ? 3 : 2) void gq_fwd_jobs_kernel(const gt_jobs m) {
+    __shared__ __attribute__((aligned(1024))) char ring[2 * (BM + 128) * 128];
+    __shared__ __attribute__((aligned(16))) float scales[4][256];
+    __shared__ gq_lds<false> lds;
+    const int j = gt_job_of(m, (int)blockIdx.x);
+    gq_body<GG_FWD, EPI, false, F8, BM, 128>(m.a[j], ring, scales, lds, (int)blockIdx.x - m.start[j], m.start[j + 1] - m.start[j]);
+}
+template <int EPI, bool F32, int F8>
+__global__ __launch_bounds__(256, 2) void gq_bwd_jobs_kernel(const gt_jobs m) {
+    __shared__ __attribute__((aligned(1024))) char ring[2 * 256 * 128];
+    __shared__ __attribute__((aligned(16))) float scales[4][256];
+    __shared__ gq_lds<false> lds;
+    const int j = gt_job_of(m, (int)blockIdx.x), block = (int)blockIdx.x - m.start[j], G = m.start[j + 1] - m.start[j];
+    if (j < 2) gq_body<GG_DGRAD, EPI, false, F8, 64, 128>(m.a[j], ring, scales, lds, block, G);
+    else gq_body<GG_WGRAD, GG_EPI_STORE, F32, F8, 128, 128>(m.a[j], ring, scales, lds, block, G);
+}
 
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
+static int64_t gq_tiles(int mode, int epi, int bm, int bn, const gg_args& a) {
+    const int64_t cols = epi == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, bn / 2) : ceil_div64(mode == GG_FWD ? a.N : a.K, bn);
+    return cols * (mode == GG_WGRAD ? a.E * ceil_div64(a.N, bm) : ceil_div64(a.Rcap, bm) + a.E);
+}
+int64_t gq_blocks(int mode, int epi, int bm, const gg_args& a) { return ceil_div64(gq_tiles(mode, epi, bm, 128, a), 8) * 8; }
 template <int MODE, int EPI, bool F32, int F8, int BM, int BN = 128>
 static void gq_go(hipStream_t s, const gg_args& a, int cu) {
-    const int64_t cols = EPI == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, BN / 2) : ceil_div64(MODE == GG_FWD ? a.N : a.K, BN);
-    int64_t n = cols * (MODE == GG_WGRAD ? a.E * ceil_div64(a.N, BM) : ceil_div64(a.Rcap, BM) + a.E);
+    int64_t n = gq_tiles(MODE, EPI, BM, BN, a);
     if (BM == 256 && n > cu) n = cu;
     hipLaunchKernelGGL((gq_kernel<MODE, EPI, F32, F8, BM, BN>), dim3((unsigned)(ceil_div64(n, 8) * 8)), dim3(256), 0, s, a);
 }
@@ -501,9 +539,38 @@ int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg
     return wg || r128 >= 1.5 ? 2 : 1;
 }
 void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a) {
-    const int cu = ctx->num_cu >= 8 ? ctx->num_cu & ~7 : 256;
+    const int cu = ctx && ctx->num_cu >= 8 ? ctx->num_cu & ~7 : 256;   // (ctx: 256 x 256 tiles only)
     if (mx && tile == 3 && mode == GG_WGRAD) moe_launch_fill_i32(a.tile_counter, 1, 0, s);
     if (mx && tile == 3) gq_call<2, 256, 256>(s, mode, epi, out_f32, a, cu);
     else if (mx) tile == 1 ? gq_call<2, 64>(s, mode, epi, out_f32, a, cu) : gq_call<2, 128>(s, mode, epi, out_f32, a, cu);
     else tile == 1 ? gq_call<1, 64>(s, mode, epi, out_f32, a, cu) : gq_call<1, 128>(s, mode, epi, out_f32, a, cu);
+}
+template <int F8>
+static void gq_jobs(hipStream_t s, bool fwd, int epi, bool f32, int tile, const gt_jobs& m) {
+    const dim3 grid((unsigned)m.start[GT_JOBS]), block(256);
+    if (fwd && epi == GG_EPI_SWIGLU) {
+        if (tile == 1) hipLaunchKernelGGL((gq_fwd_jobs_kernel<GG_EPI_SWIGLU, F8, 64>), grid, block, 0, s, m);
+        else hipLaunchKernelGGL((gq_fwd_jobs_kernel<GG_EPI_SWIGLU, F8, 128>), grid, block, 0, s, m);
+    } else if (fwd) {
+        if (tile == 1) hipLaunchKernelGGL((gq_fwd_jobs_kernel<GG_EPI_STORE, F8, 64>), grid, block, 0, s, m);
+        else hipLaunchKernelGGL((gq_fwd_jobs_kernel<GG_EPI_STORE, F8, 128>), grid, block, 0, s, m);
+    } else if (epi == GG_EPI_SWIGLU_BWD) {
+        if (f32) hipLaunchKernelGGL((gq_bwd_jobs_kernel<GG_EPI_SWIGLU_BWD, true, F8>), grid, block, 0, s, m);
+        else hipLaunchKernelGGL((gq_bwd_jobs_kernel<GG_EPI_SWIGLU_BWD, false, F8>), grid, block, 0, s, m);
+    } else {
+        if (f32) hipLaunchKernelGGL((gq_bwd_jobs_kernel<GG_EPI_STORE, true, F8>), grid, block, 0, s, m);
+        else hipLaunchKernelGGL((gq_bwd_jobs_kernel<GG_EPI_STORE, false, F8>), grid, block, 0, s, m);
+    }
+}
+void gq_launch_jobs(hipStream_t s, bool mx, bool fwd, int epi, bool f32, int tile, const gt_jobs& m) {
+    mx ? gq_jobs<2>(s, fwd, epi, f32, tile, m) : gq_jobs<1>(s, fwd, epi, f32, tile, m);
+}
+// Kept by a batch: calls on small tiles (data gradients: 64 rows), without copies of their output or with both MXFP8 ones
+bool gq_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a) {
+    if (ctx->batch && tile != 3 && !(mode == GG_DGRAD && tile == 2) && (!a.out_q || (mx && a.out_qc))) {
+        batch_gemm(ctx->batch, {s, mode, epi, 0, tile, mx ? JOB_MX : JOB_FP8, out_f32, false, a});
+        return true;
+    }
+    gq_launch(ctx, s, mode, epi, out_f32, mx, tile, a);
+    return false;
 }

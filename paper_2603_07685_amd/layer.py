@@ -212,34 +212,34 @@ class LayerState:
             self.dWs2 = torch.empty((h, sf), dtype=wdt, device=dev)
 
     # ---- fp8 helpers: quantise a row-indexed tensor (1x128) / a weight stack (128x128) ----------
-    def _q_rows(self, X, q, s, rows, cols, live=None, qc=None, sc=None):
+    def _q_rows(self, c, X, q, s, rows, cols, live=None, qc=None, sc=None):
         """Quantise a row-indexed tensor for the GEMM that contracts along its rows' elements (and, MXFP8, in the
         same pass the second copy, quantised down the rows, for the weight gradient)."""
         if self.mx:
-            B.moe_mx_quantize_rowcol(self.ctx, X, rows, cols, live, q, s, qc, sc)
+            B.moe_mx_quantize_rowcol(c, X, rows, cols, live, q, s, qc, sc)
         elif self.fp8_wgrad:
-            B.moe_fp8_quantize_rowcol(self.ctx, X, rows, cols, live, q, s, qc, sc)
+            B.moe_fp8_quantize_rowcol(c, X, rows, cols, live, q, s, qc, sc)
         else:
-            B.moe_fp8_quantize(self.ctx, X, B.Q_1x128, 1, rows, cols, live, q, s)
+            B.moe_fp8_quantize(c, X, B.Q_1x128, 1, rows, cols, live, q, s)
 
-    def _q_gather(self, X, pair_scale, groups, rows, cols, q, s, qc, sc):
+    def _q_gather(self, c, X, pair_scale, groups, rows, cols, q, s, qc, sc):
         """Both quantised copies of X's rows taken through the row map (the permuted tokens, or p * dY)."""
         fn = B.moe_mx_quantize_rowcol_gather if self.mx else B.moe_fp8_quantize_rowcol_gather
-        fn(self.ctx, X, self.src_of, self.cfg.k, pair_scale, groups, rows, cols, self.live_rows, q, s, qc, sc)
+        fn(c, X, self.src_of, self.cfg.k, pair_scale, groups, rows, cols, self.live_rows, q, s, qc, sc)
 
-    def _q_cols(self, X, qc, sc, rows, cols, live=None):
+    def _q_cols(self, c, X, qc, sc, rows, cols, live=None):
         """Blockwise recipe: the weight-gradient copy of a row-indexed tensor, 128x1 tiles down the rows (a tensor that
         two GEMMs read with different contraction dimensions is quantised once per direction, Sec. 5.3.3 / 5.4.1)."""
         if self.fp8_wgrad and not self.mx:
-            B.moe_fp8_quantize_rowcol(self.ctx, X, rows, cols, live, None, None, qc, sc)
+            B.moe_fp8_quantize_rowcol(c, X, rows, cols, live, None, None, qc, sc)
 
-    def _q_weight(self, W, q, s, qd=None, sd=None):
+    def _q_weight(self, c, W, q, s, qd=None, sd=None):
         """Quantise a weight stack for the forward GEMM (and, MXFP8, the second copy for the data gradient)."""
         g, rows, cols = q.shape
         if self.mx:
-            B.moe_mx_quantize_rowcol(self.ctx, W, g * rows, cols, None, q, s, qd, sd)
+            B.moe_mx_quantize_rowcol(c, W, g * rows, cols, None, q, s, qd, sd)
         else:
-            B.moe_fp8_quantize(self.ctx, W, B.Q_128x128, g, rows, cols, None, q, s)
+            B.moe_fp8_quantize(c, W, B.Q_128x128, g, rows, cols, None, q, s)
 
     def _route(self):
         cfg = self.cfg
@@ -348,29 +348,38 @@ class LayerState:
         idx = self.topk_idx if self.forced_idx is None else self.forced_idx
         B.moe_permute(c, None if self.fused_quant else self.X, B.BF16, idx, T, k, h, E, self.align, self.Xp, Rcap,
                       self.row_of, self.src_of, self.offsets, self.counts)
-        self._q_weight(self.W1, self.qW1, self.sW1, self.qW1d, self.sW1d)
-        self._q_weight(self.W2, self.qW2, self.sW2, self.qW2d, self.sW2d)
-        if self.fused_quant:
-            self._q_gather(self.X, None, E, Rcap, h, self.qXp, self.sXp, self.qXpc, self.sXpc)
-        else:
-            self._q_rows(self.Xp, self.qXp, self.sXp, Rcap, h, self.live_rows, self.qXpc, self.sXpc)
+        o1 = self.off_shared if sf else None
+        with self.batch as b:
+            self._q_weight(b, self.W1, self.qW1, self.sW1, self.qW1d, self.sW1d)
+            self._q_weight(b, self.W2, self.qW2, self.sW2, self.qW2d, self.sW2d)
+            if self.fused_quant:
+                self._q_gather(b, self.X, None, E, Rcap, h, self.qXp, self.sXp, self.qXpc, self.sXpc)
+            else:
+                self._q_rows(b, self.Xp, self.qXp, self.sXp, Rcap, h, self.live_rows, self.qXpc, self.sXpc)
+            if sf:
+                self._q_weight(b, self.Ws1.view(1, 2 * sf, h), self.qWs1, self.sWs1, self.qWs1d, self.sWs1d)
+                self._q_weight(b, self.Ws2.view(1, h, sf), self.qWs2, self.sWs2, self.qWs2d, self.sWs2d)
+                self._q_rows(b, self.X, self.qX, self.sX, T, h, None, self.qXc, self.sXc)
         row_prob = None
         if self.eq2:
             B.moe_gather_row_prob(c, self.topk_prob, self.src_of, Rcap, self.row_prob)
             row_prob = self.row_prob
-        self._fc1_fwd(self.qXp, self.qW1, self.offsets, E, 2 * f, h, Rcap, self.sXp, self.sW1, row_prob, self.Z, self.A,
-                      self.qA, self.sA, self.qAc, self.sAc, self.live_rows)
-        B.moe_grouped_gemm_fwd(c, self.qA, self.qW2, self.offsets, E, h, f, Rcap, F8, B.EPI_NONE,
-                               self.sA, self.sW2, self.O, None)
-        if sf:
-            o1 = self.off_shared
-            self._q_weight(self.Ws1.view(1, 2 * sf, h), self.qWs1, self.sWs1, self.qWs1d, self.sWs1d)
-            self._q_weight(self.Ws2.view(1, h, sf), self.qWs2, self.sWs2, self.qWs2d, self.sWs2d)
-            self._q_rows(self.X, self.qX, self.sX, T, h, None, self.qXc, self.sXc)
-            self._fc1_fwd(self.qX, self.qWs1, o1, 1, 2 * sf, h, T, self.sX, self.sWs1, None, self.Zs, self.As,
-                          self.qAs, self.sAs, self.qAsc, self.sAsc, None)
-            B.moe_grouped_gemm_fwd(c, self.qAs, self.qWs2, o1, 1, h, sf, T, F8, B.EPI_NONE,
-                                   self.sAs, self.sWs2, self.S, None)
+        with self.batch as b:
+            self._fc1_fwd(b, self.qXp, self.qW1, self.offsets, E, 2 * f, h, Rcap, self.sXp, self.sW1, row_prob, self.Z, self.A,
+                          self.qA, self.sA, self.qAc, self.sAc)
+            if sf:
+                self._fc1_fwd(b, self.qX, self.qWs1, o1, 1, 2 * sf, h, T, self.sX, self.sWs1, None, self.Zs, self.As,
+                              self.qAs, self.sAs, self.qAsc, self.sAsc)
+        with self.batch as b:
+            self._q_after(b, self.A, self.qA, self.sA, Rcap, f, self.live_rows, self.qAc, self.sAc)
+            if sf:
+                self._q_after(b, self.As, self.qAs, self.sAs, T, sf, None, self.qAsc, self.sAsc)
+        with self.batch as b:
+            B.moe_grouped_gemm_fwd(b, self.qA, self.qW2, self.offsets, E, h, f, Rcap, F8, B.EPI_NONE,
+                                   self.sA, self.sW2, self.O, None)
+            if sf:
+                B.moe_grouped_gemm_fwd(b, self.qAs, self.qWs2, o1, 1, h, sf, T, F8, B.EPI_NONE,
+                                       self.sAs, self.sWs2, self.S, None)
         B.moe_unpermute_combine(c, self.O, B.BF16, self.row_of, None if self.eq2 else self.topk_prob,
                                 self.S if sf else None, T, k, h, self.Y)
 
@@ -378,75 +387,77 @@ class LayerState:
         c, cfg = self.ctx, self.cfg
         T, k, E, h, f, sf, Rcap = cfg.T, cfg.k, cfg.E, cfg.h, cfg.f, self.sf, self.Rcap
         F8, wdt = self.f8dt, self.wgrad_dt
-        if self.fused_quant:
-            # dO = p * dY (eq. (2): plain copies of dY) goes from dY to its two quantised copies in one pass
-            if not self.eq2:
-                B.moe_unpermute_combine_bwd(c, self.dY, self.O, B.BF16, self.row_of, self.src_of, self.topk_prob,
-                                            T, k, h, Rcap, None, self.dprob)
-            self._q_gather(self.dY, None if self.eq2 else self.topk_prob, E, Rcap, h, self.qdO, self.sdO, self.qdOc, self.sdOc)
-        else:
-            if self.eq2:
-                B.moe_unpermute_combine_bwd(c, self.dY, None, B.BF16, self.row_of, self.src_of, None,
-                                            T, k, h, Rcap, self.dO, None)
+        o1 = self.off_shared if sf else None
+        if not (self.fused_quant and self.eq2):   # (fused: only dprob comes from here)
+            B.moe_unpermute_combine_bwd(c, self.dY, None if self.eq2 else self.O, B.BF16, self.row_of, self.src_of,
+                                        None if self.eq2 else self.topk_prob, T, k, h, Rcap,
+                                        None if self.fused_quant else self.dO, None if self.eq2 else self.dprob)
+        with self.batch as b:
+            if self.fused_quant:   # dO = p * dY (eq. (2): plain copies of dY) goes from dY to its two quantised copies in one pass
+                self._q_gather(b, self.dY, None if self.eq2 else self.topk_prob, E, Rcap, h, self.qdO, self.sdO, self.qdOc, self.sdOc)
             else:
-                B.moe_unpermute_combine_bwd(c, self.dY, self.O, B.BF16, self.row_of, self.src_of, self.topk_prob,
-                                            T, k, h, Rcap, self.dO, self.dprob)
-            self._q_rows(self.dO, self.qdO, self.sdO, Rcap, h, self.live_rows, self.qdOc, self.sdOc)
-        self._wgrad(self.A, self.dO, self.qAc, self.sAc, self.qdOc, self.sdOc, self.offsets, E, h, f, Rcap, self.dW2)
-        self._fc2_dgrad(self.qdO, self.qW2d, self.offsets, E, h, f, Rcap, self.Z, self.sdO, self.sW2d,
-                        self.row_prob if self.eq2 else None, self.dZ, self.dprob_part if self.eq2 else None,
-                        self.qdZ, self.sdZ, self.qdZc, self.sdZc, self.live_rows)
+                self._q_rows(b, self.dO, self.qdO, self.sdO, Rcap, h, self.live_rows, self.qdOc, self.sdOc)
+            if sf:
+                self._q_rows(b, self.dY, self.qdY, self.sdY, T, h, None, self.qdYc, self.sdYc)
+        with self.batch as b:
+            self._wgrad(b, self.A, self.dO, self.qAc, self.sAc, self.qdOc, self.sdOc, self.offsets, E, h, f, Rcap, self.dW2)
+            self._fc2_dgrad(b, self.qdO, self.qW2d, self.offsets, E, h, f, Rcap, self.Z, self.sdO, self.sW2d,
+                            self.row_prob if self.eq2 else None, self.dZ, self.dprob_part if self.eq2 else None,
+                            self.qdZ, self.sdZ, self.qdZc, self.sdZc)
+            if sf:
+                self._wgrad(b, self.As, self.dY, self.qAsc, self.sAsc, self.qdYc, self.sdYc, o1, 1, h, sf, T, self.dWs2)
+                self._fc2_dgrad(b, self.qdY, self.qWs2d, o1, 1, h, sf, T, self.Zs, self.sdY, self.sWs2d, None, self.dZs, None,
+                                self.qdZs, self.sdZs, self.qdZsc, self.sdZsc)
+        with self.batch as b:
+            self._q_after(b, self.dZ, self.qdZ, self.sdZ, Rcap, 2 * f, self.live_rows, self.qdZc, self.sdZc)
+            if sf:
+                self._q_after(b, self.dZs, self.qdZs, self.sdZs, T, 2 * sf, None, self.qdZsc, self.sdZsc)
         if self.eq2:
             B.moe_scatter_row_dprob(c, self.dprob_part, self.dprob_parts, self.row_of, T, k, self.dprob)
-        self._wgrad(self.Xp, self.dZ, self.qXpc, self.sXpc, self.qdZc, self.sdZc, self.offsets, E, 2 * f, h, Rcap, self.dW1)
-        B.moe_grouped_gemm_dgrad(c, self.qdZ, self.qW1d, self.offsets, E, 2 * f, h, Rcap, F8, None, self.sdZ, self.sW1d,
-                                 self.dXp)
-        if sf:
-            o1 = self.off_shared
-            self._q_rows(self.dY, self.qdY, self.sdY, T, h, None, self.qdYc, self.sdYc)
-            self._wgrad(self.As, self.dY, self.qAsc, self.sAsc, self.qdYc, self.sdYc, o1, 1, h, sf, T, self.dWs2)
-            self._fc2_dgrad(self.qdY, self.qWs2d, o1, 1, h, sf, T, self.Zs, self.sdY, self.sWs2d, None, self.dZs, None,
-                            self.qdZs, self.sdZs, self.qdZsc, self.sdZsc, None)
-            self._wgrad(self.X, self.dZs, self.qXc, self.sXc, self.qdZsc, self.sdZsc, o1, 1, 2 * sf, h, T, self.dWs1)
-            B.moe_grouped_gemm_dgrad(c, self.qdZs, self.qWs1d, o1, 1, 2 * sf, h, T, F8, None, self.sdZs, self.sWs1d,
-                                     self.dXs)
+        with self.batch as b:
+            self._wgrad(b, self.Xp, self.dZ, self.qXpc, self.sXpc, self.qdZc, self.sdZc, self.offsets, E, 2 * f, h, Rcap, self.dW1)
+            B.moe_grouped_gemm_dgrad(b, self.qdZ, self.qW1d, self.offsets, E, 2 * f, h, Rcap, F8, None, self.sdZ, self.sW1d,
+                                     self.dXp)
+            if sf:
+                self._wgrad(b, self.X, self.dZs, self.qXc, self.sXc, self.qdZsc, self.sdZsc, o1, 1, 2 * sf, h, T, self.dWs1)
+                B.moe_grouped_gemm_dgrad(b, self.qdZs, self.qWs1d, o1, 1, 2 * sf, h, T, F8, None, self.sdZs, self.sWs1d,
+                                         self.dXs)
         B.moe_unpermute_combine(c, self.dXp, B.BF16, self.row_of, None, self.dXs if sf else None, T, k, h, self.dX)
 
-    def _fc1_fwd(self, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc, live):
-        """fc1 + SwiGLU and the quantised copies of the activation fc2 and its weight gradient read: from the GEMM call
-        itself (Sec. 5.4.2) where that is switched on, else by quantiser calls."""
-        c, eq = self.ctx, self.epilogue_quant
+    def _fc1_fwd(self, c, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc):
+        """fc1 + SwiGLU and, where that is switched on, the quantised copies of the activation fc2 and its weight gradient
+        read from the GEMM call itself (Sec. 5.4.2); else _q_after makes them."""
+        eq = self.epilogue_quant
         if eq and self.mx:
             B.moe_grouped_gemm_fwd_quant_mx(c, qX, qW, offsets, E, N, K, rows, sX, sW, row_prob, Z, A, qA, sA, qAc, sAc)
-            return
-        B.moe_grouped_gemm_fwd_quant(c, qX, qW, offsets, E, N, K, rows, self.f8dt, B.EPI_SWIGLU, sX, sW, row_prob, Z, A,
-                                     qA if eq else None, sA if eq else None)
-        if not eq:
-            self._q_rows(A, qA, sA, rows, N // 2, live, qAc, sAc)
         else:
-            self._q_cols(A, qAc, sAc, rows, N // 2, live)
+            B.moe_grouped_gemm_fwd_quant(c, qX, qW, offsets, E, N, K, rows, self.f8dt, B.EPI_SWIGLU, sX, sW, row_prob, Z, A,
+                                         qA if eq else None, sA if eq else None)
 
-    def _fc2_dgrad(self, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part, qdZ, sdZ, qdZc, sdZc, live):
+    def _fc2_dgrad(self, c, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part, qdZ, sdZ, qdZc, sdZc):
         """fc2 data gradient + SwiGLU backward and the quantised copies of dZ, as in _fc1_fwd."""
-        c, eq = self.ctx, self.epilogue_quant
+        eq = self.epilogue_quant
         if eq and self.mx:
             B.moe_grouped_gemm_dgrad_quant_mx(c, qdO, qW, offsets, E, N, K, rows, Z, sdO, sW, row_prob, dZ, dprob_part,
                                               qdZ, sdZ, qdZc, sdZc)
-            return
-        B.moe_grouped_gemm_dgrad_quant(c, qdO, qW, offsets, E, N, K, rows, self.f8dt, Z, sdO, sW, row_prob, dZ, dprob_part,
-                                       qdZ if eq else None, sdZ if eq else None)
-        if not eq:
-            self._q_rows(dZ, qdZ, sdZ, rows, 2 * K, live, qdZc, sdZc)
         else:
-            self._q_cols(dZ, qdZc, sdZc, rows, 2 * K, live)
+            B.moe_grouped_gemm_dgrad_quant(c, qdO, qW, offsets, E, N, K, rows, self.f8dt, Z, sdO, sW, row_prob, dZ, dprob_part,
+                                           qdZ if eq else None, sdZ if eq else None)
 
-    def _wgrad(self, A, dC, qA, sA, qdC, sdC, offsets, E, N, K, rows, dW):
+    def _q_after(self, c, X, q, s, rows, cols, live, qc, sc):
+        """The quantised copies of A or dZ that their GEMM call has not made."""
+        if not self.epilogue_quant:
+            self._q_rows(c, X, q, s, rows, cols, live, qc, sc)
+        elif not self.mx:
+            self._q_cols(c, X, qc, sc, rows, cols, live)
+
+    def _wgrad(self, c, A, dC, qA, sA, qdC, sdC, offsets, E, N, K, rows, dW):
         """dW = dC^T A per expert: on the copies quantised down the rows (MXFP8: 32x1 blocks; blockwise: 128x1 tiles) or,
         with fp8_wgrad off, on the bf16 tensors."""
         if self.mx or self.fp8_wgrad:
-            B.moe_grouped_gemm_wgrad(self.ctx, qA, qdC, offsets, E, N, K, rows, self.f8dt, sA, sdC, 0, self.wgrad_dt, dW)
+            B.moe_grouped_gemm_wgrad(c, qA, qdC, offsets, E, N, K, rows, self.f8dt, sA, sdC, 0, self.wgrad_dt, dW)
         else:
-            B.moe_grouped_gemm_wgrad(self.ctx, A, dC, offsets, E, N, K, rows, B.BF16, None, None, 0, self.wgrad_dt, dW)
+            B.moe_grouped_gemm_wgrad(c, A, dC, offsets, E, N, K, rows, B.BF16, None, None, 0, self.wgrad_dt, dW)
 
     def step(self):
         self.forward()

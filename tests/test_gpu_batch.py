@@ -45,6 +45,8 @@ def _layers(size, shared, **kw):
 
 
 OUT = ("Y", "A", "Z", "O", "dX", "dZ", "dW1", "dW2", "dprob")
+QUANT = ("qXp", "sXp", "qXpc", "sXpc", "qA", "sA", "qAc", "sAc", "qdO", "sdO", "qdOc", "sdOc", "qdZ", "sdZ", "qdZc", "sdZc", "qW1", "sW1",
+         "qW2d", "sW2d", "qWs1", "sWs1", "qWs2d", "sWs2d", "qX", "sX", "qXc", "qAs", "qAsc", "sAsc", "qdY", "sdYc", "qdZs", "qdZsc", "sdZsc")
 SHARED = ("S", "As", "Zs", "dZs", "dXs", "dWs1", "dWs2")
 
 
@@ -66,6 +68,30 @@ def _compare(pair, shared):
 @pytest.mark.parametrize("shared", [False, True])
 def test_layer_is_that_of_single_calls(size, kw, shared):
     _compare(_layers(SIZES[size], shared, **kw), shared)
+
+
+@pytest.mark.parametrize("size", range(len(SIZES)))
+@pytest.mark.parametrize("kw", [{}, dict(wgrad_f32=True), dict(eq2=True), dict(epilogue_quant=True), dict(fp8_wgrad=False)],
+                         ids=lambda kw: "+".join(kw) or "plain")
+@pytest.mark.parametrize("recipe", ["fp8", "mxfp8"])
+def test_one_byte_layer_is_that_of_single_calls(recipe, size, kw):
+    if recipe == "mxfp8" and ("epilogue_quant" in kw or "fp8_wgrad" in kw):
+        kw = dict(epilogue_quant=False)
+    up = lambda n: (n + 127) // 128 * 128
+    s = {n: v if n in ("E", "k") else up(v) for n, v in SIZES[size].items()}
+    pair = _layers(s, True, recipe=recipe, **kw)
+    for st in pair:
+        for n in OUT + SHARED + QUANT:
+            t = getattr(st, n)
+            if t is not None:
+                t.zero_()
+        st.step()
+    torch.cuda.synchronize()
+    a, b = pair
+    assert a.ctx.poll_error() == 0 and b.ctx.poll_error() == 0
+    for n in OUT + SHARED + QUANT:
+        t = getattr(a, n)
+        assert t is None or torch.equal(t, getattr(b, n)), n
 
 
 def test_what_is_kept_and_what_is_not():
