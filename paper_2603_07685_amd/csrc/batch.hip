@@ -77,8 +77,13 @@ static void gemm_flush(gemm_job* jobs, int n) {
             launch_alone(first);
             continue;
         }
-        // the first call's tiles serve all of a mode
-        const int tile = fwd ? first.tile : d ? d->tile : 3, wtile = w ? w->tile : 2;
+        // the tiles of the call with the most of them serve all of a mode
+        const gemm_job *most = nullptr, *wmost = nullptr;
+        for (const gemm_job* j : take) {
+            const gemm_job*& m = j && j->mode == GG_WGRAD ? wmost : most;
+            if (j && (!m || gt_blocks(j->mode, j->epi, 64, j->a) > gt_blocks(m->mode, m->epi, 64, m->a))) m = j;
+        }
+        const int tile = most ? most->tile : 3, wtile = wmost ? wmost->tile : 2;
         gt_jobs m;
         memset(&m, 0, sizeof(m));
         int64_t at = 0;

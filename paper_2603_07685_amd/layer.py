@@ -270,15 +270,17 @@ class LayerState:
             B.moe_gather_row_prob(c, self.topk_prob, self.src_of, Rcap, self.row_prob)
             row_prob = self.row_prob
         with self.batch as b:
+            # (the shared expert in front here and behind in the next: calls too large to be kept then find the tensors they
+            # hand on still cached)
+            if sf:
+                B.moe_grouped_gemm_fwd(b, self.X, self.Ws1, self.off_shared, 1, 2 * sf, h, T, self.dt, B.EPI_SWIGLU,
+                                       None, None, self.Zs, self.As)
             if self.gather:
                 B.moe_grouped_gemm_fwd_gather(b, self.X, T, self.src_of, k, self.W1, self.offsets, E, 2 * f, h, Rcap,
                                               B.EPI_SWIGLU, row_prob, self.Z, self.A)
             else:
                 B.moe_grouped_gemm_fwd_weighted(b, self.Xp, self.W1, self.offsets, E, 2 * f, h, Rcap, self.dt, B.EPI_SWIGLU,
                                                 None, None, row_prob, self.Z, self.A)
-            if sf:
-                B.moe_grouped_gemm_fwd(b, self.X, self.Ws1, self.off_shared, 1, 2 * sf, h, T, self.dt, B.EPI_SWIGLU,
-                                       None, None, self.Zs, self.As)
         with self.batch as b:
             B.moe_grouped_gemm_fwd(b, self.A, self.W2, self.offsets, E, h, f, Rcap, self.dt, B.EPI_NONE,
                                    None, None, self.O, None)
@@ -299,6 +301,9 @@ class LayerState:
                                         None if self.eq2 else self.topk_prob, T, k, h, Rcap, self.dO,
                                         None if self.eq2 else self.dprob)
         with self.batch as b:
+            if sf:
+                B.moe_grouped_gemm_wgrad(b, self.As, self.dY, o1, 1, h, sf, T, self.dt, None, None, 0, wdt, self.dWs2)
+                B.moe_grouped_gemm_dgrad(b, self.dY, self.Ws2, o1, 1, h, sf, T, self.dt, self.Zs, None, None, self.dZs)
             if self.eq2 and self.gather:
                 # dO would be plain copies of dY: both fc2 gradients fetch the rows of dY through the map instead
                 B.moe_grouped_gemm_wgrad_gather(b, self.A, self.dY, B.GATHER_DC, T, self.src_of, k, self.offsets, E, h, f, Rcap,
@@ -316,9 +321,6 @@ class LayerState:
                                          self.dW2)
                 B.moe_grouped_gemm_dgrad(b, self.dO, self.W2, self.offsets, E, h, f, Rcap, self.dt, self.Z, None, None,
                                          self.dZ)
-            if sf:
-                B.moe_grouped_gemm_wgrad(b, self.As, self.dY, o1, 1, h, sf, T, self.dt, None, None, 0, wdt, self.dWs2)
-                B.moe_grouped_gemm_dgrad(b, self.dY, self.Ws2, o1, 1, h, sf, T, self.dt, self.Zs, None, None, self.dZs)
         if self.eq2:
             B.moe_scatter_row_dprob(c, self.dprob_part, self.dprob_parts, self.row_of, T, k, self.dprob)
         with self.batch as b:
@@ -350,30 +352,30 @@ class LayerState:
                       self.row_of, self.src_of, self.offsets, self.counts)
         o1 = self.off_shared if sf else None
         with self.batch as b:
+            if sf:
+                self._q_weight(b, self.Ws1.view(1, 2 * sf, h), self.qWs1, self.sWs1, self.qWs1d, self.sWs1d)
+                self._q_weight(b, self.Ws2.view(1, h, sf), self.qWs2, self.sWs2, self.qWs2d, self.sWs2d)
+                self._q_rows(b, self.X, self.qX, self.sX, T, h, None, self.qXc, self.sXc)
             self._q_weight(b, self.W1, self.qW1, self.sW1, self.qW1d, self.sW1d)
             self._q_weight(b, self.W2, self.qW2, self.sW2, self.qW2d, self.sW2d)
             if self.fused_quant:
                 self._q_gather(b, self.X, None, E, Rcap, h, self.qXp, self.sXp, self.qXpc, self.sXpc)
             else:
                 self._q_rows(b, self.Xp, self.qXp, self.sXp, Rcap, h, self.live_rows, self.qXpc, self.sXpc)
-            if sf:
-                self._q_weight(b, self.Ws1.view(1, 2 * sf, h), self.qWs1, self.sWs1, self.qWs1d, self.sWs1d)
-                self._q_weight(b, self.Ws2.view(1, h, sf), self.qWs2, self.sWs2, self.qWs2d, self.sWs2d)
-                self._q_rows(b, self.X, self.qX, self.sX, T, h, None, self.qXc, self.sXc)
         row_prob = None
         if self.eq2:
             B.moe_gather_row_prob(c, self.topk_prob, self.src_of, Rcap, self.row_prob)
             row_prob = self.row_prob
         with self.batch as b:
-            self._fc1_fwd(b, self.qXp, self.qW1, self.offsets, E, 2 * f, h, Rcap, self.sXp, self.sW1, row_prob, self.Z, self.A,
-                          self.qA, self.sA, self.qAc, self.sAc)
             if sf:
                 self._fc1_fwd(b, self.qX, self.qWs1, o1, 1, 2 * sf, h, T, self.sX, self.sWs1, None, self.Zs, self.As,
                               self.qAs, self.sAs, self.qAsc, self.sAsc)
+            self._fc1_fwd(b, self.qXp, self.qW1, self.offsets, E, 2 * f, h, Rcap, self.sXp, self.sW1, row_prob, self.Z, self.A,
+                          self.qA, self.sA, self.qAc, self.sAc)
         with self.batch as b:
-            self._q_after(b, self.A, self.qA, self.sA, Rcap, f, self.live_rows, self.qAc, self.sAc)
             if sf:
                 self._q_after(b, self.As, self.qAs, self.sAs, T, sf, None, self.qAsc, self.sAsc)
+            self._q_after(b, self.A, self.qA, self.sA, Rcap, f, self.live_rows, self.qAc, self.sAc)
         with self.batch as b:
             B.moe_grouped_gemm_fwd(b, self.qA, self.qW2, self.offsets, E, h, f, Rcap, F8, B.EPI_NONE,
                                    self.sA, self.sW2, self.O, None)
@@ -393,25 +395,25 @@ class LayerState:
                                         None if self.eq2 else self.topk_prob, T, k, h, Rcap,
                                         None if self.fused_quant else self.dO, None if self.eq2 else self.dprob)
         with self.batch as b:
+            if sf:
+                self._q_rows(b, self.dY, self.qdY, self.sdY, T, h, None, self.qdYc, self.sdYc)
             if self.fused_quant:   # dO = p * dY (eq. (2): plain copies of dY) goes from dY to its two quantised copies in one pass
                 self._q_gather(b, self.dY, None if self.eq2 else self.topk_prob, E, Rcap, h, self.qdO, self.sdO, self.qdOc, self.sdOc)
             else:
                 self._q_rows(b, self.dO, self.qdO, self.sdO, Rcap, h, self.live_rows, self.qdOc, self.sdOc)
-            if sf:
-                self._q_rows(b, self.dY, self.qdY, self.sdY, T, h, None, self.qdYc, self.sdYc)
         with self.batch as b:
-            self._wgrad(b, self.A, self.dO, self.qAc, self.sAc, self.qdOc, self.sdOc, self.offsets, E, h, f, Rcap, self.dW2)
-            self._fc2_dgrad(b, self.qdO, self.qW2d, self.offsets, E, h, f, Rcap, self.Z, self.sdO, self.sW2d,
-                            self.row_prob if self.eq2 else None, self.dZ, self.dprob_part if self.eq2 else None,
-                            self.qdZ, self.sdZ, self.qdZc, self.sdZc)
             if sf:
                 self._wgrad(b, self.As, self.dY, self.qAsc, self.sAsc, self.qdYc, self.sdYc, o1, 1, h, sf, T, self.dWs2)
                 self._fc2_dgrad(b, self.qdY, self.qWs2d, o1, 1, h, sf, T, self.Zs, self.sdY, self.sWs2d, None, self.dZs, None,
                                 self.qdZs, self.sdZs, self.qdZsc, self.sdZsc)
+            self._wgrad(b, self.A, self.dO, self.qAc, self.sAc, self.qdOc, self.sdOc, self.offsets, E, h, f, Rcap, self.dW2)
+            self._fc2_dgrad(b, self.qdO, self.qW2d, self.offsets, E, h, f, Rcap, self.Z, self.sdO, self.sW2d,
+                            self.row_prob if self.eq2 else None, self.dZ, self.dprob_part if self.eq2 else None,
+                            self.qdZ, self.sdZ, self.qdZc, self.sdZc)
         with self.batch as b:
-            self._q_after(b, self.dZ, self.qdZ, self.sdZ, Rcap, 2 * f, self.live_rows, self.qdZc, self.sdZc)
             if sf:
                 self._q_after(b, self.dZs, self.qdZs, self.sdZs, T, 2 * sf, None, self.qdZsc, self.sdZsc)
+            self._q_after(b, self.dZ, self.qdZ, self.sdZ, Rcap, 2 * f, self.live_rows, self.qdZc, self.sdZc)
         if self.eq2:
             B.moe_scatter_row_dprob(c, self.dprob_part, self.dprob_parts, self.row_of, T, k, self.dprob)
         with self.batch as b:
