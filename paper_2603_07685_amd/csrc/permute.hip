@@ -10,10 +10,9 @@
 //   3. rank : a workgroup per chunk again, one wavefront per 64 pairs; a lane's rank among equal experts inside the 64
 //             comes from ballots over the bits of the expert id, the wavefronts' counts are scanned in LDS.  Further
 //             workgroups mark the rows that no pair owns (src_of = -1).
-// Up to PERMUTE_ONE_PAIRS pairs one workgroup does all of it in one launch.
-// Bound: launches and dependent latencies (the map of 131072 pairs is 1.5 MB).  Measured, all kernels of the map: T 256,
-// k 2, E 8: 13.5 us in four launches (and three gaps between them) : 4.2 in one; T 2048, k 2: 22 : 5.9; T 16384, k 8, E 32: 35 : 16.6
-// (fill, one wavefront per chunk, a serial scan over the chunks : this).
+// Up to PERMUTE_ALL_PAIRS pairs all of it and the row move are one launch (permute_all_kernel).
+// Bound: launches and dependent latencies (the map of 131072 pairs is 1.5 MB).  Measured, all kernels of the map: T 16384, k 8, E 32:
+// 35 : 16.6 us (fill, one wavefront per chunk, a serial scan over the chunks : this).
 // Row moves are token-major: a workgroup reads one source row once and writes
 // its k copies (permute), or reads the k expert rows once and writes one row
 // (combine), 16 bytes per lane per access, fp32 accumulation in registers.
@@ -175,74 +174,128 @@ __global__ __launch_bounds__(1024) void permute_rank_kernel(const int32_t* __res
 }
 
 // ---------------------------------------------------------------------------
-// The whole map in one workgroup: wavefront w owns pairs [w * share, (w + 1) * share).
+// Small calls: map and row move in one launch.  A workgroup owns a few tokens; it counts all pairs by itself, those in front of its own
+// apart from the others, ranks its own and copies its tokens' rows.  Every workgroup reads all expert ids (up to 64 KB, from L2), which buys two launches' gaps.
 // ---------------------------------------------------------------------------
-#define PERMUTE_ONE_PAIRS 8192
-#define PERMUTE_ONE_FREE 65536  // most rows without a pair that one workgroup marks
-__global__ __launch_bounds__(1024) void permute_one_kernel(const int32_t* __restrict__ idx, int pairs, int E, int nbits, int align,
-                                                           int64_t Rcap, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
-                                                           int32_t* __restrict__ offsets, int32_t* __restrict__ counts) {
-    extern __shared__ int32_t wcnt[];  // [16][E], then [E + 1] ends of the experts' pairs, [E + 1] offsets
-    __shared__ int64_t wsum[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < 16 * E; i += 1024) wcnt[i] = 0;
+#define PERMUTE_ALL_THREADS 512
+#define PERMUTE_ALL_PAIRS 32768  // (the map alone: half)
+#define PERMUTE_ALL_E 512
+__host__ __device__ __forceinline__ int permute_copies(int E) { return E <= 128 ? 8 : E <= 256 ? 4 : 2; }
+__global__ __launch_bounds__(PERMUTE_ALL_THREADS) void permute_all_kernel(
+    const u32x4_t* __restrict__ X, const int32_t* __restrict__ idx, int T, int k, int E, int nbits, int align, int per_wg, int vec,
+    uint64_t vec_magic, int64_t Rcap, u32x4_t* __restrict__ Xp, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+    int32_t* __restrict__ offsets, int32_t* __restrict__ counts) {
+    constexpr int NT = PERMUTE_ALL_THREADS, NW = NT / 64, AHEAD = 8;
+    extern __shared__ int32_t lds[];
+    // [E][2][copies] counts, [E] the experts' ends, [E + 1] offsets, [NW][E].  An expert's count is kept in several copies, a lane's
+    // by its number: equal addresses of a wavefront are added one by one, 64 of them under a hot expert
+    const int copies = permute_copies(E);
+    int32_t *const cnt = lds, *const ends = lds + 2 * copies * E, *const offs = ends + E, *const wcnt = offs + E + 1;
+    __shared__ int32_t rows[NT], wsum[NW];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, G = (int)gridDim.x, b = (int)blockIdx.x;
+    const int pairs = T * k, t0 = b * per_wg, nt = min(per_wg, T - t0), own0 = t0 * k, own = nt * k;
+    for (int i = tid; i < 2 * copies * E; i += NT) cnt[i] = 0;
+    for (int i = tid; i < NW * E; i += NT) wcnt[i] = 0;
     __syncthreads();
-    constexpr int STEPS = PERMUTE_ONE_PAIRS / 1024;
-    const int steps = (pairs + 1023) / 1024, j0 = wave * 64 * steps + lane;
-    int ex[STEPS];
+    // ---- counts of the pairs in front of this workgroup's, and of the others ----
+    for (int j0 = 0; j0 < pairs; j0 += NT * AHEAD) {
+        int ex[AHEAD];
 #pragma unroll
-    for (int s = 0; s < STEPS; ++s) ex[s] = s < steps && j0 + 64 * s < pairs ? idx[j0 + 64 * s] : -1;
-#pragma unroll
-    for (int s = 0; s < STEPS; ++s)
-        if (ex[s] >= 0 && ex[s] < E) atomicAdd(&wcnt[wave * E + ex[s]], 1);
-    __syncthreads();
-    int32_t tot = 0;
-    if (tid < E) {
-#pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            const int32_t v = wcnt[w * E + tid];
-            wcnt[w * E + tid] = tot;
-            tot += v;
+        for (int s = 0; s < AHEAD; ++s) {
+            const int j = j0 + s * NT + tid;
+            ex[s] = j < pairs ? idx[j] : -1;
         }
-    }
-    int64_t total;
-    const int64_t at = block_scan_1024(tid < E ? ((int64_t)tot + align - 1) / align * align : 0, wsum, &total);
-    int32_t* const ends = wcnt + 16 * E;
-    int32_t* const offs = ends + E + 1;
-    if (tid < E) {
-        offsets[tid] = (int32_t)at;
-        counts[tid] = tot;
-        offs[tid] = (int32_t)at;
-        ends[tid] = (int32_t)at + tot;
 #pragma unroll
-        for (int w = 0; w < 16; ++w) wcnt[w * E + tid] += (int32_t)at;
+        for (int s = 0; s < AHEAD; ++s)
+            if (ex[s] >= 0 && ex[s] < E)
+                atomicAdd(&cnt[(2 * ex[s] + (j0 + s * NT + tid < own0 ? 0 : 1)) * copies + (lane & (copies - 1))], 1);
+    }
+    // ---- this workgroup's pairs: peers inside a wavefront ----
+    const int e = tid < own ? idx[own0 + tid] : -1;
+    const bool valid = e >= 0 && e < E;
+    const uint64_t peers = expert_peers(e, valid, nbits);
+    const int rank = __popcll(peers & ((1ull << lane) - 1ull));
+    if (valid && rank == 0) wcnt[wave * E + e] = __popcll(peers);
+    __syncthreads();
+    // ---- offsets, and the rows that the wavefronts' pairs start at ----
+    int before = 0, tot = 0;
+    if (tid < E)
+        for (int c = 0; c < copies; ++c) {
+            before += cnt[2 * tid * copies + c];
+            tot += cnt[(2 * tid + 1) * copies + c];
+        }
+    tot += before;
+    const int padded = (tot + align - 1) / align * align;
+    int incl = padded;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+    }
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    int at = incl - padded, total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) at += wsum[w];
+        total += wsum[w];
+    }
+    if (tid < E) {
+        offs[tid] = at;
+        ends[tid] = at + tot;
+        if (b == 0) {
+            offsets[tid] = at;
+            counts[tid] = tot;
+        }
+        int run = at + before;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int v = wcnt[w * E + tid];
+            wcnt[w * E + tid] = run;
+            run += v;
+        }
     }
     if (tid == 0) {
-        offsets[E] = (int32_t)total;
-        offs[E] = (int32_t)total;
+        offs[E] = total;
+        if (b == 0) offsets[E] = total;
     }
     __syncthreads();
-#pragma unroll
-    for (int s = 0; s < STEPS; ++s) {
-        if (s >= steps) break;
-        const int e = ex[s], j = j0 + 64 * s;
-        const bool valid = e >= 0 && e < E;
-        const uint64_t peers = expert_peers(e, valid, nbits);
-        const int rank = __popcll(peers & ((1ull << lane) - 1ull));
-        if (valid) {
-            const int row = wcnt[wave * E + e] + rank;
-            row_of[j] = row;
-            src_of[row] = j;
-        } else if (j < pairs) {
-            row_of[j] = -1;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // (a wavefront's own row: its program order suffices)
-        if (valid && rank == 0) wcnt[wave * E + e] += __popcll(peers);
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    if (tid < own) {
+        const int row = valid ? wcnt[wave * E + e] + rank : -1;
+        rows[tid] = row;
+        row_of[own0 + tid] = row;
+        if (valid) src_of[row] = own0 + tid;
     }
-    for (int e = wave; e < E; e += 16)
-        for (int r = ends[e] + lane; r < offs[e + 1]; r += 64) src_of[r] = -1;
-    for (int64_t r = total + tid; r < Rcap; r += 1024) src_of[r] = -1;
+    // ---- rows that no pair owns: padding rows, spread over the workgroups, and what lies behind the last expert ----
+    if (align > 1) {
+        for (int x = wave; x < E; x += NW)
+            for (int r = ends[x] + b; r < offs[x + 1]; r += G) {
+                if (lane == 0) src_of[r] = -1;
+                if (Xp)
+                    for (int c = lane; c < vec; c += 64) Xp[(int64_t)r * vec + c] = mk4(0, 0, 0, 0);
+            }
+    }
+    for (int64_t r = total + (int64_t)b * NT + tid; r < Rcap; r += (int64_t)G * NT) src_of[r] = -1;
+    if (!Xp) return;
+    __syncthreads();
+    // ---- the tokens' rows, each read once ----
+    const u32x4_t* const src = X + (int64_t)t0 * vec;
+    for (int c0 = tid; c0 < nt * vec; c0 += 4 * NT) {
+        u32x4_t v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (c0 + u * NT < nt * vec) v[u] = src[c0 + u * NT];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = c0 + u * NT;
+            if (c >= nt * vec) break;
+            const int t = (int)(((uint64_t)c * vec_magic) >> 32), at_c = c - t * vec;   // c / vec (see permute_launch)
+            for (int s = 0; s < k; ++s) {
+                const int r = rows[t * k + s];
+                if (r >= 0) __builtin_nontemporal_store(v[u], &Xp[(int64_t)r * vec + at_c]);
+            }
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -504,23 +557,24 @@ static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int
                            int32_t* counts, int32_t* chunk_hist) {
     const int64_t pairs = (int64_t)T * k;
     const int nchunks = (int)moe_permute_chunks(pairs), nbits = bits_for(E);
-    // One workgroup while its serial share is cheaper than three launches, kernel times alone: E 32, k 4, T 256: 4.5 us
-    // against 7.5; T 1024: 6.5 against 9.2; T 2048 (the most it takes): 9.2 against 9.3, and two launches fewer.  Up to 512
-    // experts (36 KB of LDS counters).
-    if (pairs <= PERMUTE_ONE_PAIRS && E <= 512 && Rcap - pairs <= PERMUTE_ONE_FREE) {
-        hipLaunchKernelGGL(permute_one_kernel, dim3(1), dim3(1024), (size_t)(18 * E + 2) * sizeof(int32_t), s, idx, (int)pairs, E,
-                           nbits, align, Rcap, row_of, src_of, offsets, counts);
-    } else {
-        if (nchunks > 0)
-            hipLaunchKernelGGL(permute_hist_kernel, dim3(nchunks), dim3(1024), (size_t)E * sizeof(int32_t), s, idx, pairs, E, chunk_hist);
-        hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, s, chunk_hist, nchunks, E, nbits, align, counts, offsets);
-        // (rows without a pair: at most Rcap of them behind the last expert, if every slot is skipped)
-        hipLaunchKernelGGL(permute_rank_kernel, dim3(nchunks + E + (unsigned)ceil_div64(Rcap, FILL_ROWS)), dim3(1024),
-                           (size_t)16 * E * sizeof(int32_t), s, idx, pairs, E, nbits, nchunks, Rcap, chunk_hist, offsets, counts,
-                           row_of, src_of);
+    const int vec = X ? (int)((size_t)h * moe_dtype_size(dt) / 16) : 0;
+    const int per_wg = T > 256 ? (T + 255) / 256 : 1;   // a workgroup per compute unit
+    if (pairs <= (X ? PERMUTE_ALL_PAIRS : PERMUTE_ALL_PAIRS / 2) && E <= PERMUTE_ALL_E && (int64_t)per_wg * vec * vec < (1LL << 32)) {
+        // (c / vec = c * ceil(2^32 / vec) / 2^32 for c < per_wg * vec: the rounding adds less than c vec / 2^32 of a step)
+        const uint64_t magic = vec ? ((1ull << 32) + vec - 1) / vec : 0;
+        hipLaunchKernelGGL(permute_all_kernel, dim3(T > per_wg ? (T + per_wg - 1) / per_wg : 1), dim3(PERMUTE_ALL_THREADS),
+                           (size_t)((2 * permute_copies(E) + 2 + PERMUTE_ALL_THREADS / 64) * E + 1) * sizeof(int32_t), s, (const u32x4_t*)X, idx, T, k, E, nbits,
+                           align, per_wg, vec, magic, Rcap, (u32x4_t*)Xp, row_of, src_of, offsets, counts);
+        return;
     }
+    if (nchunks > 0)
+        hipLaunchKernelGGL(permute_hist_kernel, dim3(nchunks), dim3(1024), (size_t)E * sizeof(int32_t), s, idx, pairs, E, chunk_hist);
+    hipLaunchKernelGGL(permute_scan_kernel, dim3(1), dim3(1024), 0, s, chunk_hist, nchunks, E, nbits, align, counts, offsets);
+    // (rows without a pair: at most Rcap of them behind the last expert, if every slot is skipped)
+    hipLaunchKernelGGL(permute_rank_kernel, dim3(nchunks + E + (unsigned)ceil_div64(Rcap, FILL_ROWS)), dim3(1024),
+                       (size_t)16 * E * sizeof(int32_t), s, idx, pairs, E, nbits, nchunks, Rcap, chunk_hist, offsets, counts,
+                       row_of, src_of);
     if (X) {
-        const int vec = (int)((size_t)h * moe_dtype_size(dt) / 16);
         hipLaunchKernelGGL(permute_rows_kernel, dim3(T + E), dim3(MOVE_THREADS), 0, s, (const u32x4_t*)X, row_of, offsets,
                            counts, T, k, E, vec, (u32x4_t*)Xp);
     }

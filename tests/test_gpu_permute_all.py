@@ -1,0 +1,46 @@
+"""The permute of small calls, map and rows in one launch, on both sides of its bounds (32768 pairs, 512 experts): bit for bit against
+a stable sort, tokens' rows copied, padding rows zeroed, rows behind the last expert untouched."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+# tokens per workgroup 1, 2 and many with a remainder; rows of one 16-byte piece, of an odd number and of more than a pass; copies of the
+# counts 8, 4, 2 (128, 129, 256, 257 experts); a hot expert throughout
+@pytest.mark.parametrize("T,k,h,E,align,slack", [
+    (1, 1, 8, 1, 1, 0), (255, 2, 24, 8, 1, 3), (257, 3, 1000, 128, 16, 0), (300, 32, 8, 129, 1, 5000), (2048, 4, 7168, 4, 128, 1),
+    (4095, 8, 40, 256, 8, 0), (4096, 8, 64, 257, 1, 9), (4097, 8, 64, 16, 1, 0), (1000, 8, 72, 512, 128, 0), (1000, 8, 72, 513, 2, 0),
+    (32767, 1, 16, 3, 128, 0), (0, 4, 64, 5, 16, 1)])
+def test_map_and_rows(T, k, h, E, align, slack):
+    from paper_2603_07685_amd import binding as B
+    ctx = B.Context(max(T, 1), k, E, 64, 64)
+    g = np.random.default_rng(T + 7 * k + E)
+    idx = g.integers(-1, E + 1, size=(T, k)).astype(np.int32)          # some slots name no expert of this GPU
+    idx[g.random((T, k)) < 0.4] = E // 2
+    flat = idx.reshape(-1)
+    ok = (flat >= 0) & (flat < E)
+    counts = np.bincount(flat[ok], minlength=E).astype(np.int32)
+    offsets = np.concatenate([[0], np.cumsum((counts + align - 1) // align * align)]).astype(np.int32)
+    order = np.argsort(np.where(ok, flat, E), kind="stable")[: ok.sum()]
+    first = np.concatenate([[0], np.cumsum(counts)])[:-1]
+    rows = offsets[flat[order]] + np.arange(len(order)) - first[flat[order]]
+    Rcap = T * k + E * (align - 1) + slack
+    row_of, src_of = np.full(flat.shape, -1, np.int32), np.full(Rcap, -1, np.int32)
+    row_of[order], src_of[rows] = rows, order
+    X = torch.from_numpy(g.integers(-30000, 30000, size=(max(T, 1), h)).astype(np.int16)).cuda().view(torch.bfloat16)
+    Xp = torch.full((Rcap, h), 7.0, dtype=torch.bfloat16, device="cuda")
+    got = [torch.full((max(n, 1),), -9, dtype=torch.int32, device="cuda") for n in (T * k, Rcap, E + 1, E)]
+    d = torch.zeros((max(T, 1), k), dtype=torch.int32, device="cuda")
+    d[:T] = torch.from_numpy(idx)
+    B.moe_permute(ctx, X, B.BF16, d, T, k, h, E, align, Xp, Rcap, *got)
+    torch.cuda.synchronize()
+    for name, a, b in zip(("row_of", "src_of", "offsets", "counts"), got, (row_of, src_of, offsets, counts)):
+        assert np.array_equal(a.cpu().numpy()[: len(b)], b), name
+    bits = Xp.view(torch.int16).cpu().numpy()
+    want = np.full((Rcap, h), np.asarray(torch.tensor(7.0, dtype=torch.bfloat16).view(torch.int16)), np.int16)
+    want[: offsets[-1]] = 0
+    want[rows] = X.view(torch.int16).cpu().numpy()[order // k]
+    assert np.array_equal(bits, want)
