@@ -26,12 +26,18 @@ extern "C" moe_status moe_batch_end(moe_ctx* batch, void* stream, int launch) {
     if (!b) MOE_FAIL(batch, MOE_ERR_ARG, "moe_batch_end: not a batch");
     if (launch) batch_flush(b);
     b->n_gemm = b->n_quant = 0;
+    b->partials = 0;
     MOE_LAUNCH_CHECK(batch, "calls of a batch");
     return MOE_OK;
 }
 
-void batch_gemm(moe_batch* b, const gemm_job& j) {
-    if (b->n_gemm == MOE_BATCH_MAX) batch_flush(b);
+void batch_gemm(moe_ctx* ctx, gemm_job j) {
+    moe_batch* const b = ctx->batch;
+    // (pieces of two weight gradients of a launch need room side by side; a call's number of pieces does not depend on it)
+    const size_t need = j.a.split_cap >= 2 ? (size_t)j.a.split_cap * j.a.N * j.a.K * sizeof(float) : 0;
+    if (b->n_gemm == MOE_BATCH_MAX || (need && b->partials + need > ctx->ws_bytes - MOE_WS_RESERVED)) batch_flush(b);
+    if (need) j.a.partials = (float*)((char*)j.a.partials + b->partials);
+    b->partials += (need + 255) / 256 * 256;
     b->gemm[b->n_gemm++] = j;
 }
 
@@ -106,4 +112,5 @@ void batch_flush(moe_batch* b) {
     gemm_flush(b->gemm, b->n_gemm);
     quant_flush(b->quant, b->n_quant);
     b->n_gemm = b->n_quant = 0;
+    b->partials = 0;
 }

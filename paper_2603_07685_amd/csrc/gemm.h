@@ -96,6 +96,7 @@ struct gg_args {
     uint8_t* out_qc_e8;
     int* tile_counter;     // wgrad: device counter, zero at the start, for the dynamic tile order under skewed loads (see the kernel)
     // wgrad, bf16: deterministic split of the contraction for experts far above the mean load (see the kernels)
+    int split_rows;        // wgrad, small tiles: an expert of up to this many rows is not split
     int split_cap;         // how many expert-sized slices of fp32 partial results `partials` can hold (0: never split)
     float* partials;       // [split_cap] slices: 256 x 256 kernel [tiles per expert][256 x 256], small tiles [N][K]
     int* split_info;       // [1 + 3 * GG_MAX_SPLIT_EXPERTS]: count, then (expert, pieces, first slice) for the reduce kernel
@@ -116,8 +117,10 @@ struct gg_args {
 // Small-tile kernels for bf16 operands (gemm_tile.hip).  gt_tile: which of them serves a call (0: none, the 256 x 256
 // kernel of gemm.hip is the better one); gt_launch: run it.
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a);
-// Rows from which on a weight gradient on small tiles may split its contraction (set split_cap and partials)
-#define GT_SPLIT_ROWS 24576
+// Weight gradients on small tiles: whether experts are split (sets split_rows, split_cap); `slices`: room for so many fp32 results of
+// an expert.
+#define GT_MAX_PIECES 32
+void gt_spread(const moe_ctx* ctx, gg_args& a, int64_t slices);
 void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
 // the same for one-byte operands (gemm_tile8.hip); `quant`: the call also asks for quantised copies of its output
 int gq_tile(const moe_ctx* ctx, int mode, int epi, bool mx, bool quant, const gg_args& a);
@@ -165,9 +168,10 @@ struct moe_batch {
     gemm_job gemm[MOE_BATCH_MAX];
     quant_job quant[MOE_BATCH_MAX];   // (launched behind the GEMMs: among them the quantised copies of their outputs)
     int n_gemm, n_quant;
+    size_t partials;                  // bytes of the workspace that kept weight gradients leave pieces' results in
 };
 void batch_flush(moe_batch* b);
-void batch_gemm(moe_batch* b, const gemm_job& j);
+void batch_gemm(moe_ctx* ctx, gemm_job j);
 // gt_submit, gq_submit: launch a call, or keep it in the context's batch (true)
 bool gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a);
 bool gq_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a);

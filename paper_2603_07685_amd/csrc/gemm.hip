@@ -2264,7 +2264,7 @@ static moe_status gg_wgrad_all(moe_ctx* ctx, void* stream, const void* A, const 
     a.partials = (float*)((char*)ctx->ws + MOE_WS_RESERVED);
     auto slices = [&](size_t bytes) { return (int)(ws_free / bytes < GG_MAX_SPLIT ? ws_free / bytes : GG_MAX_SPLIT); };
     if (const int tile = (mx || bw) ? gq_tile(ctx, GG_WGRAD, GG_EPI_STORE, mx, false, a) : gt_tile(ctx, GG_WGRAD, GG_EPI_STORE, a)) {
-        if (!mx && !bw && Rcap > GT_SPLIT_ROWS) a.split_cap = slices((size_t)N * K * sizeof(float));
+        if (!mx && !bw) gt_spread(ctx, a, (int64_t)(ws_free / ((size_t)N * K * sizeof(float))));
         if (mx || bw) gq_submit(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, mx, tile, a);
         else gt_submit(ctx, (hipStream_t)stream, GG_WGRAD, GG_EPI_STORE, out_dt == MOE_F32, gath, tile, a);
         MOE_LAUNCH_CHECK(ctx, "gt_kernel<wgrad>");

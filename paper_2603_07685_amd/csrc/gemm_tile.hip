@@ -25,16 +25,15 @@
 // ahead, and three workgroups to a unit (gt_one_buffer).
 #include "gemm_tile.h"
 
-// Weight gradients of many rows: an expert of more than split_limit rows is cut into pieces of at most that many, each with its
-// own tiles, which leave their results as fp32 in a slice of the workspace; gt_add_kernel adds an expert's slices in order.
-// One workgroup would otherwise walk all its rows (0.54 us per 64; the 256 x 256 kernel splits too).  The limit is the
-// smallest with which the pieces of any load fit the slices: with R <= n lim, the m experts above lim have at most
-// n - 1 + m <= 2 n - 2 pieces.  Measured (us a call, 256 x 256 kernel, whole : pieces): T 16384, k 8, h 256, f 256, 32 experts, one
-// with half of the rows 317, 560 : 198; with 95 % 444, 1059 : 228; even 111, 47 : 49; T 8192, k 8, 64 experts, half 252, 283 : 105.
-__device__ __forceinline__ int split_limit(const int32_t* __restrict__ offsets, int E, int cap) {
+// Weight gradients that are split (gt_spread): an expert of more than split_limit rows is cut into pieces of at most that many,
+// each with its own tiles, which leave their results as fp32 in a slice of the workspace; gt_add_kernel adds an expert's slices in
+// order.  One workgroup would otherwise walk all its rows (0.54 us per 64).  The limit is at least `least` and such that the pieces of any
+// load fit the slices: with R <= n lim, the m <= min(n - 1, E) experts above lim have at most n - 1 + m pieces, which is cap for
+// n = cap / 2 + 1 and for n = cap - E alike.
+__device__ __forceinline__ int split_limit(const int32_t* __restrict__ offsets, int E, int cap, int least) {
     if (cap < 2) return 0;
-    const int rows = offsets[E] - offsets[0], n = cap / 2 + 1;
-    return max((int)(((int64_t)rows + n * 64 - 1) / (n * 64)) * 64, 2048);   // (small results: not worth cutting)
+    const int rows = offsets[E] - offsets[0], n = max(cap / 2 + 1, cap - E);
+    return max((int)(((int64_t)rows + n * 64 - 1) / (n * 64)) * 64, least);
 }
 
 // The LDS of a workgroup
@@ -73,7 +72,7 @@ __device__ __forceinline__ void gt_body(const gg_args& a, gt_lds<MODE, GATH, BM,
     const int tiles_iw = (N + BM - 1) / BM;             // wgrad
 
     int e, u, row_lo, row_hi;
-    const int lim = SPLIT ? split_limit(a.offsets, a.E, a.split_cap) : 0;
+    const int lim = SPLIT ? split_limit(a.offsets, a.E, a.split_cap, a.split_rows) : 0;
     tile_sums<256> sums;
     // A weight gradient without pieces has the same number of tiles for every expert: its tile is found without a sum over the
     // experts.  The check of all offsets goes on while the first operands are on their way (from rows made safe by
@@ -98,7 +97,7 @@ __device__ __forceinline__ void gt_body(const gg_args& a, gt_lds<MODE, GATH, BM,
         if (!tile_find(sums, block, pick, e, u, row_lo, row_hi)) return;
     }
     int slice = -1;   // >= 0: a piece, its place among the partial results
-    if (SPLIT) {
+    if (SPLIT && lim > 0) {   // (0: a call without pieces beside one that has them)
         const int pieces = __builtin_amdgcn_readfirstlane(split_pieces(row_hi - row_lo, lim));
         if (pieces > 1) {
             int n = 0;
@@ -366,7 +365,7 @@ __global__ __launch_bounds__(256, NBUF == 2 && BM == 64 ? 3 : 2) void gt_fwd_job
     gt_body<GG_FWD, EPI, false, 3, BM, NBUF, false>(m.a[j], lds, (int)blockIdx.x - m.start[j]);
 }
 // data gradients with one epilogue (calls 0, 1) and weight gradients (2, 3)
-template <int EPI, int BM, int NBUF, bool F32, int WGATH, int WBUF>
+template <int EPI, int BM, int NBUF, bool F32, int WGATH, int WBUF, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void gt_bwd_jobs_kernel(const gt_jobs m) {
     __shared__ union {
         gt_lds<GG_DGRAD, 3, BM, NBUF> d;
@@ -374,15 +373,15 @@ __global__ __launch_bounds__(256, 2) void gt_bwd_jobs_kernel(const gt_jobs m) {
     } lds;
     const int j = gt_job_of(m, (int)blockIdx.x), block = (int)blockIdx.x - m.start[j];
     if (j < 2) gt_body<GG_DGRAD, EPI, false, 3, BM, NBUF, false>(m.a[j], lds.d, block);
-    else gt_body<GG_WGRAD, GG_EPI_STORE, F32, WGATH, 128, WBUF, false>(m.a[j], lds.w, block);
+    else gt_body<GG_WGRAD, GG_EPI_STORE, F32, WGATH, 128, WBUF, SPLIT>(m.a[j], lds.w, block);
 }
 
 // Second step of a weight gradient with pieces: every workgroup finds the split experts in the offsets (at most four) and goes
 // over its share of their results, piece 0 first.  Bound: HBM, a slice read per piece; without a split expert, one look.
 template <bool OUT_F32>
 __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
-    __shared__ int at[8], rows_at[8], count;
-    const int lim = split_limit(a.offsets, a.E, a.split_cap);   // (> 0: launched with split_cap >= 2)
+    __shared__ int at[GT_MAX_PIECES], rows_at[GT_MAX_PIECES], count;
+    const int lim = split_limit(a.offsets, a.E, a.split_cap, a.split_rows);   // (> 0: launched with split_cap >= 2)
     if (threadIdx.x == 0) count = 0;
     bool bad = a.offsets[0] < 0 || a.offsets[a.E] > a.Rcap;
     for (int e = threadIdx.x; e < a.E; e += 256) bad |= a.offsets[e + 1] < a.offsets[e];
@@ -487,10 +486,35 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     return r128 < (epi == GG_EPI_SWIGLU_BWD && stages <= 24 ? 1.5 : 1) ? 1 : 2;
 }
 
+// Weight gradients are split in two cases (pieces' results out and in again and the second launch cost about 5 us and what their
+// bytes take; 540 drawn calls from cold caches):
+//   few tiles, so that one workgroup's walk over an expert's rows is the call's time: as many pieces as fill two workgroups per unit,
+//   of at least 8 stages, where that saves more than it costs.  Us, whole : pieces: one expert (a shared one) 13675 rows 256 x 576
+//   199 : 32, 10108 384 x 192 151 : 27, 3085 768 x 128 51 : 24; 6 experts 19362 320 x 192 139 : 38; 5 experts 4890 512 x 128 27.3 : 25.8;
+//   most lost: one expert 4513 rows 6144 x 512 72 : 79.
+//   many rows, where an expert with a third of them would be walked for longer than all work takes spread evenly: pieces of
+//   half that time.  9 experts 10730 rows^-1.2 192 x 320 74 : 33, 25 experts 9996 704 x 256 54 : 37; equal loads lose 2-5 us.
+void gt_spread(const moe_ctx* ctx, gg_args& a, int64_t slices) {
+    const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256, R = (double)a.Rcap, E = a.E, stages = R / E / 64;
+    const double tiles = E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128);
+    if (slices > GT_MAX_PIECES) slices = GT_MAX_PIECES;
+    if (slices < 2) return;
+    double few = 2 * cu / tiles < stages / 8 ? 2 * cu / tiles : stages / 8;   // pieces of an expert
+    if (few > slices / E) few = slices / E;
+    const double all = 0.55 * tiles * (stages + 8) / (2 * cu);                // us, were everything spread evenly
+    if (few >= 1.5 && 0.5 * stages * (1 - 1 / few) > 6 + 1.7e-6 * E * a.N * a.K * few) a.split_rows = (int)(R / E / few / 64 + 1) * 64;
+    else if (E > 1 && 0.35 * 0.5 * stages * E > all + 15) a.split_rows = all < 16 ? 1024 : (int)all * 64;
+    else return;
+    // (no more room than any load can ask for: see split_limit)
+    const int64_t n = a.Rcap / a.split_rows + 1, most = n + (n < a.E ? n : a.E);
+    a.split_cap = (int)(slices < most ? slices : most);
+}
+
 // (a multiple of 8: every XCD gets as many workgroups of a call)
 int64_t gt_blocks(int mode, int epi, int bm, const gg_args& a) {
     const int64_t cols = epi == GG_EPI_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(mode == GG_FWD ? a.N : a.K, GT_BN);
-    const int64_t n = cols * (mode == GG_WGRAD ? (a.E + a.split_cap) * ceil_div64(a.N, bm) : ceil_div64(a.Rcap, bm) + a.E);
+    const int64_t pieces = a.split_cap >= 2 ? (a.Rcap / a.split_rows < a.split_cap ? a.Rcap / a.split_rows : a.split_cap) : 0;
+    const int64_t n = cols * (mode == GG_WGRAD ? (a.E + pieces) * ceil_div64(a.N, bm) : ceil_div64(a.Rcap, bm) + a.E);
     return ceil_div64(n, 8) * 8;
 }
 template <int MODE, int EPI, bool F32, int GATH, int BM, int NBUF, bool SPLIT = false>
@@ -503,16 +527,18 @@ static void gt_rows(hipStream_t s, int tile, const gg_args& a) {
     else if (tile == 2) gt_go<MODE, EPI, false, GATH, 128, 2>(s, a);
     else gt_go<MODE, EPI, false, GATH, 64, 3>(s, a);
 }
+template <bool F32>
+static void gt_add(hipStream_t s, const gg_args& a) {
+    const int64_t blocks = ceil_div64((int64_t)a.N * a.K / 4, 256);
+    hipLaunchKernelGGL(gt_add_kernel<F32>, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, a);
+}
 // (a kernel of its own for calls that may split: the others are 5 % faster at their smallest without the choice in them)
 template <bool F32, bool SPLIT, int NBUF>
 static void gt_wgrad(hipStream_t s, int gath, const gg_args& a) {
     if (gath == 1) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 1, 128, NBUF, SPLIT>(s, a);
     else if (gath == 2) gt_go<GG_WGRAD, GG_EPI_STORE, F32, 2, 128, NBUF, SPLIT>(s, a);
     else gt_go<GG_WGRAD, GG_EPI_STORE, F32, 0, 128, NBUF, SPLIT>(s, a);
-    if (SPLIT) {
-        const int64_t blocks = ceil_div64((int64_t)a.N * a.K / 4, 256);
-        hipLaunchKernelGGL(gt_add_kernel<F32>, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, a);
-    }
+    if (SPLIT) gt_add<F32>(s, a);
 }
 void gt_launch(hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     if (mode == GG_WGRAD) {
@@ -539,9 +565,15 @@ static void gt_fwd_jobs(hipStream_t s, int tile, int64_t n, const gt_jobs& m) {
 template <int EPI, bool F32, int WGATH>
 static void gt_bwd_jobs(hipStream_t s, int tile, int wtile, int64_t n, const gt_jobs& m) {
     const dim3 grid((unsigned)n), block(256);
-    if (wtile == 4) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 1>), grid, block, 0, s, m);
-    else if (tile == 1) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 2, F32, WGATH, 2>), grid, block, 0, s, m);
-    else hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 2>), grid, block, 0, s, m);
+    bool split = false;
+    for (int x = 2; x < GT_JOBS; ++x) split |= m.a[x].split_cap >= 2;
+    if (split && tile == 1) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 2, F32, WGATH, 2, true>), grid, block, 0, s, m);
+    else if (split) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 2, true>), grid, block, 0, s, m);
+    else if (wtile == 4) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 1, false>), grid, block, 0, s, m);
+    else if (tile == 1) hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 2, F32, WGATH, 2, false>), grid, block, 0, s, m);
+    else hipLaunchKernelGGL((gt_bwd_jobs_kernel<EPI, 64, 3, F32, WGATH, 2, false>), grid, block, 0, s, m);
+    for (int x = 2; split && x < GT_JOBS; ++x)
+        if (m.a[x].split_cap >= 2) gt_add<F32>(s, m.a[x]);
 }
 void gt_launch_jobs(hipStream_t s, bool fwd, int epi, bool f32, int wgath, int tile, int wtile, const gt_jobs& m) {
     const int64_t n = m.start[GT_JOBS];
@@ -555,14 +587,13 @@ void gt_launch_jobs(hipStream_t s, bool fwd, int epi, bool f32, int wgath, int t
         else f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 0>(s, tile, wtile, n, m) : gt_bwd_jobs<GG_EPI_STORE, false, 0>(s, tile, wtile, n, m);
     }
 }
-// Calls that a batch does not keep: data gradients on 128-row tiles and weight gradients in pieces, which fill the chip by
-// themselves; weight gradients on one buffer of more than eight tiles per unit, which live off three workgroups to a unit, one
+// Calls that a batch does not keep: data gradients on 128-row tiles, which fill the chip by themselves; weight gradients on one buffer of more than eight tiles per unit, which live off three workgroups to a unit, one
 // more than beside a data gradient (a step, us, alone : together: T 112 h 5504 f 1152 E 57 k 4, 86 tiles per unit, 1433 : 1545; T 262
 // h 5696 f 704 E 16 k 2, 17 per unit, 422 : 435; T 2541 h 1088 f 384 E 54, 6 per unit, 171 : 157).
 bool gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     const int64_t cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
-    if (ctx->batch && a.split_cap < 2 && !(mode == GG_DGRAD && tile == 2) && !(tile == 4 && gt_blocks(mode, epi, 128, a) > 8 * cu)) {
-        batch_gemm(ctx->batch, {s, mode, epi, gath, tile, JOB_BF16, out_f32, false, a});
+    if (ctx->batch && !(mode == GG_DGRAD && tile == 2) && !(tile == 4 && a.split_cap < 2 && gt_blocks(mode, epi, 128, a) > 8 * cu)) {
+        batch_gemm(ctx, {s, mode, epi, gath, tile, JOB_BF16, out_f32, false, a});
         return true;
     }
     gt_launch(s, mode, epi, out_f32, gath, tile, a);

@@ -568,7 +568,7 @@ void gq_launch_jobs(hipStream_t s, bool mx, bool fwd, int epi, bool f32, int til
 // Kept by a batch: calls on small tiles (data gradients: 64 rows), without copies of their output or with both MXFP8 ones
 bool gq_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, bool mx, int tile, const gg_args& a) {
     if (ctx->batch && tile != 3 && !(mode == GG_DGRAD && tile == 2) && (!a.out_q || (mx && a.out_qc))) {
-        batch_gemm(ctx->batch, {s, mode, epi, 0, tile, mx ? JOB_MX : JOB_FP8, out_f32, false, a});
+        batch_gemm(ctx, {s, mode, epi, 0, tile, mx ? JOB_MX : JOB_FP8, out_f32, false, a});
         return true;
     }
     gq_launch(ctx, s, mode, epi, out_f32, mx, tile, a);
