@@ -443,12 +443,16 @@ static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
 
 // Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 4 = 128 x 128 on one
 // (gt_one_buffer), 0 = the 256 x 256 kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted to measured calls
-// (MI355X, bf16; rows of an expert unknown on the host, so each of several is given half a partly filled row tile, and at
-// least one tile):
-//   256 x 256: one workgroup per compute unit, whole rounds of tiles (a tenth of one over is not rounded up: it comes from
-//              the guess), a tile = 1.5 per stage + 15 (SwiGLU backward: 35); weight gradient: + 6 for the second launch
+// (MI355X, bf16).  The rows of an expert are unknown on the host: several experts are taken half way between equal ones and ones that
+// scatter, with half a partly filled row tile each and at least one tile.
+//   256 x 256: one workgroup per compute unit, whole rounds of tiles (a twentieth of one over is not rounded up: it comes from
+//              the guess), a tile = 1.5 per stage + 15 (SwiGLU backward: 34); weight gradient: + 6 for the second launch
 //   128 x 128: two workgroups per compute unit, rounds between the exact and the rounded-up count, a round = 2 x (0.62 per
 //              stage + 4)
+//   up to 96 rows per expert, where the weights' way from memory is the time: 4.9 TB/s and 6
+// Over 1814 drawn forward and data-gradient calls, from cold caches, this choice takes 1.4 % more than the best kernel of each would
+// (scattered loads alone, a tenth of a round forgiven, 48 rows: 2.3 %; T 1999 h 2880 f 1472 E 24 k 4, fc2 dgrad: 192 : 144; 450 MB of
+// weights for 272 rows, T 34 h 3328 f 1472 E 23 k 8, fc1: 159 : 103).
 // Measured against each other (us, 256 x 256 : small tiles), fc1 forward unless said otherwise:
 //   T 256 h 128 f 256 E 8 k 2       16 : 6       T 2048 h 1024 f 512 E 8 k 2       41 : 23   (its weight gradients 38, 37 : 14, 16)
 //   T 4096 h 512 f 512 E 16 k 4     56 : 43      T 4096 h 2048 f 1024 E 8 k 2     122 : 113
@@ -456,34 +460,42 @@ static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
 //   T 8192 h 1024 f 1024 E 16 k 4  200 : 230     T 64 h 7168 f 2048 E 32 k 8      429 : 312  (fc2 274 : 168)
 // These are scattered loads.  One that fills whole 256-row tiles exactly is not told apart and can lose (T 4096 h 2048 f 1024
 // E 8 k 2, 1024 rows each, plain fc1 forward 60 : 67; any other load there 93 : 82).  Skewed weight gradients: split_limit.
-// Few rows per expert (on average at most 48): the third buffer (T 64 h 4096 f 14336 E 8 k 2: 464 : 330 against 363 with two
+// Few rows per expert: the third buffer (T 64 h 4096 f 14336 E 8 k 2: 464 : 330 against 363 with two
 // buffers and 359 with 128 x 128).  The same where the 64 x 128 tiles are at most two per unit, so that a third workgroup would
 // find no work (fc1, fc2, fc2 dgrad, fc1 dgrad, two buffers : three: T 256 h 1024 f 704 E 16 k 4 18.0 : 15.4, 12.3 : 9.7, 14.6 :
 // 12.2, 15.6 : 11.4; T 400 h 512 f 512 E 8 k 2 10.9 : 8.6, 7.7 : 6.2, 10.2 : 9.1, 11.8 : 9.1; but at 2.25 per unit, T 2048 h 1024
-// f 512 E 8 k 2, 21.8 : 23.8, 12.2 : 14.1, 18.2 : 21.0).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill the chip's two workgroups per
-// unit (T 256 h 128 f 256: fc2 dgrad 6.9 against 9.5; T 4096 h 512 f 512: 27 against 34); SwiGLU backward, whose output
-// phase is long, up to one and a half times that if the contraction is not (128 x 128 : 64 x 128, T 3000 h 512 f 1536 E 12 k 2 34 : 28.5,
+// f 512 E 8 k 2, 21.8 : 23.8, 12.2 : 14.1, 18.2 : 21.0).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill six tenths of the chip's
+// two workgroups per unit (one above it: 7 experts 3298 rows 1920 x 896 fc2 39 : 28); SwiGLU backward, whose output
+// phase is long, up to twice what fills them if the contraction is not (128 x 128 : 64 x 128, T 3000 h 512 f 1536 E 12 k 2 34 : 28.5,
 // T 4096 h 512 f 512 E 8 k 4 32 : 27, T 4008 h 1536 f 2048 E 17 52 : 48; but h 3264 f 640 E 51, 10230 rows, equal loads 83 : 116, scattered
 // 119 : 115).
 int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
     const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
     const double E = a.E, R = (double)a.Rcap, one = E < R ? E : R;
-    auto row_tiles = [&](double bm) {
+    const double cols = mode == GG_FWD ? a.N : a.K, c256 = __builtin_ceil(cols / 256), c128 = __builtin_ceil(cols / 128);
+    auto rounds = [&](double n) { return n / cu < 1 ? 1 : __builtin_ceil(n / cu); };
+    if (mode == GG_WGRAD) {
+        const double stages = R / E / 64 + 0.5, n256 = c256 * E * __builtin_ceil(a.N / 256.0), r128 = c128 * E * __builtin_ceil(a.N / 128.0) / (2 * cu);
+        const double t256 = rounds(n256 - 0.1 * cu) * (1.5 * stages + 15) + 6, t128 = (r128 + __builtin_ceil(r128)) * (0.62 * stages + 4);
+        if (t128 > 1.1 * t256) return 0;   // (weight gradients of a few stages are better than the estimate)
+        return gt_one_buffer(ctx, a) ? 4 : 2;
+    }
+    const double stages = (mode == GG_FWD ? a.K : a.N) / 64.0;
+    auto scattered = [&](double bm) {
         const double n = E == 1 ? __builtin_ceil(R / bm) : R / bm + E / 2;
         return n > one ? n : one;
     };
-    const double cols = mode == GG_FWD ? a.N : a.K;
-    const double stages = mode == GG_WGRAD ? R / E / 64 + 0.5 : (mode == GG_FWD ? a.K : a.N) / 64.0;
-    const double n256 = __builtin_ceil(cols / 256) * (mode == GG_WGRAD ? E * __builtin_ceil(a.N / 256.0) : row_tiles(256));
-    const double n128 = __builtin_ceil(cols / 128) * (mode == GG_WGRAD ? E * __builtin_ceil(a.N / 128.0) : row_tiles(128));
-    const double r256 = n256 / cu < 1 ? 1 : __builtin_ceil(n256 / cu - 0.1), r128 = n128 / (2 * cu);
-    const double t256 = r256 * (1.5 * stages + (epi == GG_EPI_SWIGLU_BWD ? 35 : 15)) + (mode == GG_WGRAD ? 6 : 0);
+    auto even = [&](double bm) { return E * __builtin_ceil(R / E / bm); };
+    const double t256 = 0.5 * (rounds(c256 * scattered(256) - 0.05 * cu) + rounds(c256 * even(256) - 0.05 * cu)) * (1.5 * stages + (epi == GG_EPI_SWIGLU_BWD ? 34 : 15));
+    const double r128 = 0.5 * (scattered(128) + even(128)) * c128 / (2 * cu), n64 = 0.5 * (scattered(64) + even(64)) * c128;
     const double t128 = (r128 + __builtin_ceil(r128)) * (0.62 * stages + 4);
-    if (t128 > (mode == GG_WGRAD ? 1.1 : 1.0) * t256) return 0;   // (weight gradients of a few stages are better than the estimate)
-    if (mode == GG_WGRAD) return gt_one_buffer(ctx, a) ? 4 : 2;
-    const double n64 = __builtin_ceil(cols / 128) * row_tiles(64);
-    if (R <= 48 * E || n64 <= 2 * cu) return 3;
-    return r128 < (epi == GG_EPI_SWIGLU_BWD && stages <= 24 ? 1.5 : 1) ? 1 : 2;
+    if (R <= 96 * E) {
+        const double stream = 6 + E * a.N * a.K * 2 / 4.9e6;
+        return t256 < (stream < t128 ? stream : t128) ? 0 : 3;
+    }
+    if (t128 > t256) return 0;
+    if (n64 <= 2 * cu) return 3;
+    return r128 < (epi == GG_EPI_SWIGLU_BWD && stages <= 24 ? 2 : 0.6) ? 1 : 2;
 }
 
 // Weight gradients are split in two cases (pieces' results out and in again and the second launch cost about 5 us and what their
