@@ -43,7 +43,14 @@ void batch_gemm(moe_ctx* ctx, gemm_job j) {
 
 static void launch_alone(const gemm_job& j) {
     if (j.kind == JOB_BF16) gt_launch(j.s, j.mode, j.epi, j.f32, j.gath, j.tile, j.a);
-    else gq_launch(nullptr, j.s, j.mode, j.epi, j.f32, j.kind == JOB_MX, j.tile, j.a);
+    else if (j.kind == JOB_F32) {
+        gt_jobs m;
+        memset(&m, 0, sizeof(m));
+        const int at = j.mode == GG_WGRAD ? 2 : 0;
+        m.a[at] = j.a;
+        for (int x = at + 1; x <= GT_JOBS; ++x) m.start[x] = (int)gf_blocks(j.mode, j.epi, j.a);
+        gf_launch_jobs(j.s, j.mode == GG_FWD, j.epi, m);
+    } else gq_launch(nullptr, j.s, j.mode, j.epi, j.f32, j.kind == JOB_MX, j.tile, j.a);
 }
 
 // The calls that go with the first one left: of its kind and stream; forward calls of one epilogue, or data gradients of one epilogue
@@ -99,11 +106,14 @@ static void gemm_flush(gemm_job* jobs, int n) {
             const gemm_job& j = *take[x];
             m.a[x] = j.a;
             const int bm = j.mode == GG_WGRAD || tile == 2 ? 128 : 64;
-            at += j.kind == JOB_BF16 ? gt_blocks(j.mode, j.epi, bm, j.a) : gq_blocks(j.mode, j.epi, bm, j.a);
+            at += j.kind == JOB_BF16  ? gt_blocks(j.mode, j.epi, bm, j.a)
+                  : j.kind == JOB_F32 ? gf_blocks(j.mode, j.epi, j.a)
+                                      : gq_blocks(j.mode, j.epi, bm, j.a);
         }
         m.start[GT_JOBS] = (int)at;
         const int epi = fwd ? first.epi : d ? d->epi : w->gath == 1 ? GG_EPI_SWIGLU_BWD : GG_EPI_STORE;
         if (first.kind == JOB_BF16) gt_launch_jobs(first.s, fwd, epi, w && w->f32, w ? w->gath : 0, tile, wtile, m);
+        else if (first.kind == JOB_F32) gf_launch_jobs(first.s, fwd, epi, m);
         else gq_launch_jobs(first.s, first.kind == JOB_MX, fwd, epi, w && w->f32, tile, m);
     }
 }

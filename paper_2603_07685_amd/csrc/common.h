@@ -252,9 +252,9 @@ __device__ __forceinline__ bool tile_find(const tile_sums<THREADS>& st, int bloc
 }
 template <int THREADS>
 __device__ __forceinline__ bool tile_pick(const int32_t* __restrict__ offsets, int E, int64_t Rcap, int* dev_err, int bm,
-                                          int mult, tile_pick_lds& l, int& e, int& u, int& row_lo, int& row_hi) {
+                                          int mult, int block, tile_pick_lds& l, int& e, int& u, int& row_lo, int& row_hi) {
     tile_sums<THREADS> st;
-    return tile_scan(offsets, E, Rcap, dev_err, bm, mult, l, st, blockIdx.x == 0) && tile_find(st, (int)blockIdx.x, l, e, u, row_lo, row_hi);
+    return tile_scan(offsets, E, Rcap, dev_err, bm, mult, l, st, block == 0) && tile_find(st, block, l, e, u, row_lo, row_hi);
 }
 
 // Quantised copies of the tensor X [rows, cols] that a grouped GEMM has just stored (fp8.hip): blockwise 1x128 codes and

@@ -134,7 +134,7 @@ struct gt_jobs {
     gg_args a[GT_JOBS];
     int start[GT_JOBS + 1];
 };
-enum { JOB_BF16 = 0, JOB_FP8 = 1, JOB_MX = 2 };
+enum { JOB_BF16 = 0, JOB_FP8 = 1, JOB_MX = 2, JOB_F32 = 3 };
 struct gemm_job {
     hipStream_t s;
     int mode, epi, gath, tile, kind;
@@ -182,3 +182,6 @@ void gq_launch_jobs(hipStream_t s, bool mx, bool fwd, int epi, bool f32, int til
 // after: the copies of a kept GEMM's output
 void quant_submit(moe_ctx* ctx, hipStream_t s, const quant_args& a, bool after);
 void quant_flush(quant_job* jobs, int n);
+// fp32 calls on 64 x 64 tiles (gemm_f32.hip)
+int64_t gf_blocks(int mode, int epi, const gg_args& a);
+void gf_launch_jobs(hipStream_t s, bool fwd, int epi, const gt_jobs& m);

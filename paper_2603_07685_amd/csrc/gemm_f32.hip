@@ -23,7 +23,7 @@
 // matrix pipes busy 55-69 % (T 2048, h 1024, f 512).
 // Measured (T 2048, h 1024, f 512, 8 experts, top-2, MI355X): the six GEMMs of a training step took 29.19 ms with one
 // thread per output element (uncoalesced, no reuse); with this kernel 0.47 ms = 82 TFLOP/s (the step: 29.4 -> 0.54 ms).
-#include "common.h"
+#include "gemm.h"
 #include <type_traits>
 
 #define F32_THREADS 256
@@ -137,15 +137,21 @@ __device__ __forceinline__ void gf_output(const gf_args& a, int e, int64_t i0, i
 
 // VEC: every row starts on a 16-byte boundary (row lengths are multiples of 4 floats and so are the bases): operands move
 // 16 bytes per lane; else element by element.
+// `block`: the workgroup's place among those of its call
+template <int BT>
+struct gf_lds {
+    static constexpr int KP = GF_BK + 4, CP = BT + 4;       // pitches (floats) of the two kinds of tile
+    __attribute__((aligned(16))) float tile[2][2][BT * KP > GF_BK * CP ? BT * KP : GF_BK * CP];
+    tile_pick_lds pick;
+};
 template <int MODE, int EPI, int BT, bool VEC>
-__global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
+__device__ __forceinline__ void gf_body(const gf_args& a, gf_lds<BT>& l, const int block) {
     constexpr bool P_CMAJ = MODE == GF_WGRAD, Q_CMAJ = MODE != GF_FWD;
-    constexpr int KP = GF_BK + 4, CP = BT + 4;              // LDS pitches (floats) of the two kinds of tile
-    constexpr int TILE = BT * KP > GF_BK * CP ? BT * KP : GF_BK * CP;
+    constexpr int KP = gf_lds<BT>::KP, CP = gf_lds<BT>::CP;
     constexpr int NP = BT / 64;                             // 16-byte pieces per thread, operand and stage
     constexpr int NB = BT / 32;                             // 16 x 16 blocks per wave and direction
-    __shared__ __attribute__((aligned(16))) float lds[2][2][TILE];
-    __shared__ tile_pick_lds pick;
+    auto& lds = l.tile;
+    tile_pick_lds& pick = l.pick;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
     const int N = a.N, K = a.K;
     const int half = EPI == GF_SWIGLU ? N >> 1 : 0;
@@ -158,7 +164,7 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
     {
         int u;
         if (!tile_pick<F32_THREADS>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GF_WGRAD ? 0 : BT,
-                                    MODE == GF_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, e, u, row_lo, row_hi)) return;
+                                    MODE == GF_WGRAD ? tiles_iw * tiles_j : tiles_j, block, pick, e, u, row_lo, row_hi)) return;
         const int tiles_i = MODE == GF_WGRAD ? tiles_iw : (row_hi - row_lo + BT - 1) / BT;
         tj = u / tiles_i;
         ti = u - tj * tiles_i;
@@ -260,6 +266,38 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
     gf_output<MODE, EPI, VEC, NB, NB>(a, e, i0, i_end, j0, [&](int i, int j) { return acc[i][j]; }, [&](int i) { return p_row(i) + l16; },
                                       [&](int j) { return q_row(j) + 4 * g; });
 }
+template <int MODE, int EPI, int BT, bool VEC>
+__global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
+    __shared__ gf_lds<BT> lds;
+    gf_body<MODE, EPI, BT, VEC>(a, lds, (int)blockIdx.x);
+}
+
+// Independent small calls in one launch (a batch's; gemm_tile.hip: gt_fwd_jobs_kernel, gt_bwd_jobs_kernel), 64 x 64 tiles, 16-byte rows.
+// A step, us, one launch each : together: T 425 h 320 f 192 E 4 k 4 140 : 117; T 128 h 256 f 256 E 22 k 8 98 : 87; with a shared expert
+// T 285 h 576 f 192 E 6 k 1 194 : 97.
+struct gf_jobs {
+    gf_args a[GT_JOBS];
+    int start[GT_JOBS + 1];
+};
+__device__ __forceinline__ int gf_job_of(const gf_jobs& m) {
+    int j = 0;
+#pragma unroll
+    for (int x = 1; x < GT_JOBS; ++x) j += (int)blockIdx.x >= m.start[x];
+    return j;
+}
+template <int EPI>
+__global__ __launch_bounds__(F32_THREADS, 2) void gf_fwd_jobs_kernel(const gf_jobs m) {
+    __shared__ gf_lds<64> lds;
+    const int j = gf_job_of(m);
+    gf_body<GF_FWD, EPI, 64, true>(m.a[j], lds, (int)blockIdx.x - m.start[j]);
+}
+template <int EPI>
+__global__ __launch_bounds__(F32_THREADS, 2) void gf_bwd_jobs_kernel(const gf_jobs m) {
+    __shared__ gf_lds<64> lds;
+    const int j = gf_job_of(m), block = (int)blockIdx.x - m.start[j];
+    if (j < 2) gf_body<GF_DGRAD, EPI, 64, true>(m.a[j], lds, block);
+    else gf_body<GF_WGRAD, GF_STORE, 64, true>(m.a[j], lds, block);
+}
 
 // ---------------------------------------------------------------------------
 // The same GEMMs on the bf16 matrix instruction, without losing a bit of the operands: every fp32 element is the sum of
@@ -348,7 +386,7 @@ __global__ __launch_bounds__(F32_THREADS, BM == 64 ? 2 : 1) void gs_kernel(const
     {
         int u;
         if (!tile_pick<F32_THREADS>(a.offsets, a.E, a.Rcap, a.dev_err, MODE == GF_WGRAD ? 0 : BM,
-                                    MODE == GF_WGRAD ? tiles_iw * tiles_j : tiles_j, pick, e, u, row_lo, row_hi)) return;
+                                    MODE == GF_WGRAD ? tiles_iw * tiles_j : tiles_j, (int)blockIdx.x, pick, e, u, row_lo, row_hi)) return;
         const int tiles_i = MODE == GF_WGRAD ? tiles_iw : (row_hi - row_lo + BM - 1) / BM;
         tj = u / tiles_i;
         ti = u - tj * tiles_i;
@@ -685,8 +723,24 @@ static moe_status gf_launch(moe_ctx* ctx, hipStream_t s, const char* who, const 
         const int64_t cols = EPI == GF_SWIGLU ? ceil_div64(a.N / 2, 64) : ceil_div64(out_cols, GS_BN);
         const int64_t n = cols * (MODE == GF_WGRAD ? a.E * ceil_div64(a.N, GS_BM) : ceil_div64(a.Rcap, GS_BM) + a.E);
         hipLaunchKernelGGL((gs_kernel<MODE, EPI, GS_BM>), dim3((unsigned)(ceil_div64(n, 8) * 8)), b, 0, s, a);
-    } else
-    if (vec && bt == 128) hipLaunchKernelGGL((gf_kernel<MODE, EPI, 128, true>), g, b, 0, s, a);
+    } else if (vec && bt == 64 && ctx->batch) {
+        gg_args j;   // (the fields a batch's list has in common with this path's)
+        memset(&j, 0, sizeof(j));
+        j.P = a.P;
+        j.Q = a.Q;
+        j.offsets = a.offsets;
+        j.E = a.E;
+        j.N = a.N;
+        j.K = a.K;
+        j.Rcap = a.Rcap;
+        j.out = a.out;
+        j.out_act = (bf16_t*)a.out_act;
+        j.Zsaved = (const bf16_t*)a.Zsaved;
+        j.row_prob = a.row_prob;
+        j.accumulate = a.accumulate;
+        j.dev_err = a.dev_err;
+        batch_gemm(ctx, {s, MODE, EPI, 0, 1, JOB_F32, MODE == GF_WGRAD, false, j});
+    } else if (vec && bt == 128) hipLaunchKernelGGL((gf_kernel<MODE, EPI, 128, true>), g, b, 0, s, a);
     else if (vec) hipLaunchKernelGGL((gf_kernel<MODE, EPI, 64, true>), g, b, 0, s, a);
     else if (bt == 128) hipLaunchKernelGGL((gf_kernel<MODE, EPI, 128, false>), g, b, 0, s, a);
     else hipLaunchKernelGGL((gf_kernel<MODE, EPI, 64, false>), g, b, 0, s, a);
@@ -715,4 +769,25 @@ moe_status moe_gg_f32_wgrad(moe_ctx* ctx, hipStream_t s, const void* A, const vo
     const gf_args a = {(const float*)dC, (const float*)A, offsets, E, N, K, Rcap, (float*)dB, nullptr, nullptr, nullptr,
                        accumulate ? 1 : 0, ctx->dev_err};
     return gf_launch<GF_WGRAD, GF_STORE>(ctx, s, "moe_grouped_gemm_wgrad(f32)", a);
+}
+
+// ---- calls of a batch ----
+int64_t gf_blocks(int mode, int epi, const gg_args& a) {
+    const int64_t cols = epi == GF_SWIGLU ? ceil_div64(a.N / 2, 32) : ceil_div64(mode == GF_FWD ? a.N : a.K, 64);
+    return ceil_div64(cols * (mode == GF_WGRAD ? a.E * ceil_div64(a.N, 64) : ceil_div64(a.Rcap, 64) + a.E), 8) * 8;
+}
+void gf_launch_jobs(hipStream_t s, bool fwd, int epi, const gt_jobs& m) {
+    gf_jobs f;
+    for (int x = 0; x < GT_JOBS; ++x) {
+        const gg_args& a = m.a[x];
+        f.a[x] = {(const float*)a.P, (const float*)a.Q, a.offsets, a.E, a.N, a.K, a.Rcap, (float*)a.out, (float*)a.out_act,
+                  (const float*)a.Zsaved, a.row_prob, a.accumulate, a.dev_err};
+        f.start[x] = m.start[x];
+    }
+    f.start[GT_JOBS] = m.start[GT_JOBS];
+    const dim3 g((unsigned)f.start[GT_JOBS]), b(F32_THREADS);
+    if (fwd && epi == GF_SWIGLU) hipLaunchKernelGGL(gf_fwd_jobs_kernel<GF_SWIGLU>, g, b, 0, s, f);
+    else if (fwd) hipLaunchKernelGGL(gf_fwd_jobs_kernel<GF_STORE>, g, b, 0, s, f);
+    else if (epi == GF_SWIGLU_BWD) hipLaunchKernelGGL(gf_bwd_jobs_kernel<GF_SWIGLU_BWD>, g, b, 0, s, f);
+    else hipLaunchKernelGGL(gf_bwd_jobs_kernel<GF_STORE>, g, b, 0, s, f);
 }

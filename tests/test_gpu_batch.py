@@ -70,6 +70,12 @@ def test_layer_is_that_of_single_calls(size, kw, shared):
     _compare(_layers(SIZES[size], shared, **kw), shared)
 
 
+@pytest.mark.parametrize("size", [0, 1, 2, 3])
+@pytest.mark.parametrize("shared", [False, True])
+def test_fp32_layer_is_that_of_single_calls(size, shared):
+    _compare(_layers(SIZES[size], shared, recipe="fp32"), shared)
+
+
 @pytest.mark.parametrize("size", range(len(SIZES)))
 @pytest.mark.parametrize("kw", [{}, dict(wgrad_f32=True), dict(eq2=True), dict(epilogue_quant=True), dict(fp8_wgrad=False)],
                          ids=lambda kw: "+".join(kw) or "plain")
