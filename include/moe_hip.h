@@ -78,8 +78,8 @@ moe_status moe_ctx_destroy(moe_ctx* ctx);
 
 /*
  * A batch: a second handle on ctx (same device, same workspace) for calls that do not depend on each other, so that small
- * ones share a launch: a layer's weight and data gradient, or the routed and the shared experts' calls.  A grouped GEMM called
- * with the batch as its context is checked as ever, and either launched at once or kept until moe_batch_end, which launches what is
+ * ones share a launch: a layer's weight and data gradient, or the routed and the shared experts' calls.  A grouped GEMM or a
+ * quantiser called with the batch as its context is checked as ever, and either launched at once or kept until moe_batch_end, which launches what is
  * kept on the stream each call was given, in no particular order; every other call is launched at once.  Results are those
  * of the same calls on ctx, bit for bit.  Until moe_batch_end returns, the operands of the calls must stay valid, none may
  * read or write what another of them writes, and no other work that uses them may be enqueued.

@@ -23,9 +23,9 @@ import sys
 from collections import OrderedDict
 
 GIB = 1 << 30
-GEMMS = ("gg_kernel", "gq_kernel", "gt_kernel", "gf_kernel", "gs_kernel")
+GEMMS = ("gg_kernel", "gq_kernel", "gt_kernel", "gf_kernel", "gs_kernel", "gt_fwd_jobs", "gt_bwd_jobs", "gq_fwd_jobs", "gq_bwd_jobs", "gf_fwd_jobs", "gf_bwd_jobs")
 LEGEND = ("gg_kernel<MODE,EPI,F32,F8,NW,GATH>, gq_kernel<MODE,EPI,F32,F8,BM,BN>, gt_kernel<MODE,EPI,F32,GATH,BM,NBUF,SPLIT> (bf16), gf_kernel<MODE,EPI,BT,VEC> (fp32), gs_kernel<MODE,EPI,BM> (fp32 as three bf16 parts): MODE 0 fwd / 1 dgrad / 2 wgrad; EPI 0 store / 1 SwiGLU / 2 SwiGLU-bwd; "
-          "F8 0 bf16 / 1 blockwise fp8 / 2 MXFP8; NW waves per workgroup")
+          "F8 0 bf16 / 1 blockwise fp8 / 2 MXFP8; NW waves per workgroup; g?_fwd_jobs_kernel, g?_bwd_jobs_kernel: calls of a batch in one launch")
 
 
 def _short(name: str) -> str:
