@@ -10,6 +10,7 @@ sample of the same workload.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import sys
@@ -342,6 +343,10 @@ def main():
         st.R_live = int(st.counts.sum().item())   # rows whose expert lives here (outside the timed region)
     # timed region: K steps; every library call is followed by an event on the launch stream, so the
     # per-kernel durations come from the timed region itself (an event record costs about a microsecond)
+    # (the collector is off meanwhile: the events' Python objects set off one full collection of about 35 ms, which is a step of a
+    # small layer many times over)
+    gc.collect()
+    gc.disable()
     t0 = time.perf_counter()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     e0.record()
@@ -349,6 +354,7 @@ def main():
     e1.record()
     torch.cuda.synchronize()
     wall_ms = (time.perf_counter() - t0) * 1e3 / args.steps
+    gc.enable()
     ms = e0.elapsed_time(e1) / args.steps
     ms = max(ms, 1e-6)
     assert st.ctx.poll_error() == 0
