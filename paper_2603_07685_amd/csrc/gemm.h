@@ -129,11 +129,14 @@ void gq_launch(const moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f3
 // ---- batches (moe_batch_create; batch.hip): calls kept until the batch's end, launched together ----
 // Up to four grouped GEMMs of a launch: the workgroups of call x are start[x] .. start[x + 1] - 1, multiples of 8 of them, so
 // that the XCDs' shares of a call stay.  Forward calls from 0 on; or data gradients 0 and 1, weight gradients 2 and 3.
+// turn: the place in that list of the grid's first workgroup, 0 or start[2] (weight gradients go first; batch.hip: longer_first).
 #define GT_JOBS 4
 struct gt_jobs {
     gg_args a[GT_JOBS];
     int start[GT_JOBS + 1];
+    int turn;
 };
+__device__ __forceinline__ int gt_place_of(int block, int turn, int total) { return block + turn < total ? block + turn : block + turn - total; }
 enum { JOB_BF16 = 0, JOB_FP8 = 1, JOB_MX = 2, JOB_F32 = 3 };
 struct gemm_job {
     hipStream_t s;

@@ -277,24 +277,24 @@ __global__ __launch_bounds__(F32_THREADS, 2) void gf_kernel(const gf_args a) {
 // T 285 h 576 f 192 E 6 k 1 194 : 97.
 struct gf_jobs {
     gf_args a[GT_JOBS];
-    int start[GT_JOBS + 1];
+    int start[GT_JOBS + 1], turn;
 };
-__device__ __forceinline__ int gf_job_of(const gf_jobs& m) {
+__device__ __forceinline__ int gf_job_of(const gf_jobs& m, int block) {
     int j = 0;
 #pragma unroll
-    for (int x = 1; x < GT_JOBS; ++x) j += (int)blockIdx.x >= m.start[x];
+    for (int x = 1; x < GT_JOBS; ++x) j += block >= m.start[x];
     return j;
 }
 template <int EPI>
 __global__ __launch_bounds__(F32_THREADS, 2) void gf_fwd_jobs_kernel(const gf_jobs m) {
     __shared__ gf_lds<64> lds;
-    const int j = gf_job_of(m);
+    const int j = gf_job_of(m, (int)blockIdx.x);
     gf_body<GF_FWD, EPI, 64, true>(m.a[j], lds, (int)blockIdx.x - m.start[j]);
 }
 template <int EPI>
 __global__ __launch_bounds__(F32_THREADS, 2) void gf_bwd_jobs_kernel(const gf_jobs m) {
     __shared__ gf_lds<64> lds;
-    const int j = gf_job_of(m), block = (int)blockIdx.x - m.start[j];
+    const int at = gt_place_of((int)blockIdx.x, m.turn, m.start[GT_JOBS]), j = gf_job_of(m, at), block = at - m.start[j];
     if (j < 2) gf_body<GF_DGRAD, EPI, 64, true>(m.a[j], lds, block);
     else gf_body<GF_WGRAD, GF_STORE, 64, true>(m.a[j], lds, block);
 }
@@ -785,6 +785,7 @@ void gf_launch_jobs(hipStream_t s, bool fwd, int epi, const gt_jobs& m) {
         f.start[x] = m.start[x];
     }
     f.start[GT_JOBS] = m.start[GT_JOBS];
+    f.turn = m.turn;
     const dim3 g((unsigned)f.start[GT_JOBS]), b(F32_THREADS);
     if (fwd && epi == GF_SWIGLU) hipLaunchKernelGGL(gf_fwd_jobs_kernel<GF_SWIGLU>, g, b, 0, s, f);
     else if (fwd) hipLaunchKernelGGL(gf_fwd_jobs_kernel<GF_STORE>, g, b, 0, s, f);

@@ -356,7 +356,7 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
 // Independent calls in one launch.  Small calls leave compute units idle in their start, their output phase and the last of their rounds, and each
 // launch costs about 2 us behind another; together they fill each other's gaps.  A step, us, one launch each : together: T 256 h 128
 // f 256 E 8 k 2 52.8 : 45.1; T 377 h 2240 f 512 E 8 k 2 130 : 106; T 7394 h 128 f 192 E 24 125 : 104; with a shared expert T 27 h 576 f 512
-// E 7 k 2 105 : 60, T 873 h 896 f 2688 E 12 k 2 342 : 300.  Data gradients go first: their tiles take longer.
+// E 7 k 2 105 : 60, T 873 h 896 f 2688 E 12 k 2 342 : 300.
 // forward calls with one epilogue
 template <int EPI, int BM, int NBUF>
 __global__ __launch_bounds__(256, NBUF == 2 && BM == 64 ? 3 : 2) void gt_fwd_jobs_kernel(const gt_jobs m) {
@@ -371,7 +371,7 @@ __global__ __launch_bounds__(256, 2) void gt_bwd_jobs_kernel(const gt_jobs m) {
         gt_lds<GG_DGRAD, 3, BM, NBUF> d;
         gt_lds<GG_WGRAD, WGATH, 128, WBUF> w;
     } lds;
-    const int j = gt_job_of(m, (int)blockIdx.x), block = (int)blockIdx.x - m.start[j];
+    const int at = gt_place_of((int)blockIdx.x, m.turn, m.start[GT_JOBS]), j = gt_job_of(m, at), block = at - m.start[j];
     if (j < 2) gt_body<GG_DGRAD, EPI, false, 3, BM, NBUF, false>(m.a[j], lds.d, block);
     else gt_body<GG_WGRAD, GG_EPI_STORE, F32, WGATH, 128, WBUF, SPLIT>(m.a[j], lds.w, block);
 }

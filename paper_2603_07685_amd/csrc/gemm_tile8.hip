@@ -466,7 +466,8 @@ __global__ __launch_bounds__(256, 2) void gq_bwd_jobs_kernel(const gt_jobs m) {
     __shared__ __attribute__((aligned(1024))) char ring[2 * 256 * 128];
     __shared__ __attribute__((aligned(16))) float scales[4][256];
     __shared__ gq_lds<false> lds;
-    const int j = gt_job_of(m, (int)blockIdx.x), block = (int)blockIdx.x - m.start[j], G = m.start[j + 1] - m.start[j];
+    const int at = gt_place_of((int)blockIdx.x, m.turn, m.start[GT_JOBS]), j = gt_job_of(m, at), block = at - m.start[j];
+    const int G = m.start[j + 1] - m.start[j];
     if (j < 2) gq_body<GG_DGRAD, EPI, false, F8, 64, 128>(m.a[j], ring, scales, lds, block, G);
     else gq_body<GG_WGRAD, GG_EPI_STORE, F32, F8, 128, 128>(m.a[j], ring, scales, lds, block, G);
 }
