@@ -175,11 +175,18 @@ __global__ __launch_bounds__(1024) void permute_rank_kernel(const int32_t* __res
 
 // ---------------------------------------------------------------------------
 // Small calls: map and row move in one launch.  A workgroup owns a few tokens; it counts all pairs by itself, those in front of its own
-// apart from the others, ranks its own and copies its tokens' rows.  Every workgroup reads all expert ids (up to 64 KB, from L2), which buys two launches' gaps.
+// apart from the others, ranks its own and copies its tokens' rows.  Every workgroup reads all expert ids (up to 128 KB, from L2),
+// which buys two launches' gaps.  Rows that no pair owns are dealt to all workgroups; where there are many of them for the tokens'
+// workgroups, further ones without tokens follow (permute_all_grid).
 // ---------------------------------------------------------------------------
 #define PERMUTE_ALL_THREADS 512
+// Us, three launches for the map and one for the rows : this; h 512, loads scattered by 30 % | 95 % of the pairs on one expert.
+// 16384 pairs, k 8: E 8 14.5 : 9.6 | 14.6 : 9.5; E 512 17.3 : 10.4 | 17.3 : 14.3; 32768 pairs, k 8: E 8 17.7 : 15.4 | 17.7 : 15.2; E 256
+// 20.5 : 16.3 | 20.4 : 17.8; E 512 23.3 : 16.8 | 23.1 : 24.1 (the only loss); k 1, E 8 24.1 : 20.8.  Twice as many pairs would cost
+// twice the time here, a fifth more there.  The map alone, 16384 pairs: E 8 10.4 : 7.1 | 10.6 : 7.1; E 512 13.1 : 7.9 | 13.3 : 11.8.
 #define PERMUTE_ALL_PAIRS 32768  // (the map alone: half)
 #define PERMUTE_ALL_E 512
+#define PERMUTE_ALL_GRID 256     // most workgroups because of rows without a pair
 __host__ __device__ __forceinline__ int permute_copies(int E) { return E <= 128 ? 8 : E <= 256 ? 4 : 2; }
 __global__ __launch_bounds__(PERMUTE_ALL_THREADS) void permute_all_kernel(
     const u32x4_t* __restrict__ X, const int32_t* __restrict__ idx, int T, int k, int E, int nbits, int align, int per_wg, int vec,
@@ -193,7 +200,7 @@ __global__ __launch_bounds__(PERMUTE_ALL_THREADS) void permute_all_kernel(
     int32_t *const cnt = lds, *const ends = lds + 2 * copies * E, *const offs = ends + E, *const wcnt = offs + E + 1;
     __shared__ int32_t rows[NT], wsum[NW];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, G = (int)gridDim.x, b = (int)blockIdx.x;
-    const int pairs = T * k, t0 = b * per_wg, nt = min(per_wg, T - t0), own0 = t0 * k, own = nt * k;
+    const int pairs = T * k, t0 = min(b * per_wg, T), nt = min(per_wg, T - t0), own0 = t0 * k, own = nt * k;
     for (int i = tid; i < 2 * copies * E; i += NT) cnt[i] = 0;
     for (int i = tid; i < NW * E; i += NT) wcnt[i] = 0;
     __syncthreads();
@@ -268,8 +275,8 @@ __global__ __launch_bounds__(PERMUTE_ALL_THREADS) void permute_all_kernel(
     }
     // ---- rows that no pair owns: padding rows, spread over the workgroups, and what lies behind the last expert ----
     if (align > 1) {
-        for (int x = wave; x < E; x += NW)
-            for (int r = ends[x] + b; r < offs[x + 1]; r += G) {
+        for (int x = wave; x < E; x += NW)   // (an expert's first row goes to the workgroup behind its predecessor's last)
+            for (int r = ends[x] + (int)((b + (uint32_t)x * (uint32_t)(align - 1)) % (uint32_t)G); r < offs[x + 1]; r += G) {
                 if (lane == 0) src_of[r] = -1;
                 if (Xp)
                     for (int c = lane; c < vec; c += 64) Xp[(int64_t)r * vec + c] = mk4(0, 0, 0, 0);
@@ -550,6 +557,17 @@ static moe_status permute_check(char* err, const void* X, moe_dtype dt, const in
     return MOE_OK;
 }
 
+// Workgroups of permute_all_kernel: the tokens', or so many that none fills more than 64 KB of rows without a pair, up to one per
+// compute unit.  Us, three launches and the row move : the tokens' workgroups alone : 256 : 1024; T 1 k 8 h 7168 E 8, padded to 128 rows,
+// 20.6 : 80.9 : 7.7 : 7.7; T 64 k 8 h 4096 E 128, padded to 128, 25.4 : 26.3 : 21.9 : 24.3; T 256 k 8 h 7168 E 256, padded to 128,
+// 98.8 : 92.6 : 92.9 : 96.4; T 16 k 2 h 1024 E 8, 2^22 rows more than pairs, 13.5 : 20.5 : 7.9 : 7.9; T 1 k 8 h 1024 E 8, 2^24 more,
+// 21.6 : 846 : 15.6 : 14.7.
+static unsigned permute_all_grid(int T, int per_wg, int E, int align, int vec, int64_t free_rows) {
+    const int64_t tokens = T > per_wg ? (T + per_wg - 1) / per_wg : 1;
+    const int64_t fill = ceil_div64((int64_t)E * (align - 1) * vec * 16 + free_rows * 4, 65536);
+    return (unsigned)(fill < tokens ? tokens : fill < PERMUTE_ALL_GRID ? fill : PERMUTE_ALL_GRID > tokens ? PERMUTE_ALL_GRID : tokens);
+}
+
 // The launches of one permute call; chunk_hist = int32 [chunks, E] of device scratch (every entry is written by the
 // histogram kernel before it is read: the buffer needs no clearing).
 static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int32_t* idx, int T, int k, int h, int E,
@@ -562,7 +580,7 @@ static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int
     if (pairs <= (X ? PERMUTE_ALL_PAIRS : PERMUTE_ALL_PAIRS / 2) && E <= PERMUTE_ALL_E && (int64_t)per_wg * vec * vec < (1LL << 32)) {
         // (c / vec = c * ceil(2^32 / vec) / 2^32 for c < per_wg * vec: the rounding adds less than c vec / 2^32 of a step)
         const uint64_t magic = vec ? ((1ull << 32) + vec - 1) / vec : 0;
-        hipLaunchKernelGGL(permute_all_kernel, dim3(T > per_wg ? (T + per_wg - 1) / per_wg : 1), dim3(PERMUTE_ALL_THREADS),
+        hipLaunchKernelGGL(permute_all_kernel, dim3(permute_all_grid(T, per_wg, E, align, vec, Rcap - pairs)), dim3(PERMUTE_ALL_THREADS),
                            (size_t)((2 * permute_copies(E) + 2 + PERMUTE_ALL_THREADS / 64) * E + 1) * sizeof(int32_t), s, (const u32x4_t*)X, idx, T, k, E, nbits,
                            align, per_wg, vec, magic, Rcap, (u32x4_t*)Xp, row_of, src_of, offsets, counts);
         return;
