@@ -57,7 +57,9 @@ static void launch_alone(const gemm_job& j) {
 // others fill what they leave.  A tile takes the call's contraction: N of a data gradient, an expert's rows of a weight gradient.
 // Of several experts a hot one ends the launch, so their mean counts twice; of a single one 0.8 of its rows, as a data gradient's
 // output phase is the longer (bf16 T 1538 h 1536 f 2624 E 6 k 1, shared 2624, 1538 rows against N 1536: 445 : 462 us a step with the
-// weight gradients first).  Experts in pieces end early and do not count.
+// weight gradients first).  A call that cuts experts into pieces walks no more rows than a piece's, but may have nothing
+// to cut: counted as nothing, 40 drawn layers' backward passes of 24576 rows or fewer took 1.02 (equal loads) to 1.03 times as long (rank^-1.2),
+// T 3699 h 192 f 256 E 9 k 4 85 : 72 us.
 // Steps, us, data gradients always first : this: MXFP8 T 1920 h 512 f 256 E 8 k 8 160 : 145, T 8192 h 256 f 896 E 28, shared 896
 // 410 : 356; fp8 T 1920 h 896 f 896 E 4 k 4 250 : 230; bf16 T 773 h 960 f 384 E 5 k 4, rank^-1.2, 104 : 94.  160 drawn layers with a
 // shared expert, each with equal, by 30 % scattered and rank^-1.2 loads, mean: MXFP8 1.040, fp8 1.034, bf16 1.005; 159 others 1.018,
@@ -68,7 +70,8 @@ static bool longer_first(gemm_job* const (&take)[GT_JOBS]) {
     for (int x = 0; x < GT_JOBS; ++x) {
         if (!take[x]) continue;
         const gg_args& a = take[x]->a;
-        const double l = x < 2 ? a.N : a.split_cap >= 2 ? 0 : a.E == 1 ? 0.8 * a.Rcap : 2.0 * a.Rcap / a.E;
+        const double rows = a.E == 1 ? 0.8 * a.Rcap : 2.0 * a.Rcap / a.E;
+        const double l = x < 2 ? a.N : a.split_cap >= 2 && a.split_rows < rows ? a.split_rows : rows;
         double& most = x < 2 ? data : weight;
         if (l > most) most = l;
     }

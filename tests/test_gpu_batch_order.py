@@ -23,7 +23,7 @@ def _us(f, n=5):
 # (rows, N, K) of one expert: contractions of 256 stages in 48 tiles beside two rounds of data-gradient tiles of 24 stages; and the
 # reverse, two rounds of weight-gradient tiles of 2 stages beside data gradients of 128
 @pytest.mark.parametrize("E,R,N,K", [(1, 16384, 1536, 512), (4, 512, 8192, 512)])
-def test_joint_launch_overlaps(E, R, N, K):
+def test_joint_launch_overlaps(E, R, N, K, room=0):
     """The two together take clearly less than one behind the other: 0.82 and 0.83 of it measured, 0.98 and 0.83 with the data
     gradients always first."""
     from paper_2603_07685_amd import binding as B
@@ -32,7 +32,7 @@ def test_joint_launch_overlaps(E, R, N, K):
     r = lambda *s: torch.randn(s, generator=g, device="cuda").to(torch.bfloat16)
     A, dC, W, Z = r(R, K), r(R, N), r(E, N, K), r(R, 2 * K)
     off = torch.arange(0, R + 1, R // E, dtype=torch.int32, device="cuda")
-    ctx = B.Context(64, 1, E, 0, 0)                  # (no room for pieces: every contraction is walked whole)
+    ctx = B.Context(64, 1, E, K if room else 0, room)    # (no room for pieces: every contraction is walked whole)
     batch = B.Batch(ctx)
     dZ, dW = torch.empty((2, R, 2 * K), dtype=torch.bfloat16, device="cuda"), torch.empty((2, E, N, K), dtype=torch.bfloat16, device="cuda")
 
@@ -53,3 +53,9 @@ def test_joint_launch_overlaps(E, R, N, K):
     assert torch.equal(dZ[0], dZ[1]) and torch.equal(dW[0], dW[1])
     print(f"apart {apart:.1f} us, joint {joint:.1f} us: {joint / apart:.2f}")
     assert joint < 0.9 * apart
+
+
+def test_joint_launch_with_room_for_pieces():
+    """A weight gradient that would cut a hot expert's rows into pieces, under equal loads, where it cuts none: its long tiles go first
+    as they do without the room."""
+    test_joint_launch_overlaps(8, 28672, 512, 512, room=256)
