@@ -504,8 +504,14 @@ int gt_tile(const moe_ctx* ctx, int mode, int epi, const gg_args& a) {
 //   of at least 8 stages, where that saves more than it costs.  Us, whole : pieces: one expert (a shared one) 13675 rows 256 x 576
 //   199 : 32, 10108 384 x 192 151 : 27, 3085 768 x 128 51 : 24; 6 experts 19362 320 x 192 139 : 38; 5 experts 4890 512 x 128 27.3 : 25.8;
 //   most lost: one expert 4513 rows 6144 x 512 72 : 79.
-//   many rows, where an expert with a third of them would be walked for longer than all work takes spread evenly: pieces of
-//   half that time.  9 experts 10730 rows^-1.2 192 x 320 74 : 33, 25 experts 9996 704 x 256 54 : 37; equal loads lose 2-5 us.
+//   more than GT_SPLIT_ROWS rows of several experts, where a hot one is walked for long: pieces of the time that all work takes spread
+//   evenly, but of no less than one and a half times the mean load, so that equal loads are not cut.  The second launch costs every
+//   load 2.7 us.  Below the bound that is 6 % of a backward pass under equal loads, 5 % under ones scattered by 30 %, against 1.18x under
+//   rank^-1.2 (means of 40 drawn layers; T 1876 h 576 f 256 E 26 k 8 90 : 98 | 91 : 99 | 144 : 125): not worth it for the loads that a
+//   balanced router gives.  Above it, steps of 30 drawn layers, whole : pieces:
+//   0.990 | 0.992 | 1.17 in the mean (T 16310 h 192 f 128 E 62 k 8, backward, 223 : 230 | 250 : 257 | 1093 : 539); pieces of a fifth of all
+//   rows instead of these: 0.98 | 0.98 | 0.93 (0.73-1.004).
+#define GT_SPLIT_ROWS 24576
 void gt_spread(const moe_ctx* ctx, gg_args& a, int64_t slices) {
     const double cu = ctx->num_cu > 0 ? ctx->num_cu : 256, R = (double)a.Rcap, E = a.E, stages = R / E / 64;
     const double tiles = E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128);
@@ -515,8 +521,10 @@ void gt_spread(const moe_ctx* ctx, gg_args& a, int64_t slices) {
     if (few > slices / E) few = slices / E;
     const double all = 0.55 * tiles * (stages + 8) / (2 * cu);                // us, were everything spread evenly
     if (few >= 1.5 && 0.5 * stages * (1 - 1 / few) > 6 + 1.7e-6 * E * a.N * a.K * few) a.split_rows = (int)(R / E / few / 64 + 1) * 64;
-    else if (E > 1 && 0.35 * 0.5 * stages * E > all + 15) a.split_rows = all < 16 ? 1024 : (int)all * 64;
-    else return;
+    else if (E > 1 && R > GT_SPLIT_ROWS) {
+        const double share = 1.5 * R / E, even = all < 16 ? 1024 : all * 64, rows = share > even ? share : even;
+        a.split_rows = (int)((rows < R ? rows : R) / 64 + 1) * 64;
+    } else return;
     // (no more room than any load can ask for: see split_limit)
     const int64_t n = a.Rcap / a.split_rows + 1, most = n + (n < a.E ? n : a.E);
     a.split_cap = (int)(slices < most ? slices : most);

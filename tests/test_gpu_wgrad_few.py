@@ -14,7 +14,9 @@ CASES = [
     ([1537], 136, 72, 0), ([640], 136, 72, None),              # one expert: pieces of 8 stages and what is left; too short
     ([16384], 192, 256, 0), ([1400], 3000, 512, None),          # as many pieces as slices; output too large beside the walk
     ([6000, 0, 129, 3000], 264, 136, 0),                        # several experts, some below a piece
-    ([7000] + [40] * 24, 704, 256, 0), ([280] * 25, 704, 256, None),   # one hot expert among many tiles; equal ones
+    ([25000] + [40] * 24, 704, 256, 0), ([1000] * 25, 704, 256, None),  # one hot expert among many tiles; equal ones
+    ([7000] + [40] * 24, 704, 256, None), ([24000] + [24] * 24, 704, 256, None),   # too few rows for it; all that are too few
+    ([24000] + [25] * 23 + [2], 704, 256, 0),                               # one row more
 ]
 
 
