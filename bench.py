@@ -211,8 +211,33 @@ HOOKED = ["moe_fp8_quantize_rowcol", "moe_fp8_quantize_rowcol_gather", "moe_mx_q
           "moe_grouped_gemm_wgrad_gather", "moe_batch_end"]
 
 
-IN_BATCH = " (batch)"   # a call made with a batch for its context
-HOST_MS = 0.012         # two events with nothing launched between them: 5-10 us
+def kept_calls(st):
+    """For every library call of a step, in issue order: whether a batch has kept it (its GEMM, or the quantiser it is)."""
+    from paper_2603_07685_amd import binding as B
+    out, orig, before = [], {}, {}
+
+    def wrap(name, fn):
+        at = 0 if "grouped_gemm" in name else 1
+
+        def inner(*a, **kw):
+            r = fn(*a, **kw)
+            now = a[0].kept() if isinstance(a[0], B.Batch) else None
+            out.append(now is not None and now[at] > before.get(a[0], (0, 0))[at])
+            if now is not None:
+                before[a[0]] = now
+            return r
+        return inner
+
+    before[st.batch] = st.batch.kept()
+    for n in HOOKED:
+        orig[n] = getattr(B, n)
+        setattr(B, n, wrap(n, orig[n]))
+    try:
+        st.step()
+    finally:
+        for n in HOOKED:
+            setattr(B, n, orig[n])
+    return out
 
 
 def timed_step_with_events(st, torch, sync=True):
@@ -227,8 +252,7 @@ def timed_step_with_events(st, torch, sync=True):
             ev = torch.cuda.Event(enable_timing=True)
             ev.record()
             evs.append(ev)
-            lab, fl, by = describe_call(name, a, st)
-            recs.append((lab + IN_BATCH if lab != "batch" and isinstance(a[0], B.Batch) else lab, fl, by))
+            recs.append(describe_call(name, a, st))
             return r
         return inner
 
@@ -341,6 +365,8 @@ def main():
     torch.cuda.synchronize()
     if st.forced_idx is None and cfg.E_router > cfg.E:
         st.R_live = int(st.counts.sum().item())   # rows whose expert lives here (outside the timed region)
+    kept = kept_calls(st)
+    torch.cuda.synchronize()
     # timed region: K steps; every library call is followed by an event on the launch stream, so the
     # per-kernel durations come from the timed region itself (an event record costs about a microsecond)
     # (the collector is off meanwhile: the events' Python objects set off one full collection of about 35 ms, which is a step of a
@@ -366,13 +392,12 @@ def main():
     # a call that a batch has kept is launched, with others, by the batch's end, and its work counts there: what its own events
     # bracket is the host's way from one to the next
     kept_fl, kept_by, timed = 0.0, 0.0, []
-    for lab, fl, by, t in calls:
+    assert len(kept) == len(calls)
+    for (lab, fl, by, t), is_kept in zip(calls, kept):
         if lab == "batch":
             fl, by, kept_fl, kept_by = kept_fl or None, kept_by or None, 0.0, 0.0
-        elif lab.endswith(IN_BATCH):
-            lab = lab[:-len(IN_BATCH)]
-            if t < HOST_MS:
-                kept_fl, kept_by, fl, by = kept_fl + (fl or 0.0), kept_by + (by or 0.0), None, None
+        elif is_kept:
+            kept_fl, kept_by, fl, by = kept_fl + (fl or 0.0), kept_by + (by or 0.0), None, None
         timed.append((lab, fl, by, t))
     calls = timed
     breakdown = {}

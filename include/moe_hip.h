@@ -88,6 +88,10 @@ moe_status moe_ctx_destroy(moe_ctx* ctx);
 moe_status moe_batch_create(moe_ctx* ctx, moe_ctx** out);
 moe_status moe_batch_end(moe_ctx* batch, void* stream, int launch);
 
+/* How many grouped GEMMs and how many quantiser launches the batch has kept since it was created (host, no launch): the call before
+ * has been kept if its number has risen. */
+moe_status moe_batch_kept(moe_ctx* batch, int64_t* gemms, int64_t* quantisers);
+
 /* Host string for the last error recorded on ctx ("" if none); owned by ctx.  ctx = NULL: the message of the
  * calling host thread's last failed call that takes no context (moe_permute_static). */
 const char* moe_last_error(const moe_ctx* ctx);

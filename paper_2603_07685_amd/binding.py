@@ -39,7 +39,7 @@ EXPORTS = [
     "moe_grouped_gemm_fwd_quant_mx", "moe_grouped_gemm_dgrad_quant_mx", "moe_gate_gemm", "moe_permute_static",
     "moe_fp8_quantize_rowcol", "moe_fp8_quantize_rowcol_gather",
     "moe_grouped_gemm_fwd_gather", "moe_grouped_gemm_dgrad_gather", "moe_grouped_gemm_wgrad_gather",
-    "moe_batch_create", "moe_batch_end",
+    "moe_batch_create", "moe_batch_end", "moe_batch_kept",
 ]
 
 _vp, _i, _i64, _f = C.c_void_p, C.c_int, C.c_int64, C.c_float
@@ -66,6 +66,7 @@ def lib() -> C.CDLL:
         L.moe_ctx_poll_error.argtypes = [_vp, _vp, C.POINTER(_i)]
         L.moe_batch_create.argtypes = [_vp, C.POINTER(_vp)]
         L.moe_batch_end.argtypes = [_vp, _vp, _i]
+        L.moe_batch_kept.argtypes = [_vp, C.POINTER(_i64), C.POINTER(_i64)]
         L.moe_route_topk.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, _f, _vp, _vp, _vp]
         L.moe_permute.argtypes = [_vp, _vp, _vp, _i, _vp, _i, _i, _i, _i, _i, _vp, _i64, _vp, _vp, _vp, _vp]
         L.moe_permute_static.argtypes = [_vp, _vp, _i, _vp, _i, _i, _i, _i, _i, _vp, _i64, _vp, _vp, _vp, _vp]
@@ -199,6 +200,12 @@ class Batch(Context):
 
     def __exit__(self, exc, value, trace):
         moe_batch_end(self, exc is None)
+
+    def kept(self):
+        """(grouped GEMMs, quantiser launches) kept since the batch was created."""
+        g, q = _i64(), _i64()
+        self.check(lib().moe_batch_kept(self.h, C.byref(g), C.byref(q)), "moe_batch_kept")
+        return g.value, q.value
 
 
 def moe_batch_end(batch, launch=True):

@@ -31,6 +31,14 @@ extern "C" moe_status moe_batch_end(moe_ctx* batch, void* stream, int launch) {
     return MOE_OK;
 }
 
+extern "C" moe_status moe_batch_kept(moe_ctx* batch, int64_t* gemms, int64_t* quantisers) {
+    if (!batch) return MOE_ERR_ARG;
+    if (!batch->batch || !gemms || !quantisers) MOE_FAIL(batch, MOE_ERR_ARG, "moe_batch_kept: not a batch, or NULL pointer");
+    *gemms = batch->batch->kept_gemm;
+    *quantisers = batch->batch->kept_quant;
+    return MOE_OK;
+}
+
 void batch_gemm(moe_ctx* ctx, gemm_job j) {
     moe_batch* const b = ctx->batch;
     // (pieces of two weight gradients of a launch need room side by side; a call's number of pieces does not depend on it)
@@ -39,6 +47,7 @@ void batch_gemm(moe_ctx* ctx, gemm_job j) {
     if (need) j.a.partials = (float*)((char*)j.a.partials + b->partials);
     b->partials += (need + 255) / 256 * 256;
     b->gemm[b->n_gemm++] = j;
+    ++b->kept_gemm;
 }
 
 static void launch_alone(const gemm_job& j) {

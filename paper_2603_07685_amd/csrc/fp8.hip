@@ -692,6 +692,7 @@ void quant_submit(moe_ctx* ctx, hipStream_t s, const quant_args& a, bool after) 
     if (!b || (!after && a.blocks > QUANT_KEEP)) return quant_launch(s, a);
     if (b->n_quant == MOE_BATCH_MAX) batch_flush(b);
     b->quant[b->n_quant++] = {s, false, a};
+    ++b->kept_quant;
 }
 void quant_flush(quant_job* jobs, int n) {
     for (int i = 0; i < n; ++i) {

@@ -172,6 +172,7 @@ struct moe_batch {
     quant_job quant[MOE_BATCH_MAX];   // (launched behind the GEMMs: among them the quantised copies of their outputs)
     int n_gemm, n_quant;
     size_t partials;                  // bytes of the workspace that kept weight gradients leave pieces' results in
+    int64_t kept_gemm, kept_quant;    // since its creation
 };
 void batch_flush(moe_batch* b);
 void batch_gemm(moe_ctx* ctx, gemm_job j);
