@@ -79,10 +79,13 @@ moe_status moe_ctx_destroy(moe_ctx* ctx);
 /*
  * A batch: a second handle on ctx (same device, same workspace) for calls that do not depend on each other, so that small
  * ones share a launch: a layer's weight and data gradient, or the routed and the shared experts' calls.  A grouped GEMM or a
- * quantiser called with the batch as its context is checked as ever, and either launched at once or kept until moe_batch_end, which launches what is
- * kept on the stream each call was given, in no particular order; every other call is launched at once.  Results are those
- * of the same calls on ctx, bit for bit.  Until moe_batch_end returns, the operands of the calls must stay valid, none may
- * read or write what another of them writes, and no other work that uses them may be enqueued.
+ * quantiser called with the batch as its context is checked as ever, and either launched at once or kept until moe_batch_end,
+ * which launches what is kept on the stream each call was given, in no particular order; every other call is launched at once.
+ * Results are those of the same calls on ctx, bit for bit.  Until moe_batch_end returns, the operands of the calls must stay
+ * valid, none may read or write what another of them writes, and no other work that uses them may be enqueued.
+ * The workspace is shared: the calls of a context and of its batches, together, are those that must be stream-ordered with
+ * respect to each other.  So the calls of one batch go to one stream; on several, kept weight gradients of two launches would
+ * leave their partial results in the same place.
  * launch = 0: the kept calls are dropped instead (a call of the batch has failed).  A batch can be used again after moe_batch_end.
  * It is destroyed by moe_ctx_destroy, before ctx.  Both calls are host-only but for the launches. */
 moe_status moe_batch_create(moe_ctx* ctx, moe_ctx** out);

@@ -158,3 +158,102 @@ def test_offsets_of_any_call_are_checked(at):
     assert ctx.poll_error() == 1
     for i, t in enumerate((dA[0], dA[1], dW)):
         assert bool((t == 7).all()) == (i == at), i
+
+
+def _gradient_in_pieces(N, K, R, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    A, dC = (torch.randn((R, n), generator=g, device="cuda").to(torch.bfloat16) for n in (K, N))
+    return A, dC, torch.tensor([0, R], dtype=torch.int32, device="cuda")
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("width", [512, 2048], ids=["room for one", "room for all"])
+def test_weight_gradients_in_pieces_side_by_side(width, f32):
+    """Three weight gradients whose contraction is cut into pieces and a data gradient: their partial results lie side by side, or, where
+    the workspace has no room for the next, what is kept goes first."""
+    from paper_2603_07685_amd import binding as B
+    N, K = 1024, 512
+    dt = B.F32 if f32 else B.BF16
+    new = lambda: torch.full((N, K), float("nan"), dtype=torch.float32 if f32 else torch.bfloat16, device="cuda")
+    ops = [_gradient_in_pieces(N, K, R, 7 + R) for R in (2048, 3000, 2500)]
+    ctx, bare = B.Context(T=64, k=1, E=1, h=width, f_max=512), B.Context(T=64, k=1, E=1, h=0, f_max=0)
+    W = torch.randn((N, K), device="cuda").to(torch.bfloat16)
+
+    def weight(c, o, out):
+        A, dC, off = o
+        B.moe_grouped_gemm_wgrad(c, A, dC, off, 1, N, K, A.shape[0], B.BF16, None, None, 0, dt, out)
+
+    def data(c, out):
+        B.moe_grouped_gemm_dgrad(c, ops[0][1], W, ops[0][2], 1, N, K, 2048, B.BF16, None, None, None, out)
+
+    want, whole, got = ([new() for _ in ops] for _ in range(3))
+    dwant, dgot = (torch.zeros((2048, K), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    for o, w, v in zip(ops, want, whole):
+        weight(ctx, o, w)
+        weight(bare, o, v)
+    data(ctx, dwant)
+    if f32:
+        assert not any(torch.equal(w, v) for w, v in zip(want, whole))   # (cut: other sums)
+    batch = B.Batch(ctx)
+    for _ in range(3):                     # (the room is used again)
+        for t in got:
+            t.fill_(float("nan"))
+        dgot.zero_()
+        with batch as b:
+            for o, t in zip(ops, got):
+                weight(b, o, t)
+            data(b, dgot)
+            torch.cuda.synchronize()
+            assert [bool(t.isnan().all()) for t in got] == [width == 2048, width == 2048, True]
+        assert torch.equal(dgot, dwant)
+        for t, w in zip(got, want):
+            assert torch.equal(t, w)
+    assert ctx.poll_error() == 0 and batch.kept() == (12, 0)
+
+
+@pytest.mark.parametrize("recipe", ["bf16", "fp32", "fp8", "mxfp8"])
+@pytest.mark.parametrize("size", [1, 2, 3])
+def test_hot_and_empty_experts(recipe, size):
+    """95 % of the pairs on one expert, some experts without rows, the first and the last among them."""
+    up = (lambda n: (n + 127) // 128 * 128) if recipe in ("fp8", "mxfp8") else (lambda n: n)
+    s = {n: v if n in ("E", "k") else up(v) for n, v in SIZES[size].items()}
+    pair = _layers(s, True, recipe=recipe)
+    g = torch.Generator()
+    g.manual_seed(size)
+    idx = torch.randint(1, s["E"] - 1, (s["T"], s["k"]), generator=g)
+    idx[idx == 2] = 1
+    idx[torch.rand(idx.shape, generator=g) < 0.95] = s["E"] - 2
+    for st in pair:
+        st.forced_idx = idx.to(torch.int32).cuda()
+    _compare(pair, True)
+    assert pair[0].counts.tolist() == torch.bincount(idx.flatten(), minlength=s["E"]).tolist()
+
+
+@pytest.mark.parametrize("recipe", ["bf16", "fp32", "fp8", "mxfp8"])
+def test_captured_step_with_a_shared_expert(recipe):
+    """A step captured in a graph, batches and all: every replay gives the eager step's bits, on other loads too."""
+    pair = _layers(dict(T=512, h=256, f=128, E=6, k=2, sf=128), True, recipe=recipe)
+    st, eager = pair[0], pair[1]
+    names = OUT + SHARED
+    loads = [torch.randint(0, e, (512, 2), dtype=torch.int32, device="cuda") for e in (6, 2, 4)]
+    st.forced_idx = loads[0].clone()
+    st.step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st.step()
+    for i in (1, 0, 2, 2):
+        st.forced_idx.copy_(loads[i])
+        eager.forced_idx = loads[i]
+        eager.step()
+        for n in names:
+            getattr(st, n).zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        live = int(eager.offsets[-1])      # (rows behind the last expert hold what an earlier load has left there)
+        for n in names:
+            a, b = getattr(st, n), getattr(eager, n)
+            assert torch.equal(a[:live], b[:live]) if n in ("A", "Z", "O", "dZ") else torch.equal(a, b), (i, n)
+    assert st.ctx.poll_error() == 0 and eager.ctx.poll_error() == 0
