@@ -20,7 +20,10 @@
 // A and dZ 208, 438 : 198, 412.
 #define QUANT_THREADS 512
 
-// Calls of a batch: up to this many tiles are kept (four per compute unit and more: a launch of its own costs little)
+// Calls of a batch: up to this many tiles are kept, 16 per compute unit.  A step of 37 drawn fp8 and MXFP8 layers (T 512-14464, h 256-4096,
+// half of them with a shared expert), against 1024 tiles 0.985 in time in the mean (0.897-1.003; MXFP8 T 2304 h 2560 f 128 E 26 k 1, shared
+// 128, 223 : 200 us), 2048 0.996, 8192 and 32768 no difference (0.995-1.012): larger calls fill the chip long enough for their start not to
+// count, and a launch holds six calls of this many tiles at most.
 #define QUANT_KEEP 4096
 
 __device__ __forceinline__ float amax8(u32x4_t v) {

@@ -376,8 +376,8 @@ __global__ __launch_bounds__(256, 2) void gt_bwd_jobs_kernel(const gt_jobs m) {
     else gt_body<GG_WGRAD, GG_EPI_STORE, F32, WGATH, 128, WBUF, SPLIT>(m.a[j], lds.w, block);
 }
 
-// Second step of a weight gradient with pieces: every workgroup finds the split experts in the offsets (at most four) and goes
-// over its share of their results, piece 0 first.  Bound: HBM, a slice read per piece; without a split expert, one look.
+// Second step of a weight gradient with pieces: every workgroup finds the split experts in the offsets (at most half of
+// GT_MAX_PIECES, as each has two pieces or more) and goes over its share of their results, piece 0 first.  Bound: HBM, a slice read per piece; without a split expert, one look.
 template <bool OUT_F32>
 __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
     __shared__ int at[GT_MAX_PIECES], rows_at[GT_MAX_PIECES], count;
@@ -607,9 +607,10 @@ void gt_launch_jobs(hipStream_t s, bool fwd, int epi, bool f32, int wgath, int t
         else f32 ? gt_bwd_jobs<GG_EPI_STORE, true, 0>(s, tile, wtile, n, m) : gt_bwd_jobs<GG_EPI_STORE, false, 0>(s, tile, wtile, n, m);
     }
 }
-// Calls that a batch does not keep: data gradients on 128-row tiles, which fill the chip by themselves; weight gradients on one buffer of more than eight tiles per unit, which live off three workgroups to a unit, one
-// more than beside a data gradient (a step, us, alone : together: T 112 h 5504 f 1152 E 57 k 4, 86 tiles per unit, 1433 : 1545; T 262
-// h 5696 f 704 E 16 k 2, 17 per unit, 422 : 435; T 2541 h 1088 f 384 E 54, 6 per unit, 171 : 157).
+// Calls that a batch does not keep: data gradients on 128-row tiles, which fill the chip by themselves; weight gradients on one buffer of
+// more than eight tiles per unit, which live off three workgroups to a unit, one more than beside a data gradient (a step, us, alone :
+// together: T 112 h 5504 f 1152 E 57 k 4, 86 tiles per unit, 1433 : 1545; T 262 h 5696 f 704 E 16 k 2, 17 per unit, 422 : 435; T 2541 h
+// 1088 f 384 E 54, 6 per unit, 171 : 157).
 bool gt_submit(moe_ctx* ctx, hipStream_t s, int mode, int epi, bool out_f32, int gath, int tile, const gg_args& a) {
     const int64_t cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
     if (ctx->batch && !(mode == GG_DGRAD && tile == 2) && !(tile == 4 && a.split_cap < 2 && gt_blocks(mode, epi, 128, a) > 8 * cu)) {
