@@ -180,10 +180,15 @@ __global__ __launch_bounds__(1024) void permute_rank_kernel(const int32_t* __res
 // workgroups, further ones without tokens follow (permute_all_grid).
 // ---------------------------------------------------------------------------
 #define PERMUTE_ALL_THREADS 512
-// Us, three launches for the map and one for the rows : this; h 512, loads scattered by 30 % | 95 % of the pairs on one expert.
-// 16384 pairs, k 8: E 8 14.5 : 9.6 | 14.6 : 9.5; E 512 17.3 : 10.4 | 17.3 : 14.3; 32768 pairs, k 8: E 8 17.7 : 15.4 | 17.7 : 15.2; E 256
-// 20.5 : 16.3 | 20.4 : 17.8; E 512 23.3 : 16.8 | 23.1 : 24.1 (the only loss); k 1, E 8 24.1 : 20.8.  Twice as many pairs would cost
-// twice the time here, a fifth more there.  The map alone, 16384 pairs: E 8 10.4 : 7.1 | 10.6 : 7.1; E 512 13.1 : 7.9 | 13.3 : 11.8.
+// Us, three launches for the map and one for the rows : this; loads scattered by 30 % | 95 % of the pairs on one expert.  h 512, k 8, 16384
+// pairs: E 8 14.5 : 9.6 | 14.6 : 9.5; E 512 17.3 : 10.4 | 17.3 : 14.3; 32768 pairs: E 8 17.7 : 15.4 | 17.7 : 15.2; E 256 20.5 : 16.3 | 20.4 :
+// 17.8; E 512 23.3 : 16.8 | 23.1 : 24.1 (the only loss).  Twice as many pairs would cost twice the time here, a fifth more there.  The map
+// alone, 16384 pairs: E 8 10.4 : 7.1 | 10.6 : 7.1; E 512 13.1 : 7.9 | 13.3 : 11.8.
+// The rows of a large call move faster with a workgroup for every token, and the map is a small part of it (permute_all_rows; E 32, all
+// pairs valid | one in eight): 32768 pairs, k 1, h 1024 31.3 : 30.3 | 26.4 : 23.8, h 2048 44.1 : 48.1 | 32.2 : 34.2, h 4096 73 : 126 | 49 : 60;
+// k 8, h 1024 23.8 : 22.3 | 14.6 : 12.9, h 2048 36.2 : 36.1 | 15.3 : 17.6, h 7168 103 : 103 | 26.8 : 32.9; 16384 pairs, k 1, h 2048 28.5 : 26.6 |
+// 22.6 : 20.3, h 4096 42.9 : 44.3 | 30.5 : 30.9, h 7168 66 : 70 | 45.6 : 47.1; k 8, h 7168 57.0 : 53.4 | 18.1 : 17.4; 8192 pairs, k 1, h 7168
+// 39.2 : 38.0 | 28.3 : 26.7.
 #define PERMUTE_ALL_PAIRS 32768  // (the map alone: half)
 #define PERMUTE_ALL_E 512
 #define PERMUTE_ALL_GRID 256     // most workgroups because of rows without a pair
@@ -568,6 +573,13 @@ static unsigned permute_all_grid(int T, int per_wg, int E, int align, int vec, i
     return (unsigned)(fill < tokens ? tokens : fill < PERMUTE_ALL_GRID ? fill : PERMUTE_ALL_GRID > tokens ? PERMUTE_ALL_GRID : tokens);
 }
 
+// Whether the rows of a call are few enough for permute_all_kernel (PERMUTE_ALL_PAIRS): X up to 128 MB up to 8192 pairs, up to 64 MB
+// up to 16384, 64 MB of rows to be written above.
+static bool permute_all_rows(int64_t pairs, int T, int64_t row_bytes) {
+    const int64_t MB = 1 << 20;
+    return pairs <= 8192 ? T * row_bytes <= 128 * MB : pairs <= 16384 ? T * row_bytes <= 64 * MB : pairs * row_bytes <= 64 * MB;
+}
+
 // The launches of one permute call; chunk_hist = int32 [chunks, E] of device scratch (every entry is written by the
 // histogram kernel before it is read: the buffer needs no clearing).
 static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int32_t* idx, int T, int k, int h, int E,
@@ -577,7 +589,8 @@ static void permute_launch(hipStream_t s, const void* X, moe_dtype dt, const int
     const int nchunks = (int)moe_permute_chunks(pairs), nbits = bits_for(E);
     const int vec = X ? (int)((size_t)h * moe_dtype_size(dt) / 16) : 0;
     const int per_wg = T > 256 ? (T + 255) / 256 : 1;   // a workgroup per compute unit
-    if (pairs <= (X ? PERMUTE_ALL_PAIRS : PERMUTE_ALL_PAIRS / 2) && E <= PERMUTE_ALL_E && (int64_t)per_wg * vec * vec < (1LL << 32)) {
+    if (pairs <= (X ? PERMUTE_ALL_PAIRS : PERMUTE_ALL_PAIRS / 2) && E <= PERMUTE_ALL_E && (int64_t)per_wg * vec * vec < (1LL << 32) &&
+        permute_all_rows(pairs, T, (int64_t)vec * 16)) {
         // (c / vec = c * ceil(2^32 / vec) / 2^32 for c < per_wg * vec: the rounding adds less than c vec / 2^32 of a step)
         const uint64_t magic = vec ? ((1ull << 32) + vec - 1) / vec : 0;
         hipLaunchKernelGGL(permute_all_kernel, dim3(permute_all_grid(T, per_wg, E, align, vec, Rcap - pairs)), dim3(PERMUTE_ALL_THREADS),

@@ -84,3 +84,34 @@ def test_rows_without_a_pair_are_spread(T, k, h, E, align, slack):
     fill = us(lambda: [t.zero_() for t in filled])
     print(f"permute {call:.1f} us, fill {fill:.1f} us")
     assert call < 10 + 2 * fill
+
+
+# both sides of the bounds on the rows' bytes (64 MB of rows for more than 16384 pairs, 64 MB of X for more than 8192)
+@pytest.mark.parametrize("T,k,h,E,align,slack", [
+    (4096, 8, 1024, 8, 1, 0), (4096, 8, 1032, 16, 8, 3), (16384, 1, 2048, 32, 1, 0), (8193, 1, 4096, 32, 16, 0)])
+def test_many_bytes(T, k, h, E, align, slack):
+    test_map_and_rows(T, k, h, E, align, slack)
+
+
+def test_large_rows_move_as_fast_as_with_a_launch_of_their_own():
+    """One pair more than the one-launch kernel takes may not make a call of large rows faster: 73 us a call measured on both sides, 126 with
+    32768 pairs in one launch."""
+    from paper_2603_07685_amd import binding as B
+    h, E, times = 4096, 32, []
+    for T in (32768, 32769):
+        ctx = B.Context(T, 1, E, 64, 64)
+        X, Xp = torch.zeros((T, h), dtype=torch.bfloat16, device="cuda"), torch.empty((T, h), dtype=torch.bfloat16, device="cuda")
+        idx = torch.randint(0, E, (T, 1), dtype=torch.int32, device="cuda")
+        out = [torch.empty(n, dtype=torch.int32, device="cuda") for n in (T, T, E + 1, E)]
+        best = float("inf")
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                B.moe_permute(ctx, X, B.BF16, idx, T, 1, h, E, 1, Xp, T, *out)
+            e1.record()
+            e1.synchronize()
+            best = min(best, e0.elapsed_time(e1) * 100)
+        times.append(best)
+    print("%.1f us, %.1f us" % tuple(times))
+    assert times[0] < 1.2 * times[1]
