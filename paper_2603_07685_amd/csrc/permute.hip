@@ -10,7 +10,8 @@
 //   3. rank : a workgroup per chunk again, one wavefront per 64 pairs; a lane's rank among equal experts inside the 64
 //             comes from ballots over the bits of the expert id, the wavefronts' counts are scanned in LDS.  Further
 //             workgroups mark the rows that no pair owns (src_of = -1).
-// Up to PERMUTE_ALL_PAIRS pairs all of it and the row move are one launch (permute_all_kernel).
+// Up to PERMUTE_ALL_PAIRS pairs, unless their rows are large (permute_all_rows), all of it and the row move are one launch
+// (permute_all_kernel).
 // Bound: launches and dependent latencies (the map of 131072 pairs is 1.5 MB).  Measured, all kernels of the map: T 16384, k 8, E 32:
 // 35 : 16.6 us (fill, one wavefront per chunk, a serial scan over the chunks : this).
 // Row moves are token-major: a workgroup reads one source row once and writes
