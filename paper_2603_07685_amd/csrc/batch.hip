@@ -67,8 +67,8 @@ static void launch_alone(const gemm_job& j) {
 // Of several experts a hot one ends the launch, so their mean counts twice; of a single one 0.8 of its rows, as a data gradient's
 // output phase is the longer (bf16 T 1538 h 1536 f 2624 E 6 k 1, shared 2624, 1538 rows against N 1536: 445 : 462 us a step with the
 // weight gradients first).  A call that cuts experts into pieces walks no more rows than a piece's, but may have nothing
-// to cut: counted as nothing, 40 drawn layers' backward passes of 24576 rows or fewer took 1.02 (equal loads) to 1.03 times as long (rank^-1.2),
-// T 3699 h 192 f 256 E 9 k 4 85 : 72 us.
+// to cut: counted as nothing, 40 drawn layers' backward passes of 24576 rows or fewer took 1.02 (equal loads) to 1.03 times as long
+// (rank^-1.2), T 3699 h 192 f 256 E 9 k 4 85 : 72 us.
 // Steps, us, data gradients always first : this: MXFP8 T 1920 h 512 f 256 E 8 k 8 160 : 145, T 8192 h 256 f 896 E 28, shared 896
 // 410 : 356; fp8 T 1920 h 896 f 896 E 4 k 4 250 : 230; bf16 T 773 h 960 f 384 E 5 k 4, rank^-1.2, 104 : 94.  160 drawn layers with a
 // shared expert, each with equal, by 30 % scattered and rank^-1.2 loads, mean: MXFP8 1.040, fp8 1.034, bf16 1.005; 159 others 1.018,
@@ -126,9 +126,9 @@ static void gemm_flush(gemm_job* jobs, int n) {
         }
         // The tiles of the call with the most of them serve all of a mode.  Where the routed experts' weight gradients are on one stage
         // buffer (gt_one_buffer) the shared expert's is walked on one too, at half its pace, but it is few tiles beside many and over
-        // before them.  A backward pass of 30 drawn layers with a shared expert and such a pair (T 67-847, h 256-1472, f 320-1792, E 11-61),
-        // this : the two in launches of their own : both on two buffers: 1 : 1.10 : 1.03 in the mean, at least 1.02 and 0.993; us, T 847
-        // h 1216 f 384 E 27 62.8 : 66.1 : 63.0; T 158 h 1152 f 640 E 13, shared 384, 41.3 : 51.8 : 42.9.
+        // before them.  A backward pass of 30 drawn layers with a shared expert and such a pair (T 67-847, h 256-1472, f 320-1792, E
+        // 11-61), this : the two in launches of their own : both on two buffers: 1 : 1.10 : 1.03 in the mean, at least 1.02 and 0.993;
+        // us, T 847 h 1216 f 384 E 27 62.8 : 66.1 : 63.0; T 158 h 1152 f 640 E 13, shared 384, 41.3 : 51.8 : 42.9.
         const gemm_job *most = nullptr, *wmost = nullptr;
         for (const gemm_job* j : take) {
             const gemm_job*& m = j && j->mode == GG_WGRAD ? wmost : most;

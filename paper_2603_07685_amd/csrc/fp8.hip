@@ -16,8 +16,8 @@
 // outweighs its pieces.  Measured (us, 256 threads with every lane dividing : 512 and one division pair per column), T 1024 h 512 f 256 E 8
 // k 4: tokens and p * dY through the row map 13.8, 13.1 : 9.2, 9.3, X and dY 11.0, 10.9 : 7.2, 6.8, columns only 6.1 : 5.0, weights 6.1,
 // 5.3, 5.0 : 5.1, 4.2, 4.2; T 8192 h 1024 f 512 E 8 k 2: 27.6, 15.2 : 25.1, 13.0; T 16384 h 4096 k 4 unchanged.  MXFP8 (256 : 512), T 256
-// h 512 f 256 E 8 k 2 7.6, 7.9 : 6.3, 6.9; T 16384 h 7168 f 2048 E 32 k 8: weights 793, 376 : 739, 365, tokens and p * dY 740, 764 : 675, 715,
-// A and dZ 208, 438 : 198, 412.
+// h 512 f 256 E 8 k 2 7.6, 7.9 : 6.3, 6.9; T 16384 h 7168 f 2048 E 32 k 8: weights 793, 376 : 739, 365, tokens and p * dY 740, 764 :
+// 675, 715, A and dZ 208, 438 : 198, 412.
 #define QUANT_THREADS 512
 
 // Calls of a batch: up to this many tiles are kept, 16 per compute unit.  A step of 37 drawn fp8 and MXFP8 layers (T 512-14464, h 256-4096,

@@ -14,11 +14,11 @@
 //
 // Bound: the fixed cost around a short contraction (finding the tile, the first operands' latency, the output: about 5 us)
 // and the rate at which a compute unit's L1 takes lines from the L2 (35-45 bytes per ns here, in the 256 x 256 kernel too;
-// the matrix pipes are 13-36 % busy over the calls of T 2048, h 1024, f 512 and T 1999, h 2880, f 1472, the LDS 12-29 %).  What helped is waves: NBUF = 2 keeps two (BM = 128) or three (64)
-// workgroups on a compute unit, which cover each other's waits; with a ring of four stages and one workgroup, the same
-// bytes ahead, a call takes 1.25-1.5 times as long (fc1 forward, T 2048, h 1024, f 512, 8 experts, top-2: 24 us against
-// 33, BM = 128).  A persistent form, whose operand stream runs on across tiles, was no faster (27 us) and its static share
-// of the tiles made it slower where there are many (BM = 64, 24 experts, 8000 rows: 309 us against 251).
+// the matrix pipes are 13-36 % busy over the calls of T 2048, h 1024, f 512 and T 1999, h 2880, f 1472, the LDS 12-29 %).  What helped
+// is waves: NBUF = 2 keeps two (BM = 128) or three (64) workgroups on a compute unit, which cover each other's waits; with a ring of
+// four stages and one workgroup, the same bytes ahead, a call takes 1.25-1.5 times as long (fc1 forward, T 2048, h 1024, f 512, 8
+// experts, top-2: 24 us against 33, BM = 128).  A persistent form, whose operand stream runs on across tiles, was no faster (27 us) and
+// its static share of the tiles made it slower where there are many (BM = 64, 24 experts, 8000 rows: 309 us against 251).
 // Where the rows of an expert fit one tile and the call streams the weights, or the tiles leave at most two to a unit, a third
 // buffer is worth more than the third workgroup (decoding, 32 rows on each of 16 experts, 403 MB of fc1 weights: 92 us against
 // 98, 4.4 TB/s).  The other way round, weight gradients of a few stages and many tiles are mostly output: one buffer, no operand
@@ -353,10 +353,10 @@ __global__ __launch_bounds__(256, NBUF == 1 ? 3 : NBUF == 2 ? (BM == 64 ? 3 : 2)
     gt_body<MODE, EPI, OUT_F32, GATH, BM, NBUF, SPLIT>(a, lds, (int)blockIdx.x);
 }
 
-// Independent calls in one launch.  Small calls leave compute units idle in their start, their output phase and the last of their rounds, and each
-// launch costs about 2 us behind another; together they fill each other's gaps.  A step, us, one launch each : together: T 256 h 128
-// f 256 E 8 k 2 52.8 : 45.1; T 377 h 2240 f 512 E 8 k 2 130 : 106; T 7394 h 128 f 192 E 24 125 : 104; with a shared expert T 27 h 576 f 512
-// E 7 k 2 105 : 60, T 873 h 896 f 2688 E 12 k 2 342 : 300.
+// Independent calls in one launch.  Small calls leave compute units idle in their start, their output phase and the last of their
+// rounds, and each launch costs about 2 us behind another; together they fill each other's gaps.  A step, us, one launch each :
+// together: T 256 h 128 f 256 E 8 k 2 52.8 : 45.1; T 377 h 2240 f 512 E 8 k 2 130 : 106; T 7394 h 128 f 192 E 24 125 : 104; with a
+// shared expert T 27 h 576 f 512 E 7 k 2 105 : 60, T 873 h 896 f 2688 E 12 k 2 342 : 300.
 // forward calls with one epilogue
 template <int EPI, int BM, int NBUF>
 __global__ __launch_bounds__(256, NBUF == 2 && BM == 64 ? 3 : 2) void gt_fwd_jobs_kernel(const gt_jobs m) {
@@ -377,7 +377,8 @@ __global__ __launch_bounds__(256, 2) void gt_bwd_jobs_kernel(const gt_jobs m) {
 }
 
 // Second step of a weight gradient with pieces: every workgroup finds the split experts in the offsets (at most half of
-// GT_MAX_PIECES, as each has two pieces or more) and goes over its share of their results, piece 0 first.  Bound: HBM, a slice read per piece; without a split expert, one look.
+// GT_MAX_PIECES, as each has two pieces or more) and goes over its share of their results, piece 0 first.  Bound: HBM, a slice read per
+// piece; without a split expert, one look.
 template <bool OUT_F32>
 __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
     __shared__ int at[GT_MAX_PIECES], rows_at[GT_MAX_PIECES], count;
@@ -431,20 +432,20 @@ __global__ __launch_bounds__(256) void gt_add_kernel(const gg_args a) {
 // A hot expert's workgroups walk their rows at half the pace then, which the host cannot see; it shows once that walk is long beside
 // the output of all tiles.  Hence at most 160 rows in all for every tile per unit: up to there no load was slower, also with 95 % of
 // the rows on one expert; at 192 one such was (512 x 512 of 40 experts, 9.4 : 9.9), from 256 on most.  Two buffers : one, equal loads |
-// half on one expert | 95 %, R rows in all (per tile and unit), N x K of E experts: 512 x 512 of 64, R 512 (128) 13 : 11 | 13 : 10 | 12 : 10, R 1024 (256) 13 : 11 | 14 : 11 |
-// 14 : 16, R 4096 (1024) 14 : 12 | 23 : 27 | 39 : 46; 768 x 512 of 24, R 320 (142) 10 : 8 | 10 : 8 | 10 : 8.4, R 864 (384) 10 : 8 |
-// 10 : 9 | 11.5 : 12.4; 2048 x 1024 of 8, R 512 (128) 14 : 12 | 16 : 14 | 22 : 21, R 1024 (256) 15 : 13 | 22 : 21 | 32 : 33.5, R 2048 (512) 18 : 17 |
-// 32 : 34 | 51 : 56; 1024 x 1024 of 64, R 2304 (144) 38 : 27 | 50 : 38 | 61 : 48.  (256 rows per expert and 6144 in all are the most that
-// was measured.)
+// half on one expert | 95 %, R rows in all (per tile and unit), N x K of E experts: 512 x 512 of 64, R 512 (128) 13 : 11 | 13 : 10 | 12
+// : 10, R 1024 (256) 13 : 11 | 14 : 11 | 14 : 16, R 4096 (1024) 14 : 12 | 23 : 27 | 39 : 46; 768 x 512 of 24, R 320 (142) 10 : 8 | 10 :
+// 8 | 10 : 8.4, R 864 (384) 10 : 8 | 10 : 9 | 11.5 : 12.4; 2048 x 1024 of 8, R 512 (128) 14 : 12 | 16 : 14 | 22 : 21, R 1024 (256) 15 :
+// 13 | 22 : 21 | 32 : 33.5, R 2048 (512) 18 : 17 | 32 : 34 | 51 : 56; 1024 x 1024 of 64, R 2304 (144) 38 : 27 | 50 : 38 | 61 : 48.
+// (256 rows per expert and 6144 in all are the most that was measured.)
 static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
     const int64_t tiles = a.E * ceil_div64(a.N, 128) * ceil_div64(a.K, 128), cu = ctx->num_cu > 0 ? ctx->num_cu : 256;
     return tiles > 2 * cu && a.Rcap * cu <= 160 * tiles && a.Rcap <= 256 * (int64_t)a.E && a.Rcap <= 6144;
 }
 
 // Which kernel serves a call: 1 = 64 x 128 tiles, 2 = 128 x 128, 3 = 64 x 128 with a third stage buffer, 4 = 128 x 128 on one
-// (gt_one_buffer), 0 = the 256 x 256 kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted to measured calls
-// (MI355X, bf16).  The rows of an expert are unknown on the host: several experts are taken half way between equal ones and ones that
-// scatter, with half a partly filled row tile each and at least one tile.
+// (gt_one_buffer), 0 = the 256 x 256 kernel.  Decided from the call's sizes by two estimates of its time in microseconds, each fitted
+// to measured calls (MI355X, bf16).  The rows of an expert are unknown on the host: several experts are taken half way between equal
+// ones and ones that scatter, with half a partly filled row tile each and at least one tile.
 //   256 x 256: one workgroup per compute unit, whole rounds of tiles (a twentieth of one over is not rounded up: it comes from
 //              the guess), a tile = 1.5 per stage + 15 (SwiGLU backward: 34); weight gradient: + 6 for the second launch
 //   128 x 128: two workgroups per compute unit, rounds between the exact and the rounded-up count, a round = 2 x (0.62 per
@@ -464,8 +465,8 @@ static bool gt_one_buffer(const moe_ctx* ctx, const gg_args& a) {
 // buffers and 359 with 128 x 128).  The same where the 64 x 128 tiles are at most two per unit, so that a third workgroup would
 // find no work (fc1, fc2, fc2 dgrad, fc1 dgrad, two buffers : three: T 256 h 1024 f 704 E 16 k 4 18.0 : 15.4, 12.3 : 9.7, 14.6 :
 // 12.2, 15.6 : 11.4; T 400 h 512 f 512 E 8 k 2 10.9 : 8.6, 7.7 : 6.2, 10.2 : 9.1, 11.8 : 9.1; but at 2.25 per unit, T 2048 h 1024
-// f 512 E 8 k 2, 21.8 : 23.8, 12.2 : 14.1, 18.2 : 21.0).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill six tenths of the chip's
-// two workgroups per unit (one above it: 7 experts 3298 rows 1920 x 896 fc2 39 : 28); SwiGLU backward, whose output
+// f 512 E 8 k 2, 21.8 : 23.8, 12.2 : 14.1, 18.2 : 21.0).  Otherwise 64 x 128 while the 128 x 128 tiles would not fill six tenths of the
+// chip's two workgroups per unit (one above it: 7 experts 3298 rows 1920 x 896 fc2 39 : 28); SwiGLU backward, whose output
 // phase is long, up to twice what fills them if the contraction is not (128 x 128 : 64 x 128, T 3000 h 512 f 1536 E 12 k 2 34 : 28.5,
 // T 4096 h 512 f 512 E 8 k 4 32 : 27, T 4008 h 1536 f 2048 E 17 52 : 48; but h 3264 f 640 E 51, 10230 rows, equal loads 83 : 116, scattered
 // 119 : 115).

@@ -182,14 +182,14 @@ __global__ __launch_bounds__(1024) void permute_rank_kernel(const int32_t* __res
 // ---------------------------------------------------------------------------
 #define PERMUTE_ALL_THREADS 512
 // Us, three launches for the map and one for the rows : this; loads scattered by 30 % | 95 % of the pairs on one expert.  h 512, k 8, 16384
-// pairs: E 8 14.5 : 9.6 | 14.6 : 9.5; E 512 17.3 : 10.4 | 17.3 : 14.3; 32768 pairs: E 8 17.7 : 15.4 | 17.7 : 15.2; E 256 20.5 : 16.3 | 20.4 :
-// 17.8; E 512 23.3 : 16.8 | 23.1 : 24.1 (the only loss).  Twice as many pairs would cost twice the time here, a fifth more there.  The map
-// alone, 16384 pairs: E 8 10.4 : 7.1 | 10.6 : 7.1; E 512 13.1 : 7.9 | 13.3 : 11.8.
+// pairs: E 8 14.5 : 9.6 | 14.6 : 9.5; E 512 17.3 : 10.4 | 17.3 : 14.3; 32768 pairs: E 8 17.7 : 15.4 | 17.7 : 15.2; E 256 20.5 : 16.3 |
+// 20.4 : 17.8; E 512 23.3 : 16.8 | 23.1 : 24.1 (the only loss).  Twice as many pairs would cost twice the time here, a fifth more
+// there.  The map alone, 16384 pairs: E 8 10.4 : 7.1 | 10.6 : 7.1; E 512 13.1 : 7.9 | 13.3 : 11.8.
 // The rows of a large call move faster with a workgroup for every token, and the map is a small part of it (permute_all_rows; E 32, all
-// pairs valid | one in eight): 32768 pairs, k 1, h 1024 31.3 : 30.3 | 26.4 : 23.8, h 2048 44.1 : 48.1 | 32.2 : 34.2, h 4096 73 : 126 | 49 : 60;
-// k 8, h 1024 23.8 : 22.3 | 14.6 : 12.9, h 2048 36.2 : 36.1 | 15.3 : 17.6, h 7168 103 : 103 | 26.8 : 32.9; 16384 pairs, k 1, h 2048 28.5 : 26.6 |
-// 22.6 : 20.3, h 4096 42.9 : 44.3 | 30.5 : 30.9, h 7168 66 : 70 | 45.6 : 47.1; k 8, h 7168 57.0 : 53.4 | 18.1 : 17.4; 8192 pairs, k 1, h 7168
-// 39.2 : 38.0 | 28.3 : 26.7.
+// pairs valid | one in eight): 32768 pairs, k 1, h 1024 31.3 : 30.3 | 26.4 : 23.8, h 2048 44.1 : 48.1 | 32.2 : 34.2, h 4096 73 : 126 |
+// 49 : 60; k 8, h 1024 23.8 : 22.3 | 14.6 : 12.9, h 2048 36.2 : 36.1 | 15.3 : 17.6, h 7168 103 : 103 | 26.8 : 32.9; 16384 pairs, k 1, h
+// 2048 28.5 : 26.6 | 22.6 : 20.3, h 4096 42.9 : 44.3 | 30.5 : 30.9, h 7168 66 : 70 | 45.6 : 47.1; k 8, h 7168 57.0 : 53.4 | 18.1 :
+// 17.4; 8192 pairs, k 1, h 7168 39.2 : 38.0 | 28.3 : 26.7.
 #define PERMUTE_ALL_PAIRS 32768  // (the map alone: half)
 #define PERMUTE_ALL_E 512
 #define PERMUTE_ALL_GRID 256     // most workgroups because of rows without a pair
